@@ -2,15 +2,15 @@
 //
 // Layout shared by every kernel that votes: a theta tile of TW = 64*G columns lives in LDS
 // rho-major, one row of the tile per rho bin, two 16-bit counters per dword (see Lane below).
-// Lane l of a wave owns column c = 64*q + l of group q, so the 64 atomics one ds_add_u32
-// issues for one hit land in 32 consecutive dwords of one row, the two lanes of a dword in
-// different halves of the wave: no bank conflict, never the same address.  Hits are
-// wave-uniform: a wave maps 64 hits at a time (one per lane), compacts the valid ones into a
-// per-wave LDS stage with ballot/mbcnt, then every lane sweeps its own column over the staged
-// hits (the theta sweep of Sec. III: one column = one parallel task, hits streamed through it).
+// A wave maps 64 hits at a time, one per lane, and forms their bins in 32 columns at a time on
+// the matrix cores (vote_mfma): each half of the wave then votes one hit in 32 consecutive
+// columns per ds_add_u32, 32 different banks.  Elsewhere lane l owns column c = 64*q + l of group
+// q, hits are wave-uniform, and the two lanes of a dword lie in different halves of the wave: no
+// bank conflict, never the same address (the theta sweep of Sec. III: one column = one parallel
+// task, hits streamed through it).
 //
-// Row n_rho of the tile is a dummy row: lanes whose column lies outside [0, n_theta) carry
-// C = S = 0 and B = n_rho, so they "vote" there instead of taking a branch per vote.
+// Row n_rho of the tile is a dummy row for votes outside the grid's rows (lanes whose column
+// lies outside [0, n_theta) carry C = S = 0 and B = n_rho, so their lookups land there).
 //
 // Floating point: the bin of a hit in a column is t = fma(u, C_j, fma(v, S_j, B)) with
 // k = (int)t, exactly as the C-ABI header states.  Hits whose votes are provably all in range
@@ -55,6 +55,16 @@ __device__ __forceinline__ bool all_in_range(float u, float v, const GridArgs &g
 
 __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// The wave's number in its workgroup, as a scalar (loops over waves' shares stay scalar).
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
+// A copy of v the compiler takes for a new value: what a phase of a long kernel derives from its
+// lane number is then computed in that phase, not held in registers through all the others.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
 __device__ __forceinline__ void lds_add(uint32_t *p, uint32_t v) {
@@ -154,7 +164,6 @@ __device__ __forceinline__ StageCount stage_hits(float2 *st, const float *x,
     return stage_values(st, xi, yi, in, g, bad, slot);
 }
 
-// Steps 2-3: sweep one staged hit through the lane's columns and vote.
 // The lane's cell of row k in group q.  Periodic kernels use the per-lane row stride (a 24-bit
 // multiply-add, full rate) so that the reversed halo lanes need no other instruction.
 template <int G, bool P, bool PER = false>
@@ -165,84 +174,126 @@ __device__ __forceinline__ uint32_t *cell_of(uint32_t *tile, int k, const Cols<G
     return &tile[k * Lane<G, P>::STRIDE + (int)ln.col[q]];
 }
 
-template <int G, bool P, bool PER = false>
-__device__ __forceinline__ void vote1(uint32_t *tile, float u, float v, const Cols<G> &cl,
-                                      const Lane<G, P> &ln) {
+// Steps 2-3 on the matrix cores.  The sweep of 32 hits over 32 columns is the rank-2 product
+// t = [v u] [S; C] + B, and v_mfma_f32_32x32x2_f32 forms it as the chain of fused multiply-adds
+// fma(u, C, fma(v, S, B)) in that order, each rounded once: bit for bit the vote's arithmetic
+// (checked against fmaf on random and on denormal operands, and by every parity test).  One
+// instruction replaces two FMAs per vote, which leaves a vote one conversion, one shift-add and
+// its LDS atomic: the vote is then bound by the LDS atomics (14.6 lanes per clock and CU, 4.4
+// clocks per 64 votes, against 2 clocks of VALU), where the VALU form bound it on issue.  Measured
+// (10,000 events, 360 x 256, whole kernel): 1,075 -> 839 M VALU instructions, 11.1 -> 12.6 vote
+// lanes per clock and CU during the vote phases.
+//
+// Operands: hits in A (lane l < 32 holds v of hit l, lane l + 32 its u), columns in B (S below
+// C); both are one v_permlane32_swap away from the lane = hit and lane = column layouts.  Lane l
+// of the result holds column l mod 32 for hits 8b + 4 (l / 32) + i (b, i = 0 .. 3): a vote
+// instruction puts 32 different columns of a tile row range into each half of the wave, so
+// the packed dwords never conflict within a half, exactly as with lane = column.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// (lo, hi) := ({x lanes 0-31, y lanes 0-31}, {x lanes 32-63, y lanes 32-63}).
+__device__ __forceinline__ void swap_halves(float x, float y, float &lo, float &hi) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    lo = __uint_as_float(r[0]);
+    hi = __uint_as_float(r[1]);
+}
+
+// A tile's columns in the matrix layout: B operands per 32-column half, whether the lane's
+// column of each half is voted (in the grid, or a wrapped halo column), and for periodic kernels
+// the lane's row stride and base in bytes (as in Cols).
+template <int G>
+struct VoteCols {
+    float op[2 * G];
+    bool in[2 * G];
+    int rs[2 * G], rb[2 * G];
+};
+
+template <int G, bool PER>
+__device__ __forceinline__ VoteCols<G> vote_cols(const Cols<G> &cl, const GridArgs &g, int first_col, int lane) {
+    VoteCols<G> vc;
+    constexpr int stride = Lane<G, true>::STRIDE;
 #pragma unroll
-    for (int q = 0; q < G; ++q) {
-        const float w = __builtin_fmaf(v, cl.S[q], cl.B[q]);
-        const float t = __builtin_fmaf(u, cl.C[q], w);
-        lds_add(cell_of<G, P, PER>(tile, (int)t, cl, ln, q), ln.inc);
-    }
-}
-
-// Four staged hits, one vote each per column.
-template <int G, bool P, bool PER = false>
-__device__ __forceinline__ void vote4(uint32_t *tile, const float4 &a, const float4 &b,
-                                      const Cols<G> &cl, const Lane<G, P> &ln) {
-    vote1<G, P, PER>(tile, a.x, a.y, cl, ln);
-    vote1<G, P, PER>(tile, a.z, a.w, cl, ln);
-    vote1<G, P, PER>(tile, b.x, b.y, cl, ln);
-    vote1<G, P, PER>(tile, b.z, b.w, cl, ln);
-}
-
-// Wait for every outstanding LDS operation of the wave (lgkmcnt(0), other counters untouched).
-__device__ __forceinline__ void lds_wait() { __builtin_amdgcn_s_waitcnt(0xc07f); }
-
-// Keep the compiler's scheduler from moving instructions across this point.
-__device__ __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
-
-// The staged hits are read four at a time (two 16-byte broadcast reads), one group ahead of
-// the votes that use them, alternating between two register sets.  The read of group c + 1 is
-// issued before the atomics of group c, and LDS operations complete in order, so the votes of
-// group c + 1 wait only for operations issued before the atomics of group c: a wave never
-// waits for its latest atomics.  The fences keep the compiler from reordering the groups.
-template <int G, bool P, bool PER = false>
-__device__ __forceinline__ void vote_staged(uint32_t *tile, const float2 *st, StageCount n,
-                                            const Cols<G> &cl, const Lane<G, P> &ln, float nrho_f) {
-    const float4 *st4 = reinterpret_cast<const float4 *>(st);
-    const uint32_t n4 = n.safe >> 2;
-    if (n4) {
-        float4 a0 = st4[0], b0 = st4[1];
-        lds_wait();
-        uint32_t c = 0;
-        for (; c + 2 < n4; c += 2) {
-            const float4 a1 = st4[2 * c + 2], b1 = st4[2 * c + 3];
-            sched_fence();
-            vote4<G, P, PER>(tile, a0, b0, cl, ln);
-            sched_fence();
-            a0 = st4[2 * c + 4];
-            b0 = st4[2 * c + 5];
-            sched_fence();
-            vote4<G, P, PER>(tile, a1, b1, cl, ln);
-            sched_fence();
-        }
-        vote4<G, P, PER>(tile, a0, b0, cl, ln);
-        if (c + 1 < n4) {
-            const float4 a1 = st4[2 * c + 2], b1 = st4[2 * c + 3];
-            vote4<G, P, PER>(tile, a1, b1, cl, ln);
-        }
-    }
-    for (uint32_t h = n4 * 4; h < n.safe; ++h) vote1<G, P, PER>(tile, st[h].x, st[h].y, cl, ln);
-    for (uint32_t h = n.safe; h < n.total; ++h) {
-        const float2 p = st[h];
+    for (int q = 0; q < G; ++q) swap_halves(cl.S[q], cl.C[q], vc.op[2 * q], vc.op[2 * q + 1]);
 #pragma unroll
-        for (int q = 0; q < G; ++q) {
-            const float w = __builtin_fmaf(p.y, cl.S[q], cl.B[q]);
-            const float t = __builtin_fmaf(p.x, cl.C[q], w);
-            if (t >= 0.0f && t < nrho_f) lds_add(cell_of<G, P, PER>(tile, (int)t, cl, ln, q), ln.inc);
+    for (int h = 0; h < 2 * G; ++h) {
+        const int j = first_col + 32 * h + (lane & 31), c = 32 * (h >> 1) + (lane & 31);
+        const bool wrap = PER && (j == -1 || j == g.n_theta);
+        vc.in[h] = (j >= 0 && j < g.n_theta) || wrap;
+        vc.rs[h] = 4 * (wrap ? -stride : stride);
+        vc.rb[h] = 4 * (wrap ? (g.n_rho - 1) * stride + c : c);
+    }
+    return vc;
+}
+
+// Votes of the first `rows` (wave-uniform) of 32 hits (operand a) in the tile's columns.  CLAMP:
+// votes outside [0, n_rho) (and NaN) go to the dummy row; otherwise every vote is in range.
+// Blocks of 8 hits past `rows` are skipped; the caller makes the rest of the last block harmless.
+template <int G, bool PER, bool CLAMP>
+__device__ __forceinline__ void vote_mfma(uint32_t *tile, float a, uint32_t rows, const VoteCols<G> &vc,
+                                          const f32x16 &bf, const GridArgs &g, float dummy, int lane) {
+    constexpr int ST = Lane<G, true>::STRIDE;
+    char *base = reinterpret_cast<char *>(tile);
+#pragma unroll
+    for (int h = 0; h < 2 * G; ++h) {
+        const f32x16 t = __builtin_amdgcn_mfma_f32_32x32x2f32(a, vc.op[h], bf, 0, 0, 0);
+        if (vc.in[h]) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if (b && (uint32_t)(8 * b) >= rows) break;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float tt = t[4 * b + i];
+                    if (CLAMP) {
+                        // the literal test 0 <= t < n_rho as one unsigned compare of the bits
+                        // (negative and NaN bits are above every finite positive one; the
+                        // addition turns -0, which is in range, into +0)
+                        tt += 0.0f;
+                        tt = __float_as_uint(tt) < __float_as_uint(g.nrho_f) ? tt : dummy;
+                    }
+                    const int k = (int)tt;
+                    uint32_t *cell = PER && !CLAMP
+                        ? reinterpret_cast<uint32_t *>(base + (__mul24(k, vc.rs[h]) + vc.rb[h]))
+                        : &tile[k * ST + 32 * (h >> 1) + (lane & 31)];
+                    if (PER && CLAMP) {
+                        // a wrapped lane reverses the rows of the grid, not the dummy row
+                        const bool in = tt < g.nrho_f;
+                        cell = in ? reinterpret_cast<uint32_t *>(base + (__mul24(k, vc.rs[h]) + vc.rb[h])) : cell;
+                    }
+                    lds_add(cell, h & 1 ? 0x10000u : 1u);
+                }
+            }
         }
     }
 }
 
-// Votes of hits [hb, he); returns the number of valid hits seen.  The next 64 hits are loaded
-// while the current ones vote.  dup (duplicate suppression, else null): the event's keep bytes
-// as the duplicate pass left them; a later copy of a hit is counted as valid but not staged.
-template <int G, bool P, bool PER = false>
-__device__ uint32_t vote_range(uint32_t *tile, float2 *st, const float *x, const float *y,
-                               uint32_t hb, uint32_t he, const Cols<G> &cl, const Lane<G, P> &ln,
-                               const GridArgs &g, int lane, uint32_t &bad, const uint8_t *dup = nullptr) {
-    uint32_t n_valid = 0;
+// A chunk with at most this many valid hits whose votes may leave the grid votes them one at a
+// time with the literal range test; a chunk with more takes the clamped form for all its hits.
+// (one at a time costs about 14 instructions per hit and 64 columns, clamping 3 more per vote
+// instruction of the chunk, 192: they meet near 14 hits; most chunks hold none or one)
+constexpr uint32_t kFewUnsafe = 8;
+
+// Votes of hits [hb, he), 64 at a time, one per lane; returns the number of valid hits seen.
+// The next 64 hits are loaded while the current ones vote.  dup (duplicate suppression, else
+// null): the event's keep bytes as the duplicate pass left them; a later copy of a hit is
+// counted as valid but does not vote.
+// Lanes without a vote of their own (past he, invalid, a later copy, or voting one at a time)
+// take u = v = 0, which votes row (int)B of every column; their number is subtracted from that row
+// at the end of the range, so the vote loop carries no masks (packed sums wrap and unwrap
+// exactly, as 32-bit additions).  When B itself lies outside the grid no hit is ever
+// provably in range, so such a lane votes only in clamped chunks, as NaN, into the dummy row.
+// dummy_row: the tile's dummy row.
+template <int G, bool PER = false>
+__device__ uint32_t vote_range(uint32_t *tile, const float *x, const float *y, uint32_t hb, uint32_t he,
+                               const Cols<G> &cl, const GridArgs &g, int first_col, int lane, uint32_t &bad,
+                               float dummy_row, const uint8_t *dup = nullptr) {
+    const Lane<G, true> ln(lane);
+    const VoteCols<G> vc = vote_cols<G, PER>(cl, g, first_col, lane);
+    f32x16 bf;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bf[i] = g.Bf;
+    asm volatile("" : "+v"(bf));         // in vector registers for the whole range
+    uint32_t n_valid = 0, extra = 0;
     float xn = 0.0f, yn = 0.0f;
     if (hb + lane < he) { xn = x[hb + lane]; yn = y[hb + lane]; }
     for (uint32_t base = hb; base < he; base += 64) {
@@ -255,13 +306,61 @@ __device__ uint32_t vote_range(uint32_t *tile, float2 *st, const float *x, const
             n_valid += (uint32_t)__popcll(__ballot(copy && valid_hit(xi, yi)));
             live = live && !copy;
         }
-        int slot;
-        const StageCount n = stage_values(st, xi, yi, live, g, bad, slot);
-        n_valid += n.total;
-        vote_staged<G, P, PER>(tile, st, n, cl, ln, g.nrho_f);
-        wave_sync();
+        float u, v;
+        const bool ok = conformal(live ? xi : 0.0f, live ? yi : 0.0f, u, v);
+        if (live && !ok) bad = 1u;
+        const bool valid = live && ok, safe = valid && all_in_range(u, v, g);
+        const uint64_t bs = __ballot(safe);
+        uint64_t bu = __ballot(valid && !safe);
+        const uint32_t nu = (uint32_t)__popcll(bu), ns = (uint32_t)__popcll(bs);
+        n_valid += ns + nu;
+        const uint32_t rows = min(he - base, 64u);
+        float a0, a1;
+        if (nu <= kFewUnsafe) {
+            if (ns) {
+                swap_halves(safe ? v : 0.0f, safe ? u : 0.0f, a0, a1);
+#pragma unroll 1
+                for (uint32_t b = 0; b < rows; b += 32, a0 = a1)
+                    vote_mfma<G, PER, false>(tile, a0, rows - b, vc, bf, g, 0.0f, lane);
+                extra += ((rows + 7u) & ~7u) - ns;
+            }
+            for (; bu; bu &= bu - 1ull) {
+                const int m = __builtin_ctzll(bu);
+                const float um = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(u), m));
+                const float vm = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), m));
+#pragma unroll
+                for (int q = 0; q < G; ++q) {
+                    const float w = __builtin_fmaf(vm, cl.S[q], cl.B[q]);
+                    const float t = __builtin_fmaf(um, cl.C[q], w);
+                    if (t >= 0.0f && t < g.nrho_f) lds_add(cell_of<G, true, PER>(tile, (int)t, cl, ln, q), ln.inc);
+                }
+            }
+        } else {
+            const float nan = __uint_as_float(0x7fc00000u);
+            swap_halves(valid ? v : nan, valid ? u : nan, a0, a1);
+#pragma unroll 1
+            for (uint32_t b = 0; b < rows; b += 32, a0 = a1)
+                vote_mfma<G, PER, true>(tile, a0, rows - b, vc, bf, g, dummy_row, lane);
+        }
+    }
+    if (extra) {
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int j = first_col + 64 * q + lane;
+            const bool voted = (j >= 0 && j < g.n_theta) || (PER && (j == -1 || j == g.n_theta));
+            if (voted) lds_add(cell_of<G, true, PER>(tile, (int)g.Bf, cl, ln, q), 0u - extra * ln.inc);
+        }
     }
     return n_valid;
+}
+
+// The wave's hits [hb, he) of an event of H hits: whole blocks of 8 (the granularity of a vote
+// instruction's hits), spread evenly over the NW waves.
+template <int NW>
+__device__ __forceinline__ void wave_hits(uint32_t H, int wave, uint32_t &hb, uint32_t &he) {
+    const uint32_t blocks = (H + 7u) >> 3, w = (uint32_t)__builtin_amdgcn_readfirstlane(wave);   // scalar
+    hb = min(H, (uint32_t)((uint64_t)blocks * w / NW) * 8u);
+    he = min(H, (uint32_t)((uint64_t)blocks * (w + 1u) / NW) * 8u);
 }
 
 // Step 4 on rows [16*u, 16*u + 16) of the lane's columns: bit b of mask[q] is set iff cell
@@ -400,11 +499,17 @@ __device__ __forceinline__ void store_peak(hough_peak *out, uint32_t j, uint32_t
     *p = make_uint2((j & 0xffffu) | (k << 16), c);
 }
 
+// Dwords per word row of the fused kernels' dilated words: one more than the tile's columns, so
+// that the words of one column lie in different banks (lane = hit lookups) as well as one word
+// of different columns (lane = column lookups).
+template <int G>
+constexpr uint32_t kDilPitch = 64u * G + 1u;
+
 // Step 4 (listing) and the retention marks of step 5, shared by all waves.  pmask[wd * TW + c]
 // holds the peak bits of column c, rows 32*wd ...  Every wave computes the per-column peak
 // counts and their prefix over the tile's columns (raster order is column-major), then lists
 // the peaks of its own words at base + (peaks in earlier columns) + (peaks above in the same
-// column).  It also writes the dilated words dil[wd * TW + c]: bit b set iff a peak of column c
+// column).  It also writes the dilated words dil[wd * kDilPitch + c]: bit b set iff a peak of column c
 // lies within rho_window rows of row 32*wd + b.  For rho_window < 32 a word follows from the
 // peak words above and below it; wider windows OR the row range of every peak into dil (which
 // the peak phase cleared).  colcnt (optional): each column's peak count, summed by the peak
@@ -425,7 +530,7 @@ __device__ uint32_t emit_and_dilate(const uint32_t *tile, const uint32_t *pmask,
                                     int wave, int n_waves, float4 *tpk = nullptr,
                                     const Cols<G> *cl = nullptr, const uint32_t *colcnt = nullptr,
                                     uint32_t *edge = nullptr) {
-    constexpr int TW = 64 * G, ST = Lane<G, P>::STRIDE;
+    constexpr int TW = 64 * G, DP = (int)kDilPitch<G>, ST = Lane<G, P>::STRIDE;
     const int W = g.rho_window;
     uint32_t colbase[G];
     uint32_t carry = 0;
@@ -454,7 +559,7 @@ __device__ uint32_t emit_and_dilate(const uint32_t *tile, const uint32_t *pmask,
                 uint32_t d = m;
                 for (int sft = 1; sft <= W; ++sft)
                     d |= (m << sft) | (m >> sft) | (up >> (32 - sft)) | (dn << (32 - sft));
-                dil[wd * TW + c] = d;
+                dil[wd * DP + c] = d;
             }
             if (!m) continue;
             uint32_t idx = base + colbase[q];
@@ -478,7 +583,7 @@ __device__ uint32_t emit_and_dilate(const uint32_t *tile, const uint32_t *pmask,
                     for (int w = max(lo >> 5, w0); w <= min(hi >> 5, w1 - 1); ++w) {
                         const int a = max(lo, w * 32) - w * 32, e = min(hi, w * 32 + 31) - w * 32;
                         const uint32_t rm = (e == 31 ? ~0u : ((1u << (e + 1)) - 1u)) & ~((1u << a) - 1u);
-                        __hip_atomic_fetch_or(&dil[w * TW + c], rm, __ATOMIC_RELAXED,
+                        __hip_atomic_fetch_or(&dil[w * DP + c], rm, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
                 }
@@ -489,8 +594,8 @@ __device__ uint32_t emit_and_dilate(const uint32_t *tile, const uint32_t *pmask,
 }
 
 // Step 5 on the current tile: a hit is kept when its own cell in some column of the tile has
-// its dil bit set.  Returns bit 0 set iff kept.
-template <int G>
+// its dil bit set.  Returns bit 0 set iff kept.  PITCH: dwords per word row of dil.
+template <int G, uint32_t PITCH>
 __device__ __forceinline__ uint32_t lookup1(const uint32_t *dil, float u, float v, bool checked,
                                             const Cols<G> &cl, int lane, float nrho_f) {
     uint32_t m = 0;
@@ -500,12 +605,12 @@ __device__ __forceinline__ uint32_t lookup1(const uint32_t *dil, float u, float 
         const float t = __builtin_fmaf(u, cl.C[q], w);
         if (!checked || (t >= 0.0f && t < nrho_f)) {
             const uint32_t k = (uint32_t)(int)t;
-            // word k / 32 of the column (a shift and one shift-add: the empty asm keeps the
-            // compiler from turning the pair into shift, mask and add), then bit k mod 32 (the
-            // bit-field extract takes its offset modulo 32)
+            // word k / 32 of the column (a shift and one multiply- or shift-add: the empty asm
+            // keeps the compiler from regrouping the pair), then bit k mod 32 (the bit-field
+            // extract takes its offset modulo 32)
             uint32_t kw = k >> 5;
             asm("" : "+v"(kw));
-            m |= __builtin_amdgcn_ubfe(dil[kw * (64u * G) + 64u * q + (uint32_t)lane], k, 1u);
+            m |= __builtin_amdgcn_ubfe(dil[__umul24(kw, PITCH) + 64u * q + (uint32_t)lane], k, 1u);
         }
     }
     return m;
@@ -526,7 +631,7 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
 // time so that their reads are in flight together.  Each lane gathers its own column's verdicts
 // as bits (hit h at bit h mod 32 of one of two words) and one OR across the wave at the end
 // turns them into the mask of kept stage slots.
-template <int G>
+template <int G, uint32_t PITCH>
 __device__ __forceinline__ uint64_t lookup_staged(const uint32_t *dil, const float2 *st, StageCount n,
                                                   const Cols<G> &cl, int lane, float nrho_f) {
     const float4 *st4 = reinterpret_cast<const float4 *>(st);
@@ -546,7 +651,7 @@ __device__ __forceinline__ uint64_t lookup_staged(const uint32_t *dil, const flo
                 kk[i][q] = (uint32_t)(int)t;
                 uint32_t kw = kk[i][q] >> 5;        // see lookup1
                 asm("" : "+v"(kw));
-                wd[i][q] = kw * (64u * G) + 64u * q + (uint32_t)lane;
+                wd[i][q] = __umul24(kw, PITCH) + 64u * q + (uint32_t)lane;
             }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -566,7 +671,7 @@ __device__ __forceinline__ uint64_t lookup_staged(const uint32_t *dil, const flo
     for (; h + 4 <= n.safe; h += 4) four(w[1], h - 32);
     for (; h < n.total; ++h) {
         const float2 p = st[h];
-        const uint32_t m = lookup1<G>(dil, p.x, p.y, h >= n.safe, cl, lane, nrho_f);
+        const uint32_t m = lookup1<G, PITCH>(dil, p.x, p.y, h >= n.safe, cl, lane, nrho_f);
         if (h < 32) w[0] |= m << h; else w[1] |= m << (h - 32);
     }
     if (n.total == 0) return 0ull;
@@ -577,24 +682,73 @@ __device__ __forceinline__ uint64_t lookup_staged(const uint32_t *dil, const flo
 
 __device__ __forceinline__ uint64_t low_bits(uint32_t n) { return n >= 64 ? ~0ull : ((1ull << n) - 1ull); }
 
+// Lookups of up to 64 hits whose votes are all in range, lane = column: the hits of the lanes in
+// `who` are compacted through the wave's stage (padded to a multiple of four with u = v = 0) and
+// looked up four at a time.  Returns the lanes of `who` that are kept.
+template <int G>
+__device__ __forceinline__ uint64_t lookup_lanes(const uint32_t *dil, float2 *st, float u, float v, uint64_t who,
+                                                 const Cols<G> &cl, const GridArgs &g, int lane) {
+    if (!who) return 0ull;
+    const uint32_t n = (uint32_t)__popcll(who), pos = mbcnt(who);
+    const bool me = (who >> lane) & 1ull;
+    if (me) st[pos] = make_float2(u, v);
+    if (lane < 3 && n + (uint32_t)lane < 64u) st[n + lane] = make_float2(0.0f, 0.0f);
+    wave_sync();
+    const uint32_t n4 = (n + 3u) & ~3u;
+    const uint64_t found = lookup_staged<G, kDilPitch<G>>(dil, st, StageCount{n4, n4}, cl, lane, g.nrho_f);
+    wave_sync();
+    return __ballot(me && ((found >> pos) & 1ull));
+}
+
+// The same for hits whose votes may leave the grid, one at a time with the literal range test.
+template <int G>
+__device__ __forceinline__ uint64_t lookup_checked(const uint32_t *dil, float u, float v, uint64_t who,
+                                                   const Cols<G> &cl, const GridArgs &g, int lane) {
+    uint64_t kept = 0;
+    for (; who; who &= who - 1ull) {
+        const int m = __builtin_ctzll(who);
+        const float um = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(u), m));
+        const float vm = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), m));
+        if (__ballot(lookup1<G, kDilPitch<G>>(dil, um, vm, true, cl, lane, g.nrho_f) != 0u)) kept |= 1ull << m;
+    }
+    return kept;
+}
+
 // Hits of a wave's range that are valid and not yet kept, once there are at most 64 of them:
-// lane l holds one entry (an event-local hit index, bit 31 set for a later copy of a hit under
-// duplicate suppression) while bit l of `live` is set.  Later tiles look up only these instead
-// of mapping the whole range again.
+// lane l holds one entry (an event-local hit index and the mapped hit; bit 31 of idx set for a
+// later copy of a hit under duplicate suppression, bit 30 when every vote is in range) while bit
+// l of `live` is set.  Later tiles look up only these instead of mapping the whole range again.
 struct Pending {
     uint32_t idx;
+    float u, v;
     uint64_t live;   // wave-uniform
     bool on;         // wave-uniform
 };
+constexpr uint32_t kPendingCopy = 0x80000000u, kPendingSafe = 0x40000000u, kPendingIdx = 0x3fffffffu;
 
-// Collect the valid unkept hits of [hb, he) into the pending list (caller: at most 64 of
-// them): their indices are compacted through the wave's stage.
-__device__ void build_pending(Pending &pd, float2 *st, const float *x, const float *y,
-                             const uint8_t *ke, uint32_t hb, uint32_t he, int lane) {
+// Append the entries of the lanes in `who` after the n entries held (n + |who| <= 64): a push
+// across lanes that is a permutation of all 64 (the other lanes' values are dropped).
+__device__ __forceinline__ void push_pending(Pending &pd, uint32_t n, uint64_t who, uint32_t idx, float u, float v,
+                                             int lane) {
+    const uint32_t c = (uint32_t)__popcll(who);
+    const uint32_t to = ((who >> lane) & 1ull) ? n + mbcnt(who) : n + c + mbcnt(~who);
+    const int at = (int)((to & 63u) << 2);
+    const uint32_t ri = (uint32_t)__builtin_amdgcn_ds_permute(at, (int)idx);
+    const uint32_t ru = (uint32_t)__builtin_amdgcn_ds_permute(at, (int)__float_as_uint(u));
+    const uint32_t rv = (uint32_t)__builtin_amdgcn_ds_permute(at, (int)__float_as_uint(v));
+    if ((uint32_t)lane >= n && (uint32_t)lane < n + c) {
+        pd.idx = ri;
+        pd.u = __uint_as_float(ru);
+        pd.v = __uint_as_float(rv);
+    }
+}
+
+// Collect the valid unkept hits of [hb, he) into the pending list (caller: at most 64 of them).
+__device__ void build_pending(Pending &pd, const float *x, const float *y, const uint8_t *ke, uint32_t hb,
+                              uint32_t he, const GridArgs &g, int lane) {
     // runs once per wave and event: keep the compiler from holding its per-lane addresses in
     // registers across the whole event
     asm volatile("" : "+v"(lane));
-    uint32_t *st32 = reinterpret_cast<uint32_t *>(st);
     uint32_t n = 0;
     for (uint32_t base = hb; base < he; base += 64) {
         const uint32_t i = base + lane;
@@ -603,68 +757,119 @@ __device__ void build_pending(Pending &pd, float2 *st, const float *x, const flo
         float xi = 0.0f, yi = 0.0f;
         if (cand) { xi = x[i]; yi = y[i]; }
         float u, v;
-        const bool ok = conformal(xi, yi, u, v) && cand;
-        const uint64_t b = __ballot(ok);
-        if (ok) st32[n + mbcnt(b)] = i | ((kv & (uint32_t)kKeepDuplicate) << 30);
+        const uint64_t b = __ballot(conformal(xi, yi, u, v) && cand);
+        if (!b) continue;
+        push_pending(pd, n, b,
+                     i | ((kv & (uint32_t)kKeepDuplicate) << 30) | (all_in_range(u, v, g) ? kPendingSafe : 0u), u, v,
+                     lane);
         n += (uint32_t)__popcll(b);
     }
-    wave_sync();
     pd.on = true;
     pd.live = low_bits(n);
-    if ((uint32_t)lane < n) pd.idx = st32[lane];
-    wave_sync();
 }
 
-// Step 5 for the pending list: map and stage the live entries, look them up (every lookup
-// takes the literal range test), write the keep byte of each kept entry and drop it.
+// The keep bytes of the pending entries in `kept`, and the list without them.
+__device__ __forceinline__ uint32_t drop_pending(Pending &pd, uint64_t kept, uint8_t *ke, int lane) {
+    if ((kept >> lane) & 1ull)
+        ke[pd.idx & kPendingIdx] = (uint8_t)(1u | ((pd.idx & kPendingCopy) ? (uint32_t)kKeepDuplicate : 0u));
+    pd.live &= ~kept;
+    return (uint32_t)__popcll(kept);
+}
+
+// Step 5 for the pending list: look the live entries up, write the keep byte of each kept entry
+// and drop it.
 template <int G>
-__device__ uint32_t retain_pending(Pending &pd, const uint32_t *dil, float2 *st, const float *x,
-                                   const float *y, uint8_t *ke, const Cols<G> &cl,
+__device__ uint32_t retain_pending(Pending &pd, const uint32_t *dil, float2 *st, uint8_t *ke, const Cols<G> &cl,
                                    const GridArgs &g, int lane) {
     if (pd.live == 0ull) return 0u;
-    const bool me = (pd.live >> lane) & 1ull;
-    const uint32_t pos = mbcnt(pd.live);
-    const uint32_t idx = pd.idx & 0x7fffffffu;
-    if (me) {
-        float u, v;
-        (void)conformal(x[idx], y[idx], u, v);
-        st[pos] = make_float2(u, v);
-    }
-    wave_sync();
-    const uint64_t kept = lookup_staged<G>(dil, st, StageCount{0u, (uint32_t)__popcll(pd.live)}, cl,
-                                           lane, g.nrho_f);
-    const bool k_me = me && ((kept >> pos) & 1ull);
-    if (k_me) ke[idx] = (uint8_t)(1u | ((pd.idx >> 30) & (uint32_t)kKeepDuplicate));
-    const uint64_t kept_lanes = __ballot(k_me);
-    pd.live &= ~kept_lanes;
-    wave_sync();
-    return (uint32_t)__popcll(kept_lanes);
+    const uint64_t safe = __ballot((pd.idx & kPendingSafe) != 0u) & pd.live;
+    uint64_t kept = lookup_lanes<G>(dil, st, pd.u, pd.v, safe, cl, g, lane);
+    kept |= lookup_checked<G>(dil, pd.u, pd.v, pd.live & ~safe, cl, g, lane);
+    return drop_pending(pd, kept, ke, lane);
 }
 
-// Step 5 over the whole range [hb, he): every unkept valid hit is mapped again, staged and
-// looked up; each lane sets the kept bit of its own hit's keep byte when its stage slot was
-// kept (the event's keep bytes were cleared, or written by the duplicate pass, when it
-// started, and only this lane touches them).  Returns
-// the number of hits newly kept; `left` receives how many valid hits remain unkept.
+// Step 5 for 64 hits, one per lane, a few of the tile's columns at a time: lane l looks its own
+// bin up in the same column as every other lane, so a column costs 7 instructions for all 64 hits
+// where the lookup with lane = column costs 8 per hit.  On a tile with many peaks most hits meet
+// one in a few columns: rounds of 8 columns, evenly spaced, until a round no longer pays (each
+// hit it keeps spares the lookup of that hit in every column).  Returns the mask of kept lanes
+// among `want` (hits whose votes are all in range; the other lanes' u and v are 0, so their bins
+// are in range too).  Halo and out-of-grid columns have no dilated bits.
+// (10,000 events, 360 x 256: 839 -> 739 M VALU instructions with the pending list's lookups four
+// at a time; with the phases' registers kept apart, see opaque(), the batch takes 1.60 ms, 1.88
+// with the VALU vote and lane = column lookups alone)
 template <int G>
-__device__ uint32_t retain_range(const uint32_t *dil, float2 *st, const float *x,
-                                 const float *y, uint8_t *ke, uint32_t hb, uint32_t he,
-                                 const Cols<G> &cl, const GridArgs &g, int lane, uint32_t &left) {
-    uint32_t unused = 0, newly = 0;
+__device__ __forceinline__ uint64_t kept_by_columns(const uint32_t *dil, float u, float v, uint64_t want,
+                                                    int first_col, const GridArgs &g) {
+    typedef const __attribute__((address_space(4))) float *cfloat;       // read by scalar loads
+    const cfloat C = (cfloat)(uintptr_t)g.C, S = (cfloat)(uintptr_t)g.S;
+    uint32_t m = 0;
+    uint64_t kept = 0;
+    for (int r = 0; r < 8 * G; ++r) {
+        const int c0 = (5 * r + 2) & (8 * G - 1);                         // rounds spread over the tile too
+        uint32_t word[8], k[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int c = c0 + 8 * G * i, j = min(max(first_col + c, 0), g.n_theta - 1);
+            const float t = __builtin_fmaf(u, C[j], __builtin_fmaf(v, S[j], g.Bf));
+            k[i] = (uint32_t)(int)t;
+            uint32_t kw = k[i] >> 5;                                      // see lookup1
+            asm("" : "+v"(kw));
+            word[i] = dil[__umul24(kw, kDilPitch<G>) + (uint32_t)c];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m |= word[i] >> (k[i] & 31u);
+        const uint64_t now = __ballot((m & 1u) != 0u) & want;
+        const uint32_t newly = (uint32_t)__popcll(now & ~kept), left = (uint32_t)__popcll(want & ~now);
+        kept = now;
+        if (newly < 8u || left < 8u) break;
+    }
+    return kept;
+}
+
+// Step 5 over the whole range [hb, he): every unkept valid hit is mapped again and looked up
+// (many: kept_by_columns first, then the hits it leaves with lane = column); each lane sets the
+// kept bit of its own hit's keep byte (the event's keep bytes were cleared, or written by the
+// duplicate pass, when it started, and only this lane touches them).  The next 64 hits and keep
+// bytes are loaded while these are looked up.  When at most 64 valid hits remain unkept they
+// become the pending list.  Returns the number of hits newly kept; `left` receives how many
+// valid hits remain unkept.
+template <int G>
+__device__ uint32_t retain_range(Pending &pd, const uint32_t *dil, float2 *st, const float *x, const float *y,
+                                 uint8_t *ke, uint32_t hb, uint32_t he, const Cols<G> &cl, const GridArgs &g,
+                                 int first_col, bool many, int lane, uint32_t &left) {
+    uint32_t newly = 0;
     left = 0;
+    uint32_t kn = 1u;
+    float xn = 0.0f, yn = 0.0f;
+    if (hb + lane < he) { kn = ke[hb + lane]; xn = x[hb + lane]; yn = y[hb + lane]; }
     for (uint32_t base = hb; base < he; base += 64) {
         const uint32_t i = base + lane;
-        const uint32_t kv = (i < he) ? ke[i] : 1u;
-        const bool done = (i < he) && (kv & 1u);
-        if (__ballot((i < he) && !done) == 0ull) continue;      // whole chunk already kept
-        int slot;
-        const StageCount n = stage_hits(st, x, y, base, he, done, g, lane, unused, slot);
-        const uint64_t kept = lookup_staged<G>(dil, st, n, cl, lane, g.nrho_f);
-        if (slot >= 0 && ((kept >> slot) & 1ull)) ke[i] = (uint8_t)(kv | 1u);
-        const uint32_t nk = (uint32_t)__popcll(kept);
-        newly += nk;
-        left += n.total - nk;
-        wave_sync();
+        const uint32_t kv = kn;
+        const float xi = xn, yi = yn;
+        if (i + 64 < he) { kn = ke[i + 64]; xn = x[i + 64]; yn = y[i + 64]; }
+        const bool todo = (i < he) && !(kv & 1u);
+        if (__ballot(todo) == 0ull) continue;                   // whole chunk already kept
+        float u, v;
+        const bool valid = conformal(todo ? xi : 0.0f, todo ? yi : 0.0f, u, v) && todo;
+        const bool safe = valid && all_in_range(u, v, g);
+        const uint64_t bs = __ballot(safe), bv = __ballot(valid);
+        uint64_t kept = 0;
+        if (many && bs) kept = kept_by_columns<G>(dil, safe ? u : 0.0f, safe ? v : 0.0f, bs, first_col, g);
+        kept |= lookup_lanes<G>(dil, st, u, v, bs & ~kept, cl, g, lane);
+        kept |= lookup_checked<G>(dil, u, v, bv & ~bs, cl, g, lane);
+        if ((kept >> lane) & 1ull) ke[i] = (uint8_t)(kv | 1u);
+        newly += (uint32_t)__popcll(kept);
+        const uint64_t rest = bv & ~kept;
+        const uint32_t c = (uint32_t)__popcll(rest);
+        if (c && left + c <= 64u)
+            push_pending(pd, left, rest, i | ((kv & (uint32_t)kKeepDuplicate) << 30) | (safe ? kPendingSafe : 0u), u, v,
+                         lane);
+        left += c;
+    }
+    if (left <= 64u) {
+        pd.on = true;
+        pd.live = low_bits(left);
     }
     return newly;
 }
@@ -709,17 +914,11 @@ __device__ __forceinline__ uint64_t kept_by_peaks(const float4 *tpk, uint32_t np
 }
 
 // retain_pending with the tile's peak list.
-__device__ uint32_t retain_pending_peaks(Pending &pd, const float4 *tpk, uint32_t np, bool edge, const float *x,
-                                         const float *y, uint8_t *ke, const GridArgs &g, int lane) {
+__device__ uint32_t retain_pending_peaks(Pending &pd, const float4 *tpk, uint32_t np, bool edge, uint8_t *ke,
+                                         const GridArgs &g, int lane) {
     if (pd.live == 0ull) return 0u;
     const bool me = (pd.live >> lane) & 1ull;
-    const uint32_t idx = pd.idx & 0x7fffffffu;
-    float u = 0.0f, v = 0.0f;
-    if (me) (void)conformal(x[idx], y[idx], u, v);
-    const uint64_t kept_lanes = kept_by_peaks(tpk, np, u, v, me, edge, g);
-    if ((kept_lanes >> lane) & 1ull) ke[idx] = (uint8_t)(1u | ((pd.idx >> 30) & (uint32_t)kKeepDuplicate));
-    pd.live &= ~kept_lanes;
-    return (uint32_t)__popcll(kept_lanes);
+    return drop_pending(pd, kept_by_peaks(tpk, np, me ? pd.u : 0.0f, me ? pd.v : 0.0f, me, edge, g), ke, lane);
 }
 
 // retain_range with the tile's peak list: each lane maps and tests its own unkept hit.
@@ -805,8 +1004,8 @@ __device__ uint32_t vote_group_to_acc(const GridArgs &g, const float *__restrict
     const bool whole = r0 == 0 && r1 == g.n_rho;
     const int rows = r1 - r0;
     uint32_t *tile = lds;                                                  // [(rows + 1) * 32]
-    float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)(rows + 1) * L::STRIDE);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)(rows + 1) * L::STRIDE);     // slabs only
+    const int lane = threadIdx.x & 63, wave = wave_id();
     const int first = group * 64;
     const L ln(lane);
     const Cols<1> cl = load_cols<1>(g, first, lane, L::STRIDE, ln.col);
@@ -819,10 +1018,12 @@ __device__ uint32_t vote_group_to_acc(const GridArgs &g, const float *__restrict
         for (int i = threadIdx.x; i < (rows + 1) * L::STRIDE / 4; i += NW * 64)
             reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
-        const uint32_t hb = c0 + (uint32_t)((uint64_t)(c1 - c0) * wave / NW);
-        const uint32_t he = c0 + (uint32_t)((uint64_t)(c1 - c0) * (wave + 1) / NW);
+        uint32_t hb, he;
+        wave_hits<NW>(c1 - c0, wave, hb, he);
+        hb += c0;
+        he += c0;
         if (whole)
-            vote_range<1, true>(tile, stage + wave * 64, x, y, hb, he, cl, ln, g, lane, bad, dup);
+            vote_range<1>(tile, x, y, hb, he, cl, g, first, lane, bad, g.nrho_f, dup);
         else
             vote_range_slab<NW>(tile, stage + wave * 64, x, y, hb, he, cl, ln, g, lane, bad, dup, r0, r1);
         __syncthreads();
@@ -1467,7 +1668,7 @@ __global__ __launch_bounds__(NW * 64) void k_retain(GridArgs g, const float *__r
             cl.C[0] = row_in ? g.C[j] : 0.0f;
             cl.S[0] = row_in ? g.S[j] : 0.0f;
             cl.B[0] = row_in ? g.Bf : 0.0f;
-            kept |= lookup_staged<1>(dil + (size_t)q * words * 64, st, n, cl, lane, g.nrho_f);
+            kept |= lookup_staged<1, 64u>(dil + (size_t)q * words * 64, st, n, cl, lane, g.nrho_f);
         }
         __syncthreads();
     }
@@ -1543,7 +1744,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
                                                                                             int n_tiles, int nwords,
                                                                                             int win) {
     using L = Lane<G, true>;
-    constexpr int TW = L::TW, ST = L::STRIDE, OUT = TW - 2, NT = NW * 64;
+    constexpr int TW = L::TW, ST = L::STRIDE, DP = (int)kDilPitch<G>, OUT = TW - 2, NT = NW * 64;
     static_assert(!WIN || (G == 1 && !PER), "windowed tiles: one column group, theta not periodic");
     extern __shared__ __align__(16) uint32_t lds[];
     // tile rows (dummy row included) and peak-word rows of the LDS layout
@@ -1552,19 +1753,18 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
     uint32_t *tile = lds;                                                  // [rows_t * ST]
     float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)rows_t * ST);   // [NW * 64]
     uint32_t *pmask = reinterpret_cast<uint32_t *>(stage + NW * 64);       // [nwp * TW]
-    uint32_t *dil = pmask + (size_t)nwp * TW;                              // [(nwp + 1) * TW]
-    float4 *tpk = reinterpret_cast<float4 *>(dil + (size_t)(nwp + 1) * TW);   // [kTilePeaks]
-    uint32_t *colcnt = reinterpret_cast<uint32_t *>(tpk + kTilePeaks);            // [TW] peaks per column
+    float4 *tpk = reinterpret_cast<float4 *>(pmask + (size_t)nwp * TW);    // [kTilePeaks]
+    uint32_t *colcnt = reinterpret_cast<uint32_t *>(tpk + kTilePeaks);     // [TW] peaks per column
+    uint32_t *dil = colcnt + TW;                                           // [(nwp + 1) * DP]
     __shared__ uint32_t s_event, s_npeaks, s_flags, s_nvalid, s_nkept, s_max, s_minr2, s_wb, s_fit, s_edge;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const L ln(lane);
+    const int lane = threadIdx.x & 63, wave = wave_id();
     const int tile_words4 = rows_t * ST / 4;
 
     // the tile is all zero at the start of every tile; the dil row past the last word is read
     // by the out-of-grid columns' dummy row and stays zero
     for (int i = threadIdx.x; i < tile_words4; i += NT)
         reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
-    for (int i = threadIdx.x; i < TW; i += NT) dil[nwp * TW + i] = 0u;
+    for (int i = threadIdx.x; i < DP; i += NT) dil[nwp * DP + i] = 0u;
     for (int i = threadIdx.x; i < TW; i += NT) colcnt[i] = 0u;   // zero again after each listing
     PhaseClock pc;
     pc.start();
@@ -1614,8 +1814,8 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
             __syncthreads();
             continue;
         }
-        const uint32_t hb = (uint32_t)((uint64_t)H * wave / NW);
-        const uint32_t he = (uint32_t)((uint64_t)H * (wave + 1) / NW);
+        uint32_t hb, he;
+        wave_hits<NW>(H, wave, hb, he);
         const float *xe = a.x + h0, *ye = a.y + h0;
         hough_peak *pe = a.peaks ? a.peaks + (size_t)e * a.max_peaks : nullptr;
         const uint32_t cap = pe ? a.max_peaks : 0u;
@@ -1674,19 +1874,20 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
         // dilated words in word row w - wb / 32
         uint32_t *tile_w = WIN ? tile + (ptrdiff_t)(1 - wb) * ST : tile;
         uint32_t *pmask_w = WIN ? pmask - (ptrdiff_t)(wb >> 5) * TW : pmask;
-        uint32_t *dil_w = WIN ? dil - (ptrdiff_t)(wb >> 5) * TW : dil;
+        uint32_t *dil_w = WIN ? dil - (ptrdiff_t)(wb >> 5) * DP : dil;
         const int w_lo = WIN ? (wb >> 5) : 0;
         const float dummy_row = WIN ? (float)(wb + win + 1) : -1.0f;
         uint32_t thr = g.threshold;
-        if (a.frac_den) {
+        if (SP && a.frac_den) {              // (such launches take the SP kernels)
             // relative threshold: a first pass votes every tile only to find the event's
             // largest count (rows 0 .. n_rho-1: the dummy row is not part of the grid)
             uint32_t mloc = 0, bad0 = 0;
 #pragma unroll 1
             for (int t = 0; t < n_tiles; ++t) {
-                const Cols<G> cl = load_cols<G, PER>(g, t * OUT - 1, lane, ST, ln.col, dummy_row);
-                (void)vote_range<G, true, PER>(tile_w, stage + wave * 64, xe, ye, hb, he, cl, ln, g, lane, bad0,
-                                               g.dedup ? ke : nullptr);
+                const int vl = opaque(lane);
+                const Cols<G> cl = load_cols<G, PER>(g, t * OUT - 1, vl, ST, L(vl).col, dummy_row);
+                (void)vote_range<G, PER>(tile_w, xe, ye, hb, he, cl, g, t * OUT - 1, vl, bad0,
+                                         WIN ? dummy_row : g.nrho_f, g.dedup ? ke : nullptr);
                 __syncthreads();
                 // every tile row but the dummy one (a window's halo rows stay zero)
 #pragma unroll 1
@@ -1709,6 +1910,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
         pc.count(kPhaseEvents, 1u);
         Pending pd;
         pd.idx = 0u;
+        pd.u = pd.v = 0.0f;
         pd.live = 0ull;
         pd.on = false;
         uint32_t unkept = he - hb;           // this wave's unkept hits after its last full pass
@@ -1751,13 +1953,16 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
         const bool sparse_ev = SP && (uint64_t)H * 4u < (uint64_t)thr * (uint32_t)g.n_rho;
         for (int t = 0; t < n_tiles; ++t) {
             const int first = t * OUT - 1;      // grid column of lane 0 of group 0
-            const Cols<G> cl = load_cols<G, PER>(g, first, lane, ST, ln.col, dummy_row);
-            const uint32_t nv = vote_range<G, true, PER>(tile_w, stage + wave * 64, xe, ye, hb, he, cl, ln, g, lane,
-                                                         bad, g.dedup ? ke : nullptr);
+            const int vl = opaque(lane);
+            const Cols<G> cl = load_cols<G, PER>(g, first, vl, ST, L(vl).col, dummy_row);
+            const uint32_t nv = vote_range<G, PER>(tile_w, xe, ye, hb, he, cl, g, first, vl, bad,
+                                                   WIN ? dummy_row : g.nrho_f, g.dedup ? ke : nullptr);
             if (t == 0 && lane == 0 && nv) atomicAdd(&s_nvalid, nv);
             __syncthreads();
             pc.mark(kPhaseVote);
             if (t == 0) pc.count(kPhaseStagedHits, (uint64_t)s_nvalid * (uint64_t)n_tiles);
+            const int pl = opaque(lane);
+            const L ln(pl);
             // 16-row units of grid rows; a windowed tile tests the units inside its window (the
             // halo rows above and below are in the tile, so no unit needs bounds tests) and
             // writes zero for the other halves of the words it touches
@@ -1766,23 +1971,23 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
                 const bool interior = WIN || (u >= 1 && (u + 1) * kPeakRows < g.n_rho);
                 constexpr bool UR = NW == 16 || WIN;     // launch bound of 4 waves per SIMD: registers to spare
                 if ((WIN && (u * kPeakRows < wb || (u + 1) * kPeakRows > wb + win)) ||
-                    (sparse_ev && interior && !(PER && (t == 0 || t == n_tiles - 1)) && unit_below<G>(tile_w, u, thr, lane))) {
+                    (sparse_ev && interior && !(PER && (t == 0 || t == n_tiles - 1)) && unit_below<G>(tile_w, u, thr, pl))) {
 #pragma unroll
                     for (int q = 0; q < G; ++q) m[q] = 0u;
                 } else if (PER && (t == 0 || t == n_tiles - 1)) {
                     if (interior)
-                        peak_rows<false, G, true, true, UR>(tile, u, g.n_rho, thr, ln, lane, m, first, g.n_theta);
+                        peak_rows<false, G, true, true, UR>(tile, u, g.n_rho, thr, ln, pl, m, first, g.n_theta);
                     else
-                        peak_rows<true, G, true, true, UR>(tile, u, g.n_rho, thr, ln, lane, m, first, g.n_theta);
+                        peak_rows<true, G, true, true, UR>(tile, u, g.n_rho, thr, ln, pl, m, first, g.n_theta);
                 } else if (interior) {
-                    peak_rows<false, G, true, false, UR>(tile_w, u, g.n_rho, thr, ln, lane, m);
+                    peak_rows<false, G, true, false, UR>(tile_w, u, g.n_rho, thr, ln, pl, m);
                 } else {
-                    peak_rows<true, G, true, false, UR>(tile_w, u, g.n_rho, thr, ln, lane, m);
+                    peak_rows<true, G, true, false, UR>(tile_w, u, g.n_rho, thr, ln, pl, m);
                 }
                 uint16_t *pm16 = reinterpret_cast<uint16_t *>(pmask_w);
 #pragma unroll
                 for (int q = 0; q < G; ++q) {
-                    const int c = 64 * q + lane;
+                    const int c = 64 * q + pl;
                     const bool out_col = (c >= 1) && (c <= TW - 2) && (first + c < g.n_theta);
                     pm16[((u >> 1) * TW + c) * 2 + (u & 1)] = out_col ? (uint16_t)m[q] : (uint16_t)0;
                     if (out_col && m[q]) atomicAdd(&colcnt[c], (uint32_t)__popc(m[q]));
@@ -1790,18 +1995,19 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
             }
             if (g.rho_window >= 32) {
 #pragma unroll 1
-                for (int i = threadIdx.x; i < nwp * TW; i += NT) dil[i] = 0u;
+                for (int i = threadIdx.x; i < nwp * DP; i += NT) dil[i] = 0u;
             }
             if (SP && threadIdx.x == 0) s_edge = 0u;     // set by the listing for a peak near a rho edge
             __syncthreads();
             pc.mark(kPhasePeaks);
             const uint32_t base = s_npeaks;
+            const int el = opaque(lane);
             uint32_t np;
             if constexpr (SP)
-                np = emit_and_dilate<G, true>(tile_w, pmask_w, dil_w, w_lo, nwp, first, g, pe, cap, base, ln, lane,
+                np = emit_and_dilate<G, true>(tile_w, pmask_w, dil_w, w_lo, nwp, first, g, pe, cap, base, L(el), el,
                                               wave, NW, tpk, &cl, colcnt, &s_edge);
             else
-                np = emit_and_dilate<G, true>(tile_w, pmask_w, dil_w, w_lo, nwp, first, g, pe, cap, base, ln, lane,
+                np = emit_and_dilate<G, true>(tile_w, pmask_w, dil_w, w_lo, nwp, first, g, pe, cap, base, L(el), el,
                                               wave, NW, nullptr, nullptr, colcnt);
             __syncthreads();
             pc.mark(kPhaseList);
@@ -1821,6 +2027,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
                 // that beats looking the unkept hits up in every column's dilated words (about 7
                 // per unkept hit, plus staging).  A flush of deferred peaks reuses the list's
                 // storage, so after one this tile looks its hits up in the dilated words.
+                const int rl = opaque(lane);
                 bool few = SP && np <= kTilePeaks;
                 const bool edge = SP && s_edge != 0u;
                 if (DEF && defn) {
@@ -1832,16 +2039,20 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
                 if (pd.on) {
                     const uint32_t n = (uint32_t)__popcll(pd.live);
                     newly = (few && np * cp < n * 7u + 10u)
-                                ? retain_pending_peaks(pd, tpk, np, edge, xe, ye, ke, g, lane)
-                                : retain_pending<G>(pd, dil_w, stage + wave * 64, xe, ye, ke, cl, g, lane);
+                                ? retain_pending_peaks(pd, tpk, np, edge, ke, g, rl)
+                                : retain_pending<G>(pd, dil_w, stage + wave * 64, ke, cl, g, rl);
                 } else {
                     uint32_t left = 0;
                     const uint32_t chunks = (he - hb + 63u) >> 6;
-                    newly = (few && np * cp * chunks < unkept * 7u + chunks * 10u)
-                                ? retain_range_peaks(tpk, np, edge, xe, ye, ke, hb, he, g, lane, left)
-                                : retain_range<G>(dil_w, stage + wave * 64, xe, ye, ke, hb, he, cl, g, lane, left);
+                    if (few && np * cp * chunks < unkept * 7u + chunks * 10u) {
+                        newly = retain_range_peaks(tpk, np, edge, xe, ye, ke, hb, he, g, rl, left);
+                        if (left <= 64u) build_pending(pd, xe, ye, ke, hb, he, g, rl);
+                    } else {
+                        newly = retain_range<G>(pd, dil_w, stage + wave * 64, xe, ye, ke, hb, he, cl, g, first,
+                                                np * (2u * (uint32_t)g.rho_window + 1u) >= (uint32_t)g.n_rho, rl,
+                                                left);
+                    }
                     if (SP) unkept = left;
-                    if (left <= 64u) build_pending(pd, stage + wave * 64, xe, ye, ke, hb, he, lane);
                 }
                 if (lane == 0 && newly) atomicAdd(&s_nkept, newly);
             }
@@ -1899,7 +2110,7 @@ __device__ void retain_split(const uint32_t *dil, float2 *st, const float *x, co
         if (nb < he) { xn = x[nb]; yn = y[nb]; }
         int slot;
         const StageCount n = stage_values(st, xi, yi, base + lane < he, g, unused, slot);
-        const uint64_t kept = lookup_staged<G>(dil, st, n, cl, lane, g.nrho_f);
+        const uint64_t kept = lookup_staged<G, kDilPitch<G>>(dil, st, n, cl, lane, g.nrho_f);
         const uint64_t m = __ballot(slot >= 0 && ((kept >> slot) & 1ull));   // bit l: hit base + l
         const uint32_t sh = base & 31u;
         if (m && lane < 3) {
@@ -1918,22 +2129,21 @@ template <int NW, int G, bool PER>
 __global__ __launch_bounds__(NW * 64, G == 1 ? 6 : 4) void k_batch_split(GridArgs g, BatchArgs a, SplitArgs sp,
                                                                          int nwords) {
     using L = Lane<G, true>;
-    constexpr int TW = L::TW, ST = L::STRIDE, OUT = TW - 2, NT = NW * 64;
+    constexpr int TW = L::TW, ST = L::STRIDE, DP = (int)kDilPitch<G>, OUT = TW - 2, NT = NW * 64;
     extern __shared__ __align__(16) uint32_t lds[];
     uint32_t *tile = lds;                                                  // [(n_rho + 1) * ST]
     float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)(g.n_rho + 1) * ST);   // [NW * 64]
     uint32_t *pmask = reinterpret_cast<uint32_t *>(stage + NW * 64);       // [nwords * TW]
-    uint32_t *dil = pmask + (size_t)nwords * TW;                           // [(nwords + 1) * TW]
+    uint32_t *dil = pmask + (size_t)nwords * TW;                           // [(nwords + 1) * DP]
     __shared__ uint32_t s_item, s_flags, s_last;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const L ln(lane);
+    const int lane = threadIdx.x & 63, wave = wave_id();
     const int tile_words4 = (g.n_rho + 1) * ST / 4;
     const uint32_t T = sp.n_tiles;
     const uint32_t n_items = a.n_events * T;
 
     for (int i = threadIdx.x; i < tile_words4; i += NT)
         reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
-    for (int i = threadIdx.x; i < TW; i += NT) dil[nwords * TW + i] = 0u;
+    for (int i = threadIdx.x; i < DP; i += NT) dil[nwords * DP + i] = 0u;
 
     for (;;) {
         if (threadIdx.x == 0) {
@@ -1965,51 +2175,54 @@ __global__ __launch_bounds__(NW * 64, G == 1 ? 6 : 4) void k_batch_split(GridArg
             }
         } else if (H > 0) {
             if (g.dedup && H > kDedupMaxHits && threadIdx.x == 0 && t == 0) atomicOr(&s_flags, HOUGH_EV_DEDUP_SKIPPED);
-            const uint32_t hb = (uint32_t)((uint64_t)H * wave / NW);
-            const uint32_t he = (uint32_t)((uint64_t)H * (wave + 1) / NW);
+            uint32_t hb, he;
+            wave_hits<NW>(H, wave, hb, he);
             const float *xe = a.x + h0, *ye = a.y + h0;
             uint32_t bad = 0;
             const int first = (int)t * OUT - 1;
-            const Cols<G> cl = load_cols<G, PER>(g, first, lane, ST, ln.col);
-            vote_range<G, true, PER>(tile, stage + wave * 64, xe, ye, hb, he, cl, ln, g, lane, bad,
-                                     g.dedup ? ke : nullptr);
+            const int vl = opaque(lane);
+            const Cols<G> cl = load_cols<G, PER>(g, first, vl, ST, L(vl).col);
+            vote_range<G, PER>(tile, xe, ye, hb, he, cl, g, first, vl, bad, g.nrho_f, g.dedup ? ke : nullptr);
             if (t == 0 && __ballot(bad != 0u) && lane == 0) atomicOr(&s_flags, HOUGH_EV_INVALID_HITS);
             __syncthreads();
+            const int pl = opaque(lane);
+            const L ln(pl);
             for (int u = wave; u < 2 * nwords; u += NW) {
                 uint32_t m[G];
                 const bool interior = u >= 1 && (u + 1) * kPeakRows < g.n_rho;
                 if (PER && (t == 0 || t == T - 1)) {
                     if (interior)
-                        peak_rows<false, G, true, true>(tile, u, g.n_rho, g.threshold, ln, lane, m, first, g.n_theta);
+                        peak_rows<false, G, true, true>(tile, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
                     else
-                        peak_rows<true, G, true, true>(tile, u, g.n_rho, g.threshold, ln, lane, m, first, g.n_theta);
+                        peak_rows<true, G, true, true>(tile, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
                 } else if (interior) {
-                    peak_rows<false, G, true>(tile, u, g.n_rho, g.threshold, ln, lane, m);
+                    peak_rows<false, G, true>(tile, u, g.n_rho, g.threshold, ln, pl, m);
                 } else {
-                    peak_rows<true, G, true>(tile, u, g.n_rho, g.threshold, ln, lane, m);
+                    peak_rows<true, G, true>(tile, u, g.n_rho, g.threshold, ln, pl, m);
                 }
                 uint16_t *pm16 = reinterpret_cast<uint16_t *>(pmask);
 #pragma unroll
                 for (int q = 0; q < G; ++q) {
-                    const int c = 64 * q + lane;
+                    const int c = 64 * q + pl;
                     const bool out_col = (c >= 1) && (c <= TW - 2) && (first + c < g.n_theta);
                     pm16[((u >> 1) * TW + c) * 2 + (u & 1)] = out_col ? (uint16_t)m[q] : (uint16_t)0;
                 }
             }
             if (g.rho_window >= 32) {
 #pragma unroll 1
-                for (int i = threadIdx.x; i < nwords * TW; i += NT) dil[i] = 0u;
+                for (int i = threadIdx.x; i < nwords * DP; i += NT) dil[i] = 0u;
             }
             __syncthreads();
+            const int el = opaque(lane);
             hough_peak *slot = sp.staged + ((size_t)e * T + t) * sp.tile_cap;
             const uint32_t np = emit_and_dilate<G, true>(tile, pmask, dil, 0, nwords, first, g, slot, sp.tile_cap,
-                                                         0u, ln, lane, wave, NW);
+                                                         0u, L(el), el, wave, NW);
             __syncthreads();
             if (threadIdx.x == 0) sp.counts[(size_t)e * T + t] = np;
 #pragma unroll 1
             for (int i = threadIdx.x; i < tile_words4; i += NT)
                 reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
-            if (np) retain_split<G>(dil, stage + wave * 64, xe, ye, bits, hb, he, cl, g, lane);
+            if (np) retain_split<G>(dil, stage + wave * 64, xe, ye, bits, hb, he, cl, g, opaque(lane));
         }
         // publish this tile's results, then count it; the last tile of the event merges
         __threadfence();
@@ -2400,7 +2613,7 @@ __global__ __launch_bounds__(kSpillThreads) void k_spill(GridArgs g, BatchArgs a
                     if (__ballot(i < H && !done) == 0ull) continue;
                     int slot;
                     const StageCount n = stage_hits(&stage[wave][0], xe, ye, base, H, done, g, lane, unused, slot);
-                    const uint64_t kept = lookup_staged<1>(spill_tile, &stage[wave][0], n, cl, lane, g.nrho_f);
+                    const uint64_t kept = lookup_staged<1, 64u>(spill_tile, &stage[wave][0], n, cl, lane, g.nrho_f);
                     if (slot >= 0 && ((kept >> slot) & 1ull)) ke[i] = (uint8_t)(kv | 1u);
                     wave_sync();
                 }
@@ -2656,7 +2869,7 @@ size_t batch_lds_bytes(int n_rho, int waves, int groups, int win) {
     const size_t tw = 64u * groups;
     const size_t rows = win ? (size_t)win + 3 : (size_t)n_rho + 1;
     const size_t nwords = win ? (size_t)win / 32 + 1 : (size_t)(n_rho + 31) / 32;
-    return rows * (tw / 2) * 4 + (size_t)waves * kStageBytes + nwords * tw * 4 + (nwords + 1) * tw * 4 +
+    return rows * (tw / 2) * 4 + (size_t)waves * kStageBytes + nwords * tw * 4 + (nwords + 1) * (tw + 1) * 4 +
            kTilePeaks * sizeof(float4) + tw * 4;
 }
 
