@@ -15,7 +15,9 @@ struct hough_ctx {
     int device;
     float *d_tables;        // C[n_theta] then S[n_theta]
     uint32_t *d_work;       // [0], [1]: work and exit counters of the fused kernels; from [64]:
-                            // hough_peaks' per-block peak counts
+                            // hough_peaks' per-block peak counts; [8], [9]: the iterative
+                            // finder's running maximum and key count
+    uint64_t *d_iter_list;  // [kIterScanKeys] the iterative finder's listed candidates
     uint32_t *d_order;      // [kOrderMaxEvents] the fused kernel's largest-first schedule
     uint32_t *d_iter_bm;    // the iterative finder's suppression bitmap when it does not fit LDS
     hough::IterPlan iter1;  // the iterative finder on one event (hough_peaks_iterative)
@@ -45,17 +47,14 @@ int lds_limit_bytes(int device, size_t *out) {
 }
 
 // Tallest rho axis the library takes: the per-event path's kernels need an LDS slab of at least
-// one row (hough_vote), three theta rows of the grid (hough_peaks) and one 64-row group of
-// dilated words (hough_retain); batches of grids whose column does not fit the fused kernel's
+// one row (hough_vote) and four theta rows of the grid (hough_peaks); batches of grids whose column does not fit the fused kernel's
 // tile run through the spill path.
 constexpr int kMaxNRho = 8192;
 
 bool grid_fits(int n_rho, size_t limit) {
     if (n_rho > kMaxNRho) return false;
     if (hough::vote_slab_rows(n_rho, limit) < 1) return false;
-    if (hough::peak_block_waves(n_rho, limit) < 2) return false;
-    const size_t words = (size_t)(n_rho + 31) / 32;
-    return 8 * 64 * 8 + words * 64 * 4 + 512 <= limit;     // hough_retain's stages and one row group
+    return hough::peak_block_waves(1, n_rho, limit) >= 2;
 }
 
 bool fused_fits(int n_rho, size_t limit) {
@@ -244,7 +243,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         delete c;
         return HOUGH_ENOMEM;
     }
-    const int peak_waves = hough::peak_block_waves(p->n_rho, limit);
+    const int peak_waves = hough::peak_block_waves(p->n_theta, p->n_rho, limit);
     const size_t work_bytes = 256 + 4 * (size_t)((p->n_theta + peak_waves - 1) / peak_waves);
     if (hipMalloc(&c->d_work, work_bytes) != hipSuccess) {
         (void)hipFree(c->d_tables);
@@ -260,6 +259,10 @@ int hough_config(const hough_params *p, hough_ctx **out) {
     c->iter1 = hough::plan_iterative(p->n_theta, p->n_rho, limit, 1);
     c->iterb = hough::plan_iterative(p->n_theta, p->n_rho, limit, 2);
     if (c->iter1.gbm && hipMalloc(&c->d_iter_bm, c->iter1.bm_bytes) != hipSuccess) {
+        hough_destroy(c);
+        return HOUGH_ENOMEM;
+    }
+    if (hipMalloc(&c->d_iter_list, sizeof(uint64_t) * hough::kIterScanKeys) != hipSuccess) {
         hough_destroy(c);
         return HOUGH_ENOMEM;
     }
@@ -319,6 +322,7 @@ void hough_destroy(hough_ctx *c) {
     if (c->d_work) (void)hipFree(c->d_work);
     if (c->d_order) (void)hipFree(c->d_order);
     if (c->d_iter_bm) (void)hipFree(c->d_iter_bm);
+    if (c->d_iter_list) (void)hipFree(c->d_iter_list);
     if (c->d_spill) (void)hipFree(c->d_spill);
     delete c;
 }
@@ -402,7 +406,8 @@ int hough_peaks_iterative(hough_ctx *c, const void *acc, uint32_t frac_num, uint
     r_rho = r_rho < c->p.n_rho ? r_rho : c->p.n_rho;
     const hipError_t e = hough::launch_peaks_iterative(c->g, acc, c->p.acc_type, frac_num, frac_den,
                                                        r_theta, r_rho, peaks, cap, n_peaks, status, c->iter1,
-                                                       c->d_iter_bm, (hipStream_t)stream);
+                                                       c->d_iter_bm, c->d_iter_list, c->d_work + 8,
+                                                       (hipStream_t)stream);
     return e == hipSuccess ? HOUGH_OK : HOUGH_EDEVICE;
 }
 

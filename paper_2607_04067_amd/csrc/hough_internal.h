@@ -188,7 +188,7 @@ size_t vote_lds_bytes(int rows);
 int vote_slab_rows(int n_rho, size_t lds_limit);
 // LDS of hough_peaks' workgroup of `waves` theta rows, and the most rows that fit (0: none).
 size_t peaks_lds_bytes(int n_rho, int waves);
-int peak_block_waves(int n_rho, size_t lds_limit);
+int peak_block_waves(int n_theta, int n_rho, size_t lds_limit);
 hipError_t launch_track_params(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
                                const hough_peak *peaks, const uint32_t *n_peaks, uint32_t cap,
                                double rho_min, double rho_max, double b_tesla, hough_track *out,
@@ -196,7 +196,10 @@ hipError_t launch_track_params(const GridArgs &g, const float *x, const float *y
 hipError_t launch_peaks_iterative(const GridArgs &g, const void *acc, int acc_type, uint32_t frac_num,
                                   uint32_t frac_den, int r_theta, int r_rho, hough_peak *peaks,
                                   uint32_t cap, uint32_t *n_peaks, uint32_t *status, const IterPlan &ip,
-                                  uint32_t *gbm, hipStream_t s);
+                                  uint32_t *gbm, uint64_t *list, uint32_t *scan, hipStream_t s);
+// Keys hough_peaks_iterative's first launch may list for its second (list: that many, scan: two
+// words, zero between calls; the context's).
+constexpr uint32_t kIterScanKeys = 65536;
 // LDS of the fused kernel's workgroup: the whole column (win 0) or a window of win rows.
 size_t batch_lds_bytes(int n_rho, int waves, int groups, int win = 0);
 int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, BatchPlan *out, int win = 0,

@@ -358,7 +358,7 @@ __device__ uint32_t vote_range(uint32_t *tile, const float *x, const float *y, u
 // instruction's hits), spread evenly over the NW waves.
 template <int NW>
 __device__ __forceinline__ void wave_hits(uint32_t H, int wave, uint32_t &hb, uint32_t &he) {
-    const uint32_t blocks = (H + 7u) >> 3, w = (uint32_t)__builtin_amdgcn_readfirstlane(wave);   // scalar
+    const uint32_t blocks = (H >> 3) + ((H & 7u) != 0u), w = (uint32_t)__builtin_amdgcn_readfirstlane(wave);   // scalar
     hb = min(H, (uint32_t)((uint64_t)blocks * w / NW) * 8u);
     he = min(H, (uint32_t)((uint64_t)blocks * (w + 1u) / NW) * 8u);
 }
@@ -951,9 +951,8 @@ __device__ uint32_t retain_range_peaks(const float4 *tpk, uint32_t np, bool edge
 }
 
 // ------------------------------------------------------------------------ plain path
-// Internal accumulator form of the iterative finder's batch path: 16-bit cells stored rho-major
-// (acc[k * n_theta + j]), so that the write-out of a tile row is one contiguous run per wave.
-constexpr int kAccU16RhoMajor = 3;
+// The iterative finder's batch path keeps 16-bit cells stored rho-major (acc[k * n_theta + j]), so
+// that the write-out of a tile row is one contiguous run per wave.
 
 // Votes of hits [hb, he) into rows [r0, r1) of the lane's column only (a rho slab of the tile:
 // tile row k - r0 holds grid row k): every vote takes the range test r0 <= t < r1, which for an
@@ -988,20 +987,17 @@ __device__ uint32_t vote_range_slab(uint32_t *tile, float2 *st, const float *x, 
     return n_valid;
 }
 
-// Steps 1-3 of one event into one 64-column group of acc, rows [r0, r1) (the whole column, or a
-// rho slab of it when the column does not fit LDS), by one workgroup: all hits of the event are
-// swept through the group's tile.  Counters are packed two per dword, so the hits go through in
-// chunks of at most 65,535 (a count then fits 16 bits); each chunk's tile is written out (first
-// chunk) or added (later chunks) to acc, each element by the one thread that owns it.  dup as
-// for vote_range.  Returns this thread's invalid-hit flag.
+// Steps 1-3 of one event into one 64-column group of a rho-major 16-bit accumulator, rows
+// [r0, r1) (the whole column, or a rho slab of it when the column does not fit LDS), by one
+// workgroup: all hits of the event (at most kMaxBatchHits) are swept through the group's packed
+// tile, which is then written out.  dup as for vote_range.  Returns this thread's invalid-hit
+// flag.
 template <int NW>
 __device__ uint32_t vote_group_to_acc(const GridArgs &g, const float *__restrict__ x,
-                                      const float *__restrict__ y, uint32_t n_hits, void *acc,
-                                      int acc_type, int group, const uint8_t *dup, int r0, int r1) {
+                                      const float *__restrict__ y, uint32_t n_hits, uint16_t *acc,
+                                      int group, const uint8_t *dup, int r0, int r1) {
     using L = Lane<1, true>;
-    constexpr uint32_t kChunk = 65535u;
     extern __shared__ __align__(16) uint32_t lds[];
-    const bool whole = r0 == 0 && r1 == g.n_rho;
     const int rows = r1 - r0;
     uint32_t *tile = lds;                                                  // [(rows + 1) * 32]
     float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)(rows + 1) * L::STRIDE);     // slabs only
@@ -1010,59 +1006,136 @@ __device__ uint32_t vote_group_to_acc(const GridArgs &g, const float *__restrict
     const L ln(lane);
     const Cols<1> cl = load_cols<1>(g, first, lane, L::STRIDE, ln.col);
     const int j = first + lane;
-    const int kb = r0 + (int)((int64_t)rows * wave / NW), ke = r0 + (int)((int64_t)rows * (wave + 1) / NW);
-    uint32_t bad = 0;
-    uint32_t c0 = 0;
-    do {
-        const uint32_t c1 = n_hits - c0 > kChunk ? c0 + kChunk : n_hits;
-        for (int i = threadIdx.x; i < (rows + 1) * L::STRIDE / 4; i += NW * 64)
-            reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
-        __syncthreads();
-        uint32_t hb, he;
-        wave_hits<NW>(c1 - c0, wave, hb, he);
-        hb += c0;
-        he += c0;
-        if (whole)
-            vote_range<1>(tile, x, y, hb, he, cl, g, first, lane, bad, g.nrho_f, dup);
-        else
-            vote_range_slab<NW>(tile, stage + wave * 64, x, y, hb, he, cl, ln, g, lane, bad, dup, r0, r1);
-        __syncthreads();
-        // write-out: lane = column (theta row of acc), wave = a slice of the slab's rows
-        if (j < g.n_theta) {
-            if (acc_type == kAccU16RhoMajor) {         // acc[k][j]: a wave stores 64 adjacent cells
-                uint16_t *col = static_cast<uint16_t *>(acc) + j;
-                for (int k = kb; k < ke; ++k) {
-                    const uint32_t v = ln.count(tile[(k - r0) * L::STRIDE + ln.col[0]]);
-                    uint16_t *cell = col + (size_t)k * g.n_theta;
-                    *cell = (uint16_t)(c0 ? *cell + v : v);
-                }
-            } else if (acc_type == HOUGH_ACC_U16) {
-                uint16_t *row = static_cast<uint16_t *>(acc) + (size_t)j * g.n_rho;
-                for (int k = kb; k < ke; ++k) {
-                    const uint32_t v = ln.count(tile[(k - r0) * L::STRIDE + ln.col[0]]);
-                    row[k] = (uint16_t)(c0 ? row[k] + v : v);
-                }
-            } else {
-                uint32_t *row = static_cast<uint32_t *>(acc) + (size_t)j * g.n_rho;
-                for (int k = kb; k < ke; ++k) {
-                    const uint32_t v = ln.count(tile[(k - r0) * L::STRIDE + ln.col[0]]);
-                    row[k] = c0 ? row[k] + v : v;
-                }
-            }
-        }
-        __syncthreads();
-        c0 = c1;
-    } while (c0 < n_hits);
+    uint32_t bad = 0, hb, he;
+    for (int i = threadIdx.x; i < (rows + 1) * L::STRIDE / 4; i += NW * 64)
+        reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    wave_hits<NW>(n_hits, wave, hb, he);
+    if (r0 == 0 && r1 == g.n_rho)
+        vote_range<1>(tile, x, y, hb, he, cl, g, first, lane, bad, g.nrho_f, dup);
+    else
+        vote_range_slab<NW>(tile, stage + wave * 64, x, y, hb, he, cl, ln, g, lane, bad, dup, r0, r1);
+    __syncthreads();
+    if (j < g.n_theta) {                       // a wave stores 64 adjacent cells of a row
+        uint16_t *col = acc + j;
+        for (int k = r0 + wave; k < r1; k += NW)
+            col[(size_t)k * g.n_theta] = (uint16_t)ln.count(tile[(k - r0) * L::STRIDE + ln.col[0]]);
+    }
     return bad;
 }
 
-// hough_vote: workgroup (64-column group, rho slab of slab_rows rows).
-template <int NW>
+// hough_vote: workgroup (32-column group, rho slab of slab_rows rows), all of the event's hits swept
+// through one 32-bit counter per cell, [rows + 1][32] in LDS (the last row a dummy).  One event
+// is latency: the groups are as narrow as one matrix instruction, so that the most
+// workgroups share the votes, and the tile is written out 16 bytes per lane along a column.
+// (one event of 4,400 hits, 720 x 512: 33 us with 64-column groups and 4-byte stores that
+// touched 64 lines each, 11 us so; 1,500 hits on 1000 x 1000: 44 and 9 us)
+// SLAB: the tile holds rows [r0, r0 + nrows) only, and a vote outside goes to the dummy row.
+template <bool SLAB>
+__device__ __forceinline__ void vote_mfma32(uint32_t *tile, float a, uint32_t rows, float op, bool in,
+                                            const f32x16 &bf, const GridArgs &g, int r0, int nrows, int lane) {
+    const f32x16 t = __builtin_amdgcn_mfma_f32_32x32x2f32(a, op, bf, 0, 0, 0);
+    if (!in) return;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if (b && (uint32_t)(8 * b) >= rows) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float tt = t[4 * b + i];
+            uint32_t k;
+            if (SLAB) {
+                tt += 0.0f;                                   // see vote_mfma
+                tt = __float_as_uint(tt) < __float_as_uint(g.nrho_f) ? tt : -1.0f;
+                k = min((uint32_t)((int)tt - r0), (uint32_t)nrows);
+            } else {
+                k = (uint32_t)(int)tt;
+            }
+            lds_add(&tile[k * 32u + (uint32_t)(lane & 31)], 1u);
+        }
+    }
+}
+
+// Votes of hits [hb, he) into such a tile (the whole column when r0 = 0 and nrows = n_rho); the
+// same rules as vote_range.
+__device__ void vote_range32(uint32_t *tile, const float *x, const float *y, uint32_t hb, uint32_t he,
+                             const GridArgs &g, int first_col, int r0, int nrows, int lane) {
+    const int j = first_col + (lane & 31);
+    const bool in = j < g.n_theta;
+    const float C = in ? g.C[j] : 0.0f, S = in ? g.S[j] : 0.0f, op = lane < 32 ? S : C;
+    const bool whole = r0 == 0 && nrows == g.n_rho;
+    f32x16 bf;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bf[i] = g.Bf;
+    asm volatile("" : "+v"(bf));
+    uint32_t extra = 0;
+    float xn = 0.0f, yn = 0.0f;
+    if (hb + lane < he) { xn = x[hb + lane]; yn = y[hb + lane]; }
+    for (uint32_t base = hb; base < he; base += 64) {
+        const uint32_t i = base + lane;
+        const float xi = xn, yi = yn;
+        const bool live = i < he;
+        if (i + 64 < he) { xn = x[i + 64]; yn = y[i + 64]; }
+        float u, v;
+        const bool valid = conformal(live ? xi : 0.0f, live ? yi : 0.0f, u, v) && live;
+        const bool safe = valid && all_in_range(u, v, g);
+        const uint64_t bs = __ballot(safe);
+        uint64_t bu = __ballot(valid && !safe);
+        const uint32_t rows = min(he - base, 64u), ns = (uint32_t)__popcll(bs);
+        float a0, a1;
+        if (whole && (uint32_t)__popcll(bu) <= kFewUnsafe) {
+            if (ns) {
+                swap_halves(safe ? v : 0.0f, safe ? u : 0.0f, a0, a1);
+                vote_mfma32<false>(tile, a0, rows, op, in, bf, g, r0, nrows, lane);
+                if (rows > 32u) vote_mfma32<false>(tile, a1, rows - 32u, op, in, bf, g, r0, nrows, lane);
+                extra += ((rows + 7u) & ~7u) - ns;
+            }
+            for (; bu; bu &= bu - 1ull) {
+                const int m = __builtin_ctzll(bu);
+                const float um = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(u), m));
+                const float vm = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), m));
+                const float t = __builtin_fmaf(um, C, __builtin_fmaf(vm, S, g.Bf));
+                if (lane < 32 && in && t >= 0.0f && t < g.nrho_f) lds_add(&tile[(uint32_t)(int)t * 32u + lane], 1u);
+            }
+        } else {
+            const float nan = __uint_as_float(0x7fc00000u);
+            swap_halves(valid ? v : nan, valid ? u : nan, a0, a1);
+            vote_mfma32<true>(tile, a0, rows, op, in, bf, g, r0, nrows, lane);
+            if (rows > 32u) vote_mfma32<true>(tile, a1, rows - 32u, op, in, bf, g, r0, nrows, lane);
+        }
+    }
+    if (extra && lane < 32 && in) lds_add(&tile[(uint32_t)(int)g.Bf * 32u + lane], 0u - extra);
+}
+
+// vec: rows start on a 16-byte (8-byte for 16-bit cells) boundary and hold whole quads.
+template <int NW, typename T>
 __global__ __launch_bounds__(NW * 64) void k_vote(GridArgs g, const float *__restrict__ x,
                                                   const float *__restrict__ y, uint32_t n_hits,
-                                                  void *acc, int acc_type, int slab_rows) {
-    const int r0 = (int)blockIdx.y * slab_rows, r1 = min(r0 + slab_rows, g.n_rho);
-    (void)vote_group_to_acc<NW>(g, x, y, n_hits, acc, acc_type, (int)blockIdx.x, nullptr, r0, r1);
+                                                  T *__restrict__ acc, int slab_rows, int vec) {
+    extern __shared__ __align__(16) uint32_t tile[];                    // [(nrows + 1) * 32]
+    const int r0 = (int)blockIdx.y * slab_rows, nrows = min(slab_rows, g.n_rho - r0);
+    const int lane = threadIdx.x & 63, wave = wave_id(), first = (int)blockIdx.x * 32;
+    for (int i = threadIdx.x; i < (nrows + 1) * 8; i += NW * 64)
+        reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    uint32_t hb, he;
+    wave_hits<NW>(n_hits, wave, hb, he);
+    vote_range32(tile, x, y, hb, he, g, first, r0, nrows, lane);
+    __syncthreads();
+    const int j = first + (lane & 31);
+    if (j >= g.n_theta) return;
+    T *row = acc + (size_t)j * g.n_rho + r0;
+    const uint32_t *col = tile + (lane & 31);
+    if (vec) {
+        for (int q = 2 * wave + (lane >> 5); q < nrows / 4; q += 2 * NW) {
+            const uint32_t a = col[128 * q], b = col[128 * q + 32], c = col[128 * q + 64], d = col[128 * q + 96];
+            if constexpr (sizeof(T) == 4)
+                reinterpret_cast<uint4 *>(row)[q] = make_uint4(a, b, c, d);
+            else
+                reinterpret_cast<uint2 *>(row)[q] = make_uint2(a | (b << 16), c | (d << 16));
+        }
+    } else {
+        for (int k = 2 * wave + (lane >> 5); k < nrows; k += 2 * NW) row[k] = (T)col[32 * k];
+    }
 }
 
 // Steps 1-3 for a batch of CSR events into per-event 16-bit accumulators (the iterative
@@ -1086,8 +1159,8 @@ __global__ __launch_bounds__(NW * 64) void k_vote_batch(GridArgs g, const float 
     const uint32_t H = h1 - h0;
     const size_t cells = (size_t)g.n_theta * (size_t)g.n_rho;
     const int r0 = (int)blockIdx.z * slab_rows, r1 = min(r0 + slab_rows, g.n_rho);
-    const uint32_t bad = vote_group_to_acc<NW>(g, x + h0, y + h0, H, acc + (size_t)e * cells, kAccU16RhoMajor,
-                                               (int)blockIdx.y, g.dedup ? keep + h0 : nullptr, r0, r1);
+    const uint32_t bad = vote_group_to_acc<NW>(g, x + h0, y + h0, H, acc + (size_t)e * cells, (int)blockIdx.y,
+                                               g.dedup ? keep + h0 : nullptr, r0, r1);
     __shared__ uint32_t s_bad;
     if (threadIdx.x == 0) s_bad = 0u;
     __syncthreads();
@@ -1114,19 +1187,35 @@ __global__ __launch_bounds__(NW * 64) void k_peaks(GridArgs g, const T *__restri
                                                    hough_peak *out, uint32_t cap,
                                                    uint32_t *n_peaks, uint32_t *counts) {
     extern __shared__ __align__(16) uint32_t lds[];
-    uint32_t *rows = lds;   // [(NW + 2) * n_rho], buffer row r holds grid row jb - 1 + r
+    // [NW][nm] each row's peaks, 64 cells a word; then [(NW + 2) * n_rho], buffer row r holds grid
+    // row jb - 1 + r
+    const int nm = (g.n_rho + 63) / 64;
+    uint64_t *masks = reinterpret_cast<uint64_t *>(lds);
+    uint32_t *rows = lds + 2 * NW * nm;
     __shared__ uint32_t s_cnt[NW];
     __shared__ uint32_t s_base;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = wave_id();
     const int nr = g.n_rho;
     const int jb = (int)blockIdx.x * NW;
-    for (int idx = threadIdx.x; idx < (NW + 2) * nr; idx += NW * 64) {
-        const int r = idx / nr, k = idx - r * nr, jj = jb - 1 + r;
-        uint32_t v = 0u;
-        if (jj >= 0 && jj < g.n_theta) v = (uint32_t)acc[(size_t)jj * nr + k];
-        else if (g.periodic && (jj == -1 || jj == g.n_theta))   // the other edge, rho reversed
-            v = (uint32_t)acc[(size_t)(jj < 0 ? g.n_theta - 1 : 0) * nr + (nr - 1 - k)];
-        rows[idx] = v;
+    // the rows are one run of acc but for the grid's edges (zero, or on a periodic grid the other
+    // edge with rho reversed); eight loads in flight per thread
+    {
+        const int64_t q0 = (int64_t)(jb - 1) * nr, end = (int64_t)g.n_theta * nr;
+        constexpr int U = 8;
+        for (int i0 = threadIdx.x; i0 < (NW + 2) * nr; i0 += U * NW * 64) {
+            uint32_t v[U];
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+                const int idx = i0 + i * NW * 64;
+                int64_t q = q0 + idx;
+                if (g.periodic && q < 0) q = end - 1 - idx;                        // row -1: idx < nr
+                else if (g.periodic && q >= end) q = (int64_t)nr - 1 - (q - end);  // row n_theta (later ones: q < 0)
+                v[i] = idx < (NW + 2) * nr && q >= 0 && q < end ? (uint32_t)acc[q] : 0u;
+            }
+#pragma unroll
+            for (int i = 0; i < U; ++i)
+                if (i0 + i * NW * 64 < (NW + 2) * nr) rows[i0 + i * NW * 64] = v[i];
+        }
     }
     if (WRITE && wave == 0) {                     // peaks of the earlier blocks, and of all
         uint32_t before = 0, all = 0;
@@ -1161,7 +1250,9 @@ __global__ __launch_bounds__(NW * 64) void k_peaks(GridArgs g, const T *__restri
     if (j < g.n_theta) {
         for (int kc = 0; kc < nr; kc += 64) {
             const int k = kc + lane;
-            cnt += (uint32_t)__popcll(__ballot(k < nr && is_peak(k)));
+            const uint64_t m = __ballot(k < nr && is_peak(k));
+            if (WRITE && lane == 0) masks[wave * nm + (kc >> 6)] = m;
+            cnt += (uint32_t)__popcll(m);
         }
     }
     if (lane == 0) s_cnt[wave] = cnt;
@@ -1179,9 +1270,8 @@ __global__ __launch_bounds__(NW * 64) void k_peaks(GridArgs g, const T *__restri
     if (j < g.n_theta) {
         for (int kc = 0; kc < nr; kc += 64) {
             const int k = kc + lane;
-            const bool p = k < nr && is_peak(k);
-            const uint64_t m = __ballot(p);
-            if (p) {
+            const uint64_t m = masks[wave * nm + (kc >> 6)];
+            if ((m >> lane) & 1ull) {
                 const uint32_t idx = base + mbcnt(m);
                 if (idx < cap) store_peak(out + idx, (uint32_t)j, (uint32_t)k, mid[k]);
             }
@@ -1229,22 +1319,19 @@ __device__ __forceinline__ bool bm_test(const uint32_t *bm, uint32_t r) {
 }
 
 // Set the bits of every cell within r_theta columns and r_rho rows of (jf, kf), clipped at the
-// grid edges: per column one raster run jj * n_rho + [k0, k1], a few words each; the 64 lanes
-// take the (column, word) pairs.
+// grid edges: per column one raster run jj * n_rho + [k0, k1], a few words each; four lanes take
+// the words of a column, 16 columns at a time.
 __device__ void mark_window(uint32_t *bm, int jf, int kf, int r_theta, int r_rho, int n_theta, int n_rho,
                             uint32_t lane) {
     const int j0 = max(jf - r_theta, 0), j1 = min(jf + r_theta, n_theta - 1);
     const int k0 = max(kf - r_rho, 0), k1 = min(kf + r_rho, n_rho - 1);
-    const uint32_t per = (uint32_t)((k1 - k0) >> 5) + 2u;          // words one column can touch
-    const uint32_t units = (uint32_t)(j1 - j0 + 1) * per;
-    for (uint32_t u = lane; u < units; u += 64) {
-        const uint32_t col = (uint32_t)j0 + u / per, slot = u % per;
-        const uint32_t a = col * (uint32_t)n_rho + (uint32_t)k0, e = col * (uint32_t)n_rho + (uint32_t)k1;
-        const uint32_t w = (a >> 5) + slot;
-        if (w > (e >> 5)) continue;
-        const uint32_t lo = w == (a >> 5) ? (a & 31u) : 0u, hi = w == (e >> 5) ? (e & 31u) : 31u;
-        const uint32_t bits = (hi == 31u ? ~0u : ((1u << (hi + 1u)) - 1u)) & ~((1u << lo) - 1u);
-        __hip_atomic_fetch_or(bm + w, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int col = j0 + (int)(lane >> 2); col <= j1; col += 16) {
+        const uint32_t a = (uint32_t)col * (uint32_t)n_rho + (uint32_t)k0, e = a + (uint32_t)(k1 - k0);
+        for (uint32_t w = (a >> 5) + (lane & 3u); w <= (e >> 5); w += 4u) {
+            const uint32_t lo = w == (a >> 5) ? (a & 31u) : 0u, hi = w == (e >> 5) ? (e & 31u) : 31u;
+            const uint32_t bits = (hi == 31u ? ~0u : ((1u << (hi + 1u)) - 1u)) & ~((1u << lo) - 1u);
+            __hip_atomic_fetch_or(bm + w, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
     }
 }
 
@@ -1314,17 +1401,81 @@ __device__ void hist_fit(const uint32_t *hist, uint32_t nb, bool top, uint32_t r
     *first = wave_min(f);
 }
 
+// The threshold of the iterative finder for a largest count mx.
+__device__ __forceinline__ uint32_t iter_threshold(uint32_t mx, uint32_t frac_num, uint32_t frac_den, uint32_t floor_t) {
+    const uint64_t rel = ((uint64_t)mx * frac_num + frac_den - 1u) / frac_den;
+    return (uint32_t)min<uint64_t>(max<uint64_t>(rel, floor_t), 0xffffffffull);
+}
+
+// One event's accumulator read by the whole chip ahead of the finder (one workgroup reading 4 MB
+// took 125 of the finder's 144 us on 1000 x 1000; this pass takes 7 and the finder 20 after it): the largest count in scan[0], and in list
+// the keys of every cell that reaches the threshold (their number in scan[1]; more than kIterScanCap:
+// only counted).  Each block holds its cells in registers, raises the running maximum by its own
+// and lists the cells that reach the threshold of the maximum so far: that never exceeds the
+// final one, so the list holds every candidate and some cells more, which the finder drops.
+// The finder puts scan[0] and scan[1] back to zero.
+constexpr int kScanThreads = 256, kScanCells = 16;
+constexpr uint32_t kIterScanCap = kIterScanKeys;
+
+template <typename T>
+__global__ __launch_bounds__(kScanThreads) void k_iter_scan(const T *__restrict__ acc, uint32_t cells,
+                                                            uint32_t floor_t, uint32_t frac_num, uint32_t frac_den,
+                                                            uint64_t *__restrict__ list, uint32_t *scan) {
+    __shared__ uint32_t s_max, s_cnt, s_base, s_thr;
+    const uint32_t lane = threadIdx.x & 63;
+    constexpr uint32_t kTile = kScanThreads * kScanCells;
+    for (uint64_t b = (uint64_t)blockIdx.x * kTile; b < cells; b += (uint64_t)gridDim.x * kTile) {
+        const uint32_t base = (uint32_t)b;
+        if (threadIdx.x == 0) { s_max = 0u; s_cnt = 0u; }
+        __syncthreads();
+        uint32_t v[kScanCells], m = 0;
+#pragma unroll
+        for (int i = 0; i < kScanCells; ++i) {
+            const uint64_t c = b + (uint64_t)(i * kScanThreads) + threadIdx.x;
+            v[i] = c < cells ? (uint32_t)acc[c] : 0u;
+            m = max(m, v[i]);
+        }
+        m = wave_max(m);
+        if (lane == 0) atomicMax(&s_max, m);
+        __syncthreads();
+        if (threadIdx.x == 0) s_thr = iter_threshold(max(atomicMax(scan, s_max), s_max), frac_num, frac_den, floor_t);
+        __syncthreads();
+        const uint32_t thr = s_thr;
+        uint32_t n = 0;
+#pragma unroll
+        for (int i = 0; i < kScanCells; ++i) n += v[i] >= thr ? 1u : 0u;
+        const uint32_t incl = wave_inclusive_scan(n, (int)lane);
+        uint32_t off = 0;
+        if (lane == 63 && incl) off = atomicAdd(&s_cnt, incl);
+        off = (uint32_t)__builtin_amdgcn_readlane((int)off, 63) + incl - n;
+        __syncthreads();
+        if (threadIdx.x == 0 && s_cnt) s_base = atomicAdd(scan + 1, s_cnt);
+        __syncthreads();
+        uint32_t pos = s_base + off;
+#pragma unroll
+        for (int i = 0; i < kScanCells; ++i)
+            if (v[i] >= thr) {
+                const uint32_t r = base + (uint32_t)(i * kScanThreads) + threadIdx.x;
+                if (pos < kIterScanCap) list[pos] = ((uint64_t)v[i] << 32) | (uint64_t)(~r);
+                ++pos;
+            }
+        __syncthreads();
+    }
+}
+
 // offsets (batch form, else null): workgroup e takes event e's accumulator (rho-major 16-bit
 // cells) at acc + e * cells, writes its list at out + e * cap, n_peaks[e], and ORs
 // HOUGH_EV_PEAKS_TRUNCATED into status[e] (which the batch vote wrote); events the vote skipped
 // get no peaks.  K: keys in the LDS buffer (a power of two, kIterMinKeys .. kIterMaxKeys).
 // gbm (GBM): device bitmaps of bm_words words, one per workgroup.
+// list, scan (one event, else null): what k_iter_scan left, in place of the first pass.
 template <typename T, bool GBM>
 __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T *__restrict__ acc,
                                                              uint32_t frac_num, uint32_t frac_den, int r_theta,
                                                              int r_rho, hough_peak *out, uint32_t cap,
                                                              uint32_t *n_peaks, uint32_t *status,
-                                                             const uint32_t *offsets, uint32_t K, uint32_t *gbm) {
+                                                             const uint32_t *offsets, uint32_t K, uint32_t *gbm,
+                                                             const uint64_t *list, uint32_t *scan) {
     extern __shared__ __align__(16) uint64_t keys[];       // [K]; the histograms reuse it as 2K words
     uint32_t *hist = reinterpret_cast<uint32_t *>(keys);
     __shared__ uint32_t s_red[kIterWaves];
@@ -1333,7 +1484,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     const uint32_t nr = (uint32_t)g.n_rho, nt = (uint32_t)g.n_theta;
     const uint32_t cells = nt * nr, bm_words = (cells + 31u) / 32u, NB = 2u * K;
     const bool batch = offsets != nullptr;
-    // the batch form stores rho-major (see kAccU16RhoMajor); keys and the bitmap use raster order
+    // the batch form stores rho-major (see vote_group_to_acc); keys and the bitmap use raster order
     auto raster = [&](uint32_t c) -> uint32_t {
         if (!batch) return c;
         const uint32_t k = c / nt;
@@ -1357,22 +1508,39 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     if (tid == 0) { s_n = 0u; s_taken = 0u; }
     __syncthreads();
 
-    // pass 1: the maximum, and the candidates of the absolute floor while they fit
     const uint32_t floor_t = g.threshold;
-    uint32_t m = 0;
-    for_cells(acc, cells, [&](uint32_t c, uint32_t v, bool in) {
-        m = max(m, v);
-        const bool p = in && v >= floor_t;
-        append_key(keys, &s_n, K, p, p ? ((uint64_t)v << 32) | (uint64_t)(~raster(c)) : 0ull, lane);
-    });
-    m = wave_max(m);
-    if (lane == 0) s_red[wave] = m;
-    __syncthreads();
-    uint32_t mx = 0;
-    for (int w = 0; w < kIterWaves; ++w) mx = max(mx, s_red[w]);
-    const uint64_t rel = ((uint64_t)mx * frac_num + frac_den - 1u) / frac_den;
-    const uint32_t thr = (uint32_t)min<uint64_t>(max<uint64_t>(rel, floor_t), 0xffffffffull);
-    const uint32_t n1 = s_n;
+    uint32_t mx = 0, thr, n1;
+    bool filtered;             // the keys held reach thr (else the floor)
+    if (scan) {
+        mx = scan[0];
+        n1 = scan[1];
+        thr = iter_threshold(mx, frac_num, frac_den, floor_t);
+        const bool whole = n1 <= kIterScanCap;
+        if (whole)
+            for (uint32_t i0 = 0; i0 < n1; i0 += kIterThreads) {
+                const uint32_t i = i0 + tid;
+                const uint64_t key = i < n1 ? list[i] : 0ull;
+                append_key(keys, &s_n, K, i < n1 && (uint32_t)(key >> 32) >= thr, key, lane);
+            }
+        __syncthreads();
+        n1 = whole ? s_n : K + 1u;
+        filtered = true;
+    } else {
+        // pass 1: the maximum, and the candidates of the absolute floor while they fit
+        uint32_t m = 0;
+        for_cells(acc, cells, [&](uint32_t c, uint32_t v, bool in) {
+            m = max(m, v);
+            const bool p = in && v >= floor_t;
+            append_key(keys, &s_n, K, p, p ? ((uint64_t)v << 32) | (uint64_t)(~raster(c)) : 0ull, lane);
+        });
+        m = wave_max(m);
+        if (lane == 0) s_red[wave] = m;
+        __syncthreads();
+        for (int w = 0; w < kIterWaves; ++w) mx = max(mx, s_red[w]);
+        thr = iter_threshold(mx, frac_num, frac_den, floor_t);
+        n1 = s_n;
+        filtered = thr == floor_t;
+    }
     __syncthreads();
 
     bool bounded = false;      // keys below `hi` are what is left once a chunk has been walked
@@ -1381,8 +1549,8 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     uint32_t n = 0;
     uint64_t lo = 0;           // the chunk's lowest key (0: the chunk holds every candidate left)
     if (n1 <= K) {
-        // every floor candidate is in LDS: keep those that reach thr, in place
-        if (thr > floor_t) {
+        // every candidate is in LDS: keep those that reach thr, in place
+        if (!filtered) {
             if (tid == 0) s_n = 0u;
             __syncthreads();
             for (uint32_t i0 = 0; i0 < n1; i0 += kIterThreads) {
@@ -1480,6 +1648,29 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         while (P < n) P <<= 1;
         for (uint32_t i = n + tid; i < P; i += kIterThreads) keys[i] = 0ull;
         __syncthreads();
+        if (P <= kIterThreads) {
+            // a key per thread: partners less than a wave apart trade through the wave's lanes,
+            // so that only the others need LDS and barriers (10 of 55 steps at 1,024 keys)
+            uint64_t key = tid < P ? keys[tid] : 0ull;
+            for (uint32_t k = 2; k <= P; k <<= 1) {
+                for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+                    uint64_t other;
+                    if (j >= 64u) {
+                        if (tid < P) keys[tid] = key;
+                        __syncthreads();
+                        other = tid < P ? keys[tid ^ j] : 0ull;
+                        __syncthreads();
+                    } else {
+                        const uint32_t hi32 = (uint32_t)__shfl_xor((int)(uint32_t)(key >> 32), (int)j, 64);
+                        other = ((uint64_t)hi32 << 32) | (uint32_t)__shfl_xor((int)(uint32_t)key, (int)j, 64);
+                    }
+                    const bool larger = ((tid & k) == 0u) == ((tid & j) == 0u);       // this place takes the larger
+                    key = (key > other) == larger ? key : other;
+                }
+            }
+            if (tid < P) keys[tid] = key;
+            __syncthreads();
+        } else
         for (uint32_t k = 2; k <= P; k <<= 1) {
             for (uint32_t j = k >> 1; j > 0; j >>= 1) {
                 for (uint32_t i = tid; i < P; i += kIterThreads) {
@@ -1516,6 +1707,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
                     live = live && (int)lane != f && !(abs(j - jf) <= r_theta && abs(k - kf) <= r_rho);
                     b = __ballot(live);
                 }
+                if (base + 64u >= n && lo == 0) break;              // no key is left to suppress
                 while (took) {
                     const int f = __builtin_ctzll(took);
                     took &= took - 1ull;
@@ -1536,13 +1728,16 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         *n_peaks = taken;
         const uint32_t tr = taken > cap ? HOUGH_EV_PEAKS_TRUNCATED : 0u;
         *status = batch ? (*status | tr) : tr;
+        if (scan) { scan[0] = 0u; scan[1] = 0u; }
     }
 }
 
-// hough_track_params: one wave per peak.  The lanes sweep the event's hits 64 at a time and
-// count, with ballots, the hits the retention rule associates with the peak and how many of
-// them lie on either side of the line from the origin through the circle's centre; lane 0
-// turns the peak into the circle (double precision) and writes the record.
+// hough_track_params: one workgroup of kTrackWaves waves per peak.  The waves sweep the event's hits
+// 64 at a time (the next 64 load meanwhile) and count, with ballots, the hits the retention rule
+// associates with the peak and how many of them lie on either side of the line from the origin
+// through the circle's centre; thread 0 adds the waves' counts, turns the peak into the circle
+// (double precision) and writes the record.  (65 peaks over 1,500 hits: 11 us with a wave per
+// peak, its 24 chunks one after the other, and 5 us so.)
 constexpr int kTrackWaves = 4;
 
 __global__ __launch_bounds__(kTrackWaves * 64) void k_track_params(GridArgs g, const float *__restrict__ x,
@@ -1551,128 +1746,235 @@ __global__ __launch_bounds__(kTrackWaves * 64) void k_track_params(GridArgs g, c
                                                                    const uint32_t *n_peaks, uint32_t cap,
                                                                    double rho_min, double rho_max,
                                                                    double b_tesla, hough_track *out) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t p = blockIdx.x * kTrackWaves + (uint32_t)wave;
+    __shared__ uint32_t s_cnt[kTrackWaves][3];
+    const int lane = threadIdx.x & 63, wave = wave_id();
     const uint32_t np = min(*n_peaks, cap);
-    if (p >= np) return;
-    const uint2 rec = reinterpret_cast<const uint2 *>(peaks)[p];
-    const int j = (int)(rec.x & 0xffffu), k = (int)(rec.x >> 16);
-    const double pi = 3.14159265358979323846;
-    const double drho = (rho_max - rho_min) / (double)g.n_rho;
-    const double theta = ((double)j * pi) / (double)g.n_theta;
-    const double rho = rho_min + ((double)k + 0.5) * drho;
-    const bool in_grid = j < g.n_theta && k < g.n_rho;
-    const float Cj = in_grid ? g.C[j] : 0.0f, Sj = in_grid ? g.S[j] : 0.0f;
-    uint32_t n = 0, ccw = 0, cw = 0;
-    for (uint32_t base = 0; in_grid && base < n_hits; base += 64) {
-        const uint32_t i = base + lane;
-        float xi = 0.0f, yi = 0.0f;
-        if (i < n_hits) { xi = x[i]; yi = y[i]; }
-        float u, v;
-        const bool ok = conformal(xi, yi, u, v) && i < n_hits;
-        const float w = __builtin_fmaf(v, Sj, g.Bf);
-        const float t = __builtin_fmaf(u, Cj, w);
-        const bool in = ok && t >= 0.0f && t < g.nrho_f;
-        const int d = in ? abs((int)t - k) : 0;
-        const bool mine = in && d <= g.rho_window;
-        float side = __builtin_fmaf(Cj, yi, -(Sj * xi));
-        if (rho < 0.0) side = -side;
-        n += (uint32_t)__popcll(__ballot(mine));
-        ccw += (uint32_t)__popcll(__ballot(mine && side > 0.0f));
-        cw += (uint32_t)__popcll(__ballot(mine && side < 0.0f));
-    }
-    if (lane == 0) {
-        hough_track tr;
-        tr.a = cos(theta) / (2.0 * rho);
-        tr.b = sin(theta) / (2.0 * rho);
-        tr.radius = 1.0 / (2.0 * fabs(rho));
-        tr.pt = 0.299792458 * b_tesla * tr.radius * 1e-3;
-        tr.phi_c = atan2(tr.b, tr.a);
-        tr.charge = ccw > cw ? 1 : (ccw < cw ? -1 : 0);
-        tr.n_hits = n;
-        out[p] = tr;
+    for (uint32_t p = blockIdx.x; p < np; p += gridDim.x) {
+        const uint2 rec = reinterpret_cast<const uint2 *>(peaks)[p];
+        const int j = (int)(rec.x & 0xffffu), k = (int)(rec.x >> 16);
+        const bool in_grid = j < g.n_theta && k < g.n_rho;
+        const float Cj = in_grid ? g.C[j] : 0.0f, Sj = in_grid ? g.S[j] : 0.0f;
+        const double drho = (rho_max - rho_min) / (double)g.n_rho;
+        const double rho = rho_min + ((double)k + 0.5) * drho;
+        uint32_t n = 0, ccw = 0, cw = 0;
+        if (in_grid) {
+            uint32_t i = threadIdx.x;
+            float xn = 0.0f, yn = 0.0f;
+            if (i < n_hits) { xn = x[i]; yn = y[i]; }
+            for (uint32_t base = (uint32_t)wave * 64u; base < n_hits; base += kTrackWaves * 64u) {
+                const float xi = xn, yi = yn;
+                const bool live = i < n_hits;
+                i += kTrackWaves * 64u;
+                if (i < n_hits) { xn = x[i]; yn = y[i]; }
+                float u, v;
+                const bool ok = conformal(live ? xi : 0.0f, live ? yi : 0.0f, u, v) && live;
+                const float w = __builtin_fmaf(v, Sj, g.Bf);
+                const float t = __builtin_fmaf(u, Cj, w);
+                const bool in = ok && t >= 0.0f && t < g.nrho_f;
+                const int d = in ? abs((int)t - k) : 0;
+                const bool mine = in && d <= g.rho_window;
+                float side = __builtin_fmaf(Cj, yi, -(Sj * xi));
+                if (rho < 0.0) side = -side;
+                n += (uint32_t)__popcll(__ballot(mine));
+                ccw += (uint32_t)__popcll(__ballot(mine && side > 0.0f));
+                cw += (uint32_t)__popcll(__ballot(mine && side < 0.0f));
+            }
+        }
+        if (lane == 0) { s_cnt[wave][0] = n; s_cnt[wave][1] = ccw; s_cnt[wave][2] = cw; }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kTrackWaves; ++w) { n += s_cnt[w][0]; ccw += s_cnt[w][1]; cw += s_cnt[w][2]; }
+            const double pi = 3.14159265358979323846;
+            const double theta = ((double)j * pi) / (double)g.n_theta;
+            hough_track tr;
+            tr.a = cos(theta) / (2.0 * rho);
+            tr.b = sin(theta) / (2.0 * rho);
+            tr.radius = 1.0 / (2.0 * fabs(rho));
+            tr.pt = 0.299792458 * b_tesla * tr.radius * 1e-3;
+            tr.phi_c = atan2(tr.b, tr.a);
+            tr.charge = ccw > cw ? 1 : (ccw < cw ? -1 : 0);
+            tr.n_hits = n;
+            out[p] = tr;
+        }
+        __syncthreads();
     }
 }
 
-// hough_retain: workgroup b takes hits b*NW*64 ..., 64 per wave, mapped and staged once.  The
-// theta rows are processed in blocks that fit LDS: for each block the dilated peak bits (bit k
-// of row j set iff a peak (j, k') has |k - k'| <= W) are built from the peak list, stored as
-// [64-row group][word][row in group], and every wave looks its staged hits up 64 rows at a time
-// with lane = row, exactly as the fused kernel looks them up in its tile's columns.
-// offsets (batch form, else null): workgroup (e, b) covers hits b*NW*64 ... of event e, with
-// event e's peak list at peaks + e * cap and n_peaks[e]; the keep bytes of an event the vote
-// skipped for its size are zeroed (malformed offsets: nothing is touched).
-template <int NW>
-__global__ __launch_bounds__(NW * 64) void k_retain(GridArgs g, const float *__restrict__ x,
-                                                    const float *__restrict__ y, uint32_t n_hits,
-                                                    const hough_peak *__restrict__ peaks,
-                                                    const uint32_t *n_peaks, uint32_t cap,
-                                                    uint8_t *keep, int rows_per_block,
-                                                    const uint32_t *offsets = nullptr) {
-    extern __shared__ __align__(16) uint32_t lds[];
-    const int words = (g.n_rho + 31) / 32;
-    float2 *stage = reinterpret_cast<float2 *>(lds);              // [NW * 64]
-    uint32_t *dil = lds + 2 * NW * 64;                             // [rows_per_block / 64][words][64]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t blk = blockIdx.x;
-    if (offsets) {
-        const uint32_t e = blockIdx.x;
-        blk = blockIdx.y;
-        const uint32_t h0 = offsets[e], h1 = offsets[e + 1];
+// hough_retain: 64 hits at a time, one per lane of each wave that works on them.
+//   - Up to kRetainList peaks: they are staged once per workgroup with their columns' constants
+//     (as the fused kernel's peak list) and every lane tests its own hit against them.
+//   - More: the dilated peak bits (bit k of column j set iff a peak (j, k') has |k - k'| <= W) of
+//     a block of columns that fits LDS are built from the list, [column][word] with an odd number
+//     of words per column (different words of a column lie in different banks) and a zero one
+//     after its last, beside the columns' constants, and every lane looks its own bin up in one
+//     column after the other, until all 64 hits are kept.
+// One event (SPLIT): a workgroup takes 64 hits and its 16 waves share the peaks or the columns,
+// since the hits alone would leave most of the chip idle.  A batch (offsets given): workgroup
+// (e, b) takes event e's chunks b * 16 + wave, + 16 * gridDim.y, ..., each wave a chunk; event
+// e's peaks are at peaks + e * cap, n_peaks[e]; the keep bytes of an event the vote skipped for
+// its size are zeroed (malformed offsets: nothing is touched).
+// (one event of 4,400 hits and 14,000 peaks, 720 x 512: 50 us with 512 hits per workgroup looked
+// up with lane = column, 16 us so; 1,500 hits and 65 peaks: 46 and 4 us; 300 events of 1,500 hits
+// on 1000 x 1000: 140 us with 64 workgroups per event, most of them empty, and 21 us so)
+constexpr int kRetainWaves = 16;
+constexpr uint32_t kRetainList = 1024;
+__host__ __device__ constexpr uint32_t retain_pitch(int n_rho) { return ((uint32_t)(n_rho + 31) / 32u + 1u) | 1u; }
+
+// The hit's own bin in n columns (their constants at cs, their dilated bits at dil).  CHECK: the
+// literal range test.  Returns the kept lanes of `want`.
+template <bool CHECK>
+__device__ __forceinline__ uint64_t kept_in_columns(const uint32_t *dil, const float2 *cs, uint32_t pitch, float u,
+                                                    float v, uint64_t want, int n, const GridArgs &g) {
+    const uint32_t zero_row = ((uint32_t)g.n_rho + 31u) & ~31u;
+    uint32_t m = 0;
+    uint64_t kept = 0;
+    for (int j = 0; j < n; j += 8) {
+        uint32_t word[8], k[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int jj = min(j + i, n - 1);
+            const float2 c = cs[jj];
+            const float t = __builtin_fmaf(u, c.x, __builtin_fmaf(v, c.y, g.Bf));
+            // a bin outside the grid looks at the column's zero word
+            k[i] = !CHECK || (t >= 0.0f && t < g.nrho_f) ? (uint32_t)(int)t : zero_row;
+            word[i] = dil[(uint32_t)jj * pitch + (k[i] >> 5)];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) m |= word[i] >> (k[i] & 31u);
+        kept = __ballot((m & 1u) != 0u) & want;
+        if (kept == want) break;
+    }
+    return kept;
+}
+
+template <bool SPLIT>
+__global__ __launch_bounds__(kRetainWaves * 64) void k_retain(GridArgs g, const float *__restrict__ x,
+                                                              const float *__restrict__ y, uint32_t n_hits,
+                                                              const hough_peak *__restrict__ peaks,
+                                                              const uint32_t *n_peaks, uint32_t cap,
+                                                              uint8_t *keep, int cols_per_block,
+                                                              const uint32_t *offsets) {
+    constexpr int NT = kRetainWaves * 64;
+    // the block's columns: constants [cols_per_block], dilated bits [cols_per_block][pitch]
+    extern __shared__ __align__(16) float2 cs[];
+    uint32_t *dil = reinterpret_cast<uint32_t *>(cs + cols_per_block);
+    __shared__ float4 list[kRetainList];
+    __shared__ uint64_t s_kept[kRetainWaves];
+    __shared__ uint32_t s_edge;
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    if (!SPLIT) {
+        const uint32_t e = blockIdx.x, h0 = offsets[e], h1 = offsets[e + 1];
         if (h1 < h0) return;
         if (h1 - h0 > kMaxBatchHits) {
-            for (uint32_t i = h0 + blk * (NW * 64) + threadIdx.x; i < h1; i += gridDim.y * (NW * 64)) keep[i] = 0u;
+            for (uint32_t i = h0 + blockIdx.y * NT + threadIdx.x; i < h1; i += gridDim.y * NT) keep[i] = 0u;
             return;
         }
-        if (blk * (uint32_t)(NW * 64) >= h1 - h0) return;
+        n_hits = h1 - h0;
+        if (blockIdx.y * NT >= n_hits) return;
         x += h0;
         y += h0;
         keep += h0;
-        n_hits = h1 - h0;
         peaks += (size_t)e * cap;
         n_peaks += e;
     }
+    // this wave's chunks of 64 hits
+    const uint32_t chunks = n_hits / 64u + (n_hits % 64u != 0u);
+    const uint32_t chunk0 = SPLIT ? blockIdx.x : blockIdx.y * kRetainWaves + (uint32_t)wave;
+    const uint32_t step = SPLIT ? gridDim.x : gridDim.y * kRetainWaves;
     const uint32_t np = min(*n_peaks, cap);
-    const uint32_t base = blk * (NW * 64) + (uint32_t)wave * 64u;
-    const uint32_t i = base + (uint32_t)lane;
-    float2 *st = stage + wave * 64;
-    uint32_t unused = 0;
-    int slot;
-    const StageCount n = stage_hits(st, x, y, base, n_hits, false, g, lane, unused, slot);
-    uint64_t kept = 0;
-    for (int ja = 0; ja < g.n_theta; ja += rows_per_block) {
-        const int nrow = min(rows_per_block, g.n_theta - ja);
-        const int ngroups = (nrow + 63) / 64;
-        for (int t = threadIdx.x; t < ngroups * words * 64; t += NW * 64) dil[t] = 0u;
-        __syncthreads();
-        for (uint32_t p = threadIdx.x; p < np; p += NW * 64) {
-            const uint2 pk = reinterpret_cast<const uint2 *>(peaks)[p];
-            const int j = (int)(pk.x & 0xffffu), k = (int)(pk.x >> 16);
-            if (j < ja || j >= ja + nrow || k >= g.n_rho) continue;
-            const int lo = k - g.rho_window > 0 ? k - g.rho_window : 0;
-            const int hi = k + g.rho_window < g.n_rho - 1 ? k + g.rho_window : g.n_rho - 1;
-            const int r = j - ja;
-            uint32_t *col = dil + (size_t)(r >> 6) * words * 64 + (r & 63);
-            for (int wd = lo >> 5; wd <= (hi >> 5); ++wd) {
-                const int a = max(lo, wd * 32) - wd * 32, b = min(hi, wd * 32 + 31) - wd * 32;
-                const uint32_t m = (b == 31 ? 0xffffffffu : ((1u << (b + 1)) - 1u)) & ~((1u << a) - 1u);
-                __hip_atomic_fetch_or(&col[wd * 64], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint2 *pk = reinterpret_cast<const uint2 *>(peaks);
+    const bool listed = np <= kRetainList;
+    const uint32_t pitch = retain_pitch(g.n_rho);
+    const int W = g.rho_window;
+    if (threadIdx.x == 0) s_edge = 0u;
+    // a split workgroup's first hits, on their way while the peaks are laid out
+    float x0 = 0.0f, y0 = 0.0f;
+    if (SPLIT && chunk0 * 64u + (uint32_t)lane < n_hits) {
+        x0 = x[chunk0 * 64u + lane];
+        y0 = y[chunk0 * 64u + lane];
+    }
+    __syncthreads();
+    for (int ja = 0; ja < (listed ? 1 : g.n_theta); ja += cols_per_block) {
+        const int jn = min(cols_per_block, g.n_theta - ja);
+        if (listed) {
+            for (uint32_t p = threadIdx.x; p < np; p += NT) {
+                const uint2 r = pk[p];
+                const int j = (int)(r.x & 0xffffu), k = (int)(r.x >> 16);
+                const bool in = j < g.n_theta && k < g.n_rho;           // a cell outside the grid keeps nothing
+                list[p] = make_float4(in ? g.C[j] : 0.0f, in ? g.S[j] : 0.0f,
+                                      __int_as_float(in ? k - W : (int)0x80000000), 0.0f);
+                if (in && (k <= W || k >= g.n_rho - W)) s_edge = 1u;
+            }
+        } else {
+            if (ja) __syncthreads();                                    // the last block is still being read
+            for (int t = threadIdx.x; t < jn; t += NT) cs[t] = make_float2(g.C[ja + t], g.S[ja + t]);
+            for (uint32_t t = threadIdx.x; t < (uint32_t)jn * pitch; t += NT) dil[t] = 0u;
+            __syncthreads();
+            constexpr int U = 8;                                        // cells in flight per thread
+            for (uint32_t p0 = threadIdx.x; p0 < np; p0 += U * NT) {
+                uint32_t cell[U];
+#pragma unroll
+                for (int i = 0; i < U; ++i) cell[i] = p0 + i * NT < np ? pk[p0 + i * NT].x : 0xffffffffu;
+#pragma unroll
+                for (int i = 0; i < U; ++i) {
+                    const int j = (int)(cell[i] & 0xffffu), k = (int)(cell[i] >> 16);
+                    if (j < ja || j >= ja + jn || k >= g.n_rho) continue;
+                    const int lo = max(k - W, 0), hi = min(k + W, g.n_rho - 1);
+                    uint32_t *col = dil + (uint32_t)(j - ja) * pitch;
+                    for (int wd = lo >> 5; wd <= (hi >> 5); ++wd) {
+                        const int a = max(lo, wd * 32) - wd * 32, b = min(hi, wd * 32 + 31) - wd * 32;
+                        const uint32_t m = (b == 31 ? 0xffffffffu : ((1u << (b + 1)) - 1u)) & ~((1u << a) - 1u);
+                        __hip_atomic_fetch_or(&col[wd], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
             }
         }
         __syncthreads();
-        for (int q = 0; q < ngroups; ++q) {
-            // lane = theta row ja + 64q + lane; rows past the grid look up a zero word of row 0
-            const int j = ja + 64 * q + lane;
-            Cols<1> cl;
-            const bool row_in = j < g.n_theta;
-            cl.C[0] = row_in ? g.C[j] : 0.0f;
-            cl.S[0] = row_in ? g.S[j] : 0.0f;
-            cl.B[0] = row_in ? g.Bf : 0.0f;
-            kept |= lookup_staged<1, 64u>(dil + (size_t)q * words * 64, st, n, cl, lane, g.nrho_f);
+        const bool edge = s_edge != 0u;
+        // a split chunk's share of this wave
+        const uint32_t p0 = SPLIT ? np * (uint32_t)wave / kRetainWaves : 0u;
+        const uint32_t p1 = SPLIT ? np * (uint32_t)(wave + 1) / kRetainWaves : np;
+        const int c0 = SPLIT ? jn * wave / kRetainWaves : 0, c1 = SPLIT ? jn * (wave + 1) / kRetainWaves : jn;
+        // (every wave of a split workgroup sees the same chunks, so the barriers below are uniform)
+        for (uint32_t c = chunk0; c < chunks; c += step) {
+            const uint32_t i = c * 64u + (uint32_t)lane;
+            float xi = x0, yi = y0;
+            if (!(SPLIT && c == chunk0)) {
+                xi = yi = 0.0f;
+                if (i < n_hits) { xi = x[i]; yi = y[i]; }
+            }
+            float u, v;
+            const bool valid = conformal(xi, yi, u, v) && i < n_hits;
+            const uint64_t want = __ballot(valid);
+            uint64_t kept = 0;
+            if (listed) {
+                if (p1 > p0) kept = kept_by_peaks(list + p0, p1 - p0, valid ? u : 0.0f, valid ? v : 0.0f, valid, edge, g);
+            } else if (c1 > c0) {
+                const bool safe = valid && all_in_range(u, v, g);
+                const uint32_t *d = dil + (uint32_t)c0 * pitch;
+                const float um = valid ? u : 0.0f, vm = valid ? v : 0.0f;
+                if (__ballot(valid && !safe))
+                    kept = kept_in_columns<true>(d, cs + c0, pitch, um, vm, want, c1 - c0, g);
+                else if (want)
+                    kept = kept_in_columns<false>(d, cs + c0, pitch, um, vm, want, c1 - c0, g);
+            }
+            if (SPLIT) {
+                if (lane == 0) s_kept[wave] = kept;
+                __syncthreads();
+                if (wave == 0) {
+#pragma unroll
+                    for (int w = 1; w < kRetainWaves; ++w) kept |= s_kept[w];
+                }
+            }
+            // later blocks of columns only add to the verdicts
+            if ((!SPLIT || wave == 0) && i < n_hits) {
+                const bool k_me = (kept >> lane) & 1ull;
+                if (ja == 0) keep[i] = k_me ? 1u : 0u;
+                else if (k_me) keep[i] = 1u;
+            }
+            if (SPLIT) __syncthreads();
         }
-        __syncthreads();
     }
-    if (i < n_hits) keep[i] = (slot >= 0 && ((kept >> slot) & 1ull)) ? 1u : 0u;
 }
 
 // Phase clock of the instrumented build (compiled with HOUGH_PHASE_TIMING; the product build
@@ -2808,22 +3110,15 @@ __global__ __launch_bounds__(kDedupThreads) void k_dedup(BatchArgs a) {
     }
 }
 
-// hough_retain's LDS: the wave stages, then the dilated bits of a block of theta rows (a whole
-// number of 64-row groups, at most 60 KB of them).
-constexpr int kRetainWaves = 8;
-int retain_rows_per_block(const GridArgs &g) {
-    const size_t words = (size_t)(g.n_rho + 31) / 32;
-    const size_t budget = 60 * 1024;
-    int groups = (int)(budget / (words * 64 * 4));
-    const int need = (g.n_theta + 63) / 64;
-    if (groups > need) groups = need;
-    if (groups < 1) groups = 1;
-    return groups * 64;
+// hough_retain's LDS: the dilated bits and constants of a block of columns, at most 60 KB of them
+// beside the 16 KB peak list, so that two workgroups share a CU (808 columns of 512 rows in one
+// block, 438 of 1000).
+constexpr int kRetainDilBytes = 60 * 1024;
+int retain_cols_per_block(const GridArgs &g) {
+    const size_t cols = (size_t)kRetainDilBytes / (retain_pitch(g.n_rho) * 4 + 8);
+    return (int)std::min<size_t>(cols, (size_t)g.n_theta);
 }
-size_t retain_lds_bytes(const GridArgs &g, int rows) {
-    const size_t words = (size_t)(g.n_rho + 31) / 32;
-    return (size_t)kRetainWaves * 64 * sizeof(float2) + (size_t)(rows / 64) * words * 64 * 4;
-}
+size_t retain_lds_bytes(const GridArgs &g, int cols) { return (size_t)cols * (retain_pitch(g.n_rho) * 4 + 8); }
 
 constexpr int kVoteWaves = 16;
 constexpr int kPeakWaves = kPeakRowsPerBlock;
@@ -2851,14 +3146,19 @@ int vote_slab_rows(int n_rho, size_t lds_limit) {
     const size_t fixed = (size_t)kVoteWaves * kStageBytes + 256 + 256;    // stages, slack, static LDS
     if (lds_limit <= fixed + 2 * 128) return 0;
     const long rows = (long)((lds_limit - fixed) / 128) - 1;
-    return (int)(rows < n_rho ? rows : n_rho);
+    return (int)(rows < n_rho ? rows - rows % 4 : n_rho);      // whole quads of rows per slab
 }
 
-size_t peaks_lds_bytes(int n_rho, int waves) { return (size_t)(waves + 2) * n_rho * 4 + 256; }
+size_t peaks_lds_bytes(int n_rho, int waves) {
+    return (size_t)waves * ((n_rho + 63) / 64) * 8 + (size_t)(waves + 2) * n_rho * 4;
+}
 
-int peak_block_waves(int n_rho, size_t lds_limit) {
-    for (int w = kPeakWaves; w >= 2; w >>= 1)
-        if (peaks_lds_bytes(n_rho, w) + 256 <= lds_limit) return w;
+// Few rows per workgroup share one event's rows over more of the chip (one event, 720 x 512: 45
+// workgroups of 16 rows took 8 + 10 us, 180 of 4 take 6 + 8); every workgroup adds up all their counts, so grids of
+// many columns take more.
+int peak_block_waves(int n_theta, int n_rho, size_t lds_limit) {
+    for (int w = n_theta > 4096 ? kPeakWaves : 4; w >= 2; w >>= 1)
+        if (peaks_lds_bytes(n_rho, w) + 512 <= lds_limit) return w;
     return 0;
 }
 
@@ -2931,16 +3231,25 @@ hipError_t launch_dedup(const BatchArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename T>
+static hipError_t launch_vote_t(const GridArgs &g, const float *x, const float *y, uint32_t n_hits, T *acc,
+                                hipStream_t s) {
+    static const bool lds_ok = (allow_lds(k_vote<kVoteWaves, T>), true);
+    (void)lds_ok;
+    const int groups = (g.n_theta + 31) / 32, slabs = (g.n_rho + g.vote_rows - 1) / g.vote_rows;
+    // four cells per store where every column's (and slab's) first cell is aligned for it
+    const int vec = g.n_rho % 4 == 0 && (slabs == 1 || g.vote_rows % 4 == 0) &&
+                    (uintptr_t)acc % (4 * sizeof(T)) == 0;
+    hipLaunchKernelGGL((k_vote<kVoteWaves, T>), dim3(groups, slabs), dim3(kVoteWaves * 64),
+                       (size_t)(g.vote_rows + 1) * 128, s, g, x, y, n_hits, acc, g.vote_rows, vec);
+    return hipGetLastError();
+}
+
 hipError_t launch_vote(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
                        void *acc, int acc_type, hipStream_t s) {
     if (g.vote_rows < 1) return hipErrorInvalidValue;
-    const size_t lds = vote_lds_bytes(g.vote_rows);
-    static const bool lds_ok = (allow_lds(k_vote<kVoteWaves>), true);
-    (void)lds_ok;
-    const int groups = (g.n_theta + 63) / 64, slabs = (g.n_rho + g.vote_rows - 1) / g.vote_rows;
-    hipLaunchKernelGGL(k_vote<kVoteWaves>, dim3(groups, slabs), dim3(kVoteWaves * 64), lds, s, g, x, y,
-                       n_hits, acc, acc_type, g.vote_rows);
-    return hipGetLastError();
+    return acc_type == HOUGH_ACC_U16 ? launch_vote_t(g, x, y, n_hits, static_cast<uint16_t *>(acc), s)
+                                     : launch_vote_t(g, x, y, n_hits, static_cast<uint32_t *>(acc), s);
 }
 
 template <int NW, typename T>
@@ -3014,31 +3323,43 @@ template <typename T>
 static void launch_iter_t(const GridArgs &g, const T *acc, uint32_t frac_num, uint32_t frac_den, int r_theta,
                           int r_rho, hough_peak *peaks, uint32_t cap, uint32_t *n_peaks, uint32_t *status,
                           const uint32_t *offsets, uint32_t n_blocks, const IterPlan &ip, uint32_t *gbm,
-                          hipStream_t s) {
+                          const uint64_t *list, uint32_t *scan, hipStream_t s) {
     if (ip.gbm) {
         static const bool lds_ok = (allow_lds(k_peaks_iter<T, true>), true);
         (void)lds_ok;
         hipLaunchKernelGGL((k_peaks_iter<T, true>), dim3(n_blocks), dim3(kIterThreads), ip.lds_bytes, s, g, acc,
-                           frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, offsets, ip.keys, gbm);
+                           frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, offsets, ip.keys, gbm,
+                           list, scan);
     } else {
         static const bool lds_ok = (allow_lds(k_peaks_iter<T, false>), true);
         (void)lds_ok;
         hipLaunchKernelGGL((k_peaks_iter<T, false>), dim3(n_blocks), dim3(kIterThreads), ip.lds_bytes, s, g, acc,
                            frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, offsets, ip.keys,
-                           nullptr);
+                           nullptr, list, scan);
     }
+}
+
+template <typename T>
+static void launch_iter_one(const GridArgs &g, const T *acc, uint32_t frac_num, uint32_t frac_den, int r_theta,
+                            int r_rho, hough_peak *peaks, uint32_t cap, uint32_t *n_peaks, uint32_t *status,
+                            const IterPlan &ip, uint32_t *gbm, uint64_t *list, uint32_t *scan, hipStream_t s) {
+    const uint32_t cells = (uint32_t)g.n_theta * (uint32_t)g.n_rho, tile = kScanThreads * kScanCells;
+    hipLaunchKernelGGL(k_iter_scan<T>, dim3(std::min((cells + tile - 1u) / tile, 1024u)), dim3(kScanThreads), 0, s,
+                       acc, cells, g.threshold, frac_num, frac_den, list, scan);
+    launch_iter_t<T>(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, nullptr, 1u, ip, gbm,
+                     list, scan, s);
 }
 
 hipError_t launch_peaks_iterative(const GridArgs &g, const void *acc, int acc_type, uint32_t frac_num,
                                   uint32_t frac_den, int r_theta, int r_rho, hough_peak *peaks,
                                   uint32_t cap, uint32_t *n_peaks, uint32_t *status, const IterPlan &ip,
-                                  uint32_t *gbm, hipStream_t s) {
+                                  uint32_t *gbm, uint64_t *list, uint32_t *scan, hipStream_t s) {
     if (acc_type == HOUGH_ACC_U16)
-        launch_iter_t<uint16_t>(g, static_cast<const uint16_t *>(acc), frac_num, frac_den, r_theta, r_rho, peaks,
-                                cap, n_peaks, status, nullptr, 1u, ip, gbm, s);
+        launch_iter_one<uint16_t>(g, static_cast<const uint16_t *>(acc), frac_num, frac_den, r_theta, r_rho, peaks,
+                                  cap, n_peaks, status, ip, gbm, list, scan, s);
     else
-        launch_iter_t<uint32_t>(g, static_cast<const uint32_t *>(acc), frac_num, frac_den, r_theta, r_rho, peaks,
-                                cap, n_peaks, status, nullptr, 1u, ip, gbm, s);
+        launch_iter_one<uint32_t>(g, static_cast<const uint32_t *>(acc), frac_num, frac_den, r_theta, r_rho, peaks,
+                                  cap, n_peaks, status, ip, gbm, list, scan, s);
     return hipGetLastError();
 }
 
@@ -3047,8 +3368,7 @@ hipError_t launch_track_params(const GridArgs &g, const float *x, const float *y
                                double rho_min, double rho_max, double b_tesla, hough_track *out,
                                hipStream_t s) {
     if (cap == 0) return hipSuccess;
-    const int blocks = (int)((cap + kTrackWaves - 1) / kTrackWaves);
-    hipLaunchKernelGGL(k_track_params, dim3(blocks), dim3(kTrackWaves * 64), 0, s, g, x, y, n_hits, peaks,
+    hipLaunchKernelGGL(k_track_params, dim3(std::min(cap, 2048u)), dim3(kTrackWaves * 64), 0, s, g, x, y, n_hits, peaks,
                        n_peaks, cap, rho_min, rho_max, b_tesla, out);
     return hipGetLastError();
 }
@@ -3057,13 +3377,14 @@ hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint
                          const hough_peak *peaks, const uint32_t *n_peaks, uint32_t cap,
                          uint8_t *keep, hipStream_t s) {
     if (n_hits == 0) return hipSuccess;
-    const int rows = retain_rows_per_block(g);
-    const size_t lds = retain_lds_bytes(g, rows);
-    static const bool lds_ok = (allow_lds(k_retain<kRetainWaves>), true);
-    (void)lds_ok;
-    const int blocks = (int)((n_hits + kRetainWaves * 64 - 1) / (kRetainWaves * 64));
-    hipLaunchKernelGGL(k_retain<kRetainWaves>, dim3(blocks), dim3(kRetainWaves * 64), lds, s, g, x, y,
-                       n_hits, peaks, n_peaks, cap, keep, rows);
+    const int cols = retain_cols_per_block(g);
+    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<true>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, kRetainDilBytes);
+    if (lds_ok != hipSuccess) return lds_ok;
+    // one workgroup per 64 hits up to twice the chip, then several chunks per built block
+    const uint32_t chunks = n_hits / 64u + (n_hits % 64u != 0u);
+    hipLaunchKernelGGL(k_retain<true>, dim3(std::min(chunks, 512u)), dim3(kRetainWaves * 64),
+                       retain_lds_bytes(g, cols), s, g, x, y, n_hits, peaks, n_peaks, cap, keep, cols, nullptr);
     return hipGetLastError();
 }
 
@@ -3089,16 +3410,19 @@ hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     launch_iter_t<uint16_t>(g, acc, frac_num, frac_den, r_theta, r_rho, a.peaks, a.max_peaks, a.n_peaks, a.status,
-                            a.offsets, a.n_events, ip, gbm, s);
+                            a.offsets, a.n_events, ip, gbm, nullptr, nullptr, s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     {
-        const int rows = retain_rows_per_block(g);
-        const size_t lds = retain_lds_bytes(g, rows);
-        static const bool lds_ok = (allow_lds(k_retain<kRetainWaves>), true);
-        (void)lds_ok;
-        const uint32_t blocks = (kMaxBatchHits + kRetainWaves * 64 - 1) / (kRetainWaves * 64);
-        hipLaunchKernelGGL(k_retain<kRetainWaves>, dim3(a.n_events, blocks), dim3(kRetainWaves * 64), lds, s, g,
-                           a.x, a.y, 0u, a.peaks, a.n_peaks, a.max_peaks, a.keep, rows, a.offsets);
+        const int cols = retain_cols_per_block(g);
+        static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<false>),
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kRetainDilBytes);
+        if (lds_ok != hipSuccess) return lds_ok;
+        // a few events: several workgroups each, up to the largest event's chunks
+        const uint32_t most = (kMaxBatchHits + kRetainWaves * 64 - 1) / (kRetainWaves * 64);
+        const uint32_t blocks = std::max(1u, std::min(most, 512u / a.n_events));
+        hipLaunchKernelGGL(k_retain<false>, dim3(a.n_events, blocks), dim3(kRetainWaves * 64),
+                           retain_lds_bytes(g, cols), s, g, a.x, a.y, 0u, a.peaks, a.n_peaks, a.max_peaks, a.keep,
+                           cols, a.offsets);
         e = hipGetLastError();
     }
     return e;

@@ -106,3 +106,95 @@ def test_retention_by_columns(H, orc, T, W, groups):
     ctx.set_batch_plan(8, groups)
     _check(H, orc, ctx, g, T, W, 8192, x, y, off)
     ctx.close()
+
+
+
+# grids whose columns hold whole quads of rows and not, 32-column groups with remainders, one slab
+# and several; a 16-bit accumulator; an accumulator that is not 16-byte aligned
+@pytest.mark.parametrize("n_theta,n_rho,acc_type,shift", [(1, 3, "i32", 0), (33, 100, "i32", 0), (64, 97, "i32", 0),
+                                                          (65, 96, "u16", 0), (95, 50, "u16", 0), (40, 64, "i32", 1),
+                                                          (40, 64, "u16", 1), (31, 1400, "i32", 0),
+                                                          (31, 1401, "u16", 0), (20, 8192, "i32", 0)])
+def test_event_vote_tiles(H, orc, n_theta, n_rho, acc_type, shift):
+    import torch
+    for lo, hi in ((-0.008, 0.008), (-0.0015, 0.002)):
+        g = orc.Grid(n_theta, n_rho, lo, hi)
+        ctx = H.Context(n_theta, n_rho, lo, hi, acc_type, 3, 1, 64)
+        for n in (0, 1, 65, 1500):
+            x, y, _ = _events([n], 3 + n, 160.0, 0.03) if n else (np.zeros(0, np.float32),) * 2 + (None,)
+            dt = torch.int16 if acc_type == "u16" else torch.int32
+            buf = torch.full((n_theta * n_rho + 8,), 7, dtype=dt, device="cuda")
+            acc = buf[shift:shift + n_theta * n_rho].view(n_theta, n_rho)
+            ctx.vote(_t(x), _t(y), acc)
+            got = acc.cpu().numpy()
+            got = got.view(np.uint16).astype(np.int32) if acc_type == "u16" else got
+            assert np.array_equal(got, orc.vote(g, x, y)), (lo, n)
+            assert int(buf[shift + n_theta * n_rho].item()) == 7           # nothing past the last cell
+        ctx.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho,W", [(70, 40, 1), (300, 300, 1), (300, 300, 40), (700, 1000, 2), (37, 2000, 1)])
+@pytest.mark.parametrize("n_hits", [1, 63, 64, 65, 1500])
+def test_event_retain_forms(H, orc, n_theta, n_rho, W, n_hits):
+    """hough_retain against a peak list (up to 1,024 peaks) and against dilated bits (more, in one
+    and several blocks of columns), with peaks on the rho edges and cells outside the grid."""
+    lo, hi = -1 / 170, 1 / 170
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    x, y, _ = _events([n_hits], 9, 160.0, 0.02)
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", 3, W, 64)
+    rng = np.random.default_rng(n_hits)
+    for n in (0, 1, 17, 1022, 1023, 6000):
+        n = min(n, n_theta * n_rho)
+        cell = rng.choice(n_theta * n_rho, n, replace=False)
+        pj, pk = cell // n_rho, cell % n_rho
+        pk[: n // 5] = rng.choice([0, n_rho - 1], n // 5)           # some on the rho edges
+        rec = np.zeros((n + 2, 2), np.uint32)
+        rec[:n, 0] = pj | (pk << 16)
+        rec[n:, 0] = n_theta, n_rho << 16                          # two cells outside the grid
+        keep = ctx.retain(_t(x), _t(y), _t(rec.view(np.int32)), _t(np.array([n + 2], np.int32)), n + 2)
+        assert np.array_equal(keep.cpu().numpy(), orc.retain(g, x, y, pj, pk, W)), n
+    ctx.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho", [(1, 1), (2, 5), (37, 129), (129, 300), (500, 700)])
+@pytest.mark.parametrize("frac", [(0, 1), (1, 2), (1, 1)])
+def test_event_finder_listed_candidates(H, orc, n_theta, n_rho, frac):
+    """The iterative finder on candidates listed by the whole chip: none, a few, one per thread, more
+    than one key buffer and more than the list, on accumulators of equal and of random counts."""
+    rng = np.random.default_rng(n_theta)
+    ctx = H.Context(n_theta, n_rho, -0.005, 0.005, "i32", 4, 1, 64)
+    cap = 600
+    for kind in range(5):
+        acc = np.zeros((n_theta, n_rho), np.int32)
+        if kind == 1:
+            acc[:] = 5                                             # one flat plateau
+        elif kind == 2:
+            acc[:] = rng.integers(0, 5, acc.shape)
+            acc.flat[rng.integers(0, acc.size, 9)] = 40
+        elif kind == 3:
+            acc[:] = rng.integers(0, 60, acc.shape)
+        elif kind == 4:
+            acc[:] = rng.integers(3, 9, acc.shape)
+            acc.flat[-1] = 9
+        pk, n, st = ctx.peaks_iterative(_t(acc), cap, frac, 3, 4)
+        pj, pkk, pc, m = orc.peaks_iterative(acc, 4, frac, 3, 4, cap=cap, sorted_form=True)
+        assert int(n.item()) == m, kind
+        k = min(m, cap)
+        assert np.array_equal(H.decode_peaks(pk, k), np.stack([pj[:k], pkk[:k], pc[:k]], 1).astype(np.int64)), kind
+        assert int(st.item()) == (H.EV_PEAKS_TRUNCATED if m > cap else 0)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho", [(2, 2), (3, 70), (5, 64), (8, 100), (130, 257), (4100, 12)])
+def test_event_peaks_blocks(H, orc, n_theta, n_rho):
+    """hough_peaks' blocks of 4 (many columns: 16) rows, their edges and the periodic border."""
+    rng = np.random.default_rng(n_theta * n_rho)
+    for periodic in (False, True):
+        ctx = H.Context(n_theta, n_rho, -0.005, 0.005, "i32", 3, 1, 64, periodic=periodic)
+        for top in (4, 30):
+            acc = rng.integers(0, top, (n_theta, n_rho)).astype(np.int32)
+            pk, n = ctx.peaks(_t(acc), n_theta * n_rho)
+            pj, pkk, pc, m = orc.peaks(acc, 3, periodic=periodic)
+            assert int(n.item()) == m
+            assert np.array_equal(H.decode_peaks(pk, m), np.stack([pj, pkk, pc], 1).astype(np.int64))
+        ctx.close()
