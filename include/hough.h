@@ -199,7 +199,10 @@ int hough_retain(hough_ctx *ctx, const float *x, const float *y, uint32_t n_hits
  * peaks: n_events * max_peaks entries; event e's peaks go to peaks[e * max_peaks ...] in raster
  * order, truncated at max_peaks.  n_peaks[e]: the true peak count.  keep: offsets[n_events]
  * bytes (indexed like x), computed from ALL peaks of the event even when the list is
- * truncated.  status[e]: HOUGH_EV_* bits.  n_events == 0 is valid.  A batch of more events
+ * truncated.  status[e]: HOUGH_EV_* bits.  n_events == 0 is valid.  A batch that would leave
+ * half of the CUs without an event (at most 128 on MI355X; not with a relative threshold, and where
+ * the fused kernel holds a whole rho column) runs one workgroup per (event, theta tile), as
+ * hough_run_batch_split does, with the same results.  A batch of more events
  * than the kernel has resident workgroups (and at most 65,536 events) is preceded by a small
  * launch that schedules the events largest first; no result depends on the schedule.
  * The fused kernel keeps an event's theta tile on chip, with 16-bit counts.  What it cannot
@@ -237,7 +240,8 @@ int hough_run_batch_gather(hough_ctx *ctx, const float *x, const float *y, const
 /* The latency form of hough_run_batch / hough_run_batch_gather: the same outputs (bit for bit),
  * but each (event, theta tile) pair is a work item of its own, so the tiles of one event run on
  * different workgroups at once and a small batch finishes sooner (each tile examines the hits
- * the others have not kept yet, so a large batch finishes later than with hough_run_batch).
+ * the others have not kept yet, so a large batch finishes later than with hough_run_batch, which
+ * takes this form by itself for small batches).
  * event_ids and keep_offsets are both NULL (events are offsets' own, keep indexed like x) or
  * both given (gather form).  workspace: device buffer of at least
  * hough_split_workspace_bytes(ctx, n_events) bytes, 256-byte aligned, filled with zeros before

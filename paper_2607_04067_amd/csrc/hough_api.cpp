@@ -24,6 +24,8 @@ struct hough_ctx {
     hough::IterPlan iterb;  // ... over a batch (hough_run_batch_iterative), two workgroups per CU
     hough::GridArgs g;
     hough::BatchPlan plan;  // the fused kernel's launch shape (fused != 0)
+    hough::SplitPlan split; // the split form's (fused == 1)
+    uint32_t *d_slots;      // its slots for batches of up to split_events(n_cu) events (fused == 1)
     int fused;              // 1: the fused kernel holds the grid's whole column (and windows of it);
                             // 2: only windows of it (taller grids, theta not periodic; the split
                             // form spills every event); 0: every batch event spills
@@ -75,6 +77,15 @@ int spill_workgroups(size_t stride_words, int n_cu, bool all) {
     return n < 1 ? 1 : (int)n;
 }
 
+// Batches that would leave at least half of the CUs without an event run in the split form, on the
+// context's own slots: the fused kernel walks an event's tiles one after the other on one
+// workgroup, so its time hardly depends on the number of events up to one per CU, while the
+// split form's grows with it.  Measured, us per batch fused / split at 1, 64, 128 and 256 events on
+// 256 CUs: 180 x 128 (3 tiles) 23 / 14, 25 / 17, 26 / 21, 29 / 28; 360 x 256 (6 tiles) 73 / 21,
+// 80 / 37, 81 / 49, 84 / 82; 720 x 512 dense (12 tiles) 234 / 40, 241 / 120, 249 / 186, 255 / 348;
+// 1000 x 1000 (17 tiles) 192 / 23, 286 / 79, 287 / 138, 257 / 257.
+uint32_t split_events(int n_cu) { return (uint32_t)n_cu / 2u; }
+
 // Bound on u^2 + v^2 under which a hit's bin t = fma(u, C_j, fma(v, S_j, B)) lies strictly
 // inside (0, n_rho) for every column: |t - B| is at most A * sqrt(u^2 + v^2) plus the rounding
 // of C_j, S_j and the two fmas (a few 2^-24 of n_rho), well inside the margin kept here; the
@@ -102,7 +113,7 @@ int default_plan(hough_ctx *c) {
         hough::BatchPlan p;
         if (hough::plan_batch(c->p.n_theta, c->p.n_rho, waves_opts[wi], 1, c->lds_limit, &p) != 0) continue;
         p.per_cu = hough::prepare_batch(&p);
-        if (p.per_cu < 1 || p.split_per_cu < 1) continue;
+        if (p.per_cu < 1) continue;
         const int score = p.per_cu * p.waves;
         if (score > best) { best = score; pick = p; }
     }
@@ -124,7 +135,7 @@ int windowed_plan(const hough_ctx *c, int waves, int groups, int groups_per_cu, 
         if (hough::plan_batch(c->p.n_theta, c->p.n_rho, waves, groups, c->lds_limit, &p, win, need_split) != 0)
             continue;
         p.per_cu = hough::prepare_batch(&p);
-        if (p.per_cu >= groups_per_cu && (!need_split || p.split_per_cu >= 1)) {
+        if (p.per_cu >= groups_per_cu) {
             *out = p;
             return 0;
         }
@@ -267,6 +278,14 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         return HOUGH_ENOMEM;
     }
     c->fused = fused_fits(p->n_rho, limit) ? 1 : ((p->flags & HOUGH_FLAG_THETA_PERIODIC) ? 0 : 2);
+    const size_t slot_bytes = (size_t)(split_events(c->n_cu) + 1u) * hough::split_tiles(p->n_theta) * sizeof(uint32_t);
+    if (c->fused == 1) {
+        c->split = hough::plan_split(p->n_rho, limit);
+        if (hipMalloc(&c->d_slots, slot_bytes) != hipSuccess) {
+            hough_destroy(c);
+            return HOUGH_ENOMEM;
+        }
+    }
     c->spill_stride = hough::spill_stride(p->n_theta, p->n_rho);
     c->spill_wgs = spill_workgroups(c->spill_stride, c->n_cu, c->fused != 1);
     // fewer slices where the device cannot spare the budget
@@ -280,7 +299,8 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         c->spill_wgs = (c->spill_wgs + 1) / 2;
     }
     if (hipMemcpy(c->d_tables, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(c->d_work, 0, work_bytes) != hipSuccess) {
+        hipMemset(c->d_work, 0, work_bytes) != hipSuccess ||
+        (c->d_slots && hipMemset(c->d_slots, 0, slot_bytes) != hipSuccess)) {
         hough_destroy(c);
         return HOUGH_EDEVICE;
     }
@@ -324,6 +344,7 @@ void hough_destroy(hough_ctx *c) {
     if (c->d_iter_bm) (void)hipFree(c->d_iter_bm);
     if (c->d_iter_list) (void)hipFree(c->d_iter_list);
     if (c->d_spill) (void)hipFree(c->d_spill);
+    if (c->d_slots) (void)hipFree(c->d_slots);
     delete c;
 }
 
@@ -357,10 +378,9 @@ int hough_set_batch_plan(hough_ctx *c, int32_t waves_per_group, int32_t column_g
         if (hough::plan_batch(c->p.n_theta, c->p.n_rho, waves_per_group, column_groups, c->lds_limit, &p) != 0)
             return HOUGH_EINVAL;
         p.per_cu = hough::prepare_batch(&p);
-        if (p.per_cu >= 1 && p.split_per_cu >= 1 && groups_per_cu > p.per_cu &&
+        if (p.per_cu >= 1 && groups_per_cu > p.per_cu &&
             windowed_plan(c, waves_per_group, column_groups, groups_per_cu, &p) != 0)
             p.per_cu = 0;
-        if (p.split_per_cu < 1) p.per_cu = 0;
     } else if (windowed_plan(c, waves_per_group, column_groups, groups_per_cu > 0 ? groups_per_cu : 1, &p) != 0) {
         p.per_cu = 0;                         // only windows of the column fit
     }
@@ -513,7 +533,7 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
     // every event through the spill path: no fused kernel for this grid, or the split form on a
     // grid whose whole column does not fit it (the split form gives the same results)
     const bool spill_all = !c->fused || (split && c->fused == 2);
-    hough::SpillArgs spill{c->d_spill, c->spill_stride, c->d_work + 2, spill_all ? 1u : 0u};
+    hough::SpillArgs spill{c->d_spill, c->spill_stride, c->d_work + 2, spill_all ? 1u : 0u, nullptr, 0u};
     // otherwise the fused (or split) kernel counts the events it leaves to the spill kernel in
     // the spill kernel's first counter, so that the spill kernel skips its scan when none
     a.spill_count = spill_all ? nullptr : c->d_work + 2;
@@ -527,17 +547,20 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
     long grid = (long)plan.per_cu * c->n_cu;
     if (grid > (long)n_events) grid = n_events;
     plan.grid = (int)grid;
-    hough::SplitArgs sp;
+    hough::SplitArgs sp{};
     if (split) {
         if (!hough::split_layout(c->p.n_theta, c->p.n_rho, c->plan.groups, n_events, workspace, workspace_bytes,
                                  &sp))
             return HOUGH_EINVAL;
-        const long items = (long)n_events * sp.n_tiles;
-        if (items >= (1L << 31)) return HOUGH_EINVAL;      // the work queue counts in 32 bits
-        // the split form holds the whole column, whatever window the fused kernel's plan has
-        const int per = c->plan.per_cu < c->plan.split_per_cu ? c->plan.per_cu : c->plan.split_per_cu;
-        long g2 = (long)per * c->n_cu;
-        plan.grid = (int)(g2 < items ? g2 : items);
+        if ((long)n_events * sp.n_tiles >= (1L << 31)) return HOUGH_EINVAL;   // the work queue counts in 32 bits
+    } else if (c->fused == 1 && frac_den == 0 && n_events <= split_events(c->n_cu)) {
+        split = true;
+        sp.n_tiles = hough::split_tiles(c->p.n_theta);
+        sp.slots = c->d_slots;
+    }
+    if (split) {
+        spill.slots = sp.slots;
+        spill.n_slots = n_events * sp.n_tiles;
     }
     if (c->g.dedup) e = hough::launch_dedup(a, (hipStream_t)stream);   // marks later copies in keep
     // more events than resident workgroups: take them largest first, so that the batch does not
@@ -547,7 +570,7 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
         a.order = c->d_order;
     }
     if (e == hipSuccess)
-        e = split ? hough::launch_batch_split(c->g, plan, a, sp, (hipStream_t)stream)
+        e = split ? hough::launch_batch_split(c->g, c->split, a, sp, c->n_cu, (hipStream_t)stream)
                   : hough::launch_batch(c->g, plan, a, (hipStream_t)stream);
     // events above the fused kernel's hit limit or beyond its window (flagged and skipped there),
     // through the spill path

@@ -52,8 +52,13 @@ struct BatchPlan {
     int grid;            // persistent workgroups
     int sparse;          // retention by peak list on tiles with few peaks (see kSparseRhoRows)
     int win;             // rows of a windowed tile (0: the tile holds the whole rho column)
-    size_t split_lds_bytes;   // the split form's LDS (it always holds the whole column)
-    int split_per_cu;    // its resident workgroups per CU
+    size_t split_lds_bytes;   // LDS of the whole column (a plan must leave room for it where the
+                              // grid has a split form)
+};
+// Waves per workgroup of the split form: for batches of at most one (event, tile) item per CU, and
+// for larger ones (0: the whole column does not fit).
+struct SplitPlan {
+    int wide, narrow;
 };
 // Status bit of an event the fused (or split) kernel leaves to the spill kernel launched after
 // it: more than kMaxBatchHits hits, or hits that reach beyond the rows of a windowed tile.  The
@@ -85,17 +90,15 @@ struct BatchArgs {
                              // (zero between launches; the spill kernel clears it)
 };
 
-// Workspace of the split form (one workgroup per theta tile of an event), laid out by
-// split_layout() in the caller's buffer.  Everything in it is zero between launches.
+// The split form (one workgroup per theta tile of an event): one slot per (event, tile), zero
+// between calls (the caller's workspace, or the context's own slots).
 struct SplitArgs {
     uint32_t n_tiles;
-    uint32_t tile_cap;       // most peaks one tile can hold (no two peaks are 8-adjacent)
-    uint32_t *counts;        // [n_events * n_tiles] peaks listed by each tile
-    hough_peak *staged;      // [n_events * n_tiles * tile_cap] each tile's list, raster order
-    uint32_t *kept;          // [n_events * kSplitKeepWords] keep bits of each event's hits
-    uint32_t *done;          // [n_events] tiles finished; the last one merges
-    uint32_t *flags;         // [n_events] HOUGH_EV_* bits seen by the tiles
+    uint32_t *slots;
 };
+uint32_t split_tiles(int n_theta);
+SplitPlan plan_split(int n_rho, size_t lds_limit);
+// Keep words per event in the split form's workspace size.
 constexpr uint32_t kSplitKeepWords = (kMaxBatchHits + 31) / 32 + 1;
 size_t split_workspace_bytes(int n_theta, int n_rho, int groups, uint32_t n_events);
 bool split_layout(int n_theta, int n_rho, int groups, uint32_t n_events, void *ws, size_t bytes,
@@ -114,6 +117,8 @@ struct SpillArgs {
     uint32_t *queue;     // [3], zero between launches: all = 1: work and exit counters; all = 0:
                          // the count of events left to it, the exit counter, the block counter
     uint32_t all;
+    uint32_t *slots;     // after the split form: its slots, to be zeroed with a.queue (else n_slots 0)
+    uint32_t n_slots;
 };
 size_t spill_stride(int n_theta, int n_rho);
 hipError_t launch_spill(const GridArgs &g, const BatchArgs &a, const SpillArgs &sp, int n_wg, hipStream_t s);
@@ -179,8 +184,8 @@ hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint
                          const hough_peak *peaks, const uint32_t *n_peaks, uint32_t cap,
                          uint8_t *keep, hipStream_t s);
 hipError_t launch_batch(const GridArgs &g, const BatchPlan &p, const BatchArgs &a, hipStream_t s);
-hipError_t launch_batch_split(const GridArgs &g, const BatchPlan &p, const BatchArgs &a,
-                              const SplitArgs &sp, hipStream_t s);
+hipError_t launch_batch_split(const GridArgs &g, const SplitPlan &p, const BatchArgs &a, const SplitArgs &sp,
+                              int n_cu, hipStream_t s);
 
 // LDS needs and plans (hough_kernels.hip).
 // LDS of hough_vote's workgroup for a slab of `rows` rho rows, and the tallest slab that fits.

@@ -2387,209 +2387,179 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
 // ------------------------------------------------------------ split batch path (latency form)
 // The same results as k_batch for batches small enough that latency matters more than
 // throughput: the work items are the (event, theta tile) pairs, so the tiles of one event run
-// on different workgroups at once.  A tile votes all of its event's hits, finds its peaks, lists
-// them in raster order into its own slot of the workspace, dilates them, and sets the keep bits
-// of the event's hits it keeps.  The workgroup that finishes an event's last tile merges: the
-// tile lists in tile order (raster order) truncated at max_peaks, the true count, the status
-// and the keep bytes, and it leaves the event's part of the workspace zero again.  Every tile
-// examines all of the event's hits, so retention costs more in total than in k_batch, and
-// each publish and merge is an agent-scope release or acquire: the price of the shorter
-// latency.
+// on different workgroups at once.  A workgroup takes one item: it votes all of the event's hits,
+// finds the tile's peaks, publishes their number in the item's slot, adds up the numbers of
+// the event's earlier tiles, and lists its peaks where they belong in the event's list.  It then
+// tests the event's hits that no other tile has kept yet.  Nothing is staged or merged: the
+// tiles of an event share its slots and its keep bytes, and nothing else.
+//
+// Waiting for the earlier tiles ends: items are numbered event by event, tile by tile, and taken
+// from a counter, so every earlier tile belongs to a workgroup that is already running, and a
+// workgroup publishes before it waits.
+//
+// What the tiles share is written and read by agent-scope atomics, which pass by the L2s (one
+// per XCD, not coherent with each other); a wave's stores are waited for before the barrier
+// that precedes the publication.  Tile 0 clears the keep bytes before it publishes, the others
+// set theirs after they have seen its slot.  No cache is written back or invalidated on the way
+// (publishing with fences and merging staged lists took 11 of one event's 30 us; it takes 16
+// so).  The spill kernel launched afterwards puts the slots and the counter back to zero.
+constexpr uint32_t kSlotReady = 0x80000000u;
 
-// Step 5 of one tile in the split form: keep bits in global memory, shared by the tiles.  A
-// wave tests 64 consecutive hits at a time and merges its kept bits into (at most three) words
-// before it touches global memory, so that the tiles' atomics stay few.
-template <int G>
-__device__ void retain_split(const uint32_t *dil, float2 *st, const float *x, const float *y,
-                             uint32_t *bits, uint32_t hb, uint32_t he, const Cols<G> &cl,
-                             const GridArgs &g, int lane) {
-    uint32_t unused = 0;
+__device__ __forceinline__ uint32_t keep_load(const uint8_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void keep_store(uint8_t *p, uint32_t v) {
+    __hip_atomic_store(p, (uint8_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Step 5 of one tile in the split form, over a wave's share of the event's hits: against the
+// tile's peak list when it has one (np <= kTilePeaks), else as retain_range.
+__device__ void retain_split(const uint32_t *dil, const float4 *tpk, uint32_t np, bool edge, float2 *st,
+                             const float *x, const float *y, uint8_t *ke, uint32_t hb, uint32_t he,
+                             const Cols<1> &cl, const GridArgs &g, int first_col, int lane) {
+    const bool many = np * (2u * (uint32_t)g.rho_window + 1u) >= (uint32_t)g.n_rho;
+    uint32_t kn = 1u;
     float xn = 0.0f, yn = 0.0f;                       // the next 64 hits load while these are tested
-    if (hb + lane < he) { xn = x[hb + lane]; yn = y[hb + lane]; }
+    if (hb + lane < he) { kn = keep_load(ke + hb + lane); xn = x[hb + lane]; yn = y[hb + lane]; }
     for (uint32_t base = hb; base < he; base += 64) {
+        const uint32_t i = base + (uint32_t)lane, kv = kn;
         const float xi = xn, yi = yn;
-        const uint32_t nb = base + 64u + (uint32_t)lane;
-        if (nb < he) { xn = x[nb]; yn = y[nb]; }
-        int slot;
-        const StageCount n = stage_values(st, xi, yi, base + lane < he, g, unused, slot);
-        const uint64_t kept = lookup_staged<G, kDilPitch<G>>(dil, st, n, cl, lane, g.nrho_f);
-        const uint64_t m = __ballot(slot >= 0 && ((kept >> slot) & 1ull));   // bit l: hit base + l
-        const uint32_t sh = base & 31u;
-        if (m && lane < 3) {
-            uint64_t part;                                                    // bits of word base/32 + lane
-            if (lane == 0) part = m << sh;
-            else if (lane == 1) part = m >> (32u - sh);
-            else part = sh ? m >> (64u - sh) : 0ull;
-            part &= 0xffffffffull;
-            if (part) atomicOr(&bits[(base >> 5) + (uint32_t)lane], (uint32_t)part);
+        if (i + 64 < he) { kn = keep_load(ke + i + 64); xn = x[i + 64]; yn = y[i + 64]; }
+        const bool todo = i < he && !(kv & 1u);
+        if (__ballot(todo) == 0ull) continue;
+        float u, v;
+        const bool valid = conformal(todo ? xi : 0.0f, todo ? yi : 0.0f, u, v) && todo;
+        uint64_t kept = 0;
+        if (np <= kTilePeaks) {
+            kept = kept_by_peaks(tpk, np, valid ? u : 0.0f, valid ? v : 0.0f, valid, edge, g);
+        } else {
+            const bool safe = valid && all_in_range(u, v, g);
+            const uint64_t bs = __ballot(safe), bv = __ballot(valid);
+            if (many && bs) kept = kept_by_columns<1>(dil, safe ? u : 0.0f, safe ? v : 0.0f, bs, first_col, g);
+            kept |= lookup_lanes<1>(dil, st, u, v, bs & ~kept, cl, g, lane);
+            kept |= lookup_checked<1>(dil, u, v, bv & ~bs, cl, g, lane);
         }
-        wave_sync();
+        if ((kept >> lane) & 1ull) keep_store(ke + i, kv | 1u);
     }
 }
 
-template <int NW, int G, bool PER>
-__global__ __launch_bounds__(NW * 64, G == 1 ? 6 : 4) void k_batch_split(GridArgs g, BatchArgs a, SplitArgs sp,
-                                                                         int nwords) {
-    using L = Lane<G, true>;
-    constexpr int TW = L::TW, ST = L::STRIDE, DP = (int)kDilPitch<G>, OUT = TW - 2, NT = NW * 64;
+template <int NW, bool PER>
+__global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridArgs g, BatchArgs a, SplitArgs sp,
+                                                                           int nwords) {
+    using L = Lane<1, true>;
+    constexpr int TW = L::TW, ST = L::STRIDE, DP = (int)kDilPitch<1>, OUT = TW - 2, NT = NW * 64;
     extern __shared__ __align__(16) uint32_t lds[];
     uint32_t *tile = lds;                                                  // [(n_rho + 1) * ST]
     float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)(g.n_rho + 1) * ST);   // [NW * 64]
     uint32_t *pmask = reinterpret_cast<uint32_t *>(stage + NW * 64);       // [nwords * TW]
-    uint32_t *dil = pmask + (size_t)nwords * TW;                           // [(nwords + 1) * DP]
-    __shared__ uint32_t s_item, s_flags, s_last;
+    float4 *tpk = reinterpret_cast<float4 *>(pmask + (size_t)nwords * TW);   // [kTilePeaks]
+    uint32_t *colcnt = reinterpret_cast<uint32_t *>(tpk + kTilePeaks);     // [TW]
+    uint32_t *dil = colcnt + TW;                                           // [(nwords + 1) * DP]
+    __shared__ uint32_t s_item, s_bad, s_base, s_edge;
     const int lane = threadIdx.x & 63, wave = wave_id();
-    const int tile_words4 = (g.n_rho + 1) * ST / 4;
-    const uint32_t T = sp.n_tiles;
-    const uint32_t n_items = a.n_events * T;
-
-    for (int i = threadIdx.x; i < tile_words4; i += NT)
+    if (threadIdx.x == 0) {
+        s_item = atomicAdd(a.queue, 1u);
+        s_bad = 0u;
+        s_edge = 0u;
+    }
+    for (int i = threadIdx.x; i < (g.n_rho + 1) * ST / 4; i += NT)
         reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
     for (int i = threadIdx.x; i < DP; i += NT) dil[nwords * DP + i] = 0u;
-
-    for (;;) {
-        if (threadIdx.x == 0) {
-            s_item = atomicAdd(a.queue, 1u);
-            s_flags = 0u;
-            s_last = 0u;
+    for (int i = threadIdx.x; i < TW; i += NT) colcnt[i] = 0u;
+    if (g.rho_window >= 32)
+        for (int i = threadIdx.x; i < nwords * DP; i += NT) dil[i] = 0u;
+    __syncthreads();
+    const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_item), T = sp.n_tiles;
+    if (item >= a.n_events * T) return;                    // (the grid holds one workgroup per item)
+    const uint32_t e = item / T, t = item - e * T;
+    uint32_t *slots = sp.slots + (size_t)e * T;
+    const uint32_t pe_id = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a.ids ? a.ids[e] : e));
+    const uint32_t h0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.offsets[pe_id]);
+    const uint32_t h1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.offsets[pe_id + 1]);
+    if (h1 <= h0 || h1 - h0 > kMaxBatchHits) {
+        // malformed, empty, or left to the spill kernel (which writes everything of such an event)
+        if (threadIdx.x == 0 && t == 0) {
+            const bool spill = h1 > h0;
+            a.n_peaks[e] = 0u;
+            a.status[e] = spill ? kStatusSpill : (h1 < h0 ? HOUGH_EV_TOO_MANY_HITS : 0u);
+            if (spill && a.spill_count) atomicAdd(a.spill_count, 1u);
         }
-        __syncthreads();
-        const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_item);
-        if (item >= n_items) {
-            if (threadIdx.x == 0 && atomicAdd(a.queue + 1, 1u) == gridDim.x - 1u) {
-                __hip_atomic_store(a.queue, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(a.queue + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            break;
-        }
-        const uint32_t e = item / T, t = item - e * T;
-        const uint32_t pe_id = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a.ids ? a.ids[e] : e));
-        const uint32_t h0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.offsets[pe_id]);
-        const uint32_t h1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.offsets[pe_id + 1]);
-        const bool malformed = h1 < h0;
-        const uint32_t H = malformed ? 0u : h1 - h0;
-        uint32_t *bits = sp.kept + (size_t)e * kSplitKeepWords;
-        uint8_t *ke = a.keep + (a.ids ? (uint32_t)__builtin_amdgcn_readfirstlane((int)a.keep_offsets[e]) : h0);
-        if (malformed || H > kMaxBatchHits) {
-            if (threadIdx.x == 0 && t == 0) {
-                s_flags = HOUGH_EV_TOO_MANY_HITS;
-                if (!malformed && a.spill_count) atomicAdd(a.spill_count, 1u);
-            }
-        } else if (H > 0) {
-            if (g.dedup && H > kDedupMaxHits && threadIdx.x == 0 && t == 0) atomicOr(&s_flags, HOUGH_EV_DEDUP_SKIPPED);
-            uint32_t hb, he;
-            wave_hits<NW>(H, wave, hb, he);
-            const float *xe = a.x + h0, *ye = a.y + h0;
-            uint32_t bad = 0;
-            const int first = (int)t * OUT - 1;
-            const int vl = opaque(lane);
-            const Cols<G> cl = load_cols<G, PER>(g, first, vl, ST, L(vl).col);
-            vote_range<G, PER>(tile, xe, ye, hb, he, cl, g, first, vl, bad, g.nrho_f, g.dedup ? ke : nullptr);
-            if (t == 0 && __ballot(bad != 0u) && lane == 0) atomicOr(&s_flags, HOUGH_EV_INVALID_HITS);
-            __syncthreads();
-            const int pl = opaque(lane);
-            const L ln(pl);
-            for (int u = wave; u < 2 * nwords; u += NW) {
-                uint32_t m[G];
-                const bool interior = u >= 1 && (u + 1) * kPeakRows < g.n_rho;
-                if (PER && (t == 0 || t == T - 1)) {
-                    if (interior)
-                        peak_rows<false, G, true, true>(tile, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
-                    else
-                        peak_rows<true, G, true, true>(tile, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
-                } else if (interior) {
-                    peak_rows<false, G, true>(tile, u, g.n_rho, g.threshold, ln, pl, m);
-                } else {
-                    peak_rows<true, G, true>(tile, u, g.n_rho, g.threshold, ln, pl, m);
-                }
-                uint16_t *pm16 = reinterpret_cast<uint16_t *>(pmask);
-#pragma unroll
-                for (int q = 0; q < G; ++q) {
-                    const int c = 64 * q + pl;
-                    const bool out_col = (c >= 1) && (c <= TW - 2) && (first + c < g.n_theta);
-                    pm16[((u >> 1) * TW + c) * 2 + (u & 1)] = out_col ? (uint16_t)m[q] : (uint16_t)0;
-                }
-            }
-            if (g.rho_window >= 32) {
-#pragma unroll 1
-                for (int i = threadIdx.x; i < nwords * DP; i += NT) dil[i] = 0u;
-            }
-            __syncthreads();
-            const int el = opaque(lane);
-            hough_peak *slot = sp.staged + ((size_t)e * T + t) * sp.tile_cap;
-            const uint32_t np = emit_and_dilate<G, true>(tile, pmask, dil, 0, nwords, first, g, slot, sp.tile_cap,
-                                                         0u, L(el), el, wave, NW);
-            __syncthreads();
-            if (threadIdx.x == 0) sp.counts[(size_t)e * T + t] = np;
-#pragma unroll 1
-            for (int i = threadIdx.x; i < tile_words4; i += NT)
-                reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
-            if (np) retain_split<G>(dil, stage + wave * 64, xe, ye, bits, hb, he, cl, g, opaque(lane));
-        }
-        // publish this tile's results, then count it; the last tile of the event merges
-        __threadfence();
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            if (s_flags) atomicOr(&sp.flags[e], s_flags);
-            __threadfence();
-            s_last = atomicAdd(&sp.done[e], 1u) == T - 1u ? 1u : 0u;
-        }
-        __syncthreads();
-        if (s_last) {
-            __threadfence();
-            // the tile lists in tile order, 64 tiles at a time: wave 0 scans their counts into
-            // pref (LDS, free now), then every thread copies peaks and clears the slots
-            uint32_t *pref = pmask;
-            hough_peak *pe = a.peaks ? a.peaks + (size_t)e * a.max_peaks : nullptr;
-            const uint32_t cap = pe ? a.max_peaks : 0u;
-            uint32_t run = 0;
-            for (uint32_t t0 = 0; t0 < T; t0 += 64) {
-                const uint32_t nt = T - t0 < 64u ? T - t0 : 64u;
-                if (wave == 0) {
-                    const uint32_t c = (uint32_t)lane < nt
-                        ? __hip_atomic_load(&sp.counts[(size_t)e * T + t0 + lane], __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT)
-                        : 0u;
-                    const uint32_t incl = wave_inclusive_scan(c, lane);
-                    pref[lane] = run + incl - c;
-                    if (lane == 63) pref[64] = run + incl;
-                }
-                __syncthreads();
-                const uint32_t lo_i = pref[0], hi_i = pref[64];
-                for (uint32_t i = lo_i + threadIdx.x; i < hi_i; i += NT) {
-                    uint32_t lo = 0, hi = nt - 1;             // the last tile whose list starts at or before i
-                    while (lo < hi) {
-                        const uint32_t mid = (lo + hi + 1) >> 1;
-                        if (pref[mid] <= i) lo = mid; else hi = mid - 1;
-                    }
-                    uint2 *src = reinterpret_cast<uint2 *>(sp.staged + ((size_t)e * T + t0 + lo) * sp.tile_cap) +
-                                 (i - pref[lo]);
-                    if (i < cap) reinterpret_cast<uint2 *>(pe)[i] = *src;
-                    *src = make_uint2(0u, 0u);
-                }
-                run = hi_i;
-                __syncthreads();                              // pref is rewritten by the next chunk
-            }
-            const uint32_t total = run;                       // the event's true peak count
-            const uint32_t fl = __hip_atomic_load(&sp.flags[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (!malformed) {                     // malformed offsets: touch nothing but the counters
-                const bool skipped = H > kMaxBatchHits;
-                for (uint32_t i = threadIdx.x; i < H; i += NT)
-                    ke[i] = skipped ? (uint8_t)0 : (uint8_t)((bits[i >> 5] >> (i & 31)) & 1u);
-            }
-            __syncthreads();
-            // leave the event's workspace zero for the next launch
-            for (uint32_t i = threadIdx.x; i < (H + 31u) / 32u && i < kSplitKeepWords; i += NT) bits[i] = 0u;
-            for (uint32_t tt = threadIdx.x; tt < T; tt += NT) sp.counts[(size_t)e * T + tt] = 0u;
-            if (threadIdx.x == 0) {
-                a.n_peaks[e] = total;
-                a.status[e] = fl | (total > a.max_peaks ? HOUGH_EV_PEAKS_TRUNCATED : 0u);
-                sp.flags[e] = 0u;
-                sp.done[e] = 0u;
-            }
-        }
-        __syncthreads();
+        return;                                            // every tile of the event returns here: none waits
     }
+    const uint32_t H = h1 - h0;
+    uint8_t *ke = a.keep + (a.ids ? (uint32_t)__builtin_amdgcn_readfirstlane((int)a.keep_offsets[e]) : h0);
+    const float *xe = a.x + h0, *ye = a.y + h0;
+    hough_peak *pe = a.peaks ? a.peaks + (size_t)e * a.max_peaks : nullptr;
+    const uint32_t cap = pe ? a.max_peaks : 0u;
+    uint32_t hb, he;
+    wave_hits<NW>(H, wave, hb, he);
+    if (t == 0 && !g.dedup)                                // (the duplicate pass has written every keep byte)
+        for (uint32_t i = threadIdx.x; i < H; i += NT) keep_store(ke + i, 0u);
+    uint32_t bad = 0;
+    const int first = (int)t * OUT - 1;
+    const int vl = opaque(lane);
+    const Cols<1> cl = load_cols<1, PER>(g, first, vl, ST, L(vl).col);
+    vote_range<1, PER>(tile, xe, ye, hb, he, cl, g, first, vl, bad, g.nrho_f, g.dedup ? ke : nullptr);
+    __syncthreads();
+    const int pl = opaque(lane);
+    const L ln(pl);
+    for (int u = wave; u < 2 * nwords; u += NW) {
+        uint32_t m[1];
+        const bool interior = u >= 1 && (u + 1) * kPeakRows < g.n_rho;
+        constexpr bool UR = NW == 16;
+        if (PER && (t == 0 || t == T - 1)) {
+            if (interior)
+                peak_rows<false, 1, true, true, UR>(tile, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
+            else
+                peak_rows<true, 1, true, true, UR>(tile, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
+        } else if (interior) {
+            peak_rows<false, 1, true, false, UR>(tile, u, g.n_rho, g.threshold, ln, pl, m);
+        } else {
+            peak_rows<true, 1, true, false, UR>(tile, u, g.n_rho, g.threshold, ln, pl, m);
+        }
+        const bool out_col = pl >= 1 && pl <= TW - 2 && first + pl < g.n_theta;
+        reinterpret_cast<uint16_t *>(pmask)[((u >> 1) * TW + pl) * 2 + (u & 1)] = out_col ? (uint16_t)m[0] : (uint16_t)0;
+        if (out_col && m[0]) atomicAdd(&colcnt[pl], (uint32_t)__popc(m[0]));
+    }
+    if (t == T - 1 && __ballot(bad != 0u) && lane == 0) s_bad = 1u;
+    // this wave's keep stores (tile 0) have arrived before the barrier, so before the publication
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (wave == 0) {
+        const uint32_t np = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_sum(colcnt[lane]));
+        if (lane == 0)
+            __hip_atomic_store(slots + t, kSlotReady | np, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t before = 0;
+        for (uint32_t t0 = 0; t0 < t; t0 += 64) {
+            const bool mine = t0 + (uint32_t)lane < t;
+            uint32_t v;
+            for (;;) {
+                v = mine ? __hip_atomic_load(slots + t0 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kSlotReady;
+                if (__ballot(!(v & kSlotReady)) == 0ull) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            before += v & ~kSlotReady;
+        }
+        before = wave_sum(before);
+        if (lane == 0) {
+            s_base = before;
+            if (t == T - 1) {
+                const uint32_t total = before + np;        // the event's true peak count
+                a.n_peaks[e] = total;
+                a.status[e] = (s_bad ? HOUGH_EV_INVALID_HITS : 0u) |
+                              (g.dedup && H > kDedupMaxHits ? HOUGH_EV_DEDUP_SKIPPED : 0u) |
+                              (total > a.max_peaks ? HOUGH_EV_PEAKS_TRUNCATED : 0u);
+            }
+        }
+    }
+    asm volatile("" ::: "memory");
+    __syncthreads();
+    const int el = opaque(lane);
+    const uint32_t np = emit_and_dilate<1, true>(tile, pmask, dil, 0, nwords, first, g, pe, cap, s_base, L(el), el, wave,
+                                                 NW, tpk, &cl, colcnt, &s_edge);
+    if (np == 0u) return;
+    __syncthreads();
+    retain_split(dil, tpk, np, s_edge != 0u, stage + wave * 64, xe, ye, ke, hb, he, cl, g, first, opaque(lane));
 }
 
 // ------------------------------------------------------------ spill path (rho slabs)
@@ -2933,6 +2903,23 @@ __global__ __launch_bounds__(kSpillThreads) void k_spill(GridArgs g, BatchArgs a
         __syncthreads();
     };
 
+    // after the split form: its slots and item counter back to zero, and the later copies' marks
+    // (bit 1) out of the keep bytes of the events it processed
+    if (sp.n_slots) {
+        for (uint32_t i = blockIdx.x * kSpillThreads + threadIdx.x; i < sp.n_slots; i += gridDim.x * kSpillThreads)
+            sp.slots[i] = 0u;
+        if (blockIdx.x == 0 && threadIdx.x == 0) *a.queue = 0u;
+        if (g.dedup)
+            for (uint32_t e = blockIdx.x; e < a.n_events; e += gridDim.x) {
+                const uint32_t pe_id = a.ids ? a.ids[e] : e, h0 = a.offsets[pe_id], h1 = a.offsets[pe_id + 1];
+                if (h1 <= h0 || h1 - h0 > kDedupMaxHits) continue;
+                uint8_t *ke = a.keep + (a.ids ? a.keep_offsets[e] : h0);
+                for (uint32_t i = threadIdx.x; i < h1 - h0; i += kSpillThreads) {
+                    const uint32_t v = ke[i];
+                    if (v & kKeepDuplicate) ke[i] = (uint8_t)(v & 1u);
+                }
+            }
+    }
     if (sp.all) {
         for (;;) {
             if (threadIdx.x == 0) s_event = atomicAdd(sp.queue, 1u);
@@ -2969,7 +2956,7 @@ __global__ __launch_bounds__(kSpillThreads) void k_spill(GridArgs g, BatchArgs a
         if (threadIdx.x < kSpillBlock && e < a.n_events) {
             const uint32_t pe_id = a.ids ? a.ids[e] : e;
             const uint32_t h0 = a.offsets[pe_id], h1 = a.offsets[pe_id + 1];
-            // left here by the fused kernel (kStatusSpill), or by the split form (above its limit)
+            // left here by the fused kernel or the split form
             if ((a.status[e] & kStatusSpill) || (h1 >= h0 && h1 - h0 > kMaxBatchHits)) s_list[atomicAdd(&s_n, 1u)] = e;
         }
         __syncthreads();
@@ -3474,37 +3461,61 @@ hipError_t launch_batch(const GridArgs &g, const BatchPlan &p, const BatchArgs &
     }
 }
 
-template <int NW, int G>
-static hipError_t launch_split_t(const GridArgs &g, const BatchPlan &p, const BatchArgs &a,
-                                 const SplitArgs &sp, hipStream_t s) {
+template <int NW>
+static hipError_t launch_split_t(const GridArgs &g, const BatchArgs &a, const SplitArgs &sp, uint32_t items,
+                                 hipStream_t s) {
     const int nwords = (g.n_rho + 31) / 32;
-    if (g.periodic)
-        hipLaunchKernelGGL((k_batch_split<NW, G, true>), dim3(p.grid), dim3(NW * 64), p.split_lds_bytes, s, g, a,
-                           sp, nwords);
-    else
-        hipLaunchKernelGGL((k_batch_split<NW, G, false>), dim3(p.grid), dim3(NW * 64), p.split_lds_bytes, s, g, a,
-                           sp, nwords);
+    const size_t lds = batch_lds_bytes(g.n_rho, NW, 1, 0);
+    // one workgroup per item; a launch holds at most 2^31 threads, and the item counter runs on
+    // from launch to launch
+    for (uint32_t left = items; left > 0;) {
+        const uint32_t n = std::min(left, 1u << 21);
+        left -= n;
+        if (g.periodic)
+            hipLaunchKernelGGL((k_batch_split<NW, true>), dim3(n), dim3(NW * 64), lds, s, g, a, sp, nwords);
+        else
+            hipLaunchKernelGGL((k_batch_split<NW, false>), dim3(n), dim3(NW * 64), lds, s, g, a, sp, nwords);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_batch_split(const GridArgs &g, const BatchPlan &p, const BatchArgs &a,
-                              const SplitArgs &sp, hipStream_t s) {
-    switch (p.waves * 10 + p.groups) {
-        case 41: return launch_split_t<4, 1>(g, p, a, sp, s);
-        case 42: return launch_split_t<4, 2>(g, p, a, sp, s);
-        case 61: return launch_split_t<6, 1>(g, p, a, sp, s);
-        case 62: return launch_split_t<6, 2>(g, p, a, sp, s);
-        case 81: return launch_split_t<8, 1>(g, p, a, sp, s);
-        case 82: return launch_split_t<8, 2>(g, p, a, sp, s);
-        case 121: return launch_split_t<12, 1>(g, p, a, sp, s);
-        case 122: return launch_split_t<12, 2>(g, p, a, sp, s);
-        case 161: return launch_split_t<16, 1>(g, p, a, sp, s);
-        case 162: return launch_split_t<16, 2>(g, p, a, sp, s);
+uint32_t split_tiles(int n_theta) { return (uint32_t)(n_theta + 61) / 62u; }
+
+hipError_t launch_batch_split(const GridArgs &g, const SplitPlan &p, const BatchArgs &a, const SplitArgs &sp,
+                              int n_cu, hipStream_t s) {
+    const uint32_t items = a.n_events * sp.n_tiles;
+    // up to one item per CU the widest workgroup finishes its item first; beyond that narrower ones
+    // share a CU and overlap their phases
+    switch (items <= (uint32_t)n_cu ? p.wide : p.narrow) {
+        case 16: return launch_split_t<16>(g, a, sp, items, s);
+        case 8: return launch_split_t<8>(g, a, sp, items, s);
+        case 4: return launch_split_t<4>(g, a, sp, items, s);
         default: return hipErrorInvalidValue;
     }
 }
 
-// Workspace layout of the split form; every section starts on a 256-byte boundary.
+template <int NW>
+static bool split_fits(int n_rho, size_t lds_limit) {
+    if (batch_lds_bytes(n_rho, NW, 1, 0) + 256 > lds_limit) return false;
+    allow_lds(k_batch_split<NW, false>);
+    allow_lds(k_batch_split<NW, true>);
+    return true;
+}
+
+SplitPlan plan_split(int n_rho, size_t lds_limit) {
+    SplitPlan p{0, 0};
+    if (split_fits<4>(n_rho, lds_limit)) p.wide = p.narrow = 4;
+    if (split_fits<8>(n_rho, lds_limit)) p.wide = p.narrow = 8;
+    if (split_fits<16>(n_rho, lds_limit)) {
+        p.wide = 16;
+        if (2 * batch_lds_bytes(n_rho, 8, 1, 0) > lds_limit) p.narrow = 16;   // one per CU either way
+    }
+    return p;
+}
+
+// Workspace size of the split form, part of its interface: room for every tile's list, keep bits
+// and counters, each section on a 256-byte boundary.  The kernel uses one slot per tile, at the
+// workspace's start.
 static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 static void split_sizes(int n_theta, int n_rho, int groups, uint32_t n_events, uint32_t *n_tiles,
@@ -3534,14 +3545,10 @@ bool split_layout(int n_theta, int n_rho, int groups, uint32_t n_events, void *w
     size_t off[6];
     split_sizes(n_theta, n_rho, groups, n_events, &T, &cap, off);
     if (!ws || bytes < off[5] || ((uintptr_t)ws & 255u) != 0) return false;
-    char *b = static_cast<char *>(ws);
-    out->n_tiles = T;
-    out->tile_cap = cap;
-    out->counts = reinterpret_cast<uint32_t *>(b + off[0]);
-    out->staged = reinterpret_cast<hough_peak *>(b + off[1]);
-    out->kept = reinterpret_cast<uint32_t *>(b + off[2]);
-    out->done = reinterpret_cast<uint32_t *>(b + off[3]);
-    out->flags = reinterpret_cast<uint32_t *>(b + off[4]);
+    const uint32_t tiles = split_tiles(n_theta);
+    if (bytes / 4 < (size_t)n_events * tiles) return false;
+    out->n_tiles = tiles;
+    out->slots = static_cast<uint32_t *>(ws);
     return true;
 }
 
@@ -3553,17 +3560,13 @@ static int occupancy(K kernel, int threads, size_t lds) {
 
 template <int NW, int G>
 static int prepare_t(BatchPlan *p) {
-    // both grid topologies and both forms: a context's plan serves whichever kernel it launches
+    // both grid topologies: a context's plan serves whichever kernel it launches
     allow_lds(k_batch<NW, G, false, false, false>);
     allow_lds(k_batch<NW, G, true, false, false>);
     allow_lds(k_batch<NW, G, false, true, false>);
     allow_lds(k_batch<NW, G, true, true, false>);
-    allow_lds(k_batch_split<NW, G, false>);
-    allow_lds(k_batch_split<NW, G, true>);
     const int T = NW * 64;
-    const size_t full = p->split_lds_bytes;
-    int split = occupancy(k_batch_split<NW, G, false>, T, full);
-    split = std::min(split, occupancy(k_batch_split<NW, G, true>, T, full));
+    const size_t full = p->lds_bytes;
     int fused = 0;
     if constexpr (G == 1) {
         if (p->win) {
@@ -3579,13 +3582,11 @@ static int prepare_t(BatchPlan *p) {
         fused = std::min(fused, std::min(occupancy(k_batch<NW, G, false, true, false>, T, full),
                                          occupancy(k_batch<NW, G, true, true, false>, T, full)));
     }
-    p->split_per_cu = split;
     return fused;
 }
 
 // Allow the plan's dynamic LDS for its kernels and return how many of the fused kernel's
-// workgroups fit a CU (0 if none; split_per_cu gets the split form's).  Done once when a plan is
-// chosen, so that launches make no other runtime calls.
+// workgroups fit a CU (0 if none).  Done once when a plan is chosen, so that launches make no other runtime calls.
 int prepare_batch(BatchPlan *p) {
     switch (p->waves * 10 + p->groups) {
         case 41: return prepare_t<4, 1>(p);

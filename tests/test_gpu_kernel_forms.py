@@ -198,3 +198,58 @@ def test_event_peaks_blocks(H, orc, n_theta, n_rho):
             assert int(n.item()) == m
             assert np.array_equal(H.decode_peaks(pk, m), np.stack([pj, pkk, pc], 1).astype(np.int64))
         ctx.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho", [(1, 40), (62, 64), (63, 33), (125, 256), (200, 1000), (4000, 24)])
+@pytest.mark.parametrize("flags", ["plain", "periodic", "dedup"])
+def test_small_batches_by_tile(H, orc, n_theta, n_rho, flags):
+    """Batches of few events run one workgroup per (event, tile): 1 to 65 tiles, one batch on each
+    side of the rule's event count, empty and oversized events between ordinary ones, peaks that
+    overflow the buffer, the gather form and the latency form, each called twice (the slots and the
+    counter are left at zero)."""
+    import torch
+    periodic, dedup = flags == "periodic" and n_theta > 1, flags == "dedup"
+    lo, hi = (-1 / 180, 1 / 180)
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    half = torch.cuda.get_device_properties(0).multi_processor_count // 2
+    x, y, off = _events([700, 0, 1500, 3, 64, 33000, 900], 23, 170.0, 0.01)
+    x[100:200], y[100:200] = x[:100], y[:100]                      # copies in the first event
+    T, cap = 4, 700
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", T, 1, cap, periodic=periodic, dedup=dedup)
+    ref, n_ref, keep_ref = orc.run_batch(g, x, y, off, threshold=T, rho_window=1, cap=cap, n_threads=8,
+                                         periodic=periodic)
+    if dedup:                                                      # the event above the limit votes every hit
+        d, nd, kd = orc.run_batch(g, x, y, off, threshold=T, rho_window=1, cap=cap, n_threads=8, dedup=True)
+        small = np.diff(off) <= 8192
+        ref[small], n_ref[small] = d[small], nd[small]
+        for e in np.nonzero(small)[0]:
+            keep_ref[off[e]:off[e + 1]] = kd[off[e]:off[e + 1]]
+    xt, yt, ot = _t(x), _t(y), _t(off.astype(np.int32))
+    E = off.size - 1
+    ws = ctx.split_workspace(E)
+
+    def same(out, ids):
+        pk, npk, keep, st = out
+        torch.cuda.synchronize()
+        npk, p = npk.cpu().numpy(), pk.cpu().numpy()
+        for i, e in enumerate(ids):
+            m = int(min(n_ref[e], cap))
+            assert npk[i] == n_ref[e], (i, e)
+            assert np.array_equal(H.decode_peaks(p[i], m), ref[e, :m].astype(np.int64)), (i, e)
+        return keep.cpu().numpy()
+
+    for _ in range(2):
+        assert np.array_equal(same(ctx.run_batch(xt, yt, ot), range(E))[:x.size], keep_ref)
+        assert np.array_equal(same(ctx.run_batch_split(xt, yt, ot, ws), range(E))[:x.size], keep_ref)
+        assert int(ws.count_nonzero()) == 0
+    for n in (1, half, half + 1):                                  # by tile, by tile, by event
+        ids = (np.arange(n) * 3) % E
+        ids = ids[ids != 5] if n > 1 else ids
+        ids = np.resize(ids, n)
+        sizes = np.diff(off)[ids]
+        starts = np.concatenate([[0], np.cumsum(sizes)])
+        keep = same(ctx.run_batch_gather(xt, yt, ot, _t(ids.astype(np.int32)), _t(starts[:-1].astype(np.int32)),
+                                         keep_size=int(starts[-1])), ids)
+        want = np.concatenate([keep_ref[off[e]:off[e + 1]] for e in ids])
+        assert np.array_equal(keep[:want.size], want), n
+    ctx.close()
