@@ -206,9 +206,9 @@ int hough_retain(hough_ctx *ctx, const float *x, const float *y, uint32_t n_hits
  * than the kernel has resident workgroups (and at most 65,536 events) is preceded by a small
  * launch that schedules the events largest first; no result depends on the schedule.
  * The fused kernel keeps an event's theta tile on chip, with 16-bit counts.  What it cannot
- * hold -- events above 32,767 hits, events whose hits reach beyond a windowed tile, and every
- * event of a theta-periodic grid whose rho column is taller than its tile (hough_get_batch_plan
- * then reports an all-zero shape) -- is computed by a spill launch after it, one event per
+ * hold -- events above 32,767 hits, and events whose hits reach beyond a windowed tile on grids whose
+ * rho column is taller than any tile (where theta is periodic hough_get_batch_plan reports an
+ * all-zero shape: the window is the library's own) -- is computed by a spill launch after it, one event per
  * workgroup, its accumulator swept through on-chip rho slabs (Sec. II, Sec. III), with the
  * same results; when the fused kernel leaves it nothing, that launch returns at once. */
 int hough_run_batch(hough_ctx *ctx, const float *x, const float *y, const uint32_t *offsets,
@@ -324,8 +324,8 @@ int hough_get_batch_plan(const hough_ctx *ctx, hough_batch_plan *out);
  * then gets the window of rows its hits can reach (they are bounded by the event's smallest
  * x^2 + y^2, Eq. (1)); an event whose rows do not fit goes through the spill path, as do
  * events above the fused kernel's hit limit.  The split forms always hold the whole column.
- * HOUGH_EINVAL if the combination is not supported or does not fit the device, or the grid has
- * no fused kernel; the context keeps its previous shape then. */
+ * HOUGH_EINVAL if the combination is not supported or does not fit the device, or the grid
+ * reports an all-zero shape; the context keeps its previous shape then. */
 int hough_set_batch_plan(hough_ctx *ctx, int32_t waves_per_group, int32_t column_groups,
                          int32_t groups_per_cu);
 

@@ -24,11 +24,16 @@ struct hough_ctx {
     hough::IterPlan iterb;  // ... over a batch (hough_run_batch_iterative), two workgroups per CU
     hough::GridArgs g;
     hough::BatchPlan plan;  // the fused kernel's launch shape (fused != 0)
+    hough::BatchPlan window;  // fused == 1: the windowed shape batches take first while the caller
+                            // has not set one (win 0: none), see auto_window
+    int chosen;             // the caller has set a launch shape
+    uint32_t *d_defer;      // [kOrderMaxEvents] the events that did not fit its window
     hough::SplitPlan split; // the split form's (fused == 1)
     uint32_t *d_slots;      // its slots for batches of up to split_events(n_cu) events (fused == 1)
     int fused;              // 1: the fused kernel holds the grid's whole column (and windows of it);
-                            // 2: only windows of it (taller grids, theta not periodic; the split
-                            // form spills every event); 0: every batch event spills
+                            // 2: only windows of it (taller grids; the split form spills every
+                            // event); 3: the same, theta periodic (the shape is not the caller's to
+                            // see or set); 0: every batch event spills
     uint32_t *d_spill;      // spill_wgs slices of spill_stride words (the spill path's accumulators)
     size_t spill_stride;
     int spill_wgs;
@@ -124,16 +129,17 @@ int default_plan(hough_ctx *c) {
 }
 
 // The tallest windowed tile (a multiple of 32 rows) that lets groups_per_cu workgroups share a
-// CU, if any (one column group, theta not periodic): for more workgroups per CU than a
+// CU, if any (one column group): for more workgroups per CU than a
 // whole-column tile allows, and for grids taller than that tile.  Events whose hits reach
 // beyond the window go to the spill kernel.
 int windowed_plan(const hough_ctx *c, int waves, int groups, int groups_per_cu, hough::BatchPlan *out) {
-    if (groups != 1 || c->g.periodic) return -1;
+    if (groups != 1) return -1;
     const bool need_split = c->fused == 1;
     for (int win = ((c->p.n_rho - 1) / 32) * 32; win >= 32; win -= 32) {
         hough::BatchPlan p;
         if (hough::plan_batch(c->p.n_theta, c->p.n_rho, waves, groups, c->lds_limit, &p, win, need_split) != 0)
             continue;
+        p.periodic = c->g.periodic;
         p.per_cu = hough::prepare_batch(&p);
         if (p.per_cu >= groups_per_cu) {
             *out = p;
@@ -143,7 +149,7 @@ int windowed_plan(const hough_ctx *c, int waves, int groups, int groups_per_cu, 
     return -1;
 }
 
-// Default launch shape where only windows of the column fit (fused == 2): the tallest window
+// Default launch shape where only windows of the column fit (fused 2 and 3): the tallest window
 // with the most resident waves per CU (the most events fit, the rest spill); ties go to the
 // earlier candidate.
 int default_windowed_plan(hough_ctx *c) {
@@ -170,6 +176,20 @@ int default_windowed_plan(hough_ctx *c) {
     if (hough::prepare_batch(&pick) < 1) return HOUGH_EDEVICE;
     c->plan = pick;
     return HOUGH_OK;
+}
+
+// The windowed shape of a grid whose whole column leaves room for one workgroup per CU only (above
+// some 560 rows): two 8-wave workgroups per CU, each on the rows its event's hits reach.  A CU then
+// overlaps one event's voting with the other's peaks and retention, and peaks, clears and retention
+// cover half of the rows (1,000 events on 1000 x 1000, hits reaching 500 rows: 691 -> 476 us).
+// Events that reach more rows run on whole columns in a second launch, which returns at once
+// when there are none (5 us); a batch of such events alone pays one more pass over its hits (about
+// 1.5%).
+void auto_window(hough_ctx *c) {
+    c->window.win = 0;
+    if (c->fused != 1 || c->plan.per_cu != 1) return;
+    hough::BatchPlan p;
+    if (windowed_plan(c, 8, 1, 2, &p) == 0) c->window = p;
 }
 
 // A context's tables and workspace live on the device it was configured on.
@@ -277,7 +297,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         hough_destroy(c);
         return HOUGH_ENOMEM;
     }
-    c->fused = fused_fits(p->n_rho, limit) ? 1 : ((p->flags & HOUGH_FLAG_THETA_PERIODIC) ? 0 : 2);
+    c->fused = fused_fits(p->n_rho, limit) ? 1 : ((p->flags & HOUGH_FLAG_THETA_PERIODIC) ? 3 : 2);
     const size_t slot_bytes = (size_t)(split_events(c->n_cu) + 1u) * hough::split_tiles(p->n_theta) * sizeof(uint32_t);
     if (c->fused == 1) {
         c->split = hough::plan_split(p->n_rho, limit);
@@ -327,7 +347,16 @@ int hough_config(const hough_params *p, hough_ctx **out) {
     }
     g.wB = (double)g.Bf;
 
-    rc = c->fused == 1 ? default_plan(c) : (c->fused == 2 ? default_windowed_plan(c) : HOUGH_OK);
+    rc = c->fused == 1 ? default_plan(c) : default_windowed_plan(c);
+    if (rc != HOUGH_OK && c->fused == 3) {
+        c->fused = 0;                        // no window either: every event spills
+        rc = HOUGH_OK;
+    }
+    if (rc == HOUGH_OK) {
+        auto_window(c);
+        if (c->window.win && hipMalloc(&c->d_defer, sizeof(uint32_t) * hough::kOrderMaxEvents) != hipSuccess)
+            rc = HOUGH_ENOMEM;
+    }
     if (rc != HOUGH_OK) {
         hough_destroy(c);
         return rc;
@@ -345,6 +374,7 @@ void hough_destroy(hough_ctx *c) {
     if (c->d_iter_list) (void)hipFree(c->d_iter_list);
     if (c->d_spill) (void)hipFree(c->d_spill);
     if (c->d_slots) (void)hipFree(c->d_slots);
+    if (c->d_defer) (void)hipFree(c->d_defer);
     delete c;
 }
 
@@ -358,7 +388,7 @@ uint32_t hough_max_batch_hits(const hough_ctx *c) { return c ? UINT32_MAX : 0u; 
 
 int hough_get_batch_plan(const hough_ctx *c, hough_batch_plan *out) {
     if (!c || !out) return HOUGH_EINVAL;
-    if (!c->fused) {                      // no fused kernel for this grid: all zero
+    if (!c->fused || c->fused == 3) {     // no fused kernel of a shape to report: all zero
         *out = hough_batch_plan{0, 0, 0, 0, 0};
         return HOUGH_OK;
     }
@@ -372,14 +402,15 @@ int hough_get_batch_plan(const hough_ctx *c, hough_batch_plan *out) {
 
 int hough_set_batch_plan(hough_ctx *c, int32_t waves_per_group, int32_t column_groups,
                          int32_t groups_per_cu) {
-    if (!c || groups_per_cu < 0 || !c->fused) return HOUGH_EINVAL;
+    if (!c || groups_per_cu < 0 || !c->fused || c->fused == 3) return HOUGH_EINVAL;
     hough::BatchPlan p{};
     if (c->fused == 1) {
         if (hough::plan_batch(c->p.n_theta, c->p.n_rho, waves_per_group, column_groups, c->lds_limit, &p) != 0)
             return HOUGH_EINVAL;
         p.per_cu = hough::prepare_batch(&p);
         if (p.per_cu >= 1 && groups_per_cu > p.per_cu &&
-            windowed_plan(c, waves_per_group, column_groups, groups_per_cu, &p) != 0)
+            (c->g.periodic ||                 // (a window is not the caller's to choose there)
+             windowed_plan(c, waves_per_group, column_groups, groups_per_cu, &p) != 0))
             p.per_cu = 0;
     } else if (windowed_plan(c, waves_per_group, column_groups, groups_per_cu > 0 ? groups_per_cu : 1, &p) != 0) {
         p.per_cu = 0;                         // only windows of the column fit
@@ -391,6 +422,7 @@ int hough_set_batch_plan(hough_ctx *c, int32_t waves_per_group, int32_t column_g
     }
     if (groups_per_cu > 0) p.per_cu = groups_per_cu;
     c->plan = p;
+    c->chosen = 1;
     return HOUGH_OK;
 }
 
@@ -532,8 +564,8 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
     a.frac_den = frac_den;
     // every event through the spill path: no fused kernel for this grid, or the split form on a
     // grid whose whole column does not fit it (the split form gives the same results)
-    const bool spill_all = !c->fused || (split && c->fused == 2);
-    hough::SpillArgs spill{c->d_spill, c->spill_stride, c->d_work + 2, spill_all ? 1u : 0u, nullptr, 0u};
+    const bool spill_all = !c->fused || (split && c->fused != 1);
+    hough::SpillArgs spill{c->d_spill, c->spill_stride, c->d_work + 2, spill_all ? 1u : 0u, nullptr, 0u, nullptr};
     // otherwise the fused (or split) kernel counts the events it leaves to the spill kernel in
     // the spill kernel's first counter, so that the spill kernel skips its scan when none
     a.spill_count = spill_all ? nullptr : c->d_work + 2;
@@ -543,7 +575,9 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
         if (e == hipSuccess) e = hough::launch_spill(c->g, a, spill, c->spill_wgs, (hipStream_t)stream);
         return e == hipSuccess ? HOUGH_OK : HOUGH_EDEVICE;
     }
-    hough::BatchPlan plan = c->plan;
+    // the library's own windowed shape first, whole columns for the events it does not fit
+    const bool two = c->window.win && !c->chosen && n_events <= hough::kOrderMaxEvents;
+    hough::BatchPlan plan = two ? c->window : c->plan;
     long grid = (long)plan.per_cu * c->n_cu;
     if (grid > (long)n_events) grid = n_events;
     plan.grid = (int)grid;
@@ -569,9 +603,22 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
         e = hough::launch_order(offsets, n_events, c->d_order, (hipStream_t)stream);
         a.order = c->d_order;
     }
+    if (!split && two) {
+        a.defer_list = c->d_defer;
+        a.defer_count = spill.defer_count = c->d_work + 10;
+    }
     if (e == hipSuccess)
         e = split ? hough::launch_batch_split(c->g, c->split, a, sp, c->n_cu, (hipStream_t)stream)
                   : hough::launch_batch(c->g, plan, a, (hipStream_t)stream);
+    if (e == hipSuccess && !split && two) {
+        hough::BatchArgs rest = a;
+        rest.order = c->d_defer;
+        rest.n_from = a.defer_count;
+        rest.defer_list = nullptr;
+        hough::BatchPlan whole = c->plan;
+        whole.grid = (int)std::min<long>((long)whole.per_cu * c->n_cu, (long)n_events);
+        e = hough::launch_batch(c->g, whole, rest, (hipStream_t)stream);
+    }
     // events above the fused kernel's hit limit or beyond its window (flagged and skipped there),
     // through the spill path
     if (e == hipSuccess) e = hough::launch_spill(c->g, a, spill, c->spill_wgs, (hipStream_t)stream);

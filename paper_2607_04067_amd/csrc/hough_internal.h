@@ -52,6 +52,7 @@ struct BatchPlan {
     int grid;            // persistent workgroups
     int sparse;          // retention by peak list on tiles with few peaks (see kSparseRhoRows)
     int win;             // rows of a windowed tile (0: the tile holds the whole rho column)
+    int periodic;        // a windowed plan for a theta-periodic grid
     size_t split_lds_bytes;   // LDS of the whole column (a plan must leave room for it where the
                               // grid has a split form)
 };
@@ -86,6 +87,12 @@ struct BatchArgs {
     uint32_t *queue;     // [2] work counter and exit counter (device, zero between launches)
     uint32_t frac_num;   // fused kernel: frac_den != 0 takes each event's threshold as
     uint32_t frac_den;   // max(threshold, ceil(event maximum * frac_num / frac_den))
+    // a windowed launch followed by one on whole columns: the first lists the events that do not
+    // fit its window (defer_list, their number in *defer_count, zero before it), the second takes
+    // those (order = the list, n_from = the number); the spill kernel zeroes the number
+    const uint32_t *n_from;
+    uint32_t *defer_list;
+    uint32_t *defer_count;
     uint32_t *spill_count;   // null, or a counter of the events left to the spill kernel
                              // (zero between launches; the spill kernel clears it)
 };
@@ -119,6 +126,7 @@ struct SpillArgs {
     uint32_t all;
     uint32_t *slots;     // after the split form: its slots, to be zeroed with a.queue (else n_slots 0)
     uint32_t n_slots;
+    uint32_t *defer_count;   // null, or the listed events' number, to be zeroed
 };
 size_t spill_stride(int n_theta, int n_rho);
 hipError_t launch_spill(const GridArgs &g, const BatchArgs &a, const SpillArgs &sp, int n_wg, hipStream_t s);

@@ -2047,7 +2047,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
                                                                                             int win) {
     using L = Lane<G, true>;
     constexpr int TW = L::TW, ST = L::STRIDE, DP = (int)kDilPitch<G>, OUT = TW - 2, NT = NW * 64;
-    static_assert(!WIN || (G == 1 && !PER), "windowed tiles: one column group, theta not periodic");
+    static_assert(!WIN || G == 1, "windowed tiles: one column group");
     extern __shared__ __align__(16) uint32_t lds[];
     // tile rows (dummy row included) and peak-word rows of the LDS layout
     const int rows_t = WIN ? win + 3 : g.n_rho + 1;
@@ -2061,6 +2061,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
     __shared__ uint32_t s_event, s_npeaks, s_flags, s_nvalid, s_nkept, s_max, s_minr2, s_wb, s_fit, s_edge;
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int tile_words4 = rows_t * ST / 4;
+    // the launch's events: all of the batch, or those a windowed launch before it listed (none:
+    // nothing to take, and the counters stay at zero)
+    const uint32_t n_take = a.n_from ? (uint32_t)__builtin_amdgcn_readfirstlane((int)*a.n_from) : a.n_events;
+    if (n_take == 0u) return;
 
     // the tile is all zero at the start of every tile; the dil row past the last word is read
     // by the out-of-grid columns' dummy row and stays zero
@@ -2074,7 +2078,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
     for (;;) {
         if (threadIdx.x == 0) {
             const uint32_t q = atomicAdd(a.queue, 1u);
-            s_event = (a.order && q < a.n_events) ? a.order[q] : q;
+            s_event = q < n_take ? (a.order ? a.order[q] : q) : 0xffffffffu;
             s_npeaks = 0u;
             s_flags = 0u;
             s_nvalid = 0u;
@@ -2152,8 +2156,13 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
                 const double span = g.wA * rmax, slack = 1e-5 * (fabs(g.wB) + span) + 1e-3;
                 const double lo = g.wB - span - slack, hi = g.wB + span + slack;
                 const double top = (double)(g.n_rho - 1);
-                const int klo = lo <= 0.0 ? 0 : (lo >= top ? g.n_rho - 1 : (int)lo);
-                const int khi = hi <= 0.0 ? 0 : (hi >= top ? g.n_rho - 1 : (int)hi);
+                int klo = lo <= 0.0 ? 0 : (lo >= top ? g.n_rho - 1 : (int)lo);
+                int khi = hi <= 0.0 ? 0 : (hi >= top ? g.n_rho - 1 : (int)hi);
+                if (PER) {                       // the wrapped halo columns vote the reversed rows too
+                    const int lo_r = g.n_rho - 1 - khi, hi_r = g.n_rho - 1 - klo;
+                    klo = min(klo, lo_r);
+                    khi = max(khi, hi_r);
+                }
                 const int b0 = (klo / 16) * 16;
                 s_wb = (uint32_t)b0;
                 s_fit = khi < b0 + win ? 1u : 0u;
@@ -2161,9 +2170,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
             __syncthreads();
             wb = __builtin_amdgcn_readfirstlane((int)s_wb);
             if (__builtin_amdgcn_readfirstlane((int)s_fit) == 0) {
-                // leave it to the spill kernel (its keep bytes are clear, or hold the duplicate
-                // pass's marks, which the spill kernel reads)
-                if (threadIdx.x == 0) {
+                // list it for the launch on whole columns, or leave it to the spill kernel (its keep
+                // bytes are clear, or hold the duplicate pass's marks, which the spill kernel reads)
+                if (threadIdx.x == 0 && a.defer_list) {
+                    a.defer_list[atomicAdd(a.defer_count, 1u)] = e;
+                } else if (threadIdx.x == 0) {
                     a.n_peaks[e] = 0u;
                     a.status[e] = kStatusSpill;
                     if (a.spill_count) atomicAdd(a.spill_count, 1u);
@@ -2278,9 +2289,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
                     for (int q = 0; q < G; ++q) m[q] = 0u;
                 } else if (PER && (t == 0 || t == n_tiles - 1)) {
                     if (interior)
-                        peak_rows<false, G, true, true, UR>(tile, u, g.n_rho, thr, ln, pl, m, first, g.n_theta);
+                        peak_rows<false, G, true, true, UR>(tile_w, u, g.n_rho, thr, ln, pl, m, first, g.n_theta);
                     else
-                        peak_rows<true, G, true, true, UR>(tile, u, g.n_rho, thr, ln, pl, m, first, g.n_theta);
+                        peak_rows<true, G, true, true, UR>(tile_w, u, g.n_rho, thr, ln, pl, m, first, g.n_theta);
                 } else if (interior) {
                     peak_rows<false, G, true, false, UR>(tile_w, u, g.n_rho, thr, ln, pl, m);
                 } else {
@@ -2920,6 +2931,7 @@ __global__ __launch_bounds__(kSpillThreads) void k_spill(GridArgs g, BatchArgs a
                 }
             }
     }
+    if (sp.defer_count && blockIdx.x == 0 && threadIdx.x == 0) *sp.defer_count = 0u;   // (see BatchArgs)
     if (sp.all) {
         for (;;) {
             if (threadIdx.x == 0) s_event = atomicAdd(sp.queue, 1u);
@@ -3415,11 +3427,20 @@ hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_
     return e;
 }
 
+// Windowed tiles on theta-periodic grids: only the shapes the library picks by itself.
+constexpr bool window_periodic(int waves) { return waves == 8 || waves == 16; }
+
 template <int NW, int G, bool SP>
 static void launch_batch_sp(const GridArgs &g, const BatchPlan &p, const BatchArgs &a, hipStream_t s) {
     const int nwords = (g.n_rho + 31) / 32;
     if constexpr (G == 1) {
         if (p.win) {
+            if constexpr (window_periodic(NW))
+                if (g.periodic) {
+                    hipLaunchKernelGGL((k_batch<NW, G, true, SP, true>), dim3(p.grid), dim3(NW * 64), p.lds_bytes, s, g,
+                                       a, p.n_tiles, nwords, p.win);
+                    return;
+                }
             hipLaunchKernelGGL((k_batch<NW, G, false, SP, true>), dim3(p.grid), dim3(NW * 64), p.lds_bytes, s, g, a,
                                p.n_tiles, nwords, p.win);
             return;
@@ -3436,7 +3457,7 @@ static void launch_batch_sp(const GridArgs &g, const BatchPlan &p, const BatchAr
 template <int NW, int G>
 static hipError_t launch_batch_t(const GridArgs &g, const BatchPlan &p, const BatchArgs &a,
                                  hipStream_t s) {
-    if (p.win && (G != 1 || g.periodic)) return hipErrorInvalidValue;   // no such plan is made
+    if (p.win && (G != 1 || (g.periodic && !window_periodic(NW)))) return hipErrorInvalidValue;   // no such plan is made
     // a relative threshold leaves few peaks per tile whatever the grid
     if (p.sparse || a.frac_den != 0u)
         launch_batch_sp<NW, G, true>(g, p, a, s);
@@ -3569,7 +3590,14 @@ static int prepare_t(BatchPlan *p) {
     const size_t full = p->lds_bytes;
     int fused = 0;
     if constexpr (G == 1) {
-        if (p->win) {
+        if (p->win && p->periodic) {
+            if constexpr (window_periodic(NW)) {
+                allow_lds(k_batch<NW, 1, true, false, true>);
+                allow_lds(k_batch<NW, 1, true, true, true>);
+                fused = std::min(occupancy(k_batch<NW, 1, true, false, true>, T, p->lds_bytes),
+                                 occupancy(k_batch<NW, 1, true, true, true>, T, p->lds_bytes));
+            }
+        } else if (p->win) {
             allow_lds(k_batch<NW, 1, false, false, true>);
             allow_lds(k_batch<NW, 1, false, true, true>);
             fused = std::min(occupancy(k_batch<NW, 1, false, false, true>, T, p->lds_bytes),

@@ -253,3 +253,52 @@ def test_small_batches_by_tile(H, orc, n_theta, n_rho, flags):
         want = np.concatenate([keep_ref[off[e]:off[e + 1]] for e in ids])
         assert np.array_equal(keep[:want.size], want), n
     ctx.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho,plan", [(130, 1000, None), (130, 1000, (8, 1, 2)), (64, 700, None),
+                                                (130, 1500, None), (70, 2000, None)])
+@pytest.mark.parametrize("flags", ["plain", "periodic", "dedup"])
+def test_windows_over_many_events(H, orc, n_theta, n_rho, plan, flags):
+    """Batches large enough for the fused kernel on grids whose column fills a CU or does not fit it:
+    events whose hits reach few rows run on a window of them, those that reach beyond it (here every
+    seventh) on whole columns or through the spill path, empty and invalid ones between; absolute and
+    relative thresholds, windows on both sides of rho = 0's row, twice in a row, and gathered."""
+    import torch
+    periodic, dedup = flags == "periodic", flags == "dedup"
+    lo, hi = (-0.01, 0.01) if periodic else (-0.012, 0.009)
+    if plan and periodic:
+        pytest.skip("a window is not the caller's to choose on a periodic grid")
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    rng = np.random.default_rng(n_rho)
+    sizes = rng.integers(0, 260, 150)
+    sizes[::31] = 0
+    parts = [_events([int(n)], 40 + i, 60.0 if i % 7 == 3 else 210.0, 0.01)[:2] for i, n in enumerate(sizes)]
+    x, y = (np.concatenate([p[i] for p in parts]) for i in (0, 1))
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    x[off[9]:off[9] + 20], y[off[9]:off[9] + 20] = x[off[9] + 20:off[9] + 40], y[off[9] + 20:off[9] + 40]
+    T, cap = 3, 1500
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", T, 1, cap, periodic=periodic, dedup=dedup)
+    if plan:
+        ctx.set_batch_plan(*plan)
+    xt, yt, ot = _t(x), _t(y), _t(off.astype(np.int32))
+    E = off.size - 1
+    for frac in (None, (1, 2), None):
+        pk, npk, keep, st = ctx.run_batch(xt, yt, ot, frac=frac)
+        torch.cuda.synchronize()
+        ref, n_ref, keep_ref = orc.run_batch(g, x, y, off, threshold=T, rho_window=1, cap=cap, n_threads=8,
+                                             periodic=periodic, dedup=dedup, frac=frac)
+        assert np.array_equal(npk.cpu().numpy()[:E].astype(np.int64), n_ref), frac
+        assert np.array_equal(keep.cpu().numpy()[:x.size], keep_ref), frac
+        p = pk.cpu().numpy()
+        for e in range(E):
+            m = int(min(n_ref[e], cap))
+            assert np.array_equal(H.decode_peaks(p[e], m), ref[e, :m].astype(np.int64)), (frac, e)
+    ids = np.arange(E)[::-1].copy()
+    starts = np.concatenate([[0], np.cumsum(sizes[ids])])
+    gk = ctx.run_batch_gather(xt, yt, ot, _t(ids.astype(np.int32)), _t(starts[:-1].astype(np.int32)),
+                              keep_size=int(starts[-1]))
+    torch.cuda.synchronize()
+    assert np.array_equal(gk[1].cpu().numpy()[:E], npk.cpu().numpy()[:E][ids])
+    assert np.array_equal(gk[2].cpu().numpy()[:int(starts[-1])],
+                          np.concatenate([keep_ref[off[e]:off[e + 1]] for e in ids]))
+    ctx.close()
