@@ -276,9 +276,9 @@ int hough_run_batch_split_static(hough_ctx *ctx, const float *x, const float *y,
  * keep[offsets[0] .. offsets[n_events]] one byte per hit; status[e] the HOUGH_EV_* bits.
  * Events above HOUGH_MAX_ITERATIVE_BATCH_HITS hits are skipped (HOUGH_EV_TOO_MANY_HITS);
  * HOUGH_FLAG_DEDUP applies.
- * Four kernel launches per call.  Accumulators go through HBM (n_theta * n_rho * 2 bytes per
- * event), so this is the per-event path's work done for the whole batch at once, not the fused
- * kernel. */
+ * Three kernel launches per call (four with HOUGH_FLAG_DEDUP; again for every 65,536 64-column
+ * tiles of the batch).  The workspace has room for every cell; a tile hands over the cells that can
+ * become peaks, and all of its cells only where those are many. */
 int hough_run_batch_iterative(hough_ctx *ctx, const float *x, const float *y, const uint32_t *offsets,
                               uint32_t n_events, uint32_t frac_num, uint32_t frac_den, int32_t r_theta,
                               int32_t r_rho, hough_peak *peaks, uint32_t *n_peaks, uint8_t *keep,

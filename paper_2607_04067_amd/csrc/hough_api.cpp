@@ -13,11 +13,13 @@
 struct hough_ctx {
     hough_params p;
     int device;
+    char *d_block;          // one allocation that holds the buffers up to d_defer below
     float *d_tables;        // C[n_theta] then S[n_theta]
     uint32_t *d_work;       // [0], [1]: work and exit counters of the fused kernels; from [64]:
                             // hough_peaks' per-block peak counts; [8], [9]: the iterative
                             // finder's running maximum and key count
-    uint64_t *d_iter_list;  // [kIterScanKeys] the iterative finder's listed candidates
+    uint64_t *d_iter_list;  // [kIterScanKeys] the iterative finder's listed candidates, or (batch
+                            // form) [kIterHeads] its tiles' heads
     uint32_t *d_order;      // [kOrderMaxEvents] the fused kernel's largest-first schedule
     uint32_t *d_iter_bm;    // the iterative finder's suppression bitmap when it does not fit LDS
     hough::IterPlan iter1;  // the iterative finder on one event (hough_peaks_iterative)
@@ -270,42 +272,33 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         tab[j] = (float)(A * cos(theta));
         tab[p->n_theta + j] = (float)(A * sin(theta));
     }
-    if (hipMalloc(&c->d_tables, tab.size() * sizeof(float)) != hipSuccess) {
-        delete c;
-        return HOUGH_ENOMEM;
-    }
     const int peak_waves = hough::peak_block_waves(p->n_theta, p->n_rho, limit);
-    const size_t work_bytes = 256 + 4 * (size_t)((p->n_theta + peak_waves - 1) / peak_waves);
-    if (hipMalloc(&c->d_work, work_bytes) != hipSuccess) {
-        (void)hipFree(c->d_tables);
-        delete c;
-        return HOUGH_ENOMEM;
-    }
-    if (hipMalloc(&c->d_order, sizeof(uint32_t) * hough::kOrderMaxEvents) != hipSuccess) {
-        (void)hipFree(c->d_work);
-        (void)hipFree(c->d_tables);
-        delete c;
-        return HOUGH_ENOMEM;
-    }
     c->iter1 = hough::plan_iterative(p->n_theta, p->n_rho, limit, 1);
-    c->iterb = hough::plan_iterative(p->n_theta, p->n_rho, limit, 2);
-    if (c->iter1.gbm && hipMalloc(&c->d_iter_bm, c->iter1.bm_bytes) != hipSuccess) {
-        hough_destroy(c);
-        return HOUGH_ENOMEM;
-    }
-    if (hipMalloc(&c->d_iter_list, sizeof(uint64_t) * hough::kIterScanKeys) != hipSuccess) {
-        hough_destroy(c);
-        return HOUGH_ENOMEM;
-    }
+    c->iterb = hough::plan_iterative_batch(p->n_theta, p->n_rho, limit, 2);
     c->fused = fused_fits(p->n_rho, limit) ? 1 : ((p->flags & HOUGH_FLAG_THETA_PERIODIC) ? 3 : 2);
-    const size_t slot_bytes = (size_t)(split_events(c->n_cu) + 1u) * hough::split_tiles(p->n_theta) * sizeof(uint32_t);
-    if (c->fused == 1) {
-        c->split = hough::plan_split(p->n_rho, limit);
-        if (hipMalloc(&c->d_slots, slot_bytes) != hipSuccess) {
-            hough_destroy(c);
-            return HOUGH_ENOMEM;
-        }
+    if (c->fused == 1) c->split = hough::plan_split(p->n_rho, limit);
+    // the fixed buffers in one block, each on a 256-byte boundary, those that start at zero first
+    const size_t sizes[7] = {
+        256 + 4 * (size_t)((p->n_theta + peak_waves - 1) / peak_waves),                          // d_work
+        c->fused == 1 ? (size_t)split_events(c->n_cu) * hough::split_tiles(p->n_theta) * 4 : 0,  // d_slots
+        tab.size() * sizeof(float),                                                              // d_tables
+        c->iter1.gbm ? c->iter1.bm_bytes : 0,                                                    // d_iter_bm
+        sizeof(uint64_t) * std::max(hough::kIterScanKeys, hough::kIterHeads),                    // d_iter_list
+        sizeof(uint32_t) * hough::kOrderMaxEvents,                                               // d_order
+        c->fused == 1 ? sizeof(uint32_t) * hough::kOrderMaxEvents : 0};                          // d_defer
+    size_t at[8] = {0};
+    for (int i = 0; i < 7; ++i) at[i + 1] = (at[i] + sizes[i] + 255) & ~(size_t)255;
+    if (hipMalloc(&c->d_block, at[7]) != hipSuccess) {
+        delete c;
+        return HOUGH_ENOMEM;
     }
+    c->d_work = reinterpret_cast<uint32_t *>(c->d_block + at[0]);
+    c->d_slots = reinterpret_cast<uint32_t *>(c->d_block + at[1]);
+    c->d_tables = reinterpret_cast<float *>(c->d_block + at[2]);
+    c->d_iter_bm = reinterpret_cast<uint32_t *>(c->d_block + at[3]);
+    c->d_iter_list = reinterpret_cast<uint64_t *>(c->d_block + at[4]);
+    c->d_order = reinterpret_cast<uint32_t *>(c->d_block + at[5]);
+    c->d_defer = reinterpret_cast<uint32_t *>(c->d_block + at[6]);
     c->spill_stride = hough::spill_stride(p->n_theta, p->n_rho);
     c->spill_wgs = spill_workgroups(c->spill_stride, c->n_cu, c->fused != 1);
     // fewer slices where the device cannot spare the budget
@@ -319,8 +312,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         c->spill_wgs = (c->spill_wgs + 1) / 2;
     }
     if (hipMemcpy(c->d_tables, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(c->d_work, 0, work_bytes) != hipSuccess ||
-        (c->d_slots && hipMemset(c->d_slots, 0, slot_bytes) != hipSuccess)) {
+        hipMemset(c->d_block, 0, at[2]) != hipSuccess) {
         hough_destroy(c);
         return HOUGH_EDEVICE;
     }
@@ -352,11 +344,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         c->fused = 0;                        // no window either: every event spills
         rc = HOUGH_OK;
     }
-    if (rc == HOUGH_OK) {
-        auto_window(c);
-        if (c->window.win && hipMalloc(&c->d_defer, sizeof(uint32_t) * hough::kOrderMaxEvents) != hipSuccess)
-            rc = HOUGH_ENOMEM;
-    }
+    if (rc == HOUGH_OK) auto_window(c);
     if (rc != HOUGH_OK) {
         hough_destroy(c);
         return rc;
@@ -367,14 +355,8 @@ int hough_config(const hough_params *p, hough_ctx **out) {
 
 void hough_destroy(hough_ctx *c) {
     if (!c) return;
-    if (c->d_tables) (void)hipFree(c->d_tables);
-    if (c->d_work) (void)hipFree(c->d_work);
-    if (c->d_order) (void)hipFree(c->d_order);
-    if (c->d_iter_bm) (void)hipFree(c->d_iter_bm);
-    if (c->d_iter_list) (void)hipFree(c->d_iter_list);
+    if (c->d_block) (void)hipFree(c->d_block);
     if (c->d_spill) (void)hipFree(c->d_spill);
-    if (c->d_slots) (void)hipFree(c->d_slots);
-    if (c->d_defer) (void)hipFree(c->d_defer);
     delete c;
 }
 
@@ -506,7 +488,8 @@ int hough_run_batch_iterative(hough_ctx *c, const float *x, const float *y, cons
     a.frac_num = 0;
     a.frac_den = 0;
     const hipError_t e = hough::launch_batch_iterative(c->g, a, static_cast<uint16_t *>(workspace), frac_num,
-                                                       frac_den, r_theta, r_rho, c->iterb, gbm, (hipStream_t)stream);
+                                                       frac_den, r_theta, r_rho, c->iterb, gbm, c->d_iter_list,
+                                                       (hipStream_t)stream);
     return e == hipSuccess ? HOUGH_OK : HOUGH_EDEVICE;
 }
 

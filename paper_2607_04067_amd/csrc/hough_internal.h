@@ -177,11 +177,14 @@ struct IterPlan {
 };
 // per_cu: workgroups per CU the plan should leave room for (the batch form runs one per event).
 IterPlan plan_iterative(int n_theta, int n_rho, size_t lds_limit, int per_cu);
-// The iterative finder over a CSR batch (a.ids must be null): acc holds n_events accumulators
-// of n_theta * n_rho 16-bit cells; gbm (ip.gbm): n_events bitmaps of ip.bm_bytes.
+IterPlan plan_iterative_batch(int n_theta, int n_rho, size_t lds_limit, int per_cu);
+// The iterative finder over a CSR batch (a.ids must be null): acc has room for n_events accumulators
+// of n_theta * n_rho 16-bit cells; gbm (ip.gbm): n_events bitmaps of ip.bm_bytes; head: kIterHeads
+// 8-byte heads, one per (event, 64-column tile) of as many events at a time as fit (the context's).
+constexpr uint32_t kIterHeads = 65536;
 hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_t *acc, uint32_t frac_num,
                                   uint32_t frac_den, int r_theta, int r_rho, const IterPlan &ip, uint32_t *gbm,
-                                  hipStream_t s);
+                                  void *head, hipStream_t s);
 hipError_t launch_vote(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
                        void *acc, int acc_type, hipStream_t s);
 // counts: ceil(n_theta / kPeakRowsPerBlock) counters of device scratch (the context's).
@@ -196,8 +199,7 @@ hipError_t launch_batch_split(const GridArgs &g, const SplitPlan &p, const Batch
                               int n_cu, hipStream_t s);
 
 // LDS needs and plans (hough_kernels.hip).
-// LDS of hough_vote's workgroup for a slab of `rows` rho rows, and the tallest slab that fits.
-size_t vote_lds_bytes(int rows);
+// The tallest slab of rho rows hough_vote's workgroup holds.
 int vote_slab_rows(int n_rho, size_t lds_limit);
 // LDS of hough_peaks' workgroup of `waves` theta rows, and the most rows that fit (0: none).
 size_t peaks_lds_bytes(int n_rho, int waves);

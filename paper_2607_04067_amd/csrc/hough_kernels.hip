@@ -363,6 +363,33 @@ __device__ __forceinline__ void wave_hits(uint32_t H, int wave, uint32_t &hb, ui
     he = min(H, (uint32_t)((uint64_t)blocks * (w + 1u) / NW) * 8u);
 }
 
+// First and last row any vote of an event can reach, from the smallest r2 = x^2 + y^2 among its
+// valid hits (the map's own float expression): |t - B| <= wA / sqrt(r2) with wA the largest
+// |(C_j, S_j)|; the float map and the two fmas of t add a few 2^-24 relative, far inside the 1e-6
+// and 1e-5 margins kept here.  Rows are floor(t), so the floors of the bounds are the rows.
+__device__ __forceinline__ void reached_rows(const GridArgs &g, float min_r2, int &klo, int &khi) {
+    const double rmax = (1.0 + 1e-6) / sqrt((double)min_r2);
+    const double span = g.wA * rmax, slack = 1e-5 * (fabs(g.wB) + span) + 1e-3;
+    const double lo = g.wB - span - slack, hi = g.wB + span + slack;
+    const double top = (double)(g.n_rho - 1);
+    klo = lo <= 0.0 ? 0 : (lo >= top ? g.n_rho - 1 : (int)lo);
+    khi = hi <= 0.0 ? 0 : (hi >= top ? g.n_rho - 1 : (int)hi);
+}
+
+// The smallest valid r2 of the wave's hits, as the bits of a float (positive floats order as
+// their bits), in every lane.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v);
+__device__ __forceinline__ uint32_t min_r2_bits(const float *x, const float *y, uint32_t hb, uint32_t he, int lane) {
+    uint32_t mn = __float_as_uint(FLT_MAX);
+#pragma unroll 1
+    for (uint32_t i = hb + lane; i < he; i += 64) {
+        const float xi = x[i], yi = y[i];
+        const float r2 = __builtin_fmaf(xi, xi, yi * yi);
+        if (r2 > 0.0f && r2 <= FLT_MAX) mn = min(mn, __float_as_uint(r2));
+    }
+    return wave_min(mn);
+}
+
 // Step 4 on rows [16*u, 16*u + 16) of the lane's columns: bit b of mask[q] is set iff cell
 // (column 64q + lane, row 16*u + b) is a peak.  Raster order is (theta, rho), so the column to
 // the left and the row above come first:
@@ -951,79 +978,6 @@ __device__ uint32_t retain_range_peaks(const float4 *tpk, uint32_t np, bool edge
 }
 
 // ------------------------------------------------------------------------ plain path
-// The iterative finder's batch path keeps 16-bit cells stored rho-major (acc[k * n_theta + j]), so
-// that the write-out of a tile row is one contiguous run per wave.
-
-// Votes of hits [hb, he) into rows [r0, r1) of the lane's column only (a rho slab of the tile:
-// tile row k - r0 holds grid row k): every vote takes the range test r0 <= t < r1, which for an
-// integer r0 >= 0 is the same as r0 <= (int)t, so a vote lands exactly where the whole-grid rule
-// puts it, or is left to another slab.  Returns the number of valid hits seen.
-template <int NW>
-__device__ uint32_t vote_range_slab(uint32_t *tile, float2 *st, const float *x, const float *y, uint32_t hb,
-                                    uint32_t he, const Cols<1> &cl, const Lane<1, true> &ln, const GridArgs &g,
-                                    int lane, uint32_t &bad, const uint8_t *dup, int r0, int r1) {
-    const float lo_f = (float)r0, hi_f = (float)r1;
-    uint32_t n_valid = 0;
-    for (uint32_t base = hb; base < he; base += 64) {
-        const uint32_t i = base + lane;
-        bool live = i < he;
-        float xi = 0.0f, yi = 0.0f;
-        if (live) { xi = x[i]; yi = y[i]; }
-        if (dup) {
-            const bool copy = live && (dup[i] & kKeepDuplicate) != 0;
-            n_valid += (uint32_t)__popcll(__ballot(copy && valid_hit(xi, yi)));
-            live = live && !copy;
-        }
-        int slot;
-        const StageCount n = stage_values(st, xi, yi, live, g, bad, slot);
-        n_valid += n.total;
-        for (uint32_t h = 0; h < n.total; ++h) {
-            const float2 p = st[h];
-            const float t = __builtin_fmaf(p.x, cl.C[0], __builtin_fmaf(p.y, cl.S[0], cl.B[0]));
-            if (t >= lo_f && t < hi_f) lds_add(&tile[((int)t - r0) * Lane<1, true>::STRIDE + (int)ln.col[0]], ln.inc);
-        }
-        wave_sync();
-    }
-    return n_valid;
-}
-
-// Steps 1-3 of one event into one 64-column group of a rho-major 16-bit accumulator, rows
-// [r0, r1) (the whole column, or a rho slab of it when the column does not fit LDS), by one
-// workgroup: all hits of the event (at most kMaxBatchHits) are swept through the group's packed
-// tile, which is then written out.  dup as for vote_range.  Returns this thread's invalid-hit
-// flag.
-template <int NW>
-__device__ uint32_t vote_group_to_acc(const GridArgs &g, const float *__restrict__ x,
-                                      const float *__restrict__ y, uint32_t n_hits, uint16_t *acc,
-                                      int group, const uint8_t *dup, int r0, int r1) {
-    using L = Lane<1, true>;
-    extern __shared__ __align__(16) uint32_t lds[];
-    const int rows = r1 - r0;
-    uint32_t *tile = lds;                                                  // [(rows + 1) * 32]
-    float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)(rows + 1) * L::STRIDE);     // slabs only
-    const int lane = threadIdx.x & 63, wave = wave_id();
-    const int first = group * 64;
-    const L ln(lane);
-    const Cols<1> cl = load_cols<1>(g, first, lane, L::STRIDE, ln.col);
-    const int j = first + lane;
-    uint32_t bad = 0, hb, he;
-    for (int i = threadIdx.x; i < (rows + 1) * L::STRIDE / 4; i += NW * 64)
-        reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-    wave_hits<NW>(n_hits, wave, hb, he);
-    if (r0 == 0 && r1 == g.n_rho)
-        vote_range<1>(tile, x, y, hb, he, cl, g, first, lane, bad, g.nrho_f, dup);
-    else
-        vote_range_slab<NW>(tile, stage + wave * 64, x, y, hb, he, cl, ln, g, lane, bad, dup, r0, r1);
-    __syncthreads();
-    if (j < g.n_theta) {                       // a wave stores 64 adjacent cells of a row
-        uint16_t *col = acc + j;
-        for (int k = r0 + wave; k < r1; k += NW)
-            col[(size_t)k * g.n_theta] = (uint16_t)ln.count(tile[(k - r0) * L::STRIDE + ln.col[0]]);
-    }
-    return bad;
-}
-
 // hough_vote: workgroup (32-column group, rho slab of slab_rows rows), all of the event's hits swept
 // through one 32-bit counter per cell, [rows + 1][32] in LDS (the last row a dummy).  One event
 // is latency: the groups are as narrow as one matrix instruction, so that the most
@@ -1138,38 +1092,226 @@ __global__ __launch_bounds__(NW * 64) void k_vote(GridArgs g, const float *__res
     }
 }
 
-// Steps 1-3 for a batch of CSR events into per-event 16-bit accumulators (the iterative
-// finder's batch form): workgroup (event, 64-column group, rho slab).  Workgroup (e, 0, 0) writes
-// the event's status (invalid hits, too many hits, duplicate pass skipped); the later kernels OR
-// into it.  An event above kMaxBatchHits hits, or with malformed offsets, gets no accumulator.
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
+    return v;
+}
+
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o, 64));
+    return v;
+}
+
+// The threshold of the iterative finder for a largest count mx.
+__device__ __forceinline__ uint32_t iter_threshold(uint32_t mx, uint32_t frac_num, uint32_t frac_den, uint32_t floor_t) {
+    const uint64_t top = (uint64_t)mx * frac_num + frac_den - 1u;
+    // (a 64-bit division costs some 150 instructions, and every wave makes it)
+    const uint64_t rel = top >> 32 ? top / frac_den : (uint64_t)((uint32_t)top / frac_den);
+    return (uint32_t)min<uint64_t>(max<uint64_t>(rel, floor_t), 0xffffffffull);
+}
+
+// Steps 1-3 of the iterative finder's batch form: workgroup (event, 64-column tile) votes the
+// event's hits into the rows they reach and hands the finder what it can need of the tile: the
+// keys (count << 32 | ~raster index) of the cells that reach the threshold of the tile's own
+// largest count -- never above that of the event's -- where they are few (at most kIterTileKeys),
+// else every cell as 16-bit counts, [row][column of the tile].  Either goes to the tile's part of
+// the event's accumulator in the workspace (64 n_rho cells, fewer in the last tile);
+// head[event * tiles + tile] says which: the number of keys, or kIterDense, and the tile's
+// largest count.  (Writing every accumulator and reading it back with one workgroup per event took
+// 640 of the 668 us of 300 events on 1000 x 1000; the lists hold some 20 keys per tile there, and
+// votes and finder take 138 and 64 us so.  Latency bounds the votes: half of the chip's VALU issue
+// and a third of its LDS cycles; several tiles per workgroup or 12 waves gained nothing.)
+// The LDS tile holds up to slab_rows rows (two workgroups per CU); hits that reach more go
+// through it slab by slab, cells written.  Workgroup (e, 0) writes the event's status (invalid
+// hits, too many hits, duplicate pass skipped); the finder ORs into it.  An event above
+// kMaxBatchHits hits, or with malformed offsets, gets nothing.
+constexpr uint32_t kIterTileKeys = 512;
+constexpr uint32_t kIterDense = 0xffffffffu;
+
+// A tile's keys start on the first 8-byte boundary of its part; room for how many.
+__device__ __forceinline__ uint64_t *tile_keys(uint16_t *part) {
+    return reinterpret_cast<uint64_t *>(((uintptr_t)part + 7u) & ~(uintptr_t)7u);
+}
+__device__ __forceinline__ uint32_t tile_key_room(int width, int n_rho) {
+    const uint32_t bytes = 2u * (uint32_t)width * (uint32_t)n_rho;
+    return min(bytes >= 8u ? (bytes - 6u) / 8u : 0u, kIterTileKeys);
+}
+
+// Votes of hits [hb, he) into rows [r0, r0 + rows) of a packed 64-column tile (tile row k - r0;
+// any other vote to the dummy row after them).
+__device__ void vote_range_rows(uint32_t *tile, const float *x, const float *y, uint32_t hb, uint32_t he,
+                                const Cols<1> &cl, const GridArgs &g, int first_col, int lane, uint32_t &bad,
+                                const uint8_t *dup, int r0, int rows) {
+    const VoteCols<1> vc = vote_cols<1, false>(cl, g, first_col, lane);
+    f32x16 bf;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bf[i] = g.Bf;
+    asm volatile("" : "+v"(bf));
+    for (uint32_t base = hb; base < he; base += 64) {
+        const uint32_t i = base + lane;
+        bool live = i < he;
+        float xi = 0.0f, yi = 0.0f;
+        if (live) { xi = x[i]; yi = y[i]; }
+        if (dup && live && (dup[i] & kKeepDuplicate)) live = false;
+        float u, v, a0, a1;
+        const bool ok = conformal(live ? xi : 0.0f, live ? yi : 0.0f, u, v);
+        if (live && !ok) bad = 1u;
+        const float nan = __uint_as_float(0x7fc00000u);
+        swap_halves(live && ok ? v : nan, live && ok ? u : nan, a0, a1);
+#pragma unroll 1
+        for (uint32_t b = base; b < he && b < base + 64u; b += 32u, a0 = a1) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const f32x16 t = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, vc.op[h], bf, 0, 0, 0);
+                if (vc.in[h]) {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) {
+                        const float tt = t[q] + 0.0f;                         // see vote_mfma
+                        const int k = __float_as_uint(tt) < __float_as_uint(g.nrho_f) ? (int)tt : -1;
+                        lds_add(&tile[min((uint32_t)(k - r0), (uint32_t)rows) * 32u + (uint32_t)(lane & 31)],
+                                h ? 0x10000u : 1u);
+                    }
+                }
+            }
+        }
+    }
+}
+
 template <int NW>
 __global__ __launch_bounds__(NW * 64) void k_vote_batch(GridArgs g, const float *__restrict__ x,
                                                         const float *__restrict__ y,
                                                         const uint32_t *__restrict__ offsets,
                                                         uint16_t *acc, const uint8_t *keep,
-                                                        uint32_t *status, int slab_rows) {
+                                                        uint32_t *status, int slab_rows, uint32_t frac_num,
+                                                        uint32_t frac_den, uint2 *head) {
+    using L = Lane<1, true>;
+    typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+    constexpr int NT = NW * 64;
+    extern __shared__ __align__(16) uint32_t tile[];                       // [(slab_rows + 1) * 32]
+    __shared__ uint32_t s_bad, s_minr2, s_lo, s_hi, s_max, s_cnt;
     const uint32_t e = blockIdx.x;
-    const bool first_wg = blockIdx.y == 0 && blockIdx.z == 0;
     const uint32_t h0 = offsets[e], h1 = offsets[e + 1];
     const bool ok = h1 >= h0 && h1 - h0 <= kMaxBatchHits;
     if (!ok) {
-        if (first_wg && threadIdx.x == 0) status[e] = HOUGH_EV_TOO_MANY_HITS;
+        if (blockIdx.y == 0 && threadIdx.x == 0) status[e] = HOUGH_EV_TOO_MANY_HITS;
         return;
     }
     const uint32_t H = h1 - h0;
-    const size_t cells = (size_t)g.n_theta * (size_t)g.n_rho;
-    const int r0 = (int)blockIdx.z * slab_rows, r1 = min(r0 + slab_rows, g.n_rho);
-    const uint32_t bad = vote_group_to_acc<NW>(g, x + h0, y + h0, H, acc + (size_t)e * cells, (int)blockIdx.y,
-                                               g.dedup ? keep + h0 : nullptr, r0, r1);
-    __shared__ uint32_t s_bad;
-    if (threadIdx.x == 0) s_bad = 0u;
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const uint8_t *dup = g.dedup ? keep + h0 : nullptr;
+    x += h0;
+    y += h0;
+    uint32_t hb, he;
+    wave_hits<NW>(H, wave, hb, he);
+    const uint32_t mn = min_r2_bits(x, y, hb, he, lane);
+    // (cleared while those hits are on their way)
+    for (int i = threadIdx.x; i < (slab_rows + 1) * 8; i += NT)
+        reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (threadIdx.x == 0) { s_bad = 0u; s_max = 0u; s_cnt = 0u; s_minr2 = __float_as_uint(FLT_MAX); }
     __syncthreads();
+    if (lane == 0) atomicMin(&s_minr2, mn);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int klo, khi;
+        reached_rows(g, __uint_as_float(s_minr2), klo, khi);
+        s_lo = (uint32_t)klo;
+        s_hi = (uint32_t)khi;
+    }
+    __syncthreads();
+    const int klo = __builtin_amdgcn_readfirstlane((int)s_lo), khi = __builtin_amdgcn_readfirstlane((int)s_hi);
+    const bool one = khi - klo < slab_rows;                      // one slab holds every row the hits reach
+    uint32_t bad = 0;
+    const int tl = (int)blockIdx.y;
+    const int first = tl * 64, width = min(64, g.n_theta - first);
+    uint16_t *part = acc + ((size_t)e * (size_t)g.n_theta + (size_t)first) * (size_t)g.n_rho;
+    const int vl = opaque(lane);
+    const L ln(vl);
+    const Cols<1> cl = load_cols<1>(g, first, vl, L::STRIDE, ln.col);
+    uint32_t m = 0, thr = 0, count = kIterDense;
+    for (int r0 = klo; r0 <= khi; r0 += slab_rows) {
+        const int rows = min(slab_rows, khi + 1 - r0);
+        if (r0 != klo) {
+            for (int i = threadIdx.x; i < (rows + 1) * 8; i += NT)
+                reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
+            __syncthreads();
+        }
+        if (one)
+            vote_range<1>(tile - (ptrdiff_t)r0 * L::STRIDE, x, y, hb, he, cl, g, first, lane, bad, (float)(r0 + rows), dup);
+        else
+            vote_range_rows(tile, x, y, hb, he, cl, g, first, lane, bad, dup, r0, rows);
+        __syncthreads();
+        const uint4 *q = reinterpret_cast<const uint4 *>(tile);
+        u16x2 mm = {0, 0};
+        for (int i = threadIdx.x; i < rows * 8; i += NT) {
+            const uint4 v = q[i];
+            mm = __builtin_elementwise_max(mm, __builtin_elementwise_max(
+                __builtin_elementwise_max(__builtin_bit_cast(u16x2, v.x), __builtin_bit_cast(u16x2, v.y)),
+                __builtin_elementwise_max(__builtin_bit_cast(u16x2, v.z), __builtin_bit_cast(u16x2, v.w))));
+        }
+        const uint32_t own = max((uint32_t)mm.x, (uint32_t)mm.y);      // the largest of this thread's cells
+        m = wave_max(max(m, own));
+        if (one) {
+            if (lane == 0) atomicMax(&s_max, m);
+            __syncthreads();
+            thr = iter_threshold((uint32_t)__builtin_amdgcn_readfirstlane((int)s_max), frac_num, frac_den, g.threshold);
+            // counted first, so that a tile of many is not half listed
+            uint32_t n = 0;
+            for (int i = threadIdx.x; own >= thr && i < rows * 8; i += NT) {
+                const uint4 v = q[i];
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) n += ((w[c] & 0xffffu) >= thr ? 1u : 0u) + ((w[c] >> 16) >= thr ? 1u : 0u);
+            }
+            const uint32_t incl = wave_inclusive_scan(n, lane);
+            uint32_t off = 0;
+            if (lane == 63 && incl) off = atomicAdd(&s_cnt, incl);
+            off = (uint32_t)__builtin_amdgcn_readlane((int)off, 63) + incl - n;
+            __syncthreads();
+            const uint32_t total = s_cnt;
+            if (total <= tile_key_room(width, g.n_rho)) {
+                count = total;
+                uint64_t *keys = tile_keys(part);
+                if (n)
+                    for (int i = threadIdx.x; i < rows * 8; i += NT) {
+                        const uint4 v = q[i];
+                        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            const int k = r0 + (i >> 3), col = 4 * (i & 7) + c;
+#pragma unroll
+                            for (int hi = 0; hi < 2; ++hi) {
+                                const uint32_t cv = hi ? w[c] >> 16 : w[c] & 0xffffu;
+                                if (cv >= thr) {
+                                    const uint32_t r = (uint32_t)(first + col + 32 * hi) * (uint32_t)g.n_rho + (uint32_t)k;
+                                    keys[off++] = ((uint64_t)cv << 32) | (uint64_t)(~r);
+                                }
+                            }
+                        }
+                    }
+                break;
+            }
+        }
+        if (lane < width)                       // every cell: a wave stores a row of the tile
+            for (int k = r0 + wave; k < r0 + rows; k += NW)
+                part[(size_t)k * width + lane] = (uint16_t)ln.count(tile[(k - r0) * L::STRIDE + ln.col[0]]);
+        __syncthreads();
+    }
+    if (count == kIterDense) {                  // the rows no hit reaches
+        for (int i = threadIdx.x; i < klo * width; i += NT) part[i] = 0;
+        for (int i = (khi + 1) * width + (int)threadIdx.x; i < g.n_rho * width; i += NT) part[i] = 0;
+    }
+    if (!one && lane == 0) atomicMax(&s_max, m);
     if (bad) s_bad = 1u;
     __syncthreads();
-    // every workgroup sees every hit of the event, so the first one's flags are the event's
-    if (first_wg && threadIdx.x == 0)
-        status[e] = (s_bad ? HOUGH_EV_INVALID_HITS : 0u) |
-                    (g.dedup && H > kDedupMaxHits ? HOUGH_EV_DEDUP_SKIPPED : 0u);
+    if (threadIdx.x == 0) {
+        head[(size_t)e * gridDim.y + tl] = make_uint2(count, s_max);
+        // every workgroup sees every hit of the event, so the first one's flags are the event's
+        if (blockIdx.y == 0)
+            status[e] = (s_bad ? HOUGH_EV_INVALID_HITS : 0u) |
+                        (g.dedup && H > kDedupMaxHits ? HOUGH_EV_DEDUP_SKIPPED : 0u);
+    }
 }
 
 // hough_peaks: workgroup b tests theta rows [NW*b, NW*b + NW), staged in LDS with one halo row
@@ -1299,18 +1441,6 @@ constexpr uint32_t kIterThreads = kIterWaves * 64;
 constexpr uint32_t kIterMaxKeys = 16384;     // 128 KB of LDS
 constexpr uint32_t kIterMinKeys = 1024;
 
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
-}
-
-__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
-}
-
 // The suppression bitmap: every access comes from the event's own workgroup, so workgroup-scope
 // atomics order the marks of wave 0 against the later reads of every wave (LDS or device memory).
 __device__ __forceinline__ bool bm_test(const uint32_t *bm, uint32_t r) {
@@ -1401,12 +1531,6 @@ __device__ void hist_fit(const uint32_t *hist, uint32_t nb, bool top, uint32_t r
     *first = wave_min(f);
 }
 
-// The threshold of the iterative finder for a largest count mx.
-__device__ __forceinline__ uint32_t iter_threshold(uint32_t mx, uint32_t frac_num, uint32_t frac_den, uint32_t floor_t) {
-    const uint64_t rel = ((uint64_t)mx * frac_num + frac_den - 1u) / frac_den;
-    return (uint32_t)min<uint64_t>(max<uint64_t>(rel, floor_t), 0xffffffffull);
-}
-
 // One event's accumulator read by the whole chip ahead of the finder (one workgroup reading 4 MB
 // took 125 of the finder's 144 us on 1000 x 1000; this pass takes 7 and the finder 20 after it): the largest count in scan[0], and in list
 // the keys of every cell that reaches the threshold (their number in scan[1]; more than kIterScanCap:
@@ -1463,19 +1587,20 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(const T *__restrict_
     }
 }
 
-// offsets (batch form, else null): workgroup e takes event e's accumulator (rho-major 16-bit
-// cells) at acc + e * cells, writes its list at out + e * cap, n_peaks[e], and ORs
+// BATCH (offsets given): workgroup e takes what k_vote_batch left of event e at acc + e * cells and
+// head + e * tiles, writes its list at out + e * cap, n_peaks[e], and ORs
 // HOUGH_EV_PEAKS_TRUNCATED into status[e] (which the batch vote wrote); events the vote skipped
 // get no peaks.  K: keys in the LDS buffer (a power of two, kIterMinKeys .. kIterMaxKeys).
 // gbm (GBM): device bitmaps of bm_words words, one per workgroup.
 // list, scan (one event, else null): what k_iter_scan left, in place of the first pass.
-template <typename T, bool GBM>
+template <typename T, bool GBM, bool BATCH>
 __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T *__restrict__ acc,
                                                              uint32_t frac_num, uint32_t frac_den, int r_theta,
                                                              int r_rho, hough_peak *out, uint32_t cap,
                                                              uint32_t *n_peaks, uint32_t *status,
                                                              const uint32_t *offsets, uint32_t K, uint32_t *gbm,
-                                                             const uint64_t *list, uint32_t *scan) {
+                                                             const uint64_t *list, uint32_t *scan,
+                                                             const uint2 *head) {
     extern __shared__ __align__(16) uint64_t keys[];       // [K]; the histograms reuse it as 2K words
     uint32_t *hist = reinterpret_cast<uint32_t *>(keys);
     __shared__ uint32_t s_red[kIterWaves];
@@ -1483,14 +1608,10 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t nr = (uint32_t)g.n_rho, nt = (uint32_t)g.n_theta;
     const uint32_t cells = nt * nr, bm_words = (cells + 31u) / 32u, NB = 2u * K;
-    const bool batch = offsets != nullptr;
-    // the batch form stores rho-major (see vote_group_to_acc); keys and the bitmap use raster order
-    auto raster = [&](uint32_t c) -> uint32_t {
-        if (!batch) return c;
-        const uint32_t k = c / nt;
-        return (c - k * nt) * nr + k;
-    };
-    if (batch) {
+    const uint32_t tiles = (nt + 63u) / 64u;
+    // (batch) first listed key of each tile, [tiles + 1] after the keys and an LDS bitmap
+    uint32_t *s_tile = reinterpret_cast<uint32_t *>(keys + K) + (GBM ? 0u : (bm_words + 3u) & ~3u);
+    if constexpr (BATCH) {
         const uint32_t e = blockIdx.x;
         acc += (size_t)e * cells;
         out = out ? out + (size_t)e * cap : nullptr;
@@ -1501,17 +1622,76 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
             if (tid == 0) *n_peaks = 0u;
             return;
         }
+        head += (size_t)e * tiles;
     }
-    uint32_t *bm = GBM ? gbm + (batch ? (size_t)blockIdx.x * bm_words : (size_t)0)
+    uint32_t *bm = GBM ? gbm + (BATCH ? (size_t)blockIdx.x * bm_words : (size_t)0)
                        : reinterpret_cast<uint32_t *>(keys + K);
-    for (uint32_t w = tid; w < bm_words; w += kIterThreads) bm[w] = 0u;
+    if constexpr (!GBM) {
+        // (whole quads: the LDS bitmap ends on a 16-byte boundary)
+        for (uint32_t w = tid; w < (bm_words + 3u) / 4u; w += kIterThreads)
+            reinterpret_cast<uint4 *>(bm)[w] = make_uint4(0u, 0u, 0u, 0u);
+    } else {
+        for (uint32_t w = tid; w < bm_words; w += kIterThreads) bm[w] = 0u;
+    }
     if (tid == 0) { s_n = 0u; s_taken = 0u; }
     __syncthreads();
 
+    // every cell that can be a candidate, as f(count, raster index, valid), all lanes of a wave
+    // together: the accumulator's cells; of a batch event the listed keys of its tiles and the
+    // cells of those that list none
+    auto each = [&](auto &&f) {
+        if constexpr (!BATCH) {
+            for_cells(acc, cells, [&](uint32_t c, uint32_t v, bool in) { f(v, c, in); });
+        } else {
+            const uint32_t listed = s_tile[tiles];
+            for (uint32_t i0 = 0; i0 < listed; i0 += kIterThreads) {
+                const uint32_t i = i0 + tid;
+                uint64_t key = 0;
+                if (i < listed) {
+                    uint32_t lo = 0, hi = tiles - 1u;             // the last tile whose keys start at or before i
+                    while (lo < hi) {
+                        const uint32_t mid = (lo + hi + 1u) >> 1;
+                        if (s_tile[mid] <= i) lo = mid; else hi = mid - 1u;
+                    }
+                    key = tile_keys(const_cast<uint16_t *>(acc) + (size_t)lo * 64u * nr)[i - s_tile[lo]];
+                }
+                f((uint32_t)(key >> 32), ~(uint32_t)key, i < listed);
+            }
+            for (uint32_t t = 0; t < tiles; ++t) {
+                if (head[t].x != kIterDense) continue;
+                const uint32_t w = min(64u, nt - 64u * t);
+                for_cells(acc + (size_t)t * 64u * nr, w * nr, [&](uint32_t c, uint32_t v, bool in) {
+                    const uint32_t k = c / w;
+                    f(v, (64u * t + (c - k * w)) * nr + k, in);
+                });
+            }
+        }
+    };
     const uint32_t floor_t = g.threshold;
     uint32_t mx = 0, thr, n1;
     bool filtered;             // the keys held reach thr (else the floor)
-    if (scan) {
+    if constexpr (BATCH) {
+        // the tiles' heads: the event's largest count, and where each tile's keys start
+        uint32_t m = 0, run = 0;
+        for (uint32_t t0 = 0; t0 < tiles; t0 += 64u) {            // every wave the same
+            const uint32_t t = t0 + lane;
+            const uint2 hd = t < tiles ? head[t] : make_uint2(0u, 0u);
+            const uint32_t n = hd.x == kIterDense ? 0u : hd.x, incl = wave_inclusive_scan(n, (int)lane);
+            if (wave == 0 && t < tiles) s_tile[t] = run + incl - n;
+            run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            m = max(m, hd.y);
+        }
+        if (tid == 0) s_tile[tiles] = run;
+        mx = wave_max(m);
+        thr = iter_threshold(mx, frac_num, frac_den, floor_t);
+        __syncthreads();
+        each([&](uint32_t v, uint32_t r, bool in) {
+            append_key(keys, &s_n, K, in && v >= thr, ((uint64_t)v << 32) | (uint64_t)(~r), lane);
+        });
+        __syncthreads();
+        n1 = s_n;
+        filtered = true;
+    } else if (scan) {
         mx = scan[0];
         n1 = scan[1];
         thr = iter_threshold(mx, frac_num, frac_den, floor_t);
@@ -1528,10 +1708,9 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     } else {
         // pass 1: the maximum, and the candidates of the absolute floor while they fit
         uint32_t m = 0;
-        for_cells(acc, cells, [&](uint32_t c, uint32_t v, bool in) {
+        each([&](uint32_t v, uint32_t r, bool in) {
             m = max(m, v);
-            const bool p = in && v >= floor_t;
-            append_key(keys, &s_n, K, p, p ? ((uint64_t)v << 32) | (uint64_t)(~raster(c)) : 0ull, lane);
+            append_key(keys, &s_n, K, in && v >= floor_t, ((uint64_t)v << 32) | (uint64_t)(~r), lane);
         });
         m = wave_max(m);
         if (lane == 0) s_red[wave] = m;
@@ -1573,9 +1752,8 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
                 const uint32_t w = (uint32_t)(((uint64_t)vhi - vlo + 1u + NB - 1u) / NB);
                 for (uint32_t b = tid; b < NB; b += kIterThreads) hist[b] = 0u;
                 __syncthreads();
-                for_cells(acc, cells, [&](uint32_t c, uint32_t v, bool in) {
+                each([&](uint32_t v, uint32_t r, bool in) {
                     if (!in || v < vlo || v > vhi) return;
-                    const uint32_t r = raster(c);
                     const uint64_t key = ((uint64_t)v << 32) | (uint64_t)(~r);
                     if ((bounded && key >= hi) || bm_test(bm, r)) return;
                     atomicAdd(&hist[(v - vlo) / w], 1u);
@@ -1603,9 +1781,8 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
                     const uint32_t wr = (uint32_t)(((uint64_t)rhi - rlo + 1u + NB - 1u) / NB);
                     for (uint32_t b = tid; b < NB; b += kIterThreads) hist[b] = 0u;
                     __syncthreads();
-                    for_cells(acc, cells, [&](uint32_t c, uint32_t v, bool in) {
+                    each([&](uint32_t v, uint32_t r, bool in) {
                         if (!in || v != vt) return;
-                        const uint32_t r = raster(c);
                         if (r < rlo || r > rhi || bm_test(bm, r)) return;
                         atomicAdd(&hist[(r - rlo) / wr], 1u);
                     });
@@ -1629,11 +1806,10 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
             // gather the chunk: the remaining keys in [lo, hi)
             if (tid == 0) s_n = 0u;
             __syncthreads();
-            for_cells(acc, cells, [&](uint32_t c, uint32_t v, bool in) {
+            each([&](uint32_t v, uint32_t r, bool in) {
                 bool p = in && v >= thr;
                 uint64_t key = 0;
                 if (p) {
-                    const uint32_t r = raster(c);
                     key = ((uint64_t)v << 32) | (uint64_t)(~r);
                     p = key >= lo && (!bounded || key < hi) && !bm_test(bm, r);
                 }
@@ -1727,7 +1903,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         const uint32_t taken = s_taken;
         *n_peaks = taken;
         const uint32_t tr = taken > cap ? HOUGH_EV_PEAKS_TRUNCATED : 0u;
-        *status = batch ? (*status | tr) : tr;
+        *status = BATCH ? (*status | tr) : tr;
         if (scan) { scan[0] = 0u; scan[1] = 0u; }
     }
 }
@@ -2134,30 +2310,15 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
         } else if (H > kDedupMaxHits && threadIdx.x == 0) {
             atomicOr(&s_flags, HOUGH_EV_DEDUP_SKIPPED);
         }
-        // the event's rho window: the smallest r2 = x^2 + y^2 among its valid hits (the same
-        // float expression as the map's) bounds every bin they vote into, |t - B| <= wA / sqrt(r2)
-        // with wA the largest |(C_j, S_j)|; the float map and the two fmas of t add a few 2^-24
-        // relative, far inside the 1e-6 and 1e-5 margins kept here.  Rows are floor(t), so the
-        // floors of the bounds are the first and last rows a vote can reach.
+        // the event's rho window
         int wb = 0;
         if constexpr (WIN) {
-            uint32_t mn = __float_as_uint(FLT_MAX);
-#pragma unroll 1
-            for (uint32_t i = hb + lane; i < he; i += 64) {
-                const float xi = xe[i], yi = ye[i];
-                const float r2 = __builtin_fmaf(xi, xi, yi * yi);
-                if (r2 > 0.0f && r2 <= FLT_MAX) mn = min(mn, __float_as_uint(r2));   // r2 > 0: bits order as values
-            }
-            mn = wave_min(mn);
+            const uint32_t mn = min_r2_bits(xe, ye, hb, he, lane);
             if (lane == 0) atomicMin(&s_minr2, mn);
             __syncthreads();
             if (threadIdx.x == 0) {
-                const double rmax = (1.0 + 1e-6) / sqrt((double)__uint_as_float(s_minr2));
-                const double span = g.wA * rmax, slack = 1e-5 * (fabs(g.wB) + span) + 1e-3;
-                const double lo = g.wB - span - slack, hi = g.wB + span + slack;
-                const double top = (double)(g.n_rho - 1);
-                int klo = lo <= 0.0 ? 0 : (lo >= top ? g.n_rho - 1 : (int)lo);
-                int khi = hi <= 0.0 ? 0 : (hi >= top ? g.n_rho - 1 : (int)hi);
+                int klo, khi;
+                reached_rows(g, __uint_as_float(s_minr2), klo, khi);
                 if (PER) {                       // the wrapped halo columns vote the reversed rows too
                     const int lo_r = g.n_rho - 1 - khi, hi_r = g.n_rho - 1 - klo;
                     klo = min(klo, lo_r);
@@ -3137,12 +3298,8 @@ void allow_lds(K kernel) {
 
 }  // namespace
 
-size_t vote_lds_bytes(int rows) {
-    return (size_t)(rows + 1) * 32 * 4 + (size_t)kVoteWaves * kStageBytes + 256;
-}
-
 int vote_slab_rows(int n_rho, size_t lds_limit) {
-    const size_t fixed = (size_t)kVoteWaves * kStageBytes + 256 + 256;    // stages, slack, static LDS
+    const size_t fixed = (size_t)kVoteWaves * kStageBytes + 256 + 256;    // slack
     if (lds_limit <= fixed + 2 * 128) return 0;
     const long rows = (long)((lds_limit - fixed) / 128) - 1;
     return (int)(rows < n_rho ? rows - rows % 4 : n_rho);      // whole quads of rows per slab
@@ -3290,6 +3447,19 @@ hipError_t launch_peaks(const GridArgs &g, const void *acc, int acc_type, hough_
 // of kIterMinKeys .. kIterMaxKeys keys) that fits beside an LDS bitmap of the grid, with room for
 // `per_cu` workgroups per CU when that leaves at least 4096 keys, else one; a grid whose bitmap
 // does not fit beside kIterMinKeys keys keeps it in device memory.
+// The batch form also keeps a word per 64-column tile; where that does not fit beside a bitmap, the
+// key buffer gives way.
+static size_t iter_tile_bytes(int n_theta) { return ((size_t)((n_theta + 63) / 64 + 1) * 4 + 15) & ~(size_t)15; }
+
+IterPlan plan_iterative_batch(int n_theta, int n_rho, size_t lds_limit, int per_cu) {
+    IterPlan p = plan_iterative(n_theta, n_rho, lds_limit, per_cu);
+    while (p.keys > 256 && p.lds_bytes + iter_tile_bytes(n_theta) + 512 > lds_limit) {
+        p.lds_bytes -= (size_t)p.keys * 4;
+        p.keys >>= 1;
+    }
+    return p;
+}
+
 IterPlan plan_iterative(int n_theta, int n_rho, size_t lds_limit, int per_cu) {
     IterPlan p{};
     const size_t cells = (size_t)n_theta * (size_t)n_rho;
@@ -3318,23 +3488,24 @@ IterPlan plan_iterative(int n_theta, int n_rho, size_t lds_limit, int per_cu) {
     return p;
 }
 
-template <typename T>
+template <typename T, bool BATCH>
 static void launch_iter_t(const GridArgs &g, const T *acc, uint32_t frac_num, uint32_t frac_den, int r_theta,
                           int r_rho, hough_peak *peaks, uint32_t cap, uint32_t *n_peaks, uint32_t *status,
                           const uint32_t *offsets, uint32_t n_blocks, const IterPlan &ip, uint32_t *gbm,
-                          const uint64_t *list, uint32_t *scan, hipStream_t s) {
+                          const uint64_t *list, uint32_t *scan, const uint2 *head, hipStream_t s) {
+    const size_t lds = ip.lds_bytes + (BATCH ? iter_tile_bytes(g.n_theta) : 0);
     if (ip.gbm) {
-        static const bool lds_ok = (allow_lds(k_peaks_iter<T, true>), true);
+        static const bool lds_ok = (allow_lds(k_peaks_iter<T, true, BATCH>), true);
         (void)lds_ok;
-        hipLaunchKernelGGL((k_peaks_iter<T, true>), dim3(n_blocks), dim3(kIterThreads), ip.lds_bytes, s, g, acc,
+        hipLaunchKernelGGL((k_peaks_iter<T, true, BATCH>), dim3(n_blocks), dim3(kIterThreads), lds, s, g, acc,
                            frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, offsets, ip.keys, gbm,
-                           list, scan);
+                           list, scan, head);
     } else {
-        static const bool lds_ok = (allow_lds(k_peaks_iter<T, false>), true);
+        static const bool lds_ok = (allow_lds(k_peaks_iter<T, false, BATCH>), true);
         (void)lds_ok;
-        hipLaunchKernelGGL((k_peaks_iter<T, false>), dim3(n_blocks), dim3(kIterThreads), ip.lds_bytes, s, g, acc,
+        hipLaunchKernelGGL((k_peaks_iter<T, false, BATCH>), dim3(n_blocks), dim3(kIterThreads), lds, s, g, acc,
                            frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, offsets, ip.keys,
-                           nullptr, list, scan);
+                           nullptr, list, scan, head);
     }
 }
 
@@ -3345,8 +3516,8 @@ static void launch_iter_one(const GridArgs &g, const T *acc, uint32_t frac_num, 
     const uint32_t cells = (uint32_t)g.n_theta * (uint32_t)g.n_rho, tile = kScanThreads * kScanCells;
     hipLaunchKernelGGL(k_iter_scan<T>, dim3(std::min((cells + tile - 1u) / tile, 1024u)), dim3(kScanThreads), 0, s,
                        acc, cells, g.threshold, frac_num, frac_den, list, scan);
-    launch_iter_t<T>(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, nullptr, 1u, ip, gbm,
-                     list, scan, s);
+    launch_iter_t<T, false>(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, nullptr, 1u, ip, gbm,
+                     list, scan, nullptr, s);
 }
 
 hipError_t launch_peaks_iterative(const GridArgs &g, const void *acc, int acc_type, uint32_t frac_num,
@@ -3387,42 +3558,50 @@ hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint
     return hipGetLastError();
 }
 
-// The iterative finder's batch form: (duplicate pass), vote into per-event 16-bit accumulators,
-// the finder, and retention with each event's first `cap` peaks, four launches for the batch.
+// The iterative finder's batch form: (duplicate pass), votes into each tile's candidates (or
+// cells), the finder, and retention with each event's first `cap` peaks; as many events at a time as
+// the heads have room for.
+constexpr int kIterSlabRows = 600;               // 77 KB: two workgroups per CU
+constexpr int kIterVoteWaves = 8;
 hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_t *acc, uint32_t frac_num,
                                   uint32_t frac_den, int r_theta, int r_rho, const IterPlan &ip, uint32_t *gbm,
-                                  hipStream_t s) {
+                                  void *head, hipStream_t s) {
     if (a.n_events == 0) return hipSuccess;
     hipError_t e = hipSuccess;
     if (g.dedup) {
         e = launch_dedup(a, s);
         if (e != hipSuccess) return e;
     }
-    {
-        if (g.vote_rows < 1) return hipErrorInvalidValue;
-        const size_t lds = vote_lds_bytes(g.vote_rows);
-        static const bool lds_ok = (allow_lds(k_vote_batch<kVoteWaves>), true);
-        (void)lds_ok;
-        const int groups = (g.n_theta + 63) / 64, slabs = (g.n_rho + g.vote_rows - 1) / g.vote_rows;
-        hipLaunchKernelGGL(k_vote_batch<kVoteWaves>, dim3(a.n_events, groups, slabs), dim3(kVoteWaves * 64), lds,
-                           s, g, a.x, a.y, a.offsets, acc, a.keep, a.status, g.vote_rows);
+    static const hipError_t vote_ok =
+        hipFuncSetAttribute(reinterpret_cast<const void *>(k_vote_batch<kIterVoteWaves>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (kIterSlabRows + 1) * 128);
+    static const hipError_t retain_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<false>),
+                                                            hipFuncAttributeMaxDynamicSharedMemorySize, kRetainDilBytes);
+    if (vote_ok != hipSuccess) return vote_ok;
+    if (retain_ok != hipSuccess) return retain_ok;
+    const size_t cells = (size_t)g.n_theta * (size_t)g.n_rho;
+    const uint32_t tiles = (uint32_t)(g.n_theta + 63) / 64u, most_events = kIterHeads / tiles;
+    const int rows = std::min(g.n_rho, kIterSlabRows), cols = retain_cols_per_block(g);
+    const uint32_t most_blocks = (kMaxBatchHits + kRetainWaves * 64 - 1) / (kRetainWaves * 64);
+    for (uint32_t e0 = 0; e0 < a.n_events; e0 += most_events) {
+        const uint32_t n = std::min(most_events, a.n_events - e0);
+        const uint32_t *off = a.offsets + e0;
+        hough_peak *peaks = a.peaks ? a.peaks + (size_t)e0 * a.max_peaks : nullptr;
+        uint16_t *part = acc + e0 * cells;
+        uint32_t *bm = gbm ? gbm + e0 * (ip.bm_bytes / 4) : nullptr;
+        hipLaunchKernelGGL(k_vote_batch<kIterVoteWaves>, dim3(n, tiles), dim3(kIterVoteWaves * 64), (size_t)(rows + 1) * 128, s,
+                           g, a.x, a.y, off, part, a.keep, a.status + e0, rows, frac_num, frac_den,
+                           static_cast<uint2 *>(head));
         if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    launch_iter_t<uint16_t>(g, acc, frac_num, frac_den, r_theta, r_rho, a.peaks, a.max_peaks, a.n_peaks, a.status,
-                            a.offsets, a.n_events, ip, gbm, nullptr, nullptr, s);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    {
-        const int cols = retain_cols_per_block(g);
-        static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<false>),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kRetainDilBytes);
-        if (lds_ok != hipSuccess) return lds_ok;
+        launch_iter_t<uint16_t, true>(g, part, frac_num, frac_den, r_theta, r_rho, peaks, a.max_peaks, a.n_peaks + e0,
+                                      a.status + e0, off, n, ip, bm, nullptr, nullptr, static_cast<const uint2 *>(head),
+                                      s);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
         // a few events: several workgroups each, up to the largest event's chunks
-        const uint32_t most = (kMaxBatchHits + kRetainWaves * 64 - 1) / (kRetainWaves * 64);
-        const uint32_t blocks = std::max(1u, std::min(most, 512u / a.n_events));
-        hipLaunchKernelGGL(k_retain<false>, dim3(a.n_events, blocks), dim3(kRetainWaves * 64),
-                           retain_lds_bytes(g, cols), s, g, a.x, a.y, 0u, a.peaks, a.n_peaks, a.max_peaks, a.keep,
-                           cols, a.offsets);
-        e = hipGetLastError();
+        const uint32_t blocks = std::max(1u, std::min(most_blocks, 512u / n));
+        hipLaunchKernelGGL(k_retain<false>, dim3(n, blocks), dim3(kRetainWaves * 64), retain_lds_bytes(g, cols), s, g,
+                           a.x, a.y, 0u, peaks, a.n_peaks + e0, a.max_peaks, a.keep, cols, off);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return e;
 }

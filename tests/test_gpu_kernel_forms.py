@@ -302,3 +302,45 @@ def test_windows_over_many_events(H, orc, n_theta, n_rho, plan, flags):
     assert np.array_equal(gk[2].cpu().numpy()[:int(starts[-1])],
                           np.concatenate([keep_ref[off[e]:off[e + 1]] for e in ids]))
     ctx.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho,rng_lo,rng_hi", [(1, 1, -0.01, 0.01), (3, 5, -0.01, 0.01), (65, 33, -0.006, 0.006),
+                                                         (64, 600, -0.006, 0.006), (127, 601, -0.006, 0.006),
+                                                         (129, 1000, -0.01, 0.01), (70, 1301, -0.004, 0.006),
+                                                         (1000, 1200, -0.01, 0.01)])
+@pytest.mark.parametrize("dedup", [False, True])
+def test_batch_finder_tiles(H, orc, n_theta, n_rho, rng_lo, rng_hi, dedup):
+    """The iterative finder over a batch with tiles that list their candidates and tiles that write
+    every cell (small fractions and floors), one slab of rows and several, keys that start on odd
+    accumulator boundaries, an empty event and one too large, twice on one workspace."""
+    import torch
+    g = orc.Grid(n_theta, n_rho, rng_lo, rng_hi)
+    x, y, off = _events([400, 0, 1300, 33000, 90], 31, 120.0, 0.01)
+    x[50:90], y[50:90] = x[:40], y[:40]
+    cap = 300
+    xt, yt, ot = _t(x), _t(y), _t(off.astype(np.int32))
+    E = off.size - 1
+    for floor, frac in ((2, (1, 2)), (6, (3, 4)), (1, (0, 1))):
+        if frac[0] == 0 and n_theta * n_rho > 100000:
+            continue                                               # every voted cell is a candidate: minutes in the oracle
+        ctx = H.Context(n_theta, n_rho, rng_lo, rng_hi, "i32", floor, 1, cap, dedup=dedup)
+        ws = ctx.iterative_workspace(E)
+        small = np.diff(off) <= 32767
+        keep_ids = np.nonzero(small)[0]
+        xs = np.concatenate([x[off[e]:off[e + 1]] for e in keep_ids])
+        ys = np.concatenate([y[off[e]:off[e + 1]] for e in keep_ids])
+        so = np.concatenate([[0], np.cumsum(np.diff(off)[keep_ids])])
+        ref, n_ref, keep_ref = orc.run_batch_iterative_fast(g, xs, ys, so, floor, frac, 2, 3, 1, cap, dedup=dedup,
+                                                            n_threads=8)
+        for _ in range(2):
+            pk, npk, keep, st = ctx.run_batch_iterative(xt, yt, ot, frac, 2, 3, ws)
+            torch.cuda.synchronize()
+            npk, p, kp, st = npk.cpu().numpy(), pk.cpu().numpy(), keep.cpu().numpy(), st.cpu().numpy()
+            for i, e in enumerate(keep_ids):
+                m = int(min(n_ref[i], cap))
+                assert npk[e] == n_ref[i], (floor, e)
+                assert np.array_equal(H.decode_peaks(p[e], m), ref[i, :m].astype(np.int64)), (floor, e)
+                assert np.array_equal(kp[off[e]:off[e + 1]], keep_ref[so[i]:so[i + 1]]), (floor, e)
+                assert bool(st[e] & H.EV_PEAKS_TRUNCATED) == (n_ref[i] > cap)
+            assert npk[3] == 0 and st[3] == H.EV_TOO_MANY_HITS and not kp[off[3]:off[4]].any()
+        ctx.close()
