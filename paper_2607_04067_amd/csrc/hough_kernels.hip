@@ -825,6 +825,7 @@ __device__ uint32_t retain_pending(Pending &pd, const uint32_t *dil, float2 *st,
 // (10,000 events, 360 x 256: 839 -> 739 M VALU instructions with the pending list's lookups four
 // at a time; with the phases' registers kept apart, see opaque(), the batch takes 1.60 ms, 1.88
 // with the VALU vote and lane = column lookups alone)
+constexpr int kColumnRoundHits = 8;       // a round costs as much as the lookup of this many hits
 template <int G>
 __device__ __forceinline__ uint64_t kept_by_columns(const uint32_t *dil, float u, float v, uint64_t want,
                                                     int first_col, const GridArgs &g) {
@@ -849,7 +850,7 @@ __device__ __forceinline__ uint64_t kept_by_columns(const uint32_t *dil, float u
         const uint64_t now = __ballot((m & 1u) != 0u) & want;
         const uint32_t newly = (uint32_t)__popcll(now & ~kept), left = (uint32_t)__popcll(want & ~now);
         kept = now;
-        if (newly < 8u || left < 8u) break;
+        if (newly < (uint32_t)kColumnRoundHits || left < (uint32_t)kColumnRoundHits) break;
     }
     return kept;
 }
@@ -882,7 +883,8 @@ __device__ uint32_t retain_range(Pending &pd, const uint32_t *dil, float2 *st, c
         const bool safe = valid && all_in_range(u, v, g);
         const uint64_t bs = __ballot(safe), bv = __ballot(valid);
         uint64_t kept = 0;
-        if (many && bs) kept = kept_by_columns<G>(dil, safe ? u : 0.0f, safe ? v : 0.0f, bs, first_col, g);
+        if (many && __popcll(bs) >= kColumnRoundHits)
+            kept = kept_by_columns<G>(dil, safe ? u : 0.0f, safe ? v : 0.0f, bs, first_col, g);
         kept |= lookup_lanes<G>(dil, st, u, v, bs & ~kept, cl, g, lane);
         kept |= lookup_checked<G>(dil, u, v, bv & ~bs, cl, g, lane);
         if ((kept >> lane) & 1ull) ke[i] = (uint8_t)(kv | 1u);
@@ -2585,18 +2587,31 @@ __device__ __forceinline__ void keep_store(uint8_t *p, uint32_t v) {
 }
 
 // Step 5 of one tile in the split form, over a wave's share of the event's hits: against the
-// tile's peak list when it has one (np <= kTilePeaks), else as retain_range.
+// tile's peak list when it has one (np <= kTilePeaks), else as retain_range.  The tiles of an event
+// start at different places of the share (turn of turns), so that most of the hits a tile
+// comes to later have been kept by another one already.  (64 dense events, 720 x 512: 119 us per
+// batch when every tile starts at the first hit)
 __device__ void retain_split(const uint32_t *dil, const float4 *tpk, uint32_t np, bool edge, float2 *st,
                              const float *x, const float *y, uint8_t *ke, uint32_t hb, uint32_t he,
-                             const Cols<1> &cl, const GridArgs &g, int first_col, int lane) {
+                             const Cols<1> &cl, const GridArgs &g, int first_col, uint32_t turn, uint32_t turns,
+                             int lane) {
     const bool many = np * (2u * (uint32_t)g.rho_window + 1u) >= (uint32_t)g.n_rho;
+    const uint32_t chunks = (he - hb + 63u) >> 6;
+    if (chunks == 0u) return;
+    uint32_t c = (uint32_t)((uint64_t)chunks * turn / turns);
     uint32_t kn = 1u;
     float xn = 0.0f, yn = 0.0f;                       // the next 64 hits load while these are tested
-    if (hb + lane < he) { kn = keep_load(ke + hb + lane); xn = x[hb + lane]; yn = y[hb + lane]; }
-    for (uint32_t base = hb; base < he; base += 64) {
-        const uint32_t i = base + (uint32_t)lane, kv = kn;
+    auto load = [&](uint32_t cc) {
+        const uint32_t i = hb + 64u * cc + (uint32_t)lane;
+        kn = 1u;
+        if (i < he) { kn = keep_load(ke + i); xn = x[i]; yn = y[i]; }
+    };
+    load(c);
+    for (uint32_t n = 0; n < chunks; ++n) {
+        const uint32_t i = hb + 64u * c + (uint32_t)lane, kv = kn;
         const float xi = xn, yi = yn;
-        if (i + 64 < he) { kn = keep_load(ke + i + 64); xn = x[i + 64]; yn = y[i + 64]; }
+        if (++c == chunks) c = 0;
+        if (n + 1u < chunks) load(c);
         const bool todo = i < he && !(kv & 1u);
         if (__ballot(todo) == 0ull) continue;
         float u, v;
@@ -2607,7 +2622,8 @@ __device__ void retain_split(const uint32_t *dil, const float4 *tpk, uint32_t np
         } else {
             const bool safe = valid && all_in_range(u, v, g);
             const uint64_t bs = __ballot(safe), bv = __ballot(valid);
-            if (many && bs) kept = kept_by_columns<1>(dil, safe ? u : 0.0f, safe ? v : 0.0f, bs, first_col, g);
+            if (many && __popcll(bs) >= kColumnRoundHits)
+                kept = kept_by_columns<1>(dil, safe ? u : 0.0f, safe ? v : 0.0f, bs, first_col, g);
             kept |= lookup_lanes<1>(dil, st, u, v, bs & ~kept, cl, g, lane);
             kept |= lookup_checked<1>(dil, u, v, bv & ~bs, cl, g, lane);
         }
@@ -2731,7 +2747,8 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridA
                                                  NW, tpk, &cl, colcnt, &s_edge);
     if (np == 0u) return;
     __syncthreads();
-    retain_split(dil, tpk, np, s_edge != 0u, stage + wave * 64, xe, ye, ke, hb, he, cl, g, first, opaque(lane));
+    retain_split(dil, tpk, np, s_edge != 0u, stage + wave * 64, xe, ye, ke, hb, he, cl, g, first, t, T,
+                 opaque(lane));
 }
 
 // ------------------------------------------------------------ spill path (rho slabs)
@@ -3113,11 +3130,9 @@ __global__ __launch_bounds__(kSpillThreads) void k_spill(GridArgs g, BatchArgs a
     // process the left ones of each block, so that a batch whose events mostly spill (a window
     // its events do not fit) keeps every workgroup busy.  The last workgroup to leave clears
     // the count and both counters.
-    if (threadIdx.x == 0) s_n = __hip_atomic_load(sp.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    const bool any = uni(s_n) != 0u;
-    __syncthreads();
-    while (any) {
+    const uint32_t left = __hip_atomic_load(sp.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (uni(left) == 0u) return;               // (and the counters stay at zero)
+    for (;;) {
         if (threadIdx.x == 0) {
             s_event = atomicAdd(sp.queue + 2, 1u);
             s_n = 0u;
@@ -3688,6 +3703,7 @@ hipError_t launch_batch_split(const GridArgs &g, const SplitPlan &p, const Batch
     // share a CU and overlap their phases
     switch (items <= (uint32_t)n_cu ? p.wide : p.narrow) {
         case 16: return launch_split_t<16>(g, a, sp, items, s);
+        case 12: return launch_split_t<12>(g, a, sp, items, s);
         case 8: return launch_split_t<8>(g, a, sp, items, s);
         case 4: return launch_split_t<4>(g, a, sp, items, s);
         default: return hipErrorInvalidValue;
@@ -3706,6 +3722,10 @@ SplitPlan plan_split(int n_rho, size_t lds_limit) {
     SplitPlan p{0, 0};
     if (split_fits<4>(n_rho, lds_limit)) p.wide = p.narrow = 4;
     if (split_fits<8>(n_rho, lds_limit)) p.wide = p.narrow = 8;
+    // two workgroups per CU but not three: 12 waves each
+    if (3 * batch_lds_bytes(n_rho, 8, 1, 0) > lds_limit && 2 * (batch_lds_bytes(n_rho, 12, 1, 0) + 256) <= lds_limit &&
+        split_fits<12>(n_rho, lds_limit))
+        p.narrow = 12;
     if (split_fits<16>(n_rho, lds_limit)) {
         p.wide = 16;
         if (2 * batch_lds_bytes(n_rho, 8, 1, 0) > lds_limit) p.narrow = 16;   // one per CU either way
