@@ -13,7 +13,7 @@
 struct hough_ctx {
     hough_params p;
     int device;
-    char *d_block;          // one allocation that holds the buffers up to d_defer below
+    char *d_block;          // one allocation that holds the buffers up to d_uv below
     float *d_tables;        // C[n_theta] then S[n_theta]
     uint32_t *d_work;       // [0], [1]: work and exit counters of the fused kernels; from [64]:
                             // hough_peaks' per-block peak counts; [8], [9]: the iterative
@@ -30,6 +30,7 @@ struct hough_ctx {
                             // has not set one (win 0: none), see auto_window
     int chosen;             // the caller has set a launch shape
     uint32_t *d_defer;      // [kOrderMaxEvents] the events that did not fit its window
+    float *d_uv;            // [kMappedFloats] the fused kernel's mapped hits, shared out by launch
     hough::SplitPlan split; // the split form's (fused == 1)
     uint32_t *d_slots;      // its slots for batches of up to split_events(n_cu) events (fused == 1)
     int fused;              // 1: the fused kernel holds the grid's whole column (and windows of it);
@@ -92,6 +93,11 @@ int spill_workgroups(size_t stride_words, int n_cu, bool all) {
 // 80 / 37, 81 / 49, 84 / 82; 720 x 512 dense (12 tiles) 234 / 40, 241 / 120, 249 / 186, 255 / 348;
 // 1000 x 1000 (17 tiles) 192 / 23, 286 / 79, 287 / 138, 257 / 257.
 uint32_t split_events(int n_cu) { return (uint32_t)n_cu / 2u; }
+
+// Room for the mapped hits of the events in flight: 32 MiB, 5,440 hits for each of 768 workgroups
+// (the largest launch of 360 x 256), 8,192 for 512.  What is beyond is mapped again for every tile.
+constexpr size_t kMappedFloats = (size_t)8 << 20;
+uint32_t mapped_hits(int grid) { return (uint32_t)(kMappedFloats / 2 / (size_t)grid) & ~63u; }
 
 // Bound on u^2 + v^2 under which a hit's bin t = fma(u, C_j, fma(v, S_j, B)) lies strictly
 // inside (0, n_rho) for every column: |t - B| is at most A * sqrt(u^2 + v^2) plus the rounding
@@ -278,17 +284,18 @@ int hough_config(const hough_params *p, hough_ctx **out) {
     c->fused = fused_fits(p->n_rho, limit) ? 1 : ((p->flags & HOUGH_FLAG_THETA_PERIODIC) ? 3 : 2);
     if (c->fused == 1) c->split = hough::plan_split(p->n_rho, limit);
     // the fixed buffers in one block, each on a 256-byte boundary, those that start at zero first
-    const size_t sizes[7] = {
+    const size_t sizes[8] = {
         256 + 4 * (size_t)((p->n_theta + peak_waves - 1) / peak_waves),                          // d_work
         c->fused == 1 ? (size_t)split_events(c->n_cu) * hough::split_tiles(p->n_theta) * 4 : 0,  // d_slots
         tab.size() * sizeof(float),                                                              // d_tables
         c->iter1.gbm ? c->iter1.bm_bytes : 0,                                                    // d_iter_bm
         sizeof(uint64_t) * std::max(hough::kIterScanKeys, hough::kIterHeads),                    // d_iter_list
         sizeof(uint32_t) * hough::kOrderMaxEvents,                                               // d_order
-        c->fused == 1 ? sizeof(uint32_t) * hough::kOrderMaxEvents : 0};                          // d_defer
-    size_t at[8] = {0};
-    for (int i = 0; i < 7; ++i) at[i + 1] = (at[i] + sizes[i] + 255) & ~(size_t)255;
-    if (hipMalloc(&c->d_block, at[7]) != hipSuccess) {
+        c->fused == 1 ? sizeof(uint32_t) * hough::kOrderMaxEvents : 0,                           // d_defer
+        c->fused ? kMappedFloats * sizeof(float) : 0};                                           // d_uv
+    size_t at[9] = {0};
+    for (int i = 0; i < 8; ++i) at[i + 1] = (at[i] + sizes[i] + 255) & ~(size_t)255;
+    if (hipMalloc(&c->d_block, at[8]) != hipSuccess) {
         delete c;
         return HOUGH_ENOMEM;
     }
@@ -299,6 +306,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
     c->d_iter_list = reinterpret_cast<uint64_t *>(c->d_block + at[4]);
     c->d_order = reinterpret_cast<uint32_t *>(c->d_block + at[5]);
     c->d_defer = reinterpret_cast<uint32_t *>(c->d_block + at[6]);
+    c->d_uv = reinterpret_cast<float *>(c->d_block + at[7]);
     c->spill_stride = hough::spill_stride(p->n_theta, p->n_rho);
     c->spill_wgs = spill_workgroups(c->spill_stride, c->n_cu, c->fused != 1);
     // fewer slices where the device cannot spare the budget
@@ -564,6 +572,8 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
     long grid = (long)plan.per_cu * c->n_cu;
     if (grid > (long)n_events) grid = n_events;
     plan.grid = (int)grid;
+    a.uv = c->d_uv;
+    a.uv_hits = mapped_hits(plan.grid);
     hough::SplitArgs sp{};
     if (split) {
         if (!hough::split_layout(c->p.n_theta, c->p.n_rho, c->plan.groups, n_events, workspace, workspace_bytes,
@@ -600,6 +610,7 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
         rest.defer_list = nullptr;
         hough::BatchPlan whole = c->plan;
         whole.grid = (int)std::min<long>((long)whole.per_cu * c->n_cu, (long)n_events);
+        rest.uv_hits = mapped_hits(whole.grid);
         e = hough::launch_batch(c->g, whole, rest, (hipStream_t)stream);
     }
     // events above the fused kernel's hit limit or beyond its window (flagged and skipped there),

@@ -87,6 +87,8 @@ struct BatchArgs {
     uint32_t *queue;     // [2] work counter and exit counter (device, zero between launches)
     uint32_t frac_num;   // fused kernel: frac_den != 0 takes each event's threshold as
     uint32_t frac_den;   // max(threshold, ceil(event maximum * frac_num / frac_den))
+    float *uv;           // fused kernel: per workgroup 2 * uv_hits floats for the mapped hits of its
+    uint32_t uv_hits;    // event (null: none), see vote_range
     // a windowed launch followed by one on whole columns: the first lists the events that do not
     // fit its window (defer_list, their number in *defer_count, zero before it), the second takes
     // those (order = the list, n_from = the number); the spill kernel zeroes the number
