@@ -116,8 +116,9 @@ float safe_radius2(double A, double B, int n_rho) {
 // Default launch shape of the fused kernel: the candidate with the most resident waves per CU
 // (from the occupancy API, which accounts for LDS, VGPRs and SGPRs); ties go to the earlier
 // candidate.  8 waves split the 16-row peak units and the 32-row words of a 256-row tile evenly
-// and measured fastest wherever they tie with 6, 12 or 16; 12 waves win where the tile leaves
-// room for two workgroups per CU only (720 x 512: 24 resident waves instead of 16, 8% faster).
+// and measured fastest wherever they tie with 6, 12 or 16 (360 x 256: four workgroups, 32 waves);
+// 12 waves win where the tile leaves room for two workgroups per CU only (720 x 512: 24 resident
+// waves instead of 16, 11% faster).
 int default_plan(hough_ctx *c) {
     int best = -1;
     hough::BatchPlan pick{};

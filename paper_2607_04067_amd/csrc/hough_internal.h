@@ -48,6 +48,7 @@ struct BatchPlan {
     int out_cols;        // tile_cols - 2 output columns per tile
     int n_tiles;         // ceil(n_theta / out_cols)
     size_t lds_bytes;    // dynamic LDS per workgroup
+    size_t sp_lds_bytes; // the same with the peak list (sparse grids, relative launches)
     int per_cu;          // resident workgroups per CU (occupancy API)
     int grid;            // persistent workgroups
     int sparse;          // retention by peak list on tiles with few peaks (see kSparseRhoRows)
@@ -175,6 +176,7 @@ struct IterPlan {
     uint32_t keys;
     int gbm;
     size_t lds_bytes;    // dynamic LDS per workgroup
+    size_t sp_lds_bytes; // the same with the peak list (sparse grids, relative launches)
     size_t bm_bytes;     // bitmap bytes of one event (one bit per cell, whole 32-bit words)
 };
 // per_cu: workgroups per CU the plan should leave room for (the batch form runs one per event).
@@ -218,7 +220,7 @@ hipError_t launch_peaks_iterative(const GridArgs &g, const void *acc, int acc_ty
 // words, zero between calls; the context's).
 constexpr uint32_t kIterScanKeys = 65536;
 // LDS of the fused kernel's workgroup: the whole column (win 0) or a window of win rows.
-size_t batch_lds_bytes(int n_rho, int waves, int groups, int win = 0);
+size_t batch_lds_bytes(int n_rho, int waves, int groups, int win, bool sparse);
 int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, BatchPlan *out, int win = 0,
                bool need_split = true);
 int prepare_batch(BatchPlan *p);

@@ -27,6 +27,11 @@ namespace hough {
 namespace {
 
 constexpr int kStageBytes = kWave * (int)sizeof(float2);
+// Words of the space the waves' stages and a tile's peak words share.
+template <int NW>
+__host__ __device__ constexpr int stage_words(int peak_words) {
+    return NW * (kStageBytes / 4) > peak_words ? NW * (kStageBytes / 4) : peak_words;
+}
 
 // ------------------------------------------------------------------ per-hit arithmetic
 // Eq. (1).  Returns false for a hit whose r2 is zero, non-finite or overflowed.
@@ -65,6 +70,14 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 __device__ __forceinline__ int opaque(int v) {
     asm volatile("" : "+v"(v));
     return v;
+}
+
+// Zero the n 16-byte words at p, NT threads together (addresses and zeros are made here: see opaque).
+template <int NT>
+__device__ __forceinline__ void clear_quads(uint32_t *p, int n) {
+    const uint32_t z = (uint32_t)opaque(0);
+#pragma unroll 1
+    for (int i = opaque((int)threadIdx.x); i < n; i += NT) reinterpret_cast<uint4 *>(p)[i] = make_uint4(z, z, z, z);
 }
 
 // Element i of a wave-uniform array through a 32-bit byte offset (i below 2^30: events of at most
@@ -384,7 +397,8 @@ __device__ uint32_t vote_range(uint32_t *tile, const float *x, const float *y, u
         for (int q = 0; q < G; ++q) {
             const int j = first_col + 64 * q + lane;
             const bool voted = (j >= 0 && j < g.n_theta) || (PER && (j == -1 || j == g.n_theta));
-            if (voted) lds_add(cell_of<G, true, PER>(tile, (int)g.Bf, cl, ln, q), 0u - extra * ln.inc);
+            if (voted)
+                lds_add(cell_of<G, true, PER>(tile, __builtin_amdgcn_readfirstlane((int)g.Bf), cl, ln, q), 0u - extra * ln.inc);
         }
     }
     return n_valid;
@@ -755,7 +769,8 @@ __device__ __forceinline__ uint64_t lookup_lanes(const uint32_t *dil, float2 *st
     const uint32_t n = (uint32_t)__popcll(who), pos = mbcnt(who);
     const bool me = (who >> lane) & 1ull;
     if (me) st[pos] = make_float2(u, v);
-    if (lane < 3 && n + (uint32_t)lane < 64u) st[n + lane] = make_float2(0.0f, 0.0f);
+    const float z = __int_as_float(opaque(0));
+    if (lane < 3 && n + (uint32_t)lane < 64u) st[n + lane] = make_float2(z, z);
     wave_sync();
     const uint32_t n4 = (n + 3u) & ~3u;
     const uint64_t found = lookup_staged<G, kDilPitch<G>>(dil, st, StageCount{n4, n4}, cl, lane, g.nrho_f);
@@ -793,6 +808,7 @@ constexpr uint32_t kPendingCopy = 0x80000000u, kPendingSafe = 0x40000000u, kPend
 // across lanes that is a permutation of all 64 (the other lanes' values are dropped).
 __device__ __forceinline__ void push_pending(Pending &pd, uint32_t n, uint64_t who, uint32_t idx, float u, float v,
                                              int lane) {
+    lane = opaque(lane);
     const uint32_t c = (uint32_t)__popcll(who);
     const uint32_t to = ((who >> lane) & 1ull) ? n + mbcnt(who) : n + c + mbcnt(~who);
     const int at = (int)((to & 63u) << 2);
@@ -2248,9 +2264,12 @@ struct PhaseClock {
 // which is what the window is for: on the paper's grid (rho range twice the reach of hits at
 // 200 mm and beyond) half of the 1000 rows are enough.
 // Launch bounds: a windowed tile exists to fit two or three workgroups of at most 8 waves on a
-// CU, so 4 waves per SIMD are enough for it and leave it registers to spare.
+// CU, so 4 waves per SIMD are enough for it and leave it registers to spare.  The 8-wave kernel of
+// dense grids fits 64 registers, so that four workgroups of a 360 x 256 tile (39.6 KB of LDS)
+// share a CU: 32 waves hide the phases' latencies better than 24 (10,000 events 1,559 -> 1,470 us;
+// 1,000 events, which then all run at once, 159 -> 166 us).  The others keep 80.
 template <int NW, int G, bool PER, bool SP, bool WIN>
-__global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) void k_batch(GridArgs g, BatchArgs a,
+__global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? (NW == 8 && !SP ? 8 : 6) : 4)) void k_batch(GridArgs g, BatchArgs a,
                                                                                             int n_tiles, int nwords,
                                                                                             int win) {
     using L = Lane<G, true>;
@@ -2261,10 +2280,12 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
     const int rows_t = WIN ? win + 3 : g.n_rho + 1;
     const int nwp = WIN ? win / 32 + 1 : nwords;
     uint32_t *tile = lds;                                                  // [rows_t * ST]
+    // the lookups' stage takes the peak words' place, which are dead once listed (not in a windowed
+    // tile, whose size sets the window's height)
     float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)rows_t * ST);   // [NW * 64]
-    uint32_t *pmask = reinterpret_cast<uint32_t *>(stage + NW * 64);       // [nwp * TW]
-    float4 *tpk = reinterpret_cast<float4 *>(pmask + (size_t)nwp * TW);    // [kTilePeaks]
-    uint32_t *colcnt = reinterpret_cast<uint32_t *>(tpk + kTilePeaks);     // [TW] peaks per column
+    uint32_t *pmask = reinterpret_cast<uint32_t *>(stage) + (WIN ? NW * (kStageBytes / 4) : 0);   // [nwp * TW]
+    float4 *tpk = reinterpret_cast<float4 *>(pmask + (WIN ? nwp * TW : stage_words<NW>(nwp * TW)));   // [kTilePeaks] (SP)
+    uint32_t *colcnt = reinterpret_cast<uint32_t *>(tpk + (SP ? kTilePeaks : 0));   // [TW] peaks per column
     uint32_t *dil = colcnt + TW;                                           // [(nwp + 1) * DP]
     __shared__ uint32_t s_event, s_npeaks, s_flags, s_nvalid, s_nkept, s_max, s_minr2, s_wb, s_fit, s_edge;
     const int lane = threadIdx.x & 63, wave = wave_id();
@@ -2319,7 +2340,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
         const uint32_t H = h1 - h0;
         if (H > kMaxBatchHits || H == 0u) {      // above the 16-bit counters: the spill kernel's
             uint8_t *ke = a.keep + (a.ids ? a.keep_offsets[e] : h0);
-            for (uint32_t i = threadIdx.x; i < H; i += NT) ke[i] = 0u;
+            for (uint32_t i = (uint32_t)opaque((int)threadIdx.x); i < H; i += NT) ke[i] = 0u;
             if (threadIdx.x == 0) {
                 a.n_peaks[e] = 0u;
                 a.status[e] = H ? kStatusSpill : 0u;
@@ -2340,7 +2361,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
         // with duplicate suppression the duplicate pass has written every keep byte already
         if (!g.dedup) {
 #pragma unroll 1
-            for (uint32_t i = hb + lane; i < he; i += 64) ke[i] = 0u;
+            for (uint32_t i = hb + (uint32_t)opaque(lane); i < he; i += 64) ke[i] = 0u;
         } else if (H > kDedupMaxHits && threadIdx.x == 0) {
             atomicOr(&s_flags, HOUGH_EV_DEDUP_SKIPPED);
         }
@@ -2450,13 +2471,13 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
             if (SP && tt < 0) {
                 // every tile row but the dummy one (a window's halo rows stay zero)
 #pragma unroll 1
-                for (int i = threadIdx.x; i < (rows_t - 1) * ST / 4; i += NT) {
+                for (int i = opaque((int)threadIdx.x); i < (rows_t - 1) * ST / 4; i += NT) {
                     const uint4 d = reinterpret_cast<const uint4 *>(tile)[i];
                     mloc = max(mloc, max(max(max(d.x & 0xffffu, d.x >> 16), max(d.y & 0xffffu, d.y >> 16)),
                                          max(max(d.z & 0xffffu, d.z >> 16), max(d.w & 0xffffu, d.w >> 16))));
                     reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
                 }
-                for (int i = (rows_t - 1) * ST + threadIdx.x; i < rows_t * ST; i += NT) tile[i] = 0u;
+                for (int i = (rows_t - 1) * ST + opaque((int)threadIdx.x); i < rows_t * ST; i += NT) tile[i] = 0u;
                 if (tt == -1) {
                     mloc = wave_max(mloc);
                     if (lane == 0) atomicMax(&s_max, mloc);
@@ -2507,7 +2528,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
             }
             if (g.rho_window >= 32) {
 #pragma unroll 1
-                for (int i = threadIdx.x; i < nwp * DP; i += NT) dil[i] = 0u;
+                for (int i = opaque((int)threadIdx.x); i < nwp * DP; i += NT) dil[i] = 0u;
             }
             if (SP && threadIdx.x == 0) s_edge = 0u;     // set by the listing for a peak near a rho edge
             __syncthreads();
@@ -2524,11 +2545,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
             __syncthreads();
             pc.mark(kPhaseList);
             if (threadIdx.x == 0) s_npeaks = base + np;
-            for (int i = threadIdx.x; i < TW; i += NT) colcnt[i] = 0u;
+            for (int i = opaque((int)threadIdx.x); i < TW; i += NT) colcnt[i] = 0u;
             // the counts are dead: clear the tile for the next one while retention reads dil
-#pragma unroll 1
-            for (int i = threadIdx.x; i < tile_words4; i += NT)
-                reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
+            clear_quads<NT>(tile, tile_words4);
             if (DEF && np && s_nkept < s_nvalid && pe && np <= kDeferTilePeaks && base + np <= cap &&
                 defn + np <= kDeferPeaks) {
                 if (defn == 0) def0 = base;          // the deferred peaks stay contiguous
@@ -2578,7 +2597,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? 6 : 4)) 
         if (__ballot(bad != 0u) && lane == 0) atomicOr(&s_flags, HOUGH_EV_INVALID_HITS);
         if (g.dedup) {                       // drop the later-copy bit, leaving the kept bit
 #pragma unroll 1
-            for (uint32_t i = hb + lane; i < he; i += 64) {
+            for (uint32_t i = hb + (uint32_t)opaque(lane); i < he; i += 64) {
                 const uint32_t v = ke[i];
                 if (v & kKeepDuplicate) ke[i] = (uint8_t)(v & 1u);
             }
@@ -2675,8 +2694,8 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridA
     extern __shared__ __align__(16) uint32_t lds[];
     uint32_t *tile = lds;                                                  // [(n_rho + 1) * ST]
     float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)(g.n_rho + 1) * ST);   // [NW * 64]
-    uint32_t *pmask = reinterpret_cast<uint32_t *>(stage + NW * 64);       // [nwords * TW]
-    float4 *tpk = reinterpret_cast<float4 *>(pmask + (size_t)nwords * TW);   // [kTilePeaks]
+    uint32_t *pmask = reinterpret_cast<uint32_t *>(stage);                 // [nwords * TW], dead once listed
+    float4 *tpk = reinterpret_cast<float4 *>(pmask + stage_words<NW>(nwords * TW));   // [kTilePeaks]
     uint32_t *colcnt = reinterpret_cast<uint32_t *>(tpk + kTilePeaks);     // [TW]
     uint32_t *dil = colcnt + TW;                                           // [(nwords + 1) * DP]
     __shared__ uint32_t s_item, s_bad, s_base, s_edge;
@@ -3372,12 +3391,13 @@ int peak_block_waves(int n_theta, int n_rho, size_t lds_limit) {
 // The fused kernel's dynamic LDS: the packed tile with its dummy row (a windowed tile: `win`
 // rows, a zero halo row on each side and the dummy row), the wave stages, the peak and dilated
 // words, the tile's peak list and the per-column peak counts.
-size_t batch_lds_bytes(int n_rho, int waves, int groups, int win) {
+size_t batch_lds_bytes(int n_rho, int waves, int groups, int win, bool sparse) {
     const size_t tw = 64u * groups;
     const size_t rows = win ? (size_t)win + 3 : (size_t)n_rho + 1;
     const size_t nwords = win ? (size_t)win / 32 + 1 : (size_t)(n_rho + 31) / 32;
-    return rows * (tw / 2) * 4 + (size_t)waves * kStageBytes + nwords * tw * 4 + (nwords + 1) * (tw + 1) * 4 +
-           kTilePeaks * sizeof(float4) + tw * 4;
+    const size_t stages = (size_t)waves * kStageBytes, peak_words = nwords * tw * 4;
+    return rows * (tw / 2) * 4 + (win ? stages + peak_words : std::max(stages, peak_words)) + (nwords + 1) * (tw + 1) * 4 +
+           (sparse ? kTilePeaks * sizeof(float4) : 0) + tw * 4;
 }
 
 int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, BatchPlan *out, int win,
@@ -3392,12 +3412,13 @@ int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, 
     p.out_cols = p.tile_cols - 2;
     p.n_tiles = (n_theta + p.out_cols - 1) / p.out_cols;
     p.win = win;
-    p.lds_bytes = batch_lds_bytes(n_rho, waves, groups, win);
-    p.split_lds_bytes = batch_lds_bytes(n_rho, waves, groups, 0);
     p.sparse = n_rho >= kSparseRhoRows ? 1 : 0;
+    p.lds_bytes = batch_lds_bytes(n_rho, waves, groups, win, p.sparse != 0);
+    p.sp_lds_bytes = batch_lds_bytes(n_rho, waves, groups, win, true);
+    p.split_lds_bytes = batch_lds_bytes(n_rho, waves, groups, 0, true);
     // room for the kernel's static LDS; the split form always holds the whole column (grids
     // taller than that run their split calls through the spill kernel: need_split false)
-    if (p.lds_bytes + 256 > lds_limit || (need_split && p.split_lds_bytes + 256 > lds_limit)) return -1;
+    if (p.sp_lds_bytes + 256 > lds_limit || (need_split && p.split_lds_bytes + 256 > lds_limit)) return -1;
     p.grid = 0;
     *out = p;
     return 0;
@@ -3663,24 +3684,25 @@ constexpr bool window_periodic(int waves) { return waves == 8 || waves == 16; }
 template <int NW, int G, bool SP>
 static void launch_batch_sp(const GridArgs &g, const BatchPlan &p, const BatchArgs &a, hipStream_t s) {
     const int nwords = (g.n_rho + 31) / 32;
+    const size_t lds = SP ? p.sp_lds_bytes : p.lds_bytes;
     if constexpr (G == 1) {
         if (p.win) {
             if constexpr (window_periodic(NW))
                 if (g.periodic) {
-                    hipLaunchKernelGGL((k_batch<NW, G, true, SP, true>), dim3(p.grid), dim3(NW * 64), p.lds_bytes, s, g,
+                    hipLaunchKernelGGL((k_batch<NW, G, true, SP, true>), dim3(p.grid), dim3(NW * 64), lds, s, g,
                                        a, p.n_tiles, nwords, p.win);
                     return;
                 }
-            hipLaunchKernelGGL((k_batch<NW, G, false, SP, true>), dim3(p.grid), dim3(NW * 64), p.lds_bytes, s, g, a,
+            hipLaunchKernelGGL((k_batch<NW, G, false, SP, true>), dim3(p.grid), dim3(NW * 64), lds, s, g, a,
                                p.n_tiles, nwords, p.win);
             return;
         }
     }
     if (g.periodic)
-        hipLaunchKernelGGL((k_batch<NW, G, true, SP, false>), dim3(p.grid), dim3(NW * 64), p.lds_bytes, s, g, a,
+        hipLaunchKernelGGL((k_batch<NW, G, true, SP, false>), dim3(p.grid), dim3(NW * 64), lds, s, g, a,
                            p.n_tiles, nwords, 0);
     else
-        hipLaunchKernelGGL((k_batch<NW, G, false, SP, false>), dim3(p.grid), dim3(NW * 64), p.lds_bytes, s, g, a,
+        hipLaunchKernelGGL((k_batch<NW, G, false, SP, false>), dim3(p.grid), dim3(NW * 64), lds, s, g, a,
                            p.n_tiles, nwords, 0);
 }
 
@@ -3716,7 +3738,7 @@ template <int NW>
 static hipError_t launch_split_t(const GridArgs &g, const BatchArgs &a, const SplitArgs &sp, uint32_t items,
                                  hipStream_t s) {
     const int nwords = (g.n_rho + 31) / 32;
-    const size_t lds = batch_lds_bytes(g.n_rho, NW, 1, 0);
+    const size_t lds = batch_lds_bytes(g.n_rho, NW, 1, 0, true);
     // one workgroup per item; a launch holds at most 2^31 threads, and the item counter runs on
     // from launch to launch
     for (uint32_t left = items; left > 0;) {
@@ -3748,7 +3770,7 @@ hipError_t launch_batch_split(const GridArgs &g, const SplitPlan &p, const Batch
 
 template <int NW>
 static bool split_fits(int n_rho, size_t lds_limit) {
-    if (batch_lds_bytes(n_rho, NW, 1, 0) + 256 > lds_limit) return false;
+    if (batch_lds_bytes(n_rho, NW, 1, 0, true) + 256 > lds_limit) return false;
     allow_lds(k_batch_split<NW, false>);
     allow_lds(k_batch_split<NW, true>);
     return true;
@@ -3759,12 +3781,12 @@ SplitPlan plan_split(int n_rho, size_t lds_limit) {
     if (split_fits<4>(n_rho, lds_limit)) p.wide = p.narrow = 4;
     if (split_fits<8>(n_rho, lds_limit)) p.wide = p.narrow = 8;
     // two workgroups per CU but not three: 12 waves each
-    if (3 * batch_lds_bytes(n_rho, 8, 1, 0) > lds_limit && 2 * (batch_lds_bytes(n_rho, 12, 1, 0) + 256) <= lds_limit &&
+    if (3 * batch_lds_bytes(n_rho, 8, 1, 0, true) > lds_limit && 2 * (batch_lds_bytes(n_rho, 12, 1, 0, true) + 256) <= lds_limit &&
         split_fits<12>(n_rho, lds_limit))
         p.narrow = 12;
     if (split_fits<16>(n_rho, lds_limit)) {
         p.wide = 16;
-        if (2 * batch_lds_bytes(n_rho, 8, 1, 0) > lds_limit) p.narrow = 16;   // one per CU either way
+        if (2 * batch_lds_bytes(n_rho, 8, 1, 0, true) > lds_limit) p.narrow = 16;   // one per CU either way
     }
     return p;
 }
@@ -3816,36 +3838,36 @@ static int occupancy(K kernel, int threads, size_t lds) {
 
 template <int NW, int G>
 static int prepare_t(BatchPlan *p) {
-    // both grid topologies: a context's plan serves whichever kernel it launches
+    // both grid topologies: a context's plan serves whichever kernel it launches.  The workgroups per
+    // CU are those of the kernels its plain launches run; a relative launch on a grid that is
+    // not sparse needs the peak list's LDS as well and may hold fewer at a time.
     allow_lds(k_batch<NW, G, false, false, false>);
     allow_lds(k_batch<NW, G, true, false, false>);
     allow_lds(k_batch<NW, G, false, true, false>);
     allow_lds(k_batch<NW, G, true, true, false>);
     const int T = NW * 64;
-    const size_t full = p->lds_bytes;
-    int fused = 0;
     if constexpr (G == 1) {
         if (p->win && p->periodic) {
             if constexpr (window_periodic(NW)) {
                 allow_lds(k_batch<NW, 1, true, false, true>);
                 allow_lds(k_batch<NW, 1, true, true, true>);
-                fused = std::min(occupancy(k_batch<NW, 1, true, false, true>, T, p->lds_bytes),
-                                 occupancy(k_batch<NW, 1, true, true, true>, T, p->lds_bytes));
+                return p->sparse ? occupancy(k_batch<NW, 1, true, true, true>, T, p->lds_bytes)
+                                 : occupancy(k_batch<NW, 1, true, false, true>, T, p->lds_bytes);
             }
-        } else if (p->win) {
+            return 0;
+        }
+        if (p->win) {
             allow_lds(k_batch<NW, 1, false, false, true>);
             allow_lds(k_batch<NW, 1, false, true, true>);
-            fused = std::min(occupancy(k_batch<NW, 1, false, false, true>, T, p->lds_bytes),
-                             occupancy(k_batch<NW, 1, false, true, true>, T, p->lds_bytes));
+            return p->sparse ? occupancy(k_batch<NW, 1, false, true, true>, T, p->lds_bytes)
+                             : occupancy(k_batch<NW, 1, false, false, true>, T, p->lds_bytes);
         }
     }
-    if (!p->win) {
-        fused = std::min(occupancy(k_batch<NW, G, false, false, false>, T, full),
-                         occupancy(k_batch<NW, G, true, false, false>, T, full));
-        fused = std::min(fused, std::min(occupancy(k_batch<NW, G, false, true, false>, T, full),
-                                         occupancy(k_batch<NW, G, true, true, false>, T, full)));
-    }
-    return fused;
+    if (p->sparse)
+        return std::min(occupancy(k_batch<NW, G, false, true, false>, T, p->lds_bytes),
+                        occupancy(k_batch<NW, G, true, true, false>, T, p->lds_bytes));
+    return std::min(occupancy(k_batch<NW, G, false, false, false>, T, p->lds_bytes),
+                    occupancy(k_batch<NW, G, true, false, false>, T, p->lds_bytes));
 }
 
 // Allow the plan's dynamic LDS for its kernels and return how many of the fused kernel's
