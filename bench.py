@@ -39,8 +39,8 @@ MAX_PEAKS = {"plain-16ev-180x128": 1024, "paper-1000ev-360x256": 8192,
 # MI355X: 256 CUs, 4 SIMD16 units each, 2.4 GHz peak engine clock.
 N_CU, LANES_PER_CU_CLK, CLOCK_HZ = 256, 64, 2.4e9
 VALU_LANE_OPS_PER_S = N_CU * LANES_PER_CU_CLK * CLOCK_HZ          # 39.3 T 32-bit lane-ops/s
-OPS_PER_VOTE = 4      # 2 FMA (rho), 1 float->int (bin), 1 index (cell address); the +1 is on the LDS
-VOTE_PEAK_PER_S = VALU_LANE_OPS_PER_S / OPS_PER_VOTE              # 9.83 T votes/s
+OPS_PER_VOTE = 2      # 1 float->int (bin), 1 index (cell address); the bin's FMAs are on the matrix cores, the +1 on the LDS
+VOTE_PEAK_PER_S = VALU_LANE_OPS_PER_S / OPS_PER_VOTE              # 19.7 T votes/s
 HBM_PEAK_GBS = 8000.0
 FP32_PEAK_TFLOPS = 157.3   # MI355X published vector fp32 peak
 FLOPS_PER_VOTE = 4         # the two fmas of the bin, 2 flops each

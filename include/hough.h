@@ -313,8 +313,8 @@ typedef struct hough_batch_plan {
  * grid whose whole rho column does not fit the fused kernel's tile gets a windowed tile (theta
  * not periodic; window_rows > 0): each event whose hits reach only that many rows runs in the
  * fused kernel, the others, and every event of the split forms, through the spill path.  All
- * zero when there is no fused kernel for the grid (a periodic grid taller than the tile: every
- * event spills). */
+ * zero on a theta-periodic grid taller than the tile (its windows are the library's own, not the
+ * caller's to see or set). */
 int hough_get_batch_plan(const hough_ctx *ctx, hough_batch_plan *out);
 
 /* Select a launch shape (for autotuning).  groups_per_cu = 0 launches as many workgroups per CU

@@ -94,8 +94,8 @@ int spill_workgroups(size_t stride_words, int n_cu, bool all) {
 // 1000 x 1000 (17 tiles) 192 / 23, 286 / 79, 287 / 138, 257 / 257.
 uint32_t split_events(int n_cu) { return (uint32_t)n_cu / 2u; }
 
-// Room for the mapped hits of the events in flight: 32 MiB, 5,440 hits for each of 768 workgroups
-// (the largest launch of 360 x 256), 8,192 for 512.  What is beyond is mapped again for every tile.
+// Room for the mapped hits of the events in flight: 32 MiB, 4,096 hits for each of 1,024 workgroups
+// (four per CU, as 360 x 256 takes), 8,192 for 512.  What is beyond is mapped again for every tile.
 constexpr size_t kMappedFloats = (size_t)8 << 20;
 uint32_t mapped_hits(int grid) { return (uint32_t)(kMappedFloats / 2 / (size_t)grid) & ~63u; }
 
@@ -192,8 +192,9 @@ int default_windowed_plan(hough_ctx *c) {
 // overlaps one event's voting with the other's peaks and retention, and peaks, clears and retention
 // cover half of the rows (1,000 events on 1000 x 1000, hits reaching 500 rows: 691 -> 476 us).
 // Events that reach more rows run on whole columns in a second launch, which returns at once
-// when there are none (5 us); a batch of such events alone pays one more pass over its hits (about
-// 1.5%).
+// when there are none (5 us); a batch of such events alone pays one more pass over its hits (38 us
+// for 1,000 of them: 1000 x 650 bins, every hit in reach of every row, 703 us on whole columns alone and
+// 750 so; 1000 x 1000, 532 and 574).
 void auto_window(hough_ctx *c) {
     c->window.win = 0;
     if (c->fused != 1 || c->plan.per_cu != 1) return;

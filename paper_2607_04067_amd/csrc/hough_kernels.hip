@@ -2807,10 +2807,9 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridA
 }
 
 // ------------------------------------------------------------ spill path (rho slabs)
-// Events whose accumulator the fused kernel cannot hold on chip: every event of a theta-periodic
-// grid whose rho column is taller than the fused kernel's LDS tile, events whose hits reach
-// beyond a windowed tile, every event of the split forms on such grids, and events above
-// kMaxBatchHits hits on any grid (counts beyond 16 bits).  One workgroup processes one event at
+// Events whose accumulator the fused kernel cannot hold on chip: events whose hits reach beyond a
+// windowed tile, every event of the caller's split forms on grids taller than a tile, and events
+// above kMaxBatchHits hits on any grid (counts beyond 16 bits).  One workgroup processes one event at
 // a time:
 //   - steps 1-4 one slab at a time in LDS (62 owned columns with halo lanes by up to 1,120 owned
 //     rows with halo rows; 32-bit counts and 544 rows for events above 65,535 hits): vote, then
