@@ -312,7 +312,7 @@ typedef struct hough_batch_plan {
 /* The launch shape hough_run_batch currently uses (the library picks one at hough_config).  A
  * grid whose whole rho column does not fit the fused kernel's tile gets a windowed tile (theta
  * not periodic; window_rows > 0): each event whose hits reach only that many rows runs in the
- * fused kernel, the others, and every event of the split forms, through the spill path.  All
+ * fused kernel, the others, and every event of the caller's split forms, through the spill path.  All
  * zero on a theta-periodic grid taller than the tile (its windows are the library's own, not the
  * caller's to see or set). */
 int hough_get_batch_plan(const hough_ctx *ctx, hough_batch_plan *out);

@@ -31,8 +31,8 @@ struct hough_ctx {
     int chosen;             // the caller has set a launch shape
     uint32_t *d_defer;      // [kOrderMaxEvents] the events that did not fit its window
     float *d_uv;            // [kMappedFloats] the fused kernel's mapped hits, shared out by launch
-    hough::SplitPlan split; // the split form's (fused == 1)
-    uint32_t *d_slots;      // its slots for batches of up to split_events(n_cu) events (fused == 1)
+    hough::SplitPlan split; // the split form's (whole columns, or windows on taller grids)
+    uint32_t *d_slots;      // its slots for batches of up to split_events(n_cu) events
     int fused;              // 1: the fused kernel holds the grid's whole column (and windows of it);
                             // 2: only windows of it (taller grids; the split form spills every
                             // event); 3: the same, theta periodic (the shape is not the caller's to
@@ -91,7 +91,12 @@ int spill_workgroups(size_t stride_words, int n_cu, bool all) {
 // split form's grows with it.  Measured, us per batch fused / split at 1, 64, 128 and 256 events on
 // 256 CUs: 180 x 128 (3 tiles) 23 / 14, 25 / 17, 26 / 21, 29 / 28; 360 x 256 (6 tiles) 73 / 21,
 // 80 / 37, 81 / 49, 84 / 82; 720 x 512 dense (12 tiles) 234 / 40, 241 / 120, 249 / 186, 255 / 348;
-// 1000 x 1000 (17 tiles) 192 / 23, 286 / 79, 287 / 138, 257 / 257.
+// 1000 x 1000 (17 tiles) 192 / 23, 286 / 79, 287 / 138, 257 / 257.  The same line holds where only
+// windows of the column fit (one 16-wave workgroup per CU either way): 1000 x 2000 at 1, 16, 64 and
+// 128 events 183 / 25, 186 / 36, 208 / 83, 208 / 146, periodic 190 / 25, 193 / 37, 214 / 84,
+// 214 / 149; 300 x 1200 110 / 25, 112 / 30, 115 / 52, 119 / 74.  There events beyond the window go
+// to the spill kernel, which reads the duplicate marks the split form would drop: batches with
+// duplicate suppression stay with the fused kernel.
 uint32_t split_events(int n_cu) { return (uint32_t)n_cu / 2u; }
 
 // Room for the mapped hits of the events in flight: 32 MiB, 4,096 hits for each of 1,024 workgroups
@@ -288,7 +293,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
     // the fixed buffers in one block, each on a 256-byte boundary, those that start at zero first
     const size_t sizes[8] = {
         256 + 4 * (size_t)((p->n_theta + peak_waves - 1) / peak_waves),                          // d_work
-        c->fused == 1 ? (size_t)split_events(c->n_cu) * hough::split_tiles(p->n_theta) * 4 : 0,  // d_slots
+        (size_t)split_events(c->n_cu) * hough::split_tiles(p->n_theta) * 4,                      // d_slots
         tab.size() * sizeof(float),                                                              // d_tables
         c->iter1.gbm ? c->iter1.bm_bytes : 0,                                                    // d_iter_bm
         sizeof(uint64_t) * std::max(hough::kIterScanKeys, hough::kIterHeads),                    // d_iter_list
@@ -355,6 +360,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         rc = HOUGH_OK;
     }
     if (rc == HOUGH_OK) auto_window(c);
+    if (rc == HOUGH_OK && c->fused >= 2) c->split = hough::plan_split_window(c->plan.win, limit);
     if (rc != HOUGH_OK) {
         hough_destroy(c);
         return rc;
@@ -582,7 +588,7 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
                                  &sp))
             return HOUGH_EINVAL;
         if ((long)n_events * sp.n_tiles >= (1L << 31)) return HOUGH_EINVAL;   // the work queue counts in 32 bits
-    } else if (c->fused == 1 && frac_den == 0 && n_events <= split_events(c->n_cu)) {
+    } else if ((c->fused == 1 || (c->split.win && !c->g.dedup)) && frac_den == 0 && n_events <= split_events(c->n_cu)) {
         split = true;
         sp.n_tiles = hough::split_tiles(c->p.n_theta);
         sp.slots = c->d_slots;

@@ -58,9 +58,10 @@ struct BatchPlan {
                               // grid has a split form)
 };
 // Waves per workgroup of the split form: for batches of at most one (event, tile) item per CU, and
-// for larger ones (0: the whole column does not fit).
+// for larger ones (0: the whole column does not fit).  win: rows of its windows where only windows
+// of the column fit (16 waves; 0: none).
 struct SplitPlan {
-    int wide, narrow;
+    int wide, narrow, win;
 };
 // Status bit of an event the fused (or split) kernel leaves to the spill kernel launched after
 // it: more than kMaxBatchHits hits, or hits that reach beyond the rows of a windowed tile.  The
@@ -108,6 +109,7 @@ struct SplitArgs {
 };
 uint32_t split_tiles(int n_theta);
 SplitPlan plan_split(int n_rho, size_t lds_limit);
+SplitPlan plan_split_window(int win, size_t lds_limit);
 // Keep words per event in the split form's workspace size.
 constexpr uint32_t kSplitKeepWords = (kMaxBatchHits + 31) / 32 + 1;
 size_t split_workspace_bytes(int n_theta, int n_rho, int groups, uint32_t n_events);

@@ -426,6 +426,21 @@ __device__ __forceinline__ void reached_rows(const GridArgs &g, float min_r2, in
     khi = hi <= 0.0 ? 0 : (hi >= top ? g.n_rho - 1 : (int)hi);
 }
 
+// The window of `win` rows that starts at the first reached row (down to a multiple of 16): whether
+// it holds every row the event reaches, those of the wrapped halo columns (reversed) included.
+template <bool PER>
+__device__ __forceinline__ bool window_of(const GridArgs &g, float min_r2, int win, int &b0) {
+    int klo, khi;
+    reached_rows(g, min_r2, klo, khi);
+    if (PER) {
+        const int lo_r = g.n_rho - 1 - khi, hi_r = g.n_rho - 1 - klo;
+        klo = min(klo, lo_r);
+        khi = max(khi, hi_r);
+    }
+    b0 = (klo / 16) * 16;
+    return khi < b0 + win;
+}
+
 // The smallest valid r2 of the wave's hits, as the bits of a float (positive floats order as
 // their bits), in every lane.
 __device__ __forceinline__ uint32_t wave_min(uint32_t v);
@@ -2372,16 +2387,9 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? (NW == 8
             if (lane == 0) atomicMin(&s_minr2, mn);
             __syncthreads();
             if (threadIdx.x == 0) {
-                int klo, khi;
-                reached_rows(g, __uint_as_float(s_minr2), klo, khi);
-                if (PER) {                       // the wrapped halo columns vote the reversed rows too
-                    const int lo_r = g.n_rho - 1 - khi, hi_r = g.n_rho - 1 - klo;
-                    klo = min(klo, lo_r);
-                    khi = max(khi, hi_r);
-                }
-                const int b0 = (klo / 16) * 16;
+                int b0;
+                s_fit = window_of<PER>(g, __uint_as_float(s_minr2), win, b0) ? 1u : 0u;
                 s_wb = (uint32_t)b0;
-                s_fit = khi < b0 + win ? 1u : 0u;
             }
             __syncthreads();
             wb = __builtin_amdgcn_readfirstlane((int)s_wb);
@@ -2632,6 +2640,10 @@ __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? (NW == 8
 // set theirs after they have seen its slot.  No cache is written back or invalidated on the way
 // (publishing with fences and merging staged lists took 11 of one event's 30 us; it takes 16
 // so).  The spill kernel launched afterwards puts the slots and the counter back to zero.
+// WIN: the tile holds the event's window of rows, as in k_batch (grids taller than a tile).  Each
+// tile finds the window itself from all of the event's hits, so all of them agree on it, and on
+// leaving an event that does not fit it to the spill kernel (1000 x 2000, one event: 183 us when
+// one workgroup walked its 17 tiles, 25 so).
 constexpr uint32_t kSlotReady = 0x80000000u;
 
 __device__ __forceinline__ uint32_t keep_load(const uint8_t *p) {
@@ -2686,31 +2698,33 @@ __device__ void retain_split(const uint32_t *dil, const float4 *tpk, uint32_t np
     }
 }
 
-template <int NW, bool PER>
+template <int NW, bool PER, bool WIN>
 __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridArgs g, BatchArgs a, SplitArgs sp,
-                                                                           int nwords) {
+                                                                           int nwords, int win) {
     using L = Lane<1, true>;
     constexpr int TW = L::TW, ST = L::STRIDE, DP = (int)kDilPitch<1>, OUT = TW - 2, NT = NW * 64;
     extern __shared__ __align__(16) uint32_t lds[];
-    uint32_t *tile = lds;                                                  // [(n_rho + 1) * ST]
-    float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)(g.n_rho + 1) * ST);   // [NW * 64]
-    uint32_t *pmask = reinterpret_cast<uint32_t *>(stage);                 // [nwords * TW], dead once listed
-    float4 *tpk = reinterpret_cast<float4 *>(pmask + stage_words<NW>(nwords * TW));   // [kTilePeaks]
+    const int rows_t = WIN ? win + 3 : g.n_rho + 1, nwp = WIN ? win / 32 + 1 : nwords;
+    uint32_t *tile = lds;                                                  // [rows_t * ST]
+    float2 *stage = reinterpret_cast<float2 *>(tile + (size_t)rows_t * ST);   // [NW * 64]
+    uint32_t *pmask = reinterpret_cast<uint32_t *>(stage);                 // [nwp * TW], dead once listed
+    float4 *tpk = reinterpret_cast<float4 *>(pmask + stage_words<NW>(nwp * TW));   // [kTilePeaks]
     uint32_t *colcnt = reinterpret_cast<uint32_t *>(tpk + kTilePeaks);     // [TW]
-    uint32_t *dil = colcnt + TW;                                           // [(nwords + 1) * DP]
-    __shared__ uint32_t s_item, s_bad, s_base, s_edge;
+    uint32_t *dil = colcnt + TW;                                           // [(nwp + 1) * DP]
+    __shared__ uint32_t s_item, s_bad, s_base, s_edge, s_minr2, s_wb, s_fit;
     const int lane = threadIdx.x & 63, wave = wave_id();
     if (threadIdx.x == 0) {
         s_item = atomicAdd(a.queue, 1u);
         s_bad = 0u;
         s_edge = 0u;
+        s_minr2 = __float_as_uint(FLT_MAX);
     }
-    for (int i = threadIdx.x; i < (g.n_rho + 1) * ST / 4; i += NT)
+    for (int i = threadIdx.x; i < rows_t * ST / 4; i += NT)
         reinterpret_cast<uint4 *>(tile)[i] = make_uint4(0u, 0u, 0u, 0u);
-    for (int i = threadIdx.x; i < DP; i += NT) dil[nwords * DP + i] = 0u;
+    for (int i = threadIdx.x; i < DP; i += NT) dil[nwp * DP + i] = 0u;
     for (int i = threadIdx.x; i < TW; i += NT) colcnt[i] = 0u;
     if (g.rho_window >= 32)
-        for (int i = threadIdx.x; i < nwords * DP; i += NT) dil[i] = 0u;
+        for (int i = threadIdx.x; i < nwp * DP; i += NT) dil[i] = 0u;
     __syncthreads();
     const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_item), T = sp.n_tiles;
     if (item >= a.n_events * T) return;                    // (the grid holds one workgroup per item)
@@ -2738,30 +2752,60 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridA
     wave_hits<NW>(H, wave, hb, he);
     if (t == 0 && !g.dedup)                                // (the duplicate pass has written every keep byte)
         for (uint32_t i = threadIdx.x; i < H; i += NT) keep_store(ke + i, 0u);
+    // the event's rho window, the same in every tile of it (see k_batch)
+    int wb = 0;
+    if constexpr (WIN) {
+        const uint32_t mn = min_r2_bits(xe, ye, hb, he, lane);
+        if (lane == 0) atomicMin(&s_minr2, mn);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int b0;
+            s_fit = window_of<PER>(g, __uint_as_float(s_minr2), win, b0) ? 1u : 0u;
+            s_wb = (uint32_t)b0;
+        }
+        __syncthreads();
+        wb = __builtin_amdgcn_readfirstlane((int)s_wb);
+        if (__builtin_amdgcn_readfirstlane((int)s_fit) == 0) {   // the spill kernel's, in every tile
+            if (threadIdx.x == 0 && t == 0) {
+                a.n_peaks[e] = 0u;
+                a.status[e] = kStatusSpill;
+                if (a.spill_count) atomicAdd(a.spill_count, 1u);
+            }
+            return;
+        }
+    }
+    uint32_t *tile_w = WIN ? tile + (ptrdiff_t)(1 - wb) * ST : tile;
+    uint32_t *pmask_w = WIN ? pmask - (ptrdiff_t)(wb >> 5) * TW : pmask;
+    uint32_t *dil_w = WIN ? dil - (ptrdiff_t)(wb >> 5) * DP : dil;
+    const int w_lo = WIN ? (wb >> 5) : 0;
+    const float dummy_row = WIN ? (float)(wb + win + 1) : -1.0f;
     uint32_t bad = 0;
     const int first = (int)t * OUT - 1;
     const int vl = opaque(lane);
-    const Cols<1> cl = load_cols<1, PER>(g, first, vl, ST, L(vl).col);
-    vote_range<1, PER>(tile, xe, ye, hb, he, cl, g, first, vl, bad, g.nrho_f, g.dedup ? ke : nullptr);
+    const Cols<1> cl = load_cols<1, PER>(g, first, vl, ST, L(vl).col, dummy_row);
+    vote_range<1, PER>(tile_w, xe, ye, hb, he, cl, g, first, vl, bad, WIN ? dummy_row : g.nrho_f,
+                       g.dedup ? ke : nullptr);
     __syncthreads();
     const int pl = opaque(lane);
     const L ln(pl);
-    for (int u = wave; u < 2 * nwords; u += NW) {
+    for (int u = 2 * w_lo + wave; u < 2 * (w_lo + nwp); u += NW) {
         uint32_t m[1];
-        const bool interior = u >= 1 && (u + 1) * kPeakRows < g.n_rho;
+        const bool interior = WIN || (u >= 1 && (u + 1) * kPeakRows < g.n_rho);
         constexpr bool UR = NW == 16;
-        if (PER && (t == 0 || t == T - 1)) {
+        if (WIN && (u * kPeakRows < wb || (u + 1) * kPeakRows > wb + win)) {
+            m[0] = 0u;
+        } else if (PER && (t == 0 || t == T - 1)) {
             if (interior)
-                peak_rows<false, 1, true, true, UR>(tile, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
+                peak_rows<false, 1, true, true, UR>(tile_w, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
             else
-                peak_rows<true, 1, true, true, UR>(tile, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
+                peak_rows<true, 1, true, true, UR>(tile_w, u, g.n_rho, g.threshold, ln, pl, m, first, g.n_theta);
         } else if (interior) {
-            peak_rows<false, 1, true, false, UR>(tile, u, g.n_rho, g.threshold, ln, pl, m);
+            peak_rows<false, 1, true, false, UR>(tile_w, u, g.n_rho, g.threshold, ln, pl, m);
         } else {
-            peak_rows<true, 1, true, false, UR>(tile, u, g.n_rho, g.threshold, ln, pl, m);
+            peak_rows<true, 1, true, false, UR>(tile_w, u, g.n_rho, g.threshold, ln, pl, m);
         }
         const bool out_col = pl >= 1 && pl <= TW - 2 && first + pl < g.n_theta;
-        reinterpret_cast<uint16_t *>(pmask)[((u >> 1) * TW + pl) * 2 + (u & 1)] = out_col ? (uint16_t)m[0] : (uint16_t)0;
+        reinterpret_cast<uint16_t *>(pmask_w)[((u >> 1) * TW + pl) * 2 + (u & 1)] = out_col ? (uint16_t)m[0] : (uint16_t)0;
         if (out_col && m[0]) atomicAdd(&colcnt[pl], (uint32_t)__popc(m[0]));
     }
     if (t == T - 1 && __ballot(bad != 0u) && lane == 0) s_bad = 1u;
@@ -2798,11 +2842,11 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridA
     asm volatile("" ::: "memory");
     __syncthreads();
     const int el = opaque(lane);
-    const uint32_t np = emit_and_dilate<1, true>(tile, pmask, dil, 0, nwords, first, g, pe, cap, s_base, L(el), el, wave,
+    const uint32_t np = emit_and_dilate<1, true>(tile_w, pmask_w, dil_w, w_lo, nwp, first, g, pe, cap, s_base, L(el), el, wave,
                                                  NW, tpk, &cl, colcnt, &s_edge);
     if (np == 0u) return;
     __syncthreads();
-    retain_split(dil, tpk, np, s_edge != 0u, stage + wave * 64, xe, ye, ke, hb, he, cl, g, first, t, T,
+    retain_split(dil_w, tpk, np, s_edge != 0u, stage + wave * 64, xe, ye, ke, hb, he, cl, g, first, t, T,
                  opaque(lane));
 }
 
@@ -3733,20 +3777,29 @@ hipError_t launch_batch(const GridArgs &g, const BatchPlan &p, const BatchArgs &
     }
 }
 
-template <int NW>
-static hipError_t launch_split_t(const GridArgs &g, const BatchArgs &a, const SplitArgs &sp, uint32_t items,
+// (a window that leaves room for one workgroup per CU wants the most waves)
+constexpr int kSplitWinWaves = 16;
+// LDS of the split kernel on windows of `win` rows.
+static size_t split_window_lds(int waves, int win) {
+    const size_t nwp = (size_t)win / 32 + 1;
+    return ((size_t)win + 3) * 128 + std::max((size_t)waves * kStageBytes, nwp * 256) + kTilePeaks * sizeof(float4) + 256 +
+           (nwp + 1) * kDilPitch<1> * 4;
+}
+
+template <int NW, bool WIN>
+static hipError_t launch_split_t(const GridArgs &g, const BatchArgs &a, const SplitArgs &sp, uint32_t items, int win,
                                  hipStream_t s) {
     const int nwords = (g.n_rho + 31) / 32;
-    const size_t lds = batch_lds_bytes(g.n_rho, NW, 1, 0, true);
+    const size_t lds = WIN ? split_window_lds(NW, win) : batch_lds_bytes(g.n_rho, NW, 1, 0, true);
     // one workgroup per item; a launch holds at most 2^31 threads, and the item counter runs on
     // from launch to launch
     for (uint32_t left = items; left > 0;) {
         const uint32_t n = std::min(left, 1u << 21);
         left -= n;
         if (g.periodic)
-            hipLaunchKernelGGL((k_batch_split<NW, true>), dim3(n), dim3(NW * 64), lds, s, g, a, sp, nwords);
+            hipLaunchKernelGGL((k_batch_split<NW, true, WIN>), dim3(n), dim3(NW * 64), lds, s, g, a, sp, nwords, win);
         else
-            hipLaunchKernelGGL((k_batch_split<NW, false>), dim3(n), dim3(NW * 64), lds, s, g, a, sp, nwords);
+            hipLaunchKernelGGL((k_batch_split<NW, false, WIN>), dim3(n), dim3(NW * 64), lds, s, g, a, sp, nwords, win);
     }
     return hipGetLastError();
 }
@@ -3758,11 +3811,12 @@ hipError_t launch_batch_split(const GridArgs &g, const SplitPlan &p, const Batch
     const uint32_t items = a.n_events * sp.n_tiles;
     // up to one item per CU the widest workgroup finishes its item first; beyond that narrower ones
     // share a CU and overlap their phases
+    if (p.win) return launch_split_t<kSplitWinWaves, true>(g, a, sp, items, p.win, s);
     switch (items <= (uint32_t)n_cu ? p.wide : p.narrow) {
-        case 16: return launch_split_t<16>(g, a, sp, items, s);
-        case 12: return launch_split_t<12>(g, a, sp, items, s);
-        case 8: return launch_split_t<8>(g, a, sp, items, s);
-        case 4: return launch_split_t<4>(g, a, sp, items, s);
+        case 16: return launch_split_t<16, false>(g, a, sp, items, 0, s);
+        case 12: return launch_split_t<12, false>(g, a, sp, items, 0, s);
+        case 8: return launch_split_t<8, false>(g, a, sp, items, 0, s);
+        case 4: return launch_split_t<4, false>(g, a, sp, items, 0, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -3770,13 +3824,22 @@ hipError_t launch_batch_split(const GridArgs &g, const SplitPlan &p, const Batch
 template <int NW>
 static bool split_fits(int n_rho, size_t lds_limit) {
     if (batch_lds_bytes(n_rho, NW, 1, 0, true) + 256 > lds_limit) return false;
-    allow_lds(k_batch_split<NW, false>);
-    allow_lds(k_batch_split<NW, true>);
+    allow_lds(k_batch_split<NW, false, false>);
+    allow_lds(k_batch_split<NW, true, false>);
     return true;
 }
 
+SplitPlan plan_split_window(int win, size_t lds_limit) {
+    SplitPlan p{0, 0, 0};
+    if (win == 0 || split_window_lds(kSplitWinWaves, win) + 256 > lds_limit) return p;
+    allow_lds(k_batch_split<kSplitWinWaves, false, true>);
+    allow_lds(k_batch_split<kSplitWinWaves, true, true>);
+    p.win = win;
+    return p;
+}
+
 SplitPlan plan_split(int n_rho, size_t lds_limit) {
-    SplitPlan p{0, 0};
+    SplitPlan p{0, 0, 0};
     if (split_fits<4>(n_rho, lds_limit)) p.wide = p.narrow = 4;
     if (split_fits<8>(n_rho, lds_limit)) p.wide = p.narrow = 8;
     // two workgroups per CU but not three: 12 waves each

@@ -304,6 +304,41 @@ def test_windows_over_many_events(H, orc, n_theta, n_rho, plan, flags):
     ctx.close()
 
 
+@pytest.mark.parametrize("n_theta,n_rho", [(2, 1500), (62, 1217), (63, 1500), (130, 2000), (1000, 1300)])
+@pytest.mark.parametrize("periodic", [False, True])
+@pytest.mark.parametrize("W", [1, 40])
+def test_small_batches_on_windows(H, orc, n_theta, n_rho, periodic, W):
+    """Few events on grids taller than a tile: one workgroup per (event, tile), each on the event's
+    window of rows.  Events that fit, events that reach beyond the window (60 mm), empty and
+    oversized ones, peaks that overflow the buffer, windows on both sides of rho = 0's row, one batch
+    on each side of the rule's event count, and gathered; every form called twice."""
+    import torch
+    lo, hi = (-0.01, 0.01) if periodic else (-0.012, 0.009)
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    half = torch.cuda.get_device_properties(0).multi_processor_count // 2
+    sizes = [900, 0, 1300, 3, 64, 33000, 700, 257]
+    parts = [_events([n], 60 + i, 60.0 if i in (3, 6) else 215.0, 0.01)[:2] for i, n in enumerate(sizes)]
+    x, y = (np.concatenate([p[i] for p in parts]) for i in (0, 1))
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    T, cap = 3, 500
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", T, W, cap, periodic=periodic)
+    for _ in range(2):
+        _, n_ref = _check(H, orc, ctx, g, T, W, cap, x, y, off, periodic)
+    xt, yt, ot = _t(x), _t(y), _t(off.astype(np.int32))
+    keep_ref = ctx.run_batch(xt, yt, ot)[2].cpu().numpy()
+    for n in (1, half, half + 1):                                  # by tile, by tile, by event
+        ids = np.resize([0, 2, 6, 1, 3, 4, 7], n)
+        starts = np.concatenate([[0], np.cumsum(np.array(sizes)[ids])])
+        for _ in range(2):
+            out = ctx.run_batch_gather(xt, yt, ot, _t(ids.astype(np.int32)), _t(starts[:-1].astype(np.int32)),
+                                       keep_size=int(starts[-1]))
+            torch.cuda.synchronize()
+            assert np.array_equal(out[1].cpu().numpy()[:n], n_ref[ids])
+            assert np.array_equal(out[2].cpu().numpy()[:int(starts[-1])],
+                                  np.concatenate([keep_ref[off[e]:off[e + 1]] for e in ids]))
+    ctx.close()
+
+
 @pytest.mark.parametrize("n_theta,n_rho,rng_lo,rng_hi", [(1, 1, -0.01, 0.01), (3, 5, -0.01, 0.01), (65, 33, -0.006, 0.006),
                                                          (64, 600, -0.006, 0.006), (127, 601, -0.006, 0.006),
                                                          (129, 1000, -0.01, 0.01), (70, 1301, -0.004, 0.006),
