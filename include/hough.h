@@ -312,7 +312,7 @@ typedef struct hough_batch_plan {
 /* The launch shape hough_run_batch currently uses (the library picks one at hough_config).  A
  * grid whose whole rho column does not fit the fused kernel's tile gets a windowed tile (theta
  * not periodic; window_rows > 0): each event whose hits reach only that many rows runs in the
- * fused kernel, the others, and every event of the caller's split forms, through the spill path.  All
+ * fused kernel, the others through the spill path.  All
  * zero on a theta-periodic grid taller than the tile (its windows are the library's own, not the
  * caller's to see or set). */
 int hough_get_batch_plan(const hough_ctx *ctx, hough_batch_plan *out);
@@ -323,7 +323,8 @@ int hough_get_batch_plan(const hough_ctx *ctx, hough_batch_plan *out);
  * tallest whole number of 32-row words that lets that many workgroups share a CU.  Each event
  * then gets the window of rows its hits can reach (they are bounded by the event's smallest
  * x^2 + y^2, Eq. (1)); an event whose rows do not fit goes through the spill path, as do
- * events above the fused kernel's hit limit.  The split forms always hold the whole column.
+ * events above the fused kernel's hit limit.  The split forms hold the whole
+ * column; where it does not fit a tile their calls are ordinary batches.
  * HOUGH_EINVAL if the combination is not supported or does not fit the device, or the grid
  * reports an all-zero shape; the context keeps its previous shape then. */
 int hough_set_batch_plan(hough_ctx *ctx, int32_t waves_per_group, int32_t column_groups,

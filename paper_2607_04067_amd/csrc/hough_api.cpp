@@ -34,8 +34,7 @@ struct hough_ctx {
     hough::SplitPlan split; // the split form's (whole columns, or windows on taller grids)
     uint32_t *d_slots;      // its slots for batches of up to split_events(n_cu) events
     int fused;              // 1: the fused kernel holds the grid's whole column (and windows of it);
-                            // 2: only windows of it (taller grids; the split form spills every
-                            // event); 3: the same, theta periodic (the shape is not the caller's to
+                            // 2: only windows of it (taller grids); 3: the same, theta periodic (the shape is not the caller's to
                             // see or set); 0: every batch event spills
     uint32_t *d_spill;      // spill_wgs slices of spill_stride words (the spill path's accumulators)
     size_t spill_stride;
@@ -561,9 +560,11 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
     a.queue = c->d_work;
     a.frac_num = frac_num;
     a.frac_den = frac_den;
-    // every event through the spill path: no fused kernel for this grid, or the split form on a
-    // grid whose whole column does not fit it (the split form gives the same results)
-    const bool spill_all = !c->fused || (split && c->fused != 1);
+    // the caller's split form has no workspace on a grid whose column does not fit a tile: such a call
+    // is an ordinary batch there (1000 x 2000, every event through the spill kernel before: 16 events 804
+    // us, 44 so; 400 events 1,584 and 328)
+    if (c->fused > 1) split = false;
+    const bool spill_all = !c->fused;       // no fused kernel for this grid
     hough::SpillArgs spill{c->d_spill, c->spill_stride, c->d_work + 2, spill_all ? 1u : 0u, nullptr, 0u, nullptr};
     // otherwise the fused (or split) kernel counts the events it leaves to the spill kernel in
     // the spill kernel's first counter, so that the spill kernel skips its scan when none
@@ -654,7 +655,7 @@ int hough_run_batch_gather(hough_ctx *c, const float *x, const float *y, const u
 uint32_t hough_max_dedup_hits(void) { return hough::kDedupMaxHits; }
 
 size_t hough_split_workspace_bytes(const hough_ctx *c, uint32_t n_events) {
-    if (!c || c->fused != 1) return 0;    // the split form spills every event: no workspace
+    if (!c || c->fused != 1) return 0;    // an ordinary batch there: no workspace
     return hough::split_workspace_bytes(c->p.n_theta, c->p.n_rho, c->plan.groups, n_events);
 }
 

@@ -118,7 +118,7 @@ bool split_layout(int n_theta, int n_rho, int groups, uint32_t n_events, void *w
 
 // Spill path of the batch entry points (k_spill): events processed one per workgroup, the
 // accumulator swept through rho slabs in LDS.  all = 1: every event (no fused kernel for the
-// grid, or the split form on a grid whose column does not fit its tile); all = 0: the events
+// grid); all = 0: the events
 // the fused or split kernel flagged (kStatusSpill: above kMaxBatchHits hits, or beyond a
 // windowed tile) and skipped.  Each workgroup owns `stride` 32-bit words of `work`: dilated
 // retention bits (ceil(n_rho / 32) * n_theta), per (column, 32-row block) a peak-row mask and

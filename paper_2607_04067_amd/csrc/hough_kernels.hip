@@ -2852,8 +2852,8 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridA
 
 // ------------------------------------------------------------ spill path (rho slabs)
 // Events whose accumulator the fused kernel cannot hold on chip: events whose hits reach beyond a
-// windowed tile, every event of the caller's split forms on grids taller than a tile, and events
-// above kMaxBatchHits hits on any grid (counts beyond 16 bits).  One workgroup processes one event at
+// windowed tile on grids taller than a whole-column one, and events above kMaxBatchHits hits on any
+// grid (counts beyond 16 bits).  One workgroup processes one event at
 // a time:
 //   - steps 1-4 one slab at a time in LDS (62 owned columns with halo lanes by up to 1,120 owned
 //     rows with halo rows; 32-bit counts and 544 rows for events above 65,535 hits): vote, then
@@ -3459,8 +3459,8 @@ int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, 
     p.lds_bytes = batch_lds_bytes(n_rho, waves, groups, win, p.sparse != 0);
     p.sp_lds_bytes = batch_lds_bytes(n_rho, waves, groups, win, true);
     p.split_lds_bytes = batch_lds_bytes(n_rho, waves, groups, 0, true);
-    // room for the kernel's static LDS; the split form always holds the whole column (grids
-    // taller than that run their split calls through the spill kernel: need_split false)
+    // room for the kernel's static LDS; the caller's split form holds the whole column (need_split
+    // false on grids taller than that)
     if (p.sp_lds_bytes + 256 > lds_limit || (need_split && p.split_lds_bytes + 256 > lds_limit)) return -1;
     p.grid = 0;
     *out = p;
