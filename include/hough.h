@@ -200,8 +200,9 @@ int hough_retain(hough_ctx *ctx, const float *x, const float *y, uint32_t n_hits
  * order, truncated at max_peaks.  n_peaks[e]: the true peak count.  keep: offsets[n_events]
  * bytes (indexed like x), computed from ALL peaks of the event even when the list is
  * truncated.  status[e]: HOUGH_EV_* bits.  n_events == 0 is valid.  A batch that would leave
- * half of the CUs without an event (at most 128 on MI355X; not with a relative threshold, and where
- * the fused kernel holds a whole rho column) runs one workgroup per (event, theta tile), as
+ * half of the CUs without an event (at most 128 on MI355X, a quarter and 192 where an event has at most
+ * 7 tiles; not with a relative threshold, nor with duplicate suppression on grids taller than a
+ * tile) runs one workgroup per (event, theta tile), as
  * hough_run_batch_split does, with the same results.  A batch of more events
  * than the kernel has resident workgroups (and at most 65,536 events) is preceded by a small
  * launch that schedules the events largest first; no result depends on the schedule.

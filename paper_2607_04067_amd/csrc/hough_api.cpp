@@ -32,7 +32,7 @@ struct hough_ctx {
     uint32_t *d_defer;      // [kOrderMaxEvents] the events that did not fit its window
     float *d_uv;            // [kMappedFloats] the fused kernel's mapped hits, shared out by launch
     hough::SplitPlan split; // the split form's (whole columns, or windows on taller grids)
-    uint32_t *d_slots;      // its slots for batches of up to split_events(n_cu) events
+    uint32_t *d_slots;      // its slots for batches of up to split_events() events
     int fused;              // 1: the fused kernel holds the grid's whole column (and windows of it);
                             // 2: only windows of it (taller grids); 3: the same, theta periodic (the shape is not the caller's to
                             // see or set); 0: every batch event spills
@@ -96,7 +96,12 @@ int spill_workgroups(size_t stride_words, int n_cu, bool all) {
 // 214 / 149; 300 x 1200 110 / 25, 112 / 30, 115 / 52, 119 / 74.  There events beyond the window go
 // to the spill kernel, which reads the duplicate marks the split form would drop: batches with
 // duplicate suppression stay with the fused kernel.
-uint32_t split_events(int n_cu) { return (uint32_t)n_cu / 2u; }
+// With at most 7 tiles per event it wins for longer (fused / split at 200 and 256 events: 288 x 343
+// dense 144 / 111, 144 / 128; 360 x 256 81 / 67, 81 / 74; 372 x 500 dense 134 / 125, 135 / 146;
+// 309 x 99 68 / 60, 69 / 68; 372 x 900 128 / 105, 128 / 125): up to three quarters of the CUs then.
+uint32_t split_events(int n_cu, int n_theta, bool whole) {
+    return whole && hough::split_tiles(n_theta) <= 7u ? (uint32_t)n_cu * 3u / 4u : (uint32_t)n_cu / 2u;
+}
 
 // Room for the mapped hits of the events in flight: 32 MiB, 4,096 hits for each of 1,024 workgroups
 // (four per CU, as 360 x 256 takes), 8,192 for 512.  What is beyond is mapped again for every tile.
@@ -195,6 +200,10 @@ int default_windowed_plan(hough_ctx *c) {
 // some 560 rows): two 8-wave workgroups per CU, each on the rows its event's hits reach.  A CU then
 // overlaps one event's voting with the other's peaks and retention, and peaks, clears and retention
 // cover half of the rows (1,000 events on 1000 x 1000, hits reaching 500 rows: 691 -> 476 us).
+// A batch of fewer events than the CUs hold workgroups stays with whole columns: 16 waves finish an
+// event sooner than 8 (us on windows / whole columns at 256, 400 and 512 events: 1000 x 1000 280 / 243,
+// 347 / 331, 364 / 385, with a relative threshold 348 / 318, 455 / 498, 456 / 533; 270 x 876 125 / 100,
+// 151 / 122, 156 / 148 and 135 / 114, 173 / 164, 174 / 185; 270 x 640 79 / 65, 104 / 114, 110 / 116).
 // Events that reach more rows run on whole columns in a second launch, which returns at once
 // when there are none (5 us); a batch of such events alone pays one more pass over its hits (38 us
 // for 1,000 of them: 1000 x 650 bins, every hit in reach of every row, 703 us on whole columns alone and
@@ -292,7 +301,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
     // the fixed buffers in one block, each on a 256-byte boundary, those that start at zero first
     const size_t sizes[8] = {
         256 + 4 * (size_t)((p->n_theta + peak_waves - 1) / peak_waves),                          // d_work
-        (size_t)split_events(c->n_cu) * hough::split_tiles(p->n_theta) * 4,                      // d_slots
+        (size_t)split_events(c->n_cu, p->n_theta, c->fused == 1) * hough::split_tiles(p->n_theta) * 4,   // d_slots
         tab.size() * sizeof(float),                                                              // d_tables
         c->iter1.gbm ? c->iter1.bm_bytes : 0,                                                    // d_iter_bm
         sizeof(uint64_t) * std::max(hough::kIterScanKeys, hough::kIterHeads),                    // d_iter_list
@@ -576,7 +585,8 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
         return e == hipSuccess ? HOUGH_OK : HOUGH_EDEVICE;
     }
     // the library's own windowed shape first, whole columns for the events it does not fit
-    const bool two = c->window.win && !c->chosen && n_events <= hough::kOrderMaxEvents;
+    const bool two = c->window.win && !c->chosen && n_events >= 2u * (uint32_t)c->n_cu &&
+                     n_events <= hough::kOrderMaxEvents;
     hough::BatchPlan plan = two ? c->window : c->plan;
     long grid = (long)plan.per_cu * c->n_cu;
     if (grid > (long)n_events) grid = n_events;
@@ -589,7 +599,8 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
                                  &sp))
             return HOUGH_EINVAL;
         if ((long)n_events * sp.n_tiles >= (1L << 31)) return HOUGH_EINVAL;   // the work queue counts in 32 bits
-    } else if ((c->fused == 1 || (c->split.win && !c->g.dedup)) && frac_den == 0 && n_events <= split_events(c->n_cu)) {
+    } else if ((c->fused == 1 || (c->split.win && !c->g.dedup)) && frac_den == 0 &&
+               n_events <= split_events(c->n_cu, c->p.n_theta, c->fused == 1)) {
         split = true;
         sp.n_tiles = hough::split_tiles(c->p.n_theta);
         sp.slots = c->d_slots;

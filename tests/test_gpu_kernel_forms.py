@@ -242,7 +242,7 @@ def test_small_batches_by_tile(H, orc, n_theta, n_rho, flags):
         assert np.array_equal(same(ctx.run_batch(xt, yt, ot), range(E))[:x.size], keep_ref)
         assert np.array_equal(same(ctx.run_batch_split(xt, yt, ot, ws), range(E))[:x.size], keep_ref)
         assert int(ws.count_nonzero()) == 0
-    for n in (1, half, half + 1):                                  # by tile, by tile, by event
+    for n in (1, half, half + 1, 3 * half // 2, 3 * half // 2 + 1):   # by tile, by tile or by event
         ids = (np.arange(n) * 3) % E
         ids = ids[ids != 5] if n > 1 else ids
         ids = np.resize(ids, n)
@@ -270,7 +270,7 @@ def test_windows_over_many_events(H, orc, n_theta, n_rho, plan, flags):
         pytest.skip("a window is not the caller's to choose on a periodic grid")
     g = orc.Grid(n_theta, n_rho, lo, hi)
     rng = np.random.default_rng(n_rho)
-    sizes = rng.integers(0, 260, 150)
+    sizes = rng.integers(0, 260, 2 * torch.cuda.get_device_properties(0).multi_processor_count + 8)
     sizes[::31] = 0
     parts = [_events([int(n)], 40 + i, 60.0 if i % 7 == 3 else 210.0, 0.01)[:2] for i, n in enumerate(sizes)]
     x, y = (np.concatenate([p[i] for p in parts]) for i in (0, 1))
