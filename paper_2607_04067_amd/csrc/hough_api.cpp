@@ -334,8 +334,12 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         }
         c->spill_wgs = (c->spill_wgs + 1) / 2;
     }
-    if (hipMemcpy(c->d_tables, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemset(c->d_block, 0, at[2]) != hipSuccess) {
+    // The tables and the zeros (work counters, slots) are waited for: the caller's first launch may be
+    // on a stream that does not wait for the null stream, and tiles of the split form wait for slots
+    // that a late clear would put back to zero.
+    if (hipMemset(c->d_block, 0, at[2]) != hipSuccess ||
+        hipMemcpy(c->d_tables, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
+        hipStreamSynchronize(nullptr) != hipSuccess) {
         hough_destroy(c);
         return HOUGH_EDEVICE;
     }

@@ -131,8 +131,10 @@ struct HipServer {
                     s.ws_bytes = std::max(s.ws_bytes,
                                           hough_split_workspace_bytes(cs, (uint32_t)cfg.split_batch_events));
             }
+            // cleared on the slot's own stream, which does not wait for the null stream (the split
+            // form's tiles wait for slots that start at zero)
             if (s.ws_bytes && (hipMalloc(&s.d_ws, s.ws_bytes) != hipSuccess ||
-                               hipMemset(s.d_ws, 0, s.ws_bytes) != hipSuccess))
+                               hipMemsetAsync(s.d_ws, 0, s.ws_bytes, s.stream) != hipSuccess))
                 return HOUGH_ENOMEM;
         }
         return HOUGH_OK;

@@ -1,0 +1,136 @@
+"""What the host side of libhough.so asks of the device, without one: a HIP runtime that runs nothing
+(fake_hip.cpp) is loaded ahead of the library in a process of its own and writes down the kernels that
+would be launched, in order, with the clears and waits between them."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_2607_04067_amd", "libhough.so")
+
+PRELUDE = r"""
+import ctypes, json, re, sys
+FAKE = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+FAKE.fake_journal.restype = ctypes.c_char_p
+L = ctypes.CDLL(sys.argv[2])
+vp, i32, u32, f64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint32, ctypes.c_double
+PERIODIC, DEDUP = 1, 2
+
+class Params(ctypes.Structure):
+    _fields_ = [("n_theta", i32), ("n_rho", i32), ("rho_min", f64), ("rho_max", f64), ("acc_type", i32),
+                ("threshold", i32), ("rho_window", i32), ("max_peaks", i32), ("flags", i32), ("reserved", i32)]
+
+class Plan(ctypes.Structure):
+    _fields_ = [("waves", i32), ("groups", i32), ("per_cu", i32), ("lds", i32), ("window", i32)]
+
+L.hough_split_workspace_bytes.restype = ctypes.c_size_t
+L.hough_split_workspace_bytes.argtypes = [vp, u32]
+X = vp(1 << 20)                                  # stands for a device array
+
+def context(n_theta, n_rho, flags=0):
+    c = vp()
+    p = Params(n_theta, n_rho, -0.01, 0.01, 2, 10, 1, 64, flags, 0)
+    rc = L.hough_config(ctypes.byref(p), ctypes.byref(c))
+    assert rc == 0, rc
+    return c
+
+def plan(c):
+    p = Plan()
+    assert L.hough_get_batch_plan(c, ctypes.byref(p)) == 0
+    return p.waves, p.groups, p.per_cu, p.window
+
+def journal(call):
+    # the call's status and what it asked for: kernels as name<template arguments>
+    FAKE.fake_clear()
+    rc = call()
+    out = []
+    for line in FAKE.fake_journal().decode().splitlines():
+        w = line.split()
+        if w[0] == "launch":
+            name, args = re.search(r"\d(k_[a-z_0-9]+?)(?:I((?:L[ib]\d+E)+)|E)", w[1]).groups()
+            out.append(name + ("<" + ",".join(re.findall(r"L[ib](\d+)E", args)) + ">" if args else ""))
+        else:
+            out.append(line)
+    return rc, out
+
+def batch(c, n):
+    return journal(lambda: L.hough_run_batch(c, X, X, X, n, X, X, X, X, None))
+
+def split(c, n, workspace=None, size=0, static=False):
+    if static:
+        return journal(lambda: L.hough_run_batch_split_static(c, X, X, X, None, None, n, X, X, X, X, None))
+    return journal(lambda: L.hough_run_batch_split(c, X, X, X, None, None, n, X, X, X, X, workspace,
+                                                   ctypes.c_size_t(size), None))
+"""
+
+SERVE = r"""
+class Pool(ctypes.Structure):
+    _fields_ = [("ctx", vp), ("x", vp), ("y", vp), ("offsets", vp), ("host_offsets", vp), ("n_events", u32),
+                ("reserved", u32), ("host_x", vp), ("host_y", vp)]
+
+class Config(ctypes.Structure):
+    _fields_ = [("n_streams", i32), ("max_batch_events", i32), ("max_batch_hits", i32), ("plain", i32),
+                ("copy_peaks", i32), ("small_batch_events", i32), ("split_batch_events", i32), ("reserved", i32),
+                ("max_wait_us", f64)]
+
+class Request(ctypes.Structure):
+    _fields_ = [("arrival_us", f64), ("kind", i32), ("event", u32)]
+
+class Result(ctypes.Structure):
+    _fields_ = [("launch_us", f64), ("done_us", f64), ("n_peaks", u32), ("status", u32), ("batch_events", u32),
+                ("slot", u32)]
+
+def serve(c, n, small=64, split=16, streams=1):
+    # n events that arrive together, as one batch
+    off = (u32 * (n + 1))(*range(0, 3 * n + 1, 3))
+    pool = (Pool * 1)(Pool(c, X, X, X, ctypes.cast(off, vp), n, 0, None, None))
+    cfg = Config(streams, 4096, 1 << 16, 0, 0, small, split, 0, 0.0)
+    req = (Request * n)(*[Request(0.0, 0, i) for i in range(n)])
+    res = (Result * n)()
+    rc, out = journal(lambda: L.hough_serve_run(pool, 1, ctypes.byref(cfg), req, u32(n), res, None, None, u32(0)))
+    return rc, out, max(r.batch_events for r in res)
+"""
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    if not os.path.exists(LIB):
+        from paper_2607_04067_amd import build
+        build.build()
+    cxx = shutil.which("g++")
+    assert cxx, "g++ not found"
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    fake = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run([cxx, "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                    "-I" + os.path.join(rocm, "include"), os.path.join(HERE, "fake_hip.cpp"), "-o", fake], check=True)
+
+    def run(body: str, **values):
+        """The value of `out` after `body`, run with the names of PRELUDE, SERVE and `values`."""
+        code = PRELUDE + SERVE + "".join(f"{k} = {v!r}\n" for k, v in values.items()) + body
+        code += "\nprint('OUT ' + json.dumps(out))\n"
+        r = subprocess.run([sys.executable, "-c", code, fake, LIB], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return json.loads([ln for ln in r.stdout.splitlines() if ln.startswith("OUT ")][-1][4:])
+
+    return run
+
+
+def test_zeros_are_in_place_before_a_kernel_can_read_them(routes):
+    """The split form waits for slots that start at zero, so a context's are cleared and waited for in
+    hough_config (its caller may launch on any stream), and a serving slot's workspace is cleared on
+    the stream its launches go to."""
+    log = routes("out = journal(lambda: context(360, 256) and 0)[1]")
+    clears = [i for i, s in enumerate(log) if s == "clear stream 0"]
+    assert clears and "wait stream 0" in log[clears[-1]:]
+    rc, log, n = routes("out = serve(context(360, 256), 4, streams=2)")
+    assert rc == 0 and n == 4
+    own = [s for s in log if s.startswith("clear stream")]
+    assert "clear stream 1" in own and "clear stream 2" in own
+    # a clear on the null stream is waited for before the first launch
+    first = next(i for i, s in enumerate(log) if s.startswith("k_batch"))
+    late = [i for i, s in enumerate(log[:first]) if s == "clear stream 0"]
+    assert all("wait stream 0" in log[i:first] for i in late)
