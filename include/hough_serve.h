@@ -22,7 +22,8 @@
  * output is an integer and events are independent).
  *
  * Batches on different streams run concurrently; each stream slot therefore launches through
- * private copies of the pools' contexts (same parameters and launch shape), made on entry.
+ * private copies of the pools' contexts (same parameters, and the same launch shape where the caller
+ * has set one), made on entry.
  * Inside a batch the events are ordered largest first (the smallest fill the kernel's tail);
  * a batch's inputs (resident: ids and keep offsets; host: offsets and hits) go to the device in
  * one copy and its n_peaks, status and keep bytes come back in one.  Small batches can take the split form (each stream slot then
@@ -66,11 +67,12 @@ typedef struct hough_serve_config {
                                        host pools: hough_run_batch on the slot's arena);
                                        1: per event                                           */
     int32_t copy_peaks;             /* 1: bring the peak lists back as part of completion    */
-    int32_t small_batch_events;     /* batches of at most this many events run with 16-wave
-                                       workgroups (one event per CU finishes sooner); 0: never */
+    int32_t small_batch_events;     /* batches of at most this many events run as on a context
+                                       whose shape nobody has set (by tile, as hough_run_batch
+                                       says; beyond that on 16-wave workgroups); 0: never      */
     int32_t split_batch_events;     /* batches of at most this many events run through
-                                       hough_run_batch_split on the 16-wave shape (an event's
-                                       theta tiles on separate workgroups); 0: never          */
+                                       hough_run_batch_split (an event's theta tiles on
+                                       separate workgroups); 0: never                          */
     int32_t reserved;               /* 0                                                     */
     double max_wait_us;             /* hold a partial batch until its oldest event waited this
                                        long while a slot is free (0: launch at once)          */

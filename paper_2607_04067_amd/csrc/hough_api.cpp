@@ -215,6 +215,10 @@ void auto_window(hough_ctx *c) {
     if (windowed_plan(c, 8, 1, 2, &p) == 0) c->window = p;
 }
 
+// Whether the context's small batches can run by tile: its whole column fits the split form, or windows
+// of it do and no duplicate marks have to reach the spill kernel (see split_events).
+bool by_tile(const hough_ctx *c) { return c->fused == 1 || (c->split.win && !c->g.dedup); }
+
 // A context's tables and workspace live on the device it was configured on.
 bool on_device(const hough_ctx *c) {
     int dev = -1;
@@ -410,8 +414,17 @@ int hough_get_batch_plan(const hough_ctx *c, hough_batch_plan *out) {
     return HOUGH_OK;
 }
 
-int hough_set_batch_plan(hough_ctx *c, int32_t waves_per_group, int32_t column_groups,
-                         int32_t groups_per_cu) {
+}  // extern "C"
+
+namespace hough {
+
+bool shape_chosen(const hough_ctx *c) { return c->chosen != 0; }
+
+uint32_t tile_batch_events(const hough_ctx *c) {
+    return by_tile(c) ? split_events(c->n_cu, c->p.n_theta, c->fused == 1) : 0u;
+}
+
+int suggest_shape(hough_ctx *c, int32_t waves_per_group, int32_t column_groups, int32_t groups_per_cu) {
     if (!c || groups_per_cu < 0 || !c->fused || c->fused == 3) return HOUGH_EINVAL;
     hough::BatchPlan p{};
     if (c->fused == 1) {
@@ -432,8 +445,18 @@ int hough_set_batch_plan(hough_ctx *c, int32_t waves_per_group, int32_t column_g
     }
     if (groups_per_cu > 0) p.per_cu = groups_per_cu;
     c->plan = p;
-    c->chosen = 1;
     return HOUGH_OK;
+}
+
+}  // namespace hough
+
+extern "C" {
+
+int hough_set_batch_plan(hough_ctx *c, int32_t waves_per_group, int32_t column_groups,
+                         int32_t groups_per_cu) {
+    const int rc = hough::suggest_shape(c, waves_per_group, column_groups, groups_per_cu);
+    if (rc == HOUGH_OK) c->chosen = 1;
+    return rc;
 }
 
 int hough_vote(hough_ctx *c, const float *x, const float *y, uint32_t n_hits, void *acc, void *stream) {
@@ -603,8 +626,7 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
                                  &sp))
             return HOUGH_EINVAL;
         if ((long)n_events * sp.n_tiles >= (1L << 31)) return HOUGH_EINVAL;   // the work queue counts in 32 bits
-    } else if ((c->fused == 1 || (c->split.win && !c->g.dedup)) && frac_den == 0 &&
-               n_events <= split_events(c->n_cu, c->p.n_theta, c->fused == 1)) {
+    } else if (frac_den == 0 && n_events <= hough::tile_batch_events(c)) {
         split = true;
         sp.n_tiles = hough::split_tiles(c->p.n_theta);
         sp.slots = c->d_slots;

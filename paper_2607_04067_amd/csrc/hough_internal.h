@@ -108,6 +108,12 @@ struct SplitArgs {
     uint32_t *slots;
 };
 uint32_t split_tiles(int n_theta);
+// For the serving loop's own contexts (hough_api.cpp).  Whether the caller has set the context's launch
+// shape; the largest batch of a context without one that runs by tile; and hough_set_batch_plan in the
+// library's own name: batches keep the routes a context takes whose caller has not set a shape.
+bool shape_chosen(const hough_ctx *c);
+uint32_t tile_batch_events(const hough_ctx *c);
+int suggest_shape(hough_ctx *c, int32_t waves_per_group, int32_t column_groups, int32_t groups_per_cu);
 SplitPlan plan_split(int n_rho, size_t lds_limit);
 SplitPlan plan_split_window(int win, size_t lds_limit);
 // Keep words per event in the split form's workspace size.

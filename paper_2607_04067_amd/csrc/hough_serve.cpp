@@ -11,6 +11,7 @@
 #include <new>
 #include <vector>
 
+#include "hough_internal.h"
 #include "serve_sched.h"
 
 namespace {
@@ -35,7 +36,8 @@ struct Kind {
 struct Slot {
     hipStream_t stream = nullptr;
     std::vector<hough_ctx *> ctx;        // one private context per kind: its own work counter
-    std::vector<hough_ctx *> ctx_small;  // the same grid with 16-wave workgroups, for small batches
+    std::vector<hough_ctx *> ctx_small;  // the same grid on the library's shapes, for small batches (null:
+                                         // ctx is on them already)
     hipEvent_t done = nullptr;
     uint32_t *d_in = nullptr;
     uint8_t *d_arena = nullptr;
@@ -78,6 +80,8 @@ struct HipServer {
         }
     }
 
+    static hough_ctx *small_ctx(const Slot &s, size_t kind) { return s.ctx_small[kind] ? s.ctx_small[kind] : s.ctx[kind]; }
+
     uint32_t hits_of(int k, uint32_t ev) const {
         const uint32_t *o = kinds[(size_t)k].pool.host_offsets;
         return o[ev + 1] - o[ev];
@@ -105,31 +109,35 @@ struct HipServer {
             if (!ok) return HOUGH_ENOMEM;
             s.koff.reserve(E);
             // batches on different streams run at the same time, so each slot launches through
-            // its own copy of every kind's context (same grid, parameters and launch shape)
+            // its own copy of every kind's context (same grid and parameters, and the launch shape
+            // where the pool's caller has set one: setting the shape a context merely reports would
+            // end the library's own choices, such as the windows it takes for large batches)
             for (const Kind &k : kinds) {
                 hough_ctx *c = nullptr;
                 const int rc = hough_config(&k.p, &c);
                 if (rc != HOUGH_OK) return rc;
                 s.ctx.push_back(c);
+                const bool chosen = hough::shape_chosen(k.pool.ctx);
                 hough_batch_plan bp;
-                if (hough_get_batch_plan(k.pool.ctx, &bp) != HOUGH_OK) return HOUGH_EINVAL;
-                const bool fused = bp.waves_per_group > 0;    // else every event spills: no shape to set
-                if (fused &&
-                    hough_set_batch_plan(c, bp.waves_per_group, bp.column_groups, bp.groups_per_cu) != HOUGH_OK)
+                if (chosen && (hough_get_batch_plan(k.pool.ctx, &bp) != HOUGH_OK ||
+                               hough_set_batch_plan(c, bp.waves_per_group, bp.column_groups, bp.groups_per_cu) !=
+                                   HOUGH_OK))
                     return HOUGH_EINVAL;
-                // a batch of fewer events than workgroup slots runs each event on one workgroup:
-                // 16 waves finish it sooner than 8 (when that shape fits; else the pool's shape)
-                hough_ctx *cs = nullptr;
-                const int rs = hough_config(&k.p, &cs);
-                if (rs != HOUGH_OK) return rs;
-                s.ctx_small.push_back(cs);
-                if (fused && hough_set_batch_plan(cs, 16, 1, 0) != HOUGH_OK &&
-                    hough_set_batch_plan(cs, bp.waves_per_group, bp.column_groups, bp.groups_per_cu) != HOUGH_OK)
-                    return HOUGH_EINVAL;
+                // Small batches run by tile; where they are too many for that but still fewer than
+                // workgroup slots, an event has one workgroup, and 16 waves finish it sooner than 8
+                // (where that shape fits).  A context whose shape is the library's does the first by itself.
+                s.ctx_small.push_back(nullptr);
+                if (!cfg.plain && (chosen || (uint32_t)cfg.small_batch_events > hough::tile_batch_events(c))) {
+                    hough_ctx *cs = nullptr;
+                    const int rs = hough_config(&k.p, &cs);
+                    if (rs != HOUGH_OK) return rs;
+                    s.ctx_small.back() = cs;
+                    (void)hough::suggest_shape(cs, 16, 1, 0);
+                }
                 // every split launch leaves the workspace zero, so the kinds can share it
                 if (!cfg.plain && cfg.split_batch_events > 0)
-                    s.ws_bytes = std::max(s.ws_bytes,
-                                          hough_split_workspace_bytes(cs, (uint32_t)cfg.split_batch_events));
+                    s.ws_bytes = std::max(s.ws_bytes, hough_split_workspace_bytes(small_ctx(s, s.ctx.size() - 1),
+                                                                                  (uint32_t)cfg.split_batch_events));
             }
             // cleared on the slot's own stream, which does not wait for the null stream (the split
             // form's tiles wait for slots that start at zero)
@@ -201,10 +209,10 @@ struct HipServer {
         int st = HOUGH_OK;
         if (!cfg.plain) {
             if (n <= (uint32_t)cfg.split_batch_events) {
-                st = hough_run_batch_split(sl.ctx_small[(size_t)b.kind], x, y, off, d_ids, d_koff, n, sl.d_peaks,
+                st = hough_run_batch_split(small_ctx(sl, (size_t)b.kind), x, y, off, d_ids, d_koff, n, sl.d_peaks,
                                            d_npk, d_keep, d_status, sl.d_ws, sl.ws_bytes, s);
             } else {
-                hough_ctx *c = n <= (uint32_t)cfg.small_batch_events ? sl.ctx_small[(size_t)b.kind]
+                hough_ctx *c = n <= (uint32_t)cfg.small_batch_events ? small_ctx(sl, (size_t)b.kind)
                                                                       : sl.ctx[(size_t)b.kind];
                 st = kd.host ? hough_run_batch(c, x, y, off, n, sl.d_peaks, d_npk, d_keep, d_status, s)
                              : hough_run_batch_gather(c, x, y, off, d_ids, d_koff, n, sl.d_peaks, d_npk, d_keep,

@@ -134,3 +134,28 @@ def test_zeros_are_in_place_before_a_kernel_can_read_them(routes):
     first = next(i for i, s in enumerate(log) if s.startswith("k_batch"))
     late = [i for i, s in enumerate(log[:first]) if s == "clear stream 0"]
     assert all("wait stream 0" in log[i:first] for i in late)
+
+
+def test_serving_keeps_the_shapes_of_a_pool_nobody_tuned(routes):
+    """A pool's context reports whole columns where its large batches take windows first: its serving
+    copies run the same kernels, with one context per stream.  A shape its caller has set is copied;
+    small batches keep the library's own shapes either way."""
+    rc, alone = routes("out = batch(context(1000, 1000), 600)")
+    assert rc == 0 and alone == ["k_order", "k_batch<8,1,0,1,1>", "k_batch<16,1,0,1,0>", "k_spill"]
+    rc, log, n = routes("out = serve(context(1000, 1000), 600, split=0)")
+    assert rc == 0 and n == 600
+    # (a gathered batch keeps the caller's order)
+    assert [s for s in log if s.startswith("k_")] == alone[1:]
+    blocks = [s for s in log if s.startswith("malloc") and int(s.split()[1]) > 32 << 20]
+    assert len(blocks) == 1
+    rc, log, n = routes("""
+c = context(1000, 1000)
+assert L.hough_set_batch_plan(c, 12, 1, 1) == 0
+out = serve(c, 600)""")
+    assert rc == 0 and [s for s in log if s.startswith("k_")] == ["k_batch<12,1,0,1,0>", "k_spill"]
+    for small, want in ((64, ["k_batch_split<16,0,0>", "k_spill"]), (1000, ["k_batch<16,1,0,0,0>", "k_spill"])):
+        rc, log, n = routes("""
+c = context(360, 256)
+assert L.hough_set_batch_plan(c, 12, 1, 1) == 0
+out = serve(c, n, small, 0)""", n=40 if small == 64 else 300, small=small)
+        assert rc == 0 and [s for s in log if s.startswith("k_")] == want
