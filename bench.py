@@ -911,7 +911,9 @@ def main(argv=None):
         out["autotune_ms"] = tuned["ms"]
         out["autotune_pick"] = tuned["plan"]
     if args.sweeps:
-        out["sweeps"] = sweeps(H, wl, ev, plan=ctx.batch_plan)
+        # (a shape nobody set is not set there either: small batches then run by tile)
+        own = not args.plan and (tuned is None or tuned["automatic"])
+        out["sweeps"] = sweeps(H, wl, ev, plan=None if own else ctx.batch_plan)
     if args.copy_reference_mb:
         n = args.copy_reference_mb << 20
         src = torch.empty(n, dtype=torch.uint8, device="cuda")

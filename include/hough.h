@@ -199,11 +199,11 @@ int hough_retain(hough_ctx *ctx, const float *x, const float *y, uint32_t n_hits
  * peaks: n_events * max_peaks entries; event e's peaks go to peaks[e * max_peaks ...] in raster
  * order, truncated at max_peaks.  n_peaks[e]: the true peak count.  keep: offsets[n_events]
  * bytes (indexed like x), computed from ALL peaks of the event even when the list is
- * truncated.  status[e]: HOUGH_EV_* bits.  n_events == 0 is valid.  A batch that would leave
- * half of the CUs without an event (at most 128 on MI355X, a quarter and 192 where an event has at most
- * 7 tiles; not with a relative threshold, nor with duplicate suppression on grids taller than a
- * tile) runs one workgroup per (event, theta tile), as
- * hough_run_batch_split does, with the same results.  A batch of more events
+ * truncated.  status[e]: HOUGH_EV_* bits.  n_events == 0 is valid.  While
+ * the caller has not set a launch shape, a batch that would leave half of the CUs without an event
+ * (at most 128 on MI355X, a quarter and 192 where an event has at most 7 tiles; not with a relative
+ * threshold, nor with duplicate suppression on grids taller than a tile) runs one workgroup per
+ * (event, theta tile), as hough_run_batch_split does, with the same results.  A batch of more events
  * than the kernel has resident workgroups (and at most 65,536 events) is preceded by a small
  * launch that schedules the events largest first; no result depends on the schedule.
  * The fused kernel keeps an event's theta tile on chip, with 16-bit counts.  What it cannot
@@ -310,7 +310,11 @@ typedef struct hough_batch_plan {
     int32_t window_rows;       /* rho rows of a windowed tile, 0 = whole column (read-only) */
 } hough_batch_plan;
 
-/* The launch shape hough_run_batch currently uses (the library picks one at hough_config).  A
+/* The fused kernel's launch shape: the one the caller has set, or the one the library picked at
+ * hough_config.  While the caller has not set one, some batches run in other ways, which this does not
+ * report and which setting the reported shape would end: small ones by tile (see hough_run_batch), and
+ * ones of at least twice as many events as CUs, on grids whose whole column leaves room for one
+ * workgroup per CU, first on windows of rows and then, for the events that reach more, in this shape.  A
  * grid whose whole rho column does not fit the fused kernel's tile gets a windowed tile (theta
  * not periodic; window_rows > 0): each event whose hits reach only that many rows runs in the
  * fused kernel, the others through the spill path.  All
@@ -318,7 +322,8 @@ typedef struct hough_batch_plan {
  * caller's to see or set). */
 int hough_get_batch_plan(const hough_ctx *ctx, hough_batch_plan *out);
 
-/* Select a launch shape (for autotuning).  groups_per_cu = 0 launches as many workgroups per CU
+/* Select a launch shape (for autotuning): every later hough_run_batch, hough_run_batch_gather and
+ * hough_run_batch_relative of the context runs in it, whatever the number of events.  groups_per_cu = 0 launches as many workgroups per CU
  * as fit; a positive value launches at most that many.  A groups_per_cu above what a tile of the
  * whole rho column allows selects a windowed tile (one column group, theta not periodic): the
  * tallest whole number of 32-row words that lets that many workgroups share a CU.  Each event

@@ -85,7 +85,7 @@ int spill_workgroups(size_t stride_words, int n_cu, bool all) {
 }
 
 // Batches that would leave at least half of the CUs without an event run in the split form, on the
-// context's own slots: the fused kernel walks an event's tiles one after the other on one
+// context's own slots, unless the caller has set a launch shape, which is the fused kernel's: the fused kernel walks an event's tiles one after the other on one
 // workgroup, so its time hardly depends on the number of events up to one per CU, while the
 // split form's grows with it.  Measured, us per batch fused / split at 1, 64, 128 and 256 events on
 // 256 CUs: 180 x 128 (3 tiles) 23 / 14, 25 / 17, 26 / 21, 29 / 28; 360 x 256 (6 tiles) 73 / 21,
@@ -599,6 +599,7 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
     // the caller's split form has no workspace on a grid whose column does not fit a tile: such a call
     // is an ordinary batch there (1000 x 2000, every event through the spill kernel before: 16 events 804
     // us, 44 so; 400 events 1,584 and 328)
+    const bool want_split = split;
     if (c->fused > 1) split = false;
     const bool spill_all = !c->fused;       // no fused kernel for this grid
     hough::SpillArgs spill{c->d_spill, c->spill_stride, c->d_work + 2, spill_all ? 1u : 0u, nullptr, 0u, nullptr};
@@ -626,7 +627,7 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
                                  &sp))
             return HOUGH_EINVAL;
         if ((long)n_events * sp.n_tiles >= (1L << 31)) return HOUGH_EINVAL;   // the work queue counts in 32 bits
-    } else if (frac_den == 0 && n_events <= hough::tile_batch_events(c)) {
+    } else if ((!c->chosen || want_split) && frac_den == 0 && n_events <= hough::tile_batch_events(c)) {
         split = true;
         sp.n_tiles = hough::split_tiles(c->p.n_theta);
         sp.slots = c->d_slots;

@@ -159,3 +159,49 @@ c = context(360, 256)
 assert L.hough_set_batch_plan(c, 12, 1, 1) == 0
 out = serve(c, n, small, 0)""", n=40 if small == 64 else 300, small=small)
         assert rc == 0 and [s for s in log if s.startswith("k_")] == want
+
+
+# (n_theta, n_rho, flags, shape to set or None, events, kernels)
+BATCH_ROUTES = [
+    (360, 256, 0, None, 1, ["k_batch_split<16,0,0>", "k_spill"]),
+    (360, 256, 0, None, 192, ["k_batch_split<8,0,0>", "k_spill"]),
+    (360, 256, 0, None, 193, ["k_batch<8,1,0,0,0>", "k_spill"]),
+    (360, 256, 0, None, 5000, ["k_order", "k_batch<8,1,0,0,0>", "k_spill"]),
+    (720, 512, 0, None, 129, ["k_batch<12,1,0,0,0>", "k_spill"]),
+    (1000, 2000, "PERIODIC", None, 64, ["k_batch_split<16,1,1>", "k_spill"]),
+    (1000, 2000, "DEDUP", None, 64, ["k_dedup", "k_batch<16,1,0,1,1>", "k_spill"]),
+    # a shape the caller has set runs every batch, small ones too
+    (360, 256, 0, (4, 2, 0), 1, ["k_batch<4,2,0,0,0>", "k_spill"]),
+    (360, 256, 0, (6, 1, 3), 16, ["k_batch<6,1,0,0,0>", "k_spill"]),
+    (360, 256, "PERIODIC", (12, 1, 0), 16, ["k_batch<12,1,1,0,0>", "k_spill"]),
+    (360, 256, "DEDUP", (8, 1, 4), 100, ["k_dedup", "k_batch<8,1,0,0,0>", "k_spill"]),
+    (720, 512, 0, (16, 2, 0), 40, ["k_batch<16,2,0,0,0>", "k_spill"]),
+    (1000, 1000, 0, (8, 1, 2), 20, ["k_batch<8,1,0,1,1>", "k_spill"]),
+    (1000, 1000, 0, (16, 1, 1), 600, ["k_order", "k_batch<16,1,0,1,0>", "k_spill"]),
+    (1000, 2000, 0, (8, 1, 0), 20, ["k_batch<8,1,0,1,1>", "k_spill"]),
+]
+
+
+@pytest.mark.parametrize("n_theta,n_rho,flags,shape,events,kernels", BATCH_ROUTES)
+def test_batch_routes(routes, n_theta, n_rho, flags, shape, events, kernels):
+    rc, log = routes(f"""
+c = context(n_theta, n_rho, {flags})
+if shape: assert L.hough_set_batch_plan(c, *shape) == 0
+out = batch(c, events)""", n_theta=n_theta, n_rho=n_rho, shape=shape, events=events)
+    assert rc == 0 and log == kernels
+
+
+def test_a_refused_shape_leaves_the_routes_alone(routes):
+    out = routes("""
+c = context(360, 256)
+rc = L.hough_set_batch_plan(c, 5, 1, 0), L.hough_set_batch_plan(c, 8, 1, 90)
+out = [rc, plan(c), batch(c, 16)]""")
+    assert out[0] == [-1, -1] and out[1] == [8, 1, 4, 0] and out[2] == [0, ["k_batch_split<16,0,0>", "k_spill"]]
+
+
+def test_the_latency_form_runs_by_tile_whatever_the_shape(routes):
+    rc, log = routes("""
+c = context(1000, 2000)
+assert L.hough_set_batch_plan(c, 8, 1, 0) == 0
+out = split(c, 16)""")
+    assert rc == 0 and log == ["k_batch_split<16,0,1>", "k_spill"]
