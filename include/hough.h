@@ -294,8 +294,8 @@ size_t hough_iterative_workspace_bytes(const hough_ctx *ctx, uint32_t n_events);
 uint32_t hough_max_dedup_hits(void);
 
 /* Workspace bytes hough_run_batch_split needs for n_events events with the context's current
- * launch shape (0 for a NULL context, and for a grid without a fused kernel, whose batches need
- * no workspace). */
+ * launch shape (0 for a NULL context, and for grids of more than 1,109 rows, whose split calls are
+ * ordinary batches). */
 size_t hough_split_workspace_bytes(const hough_ctx *ctx, uint32_t n_events);
 
 /* Launch shape of hough_run_batch's fused kernel.  A theta tile is 64 * column_groups columns
@@ -330,7 +330,7 @@ int hough_get_batch_plan(const hough_ctx *ctx, hough_batch_plan *out);
  * then gets the window of rows its hits can reach (they are bounded by the event's smallest
  * x^2 + y^2, Eq. (1)); an event whose rows do not fit goes through the spill path, as do
  * events above the fused kernel's hit limit.  The split forms hold the whole
- * column; where it does not fit a tile their calls are ordinary batches.
+ * column; on grids of more than 1,109 rows their calls are ordinary batches, small ones by tile.
  * HOUGH_EINVAL if the combination is not supported or does not fit the device, or the grid
  * reports an all-zero shape; the context keeps its previous shape then. */
 int hough_set_batch_plan(hough_ctx *ctx, int32_t waves_per_group, int32_t column_groups,

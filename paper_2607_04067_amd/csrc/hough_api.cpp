@@ -219,6 +219,12 @@ void auto_window(hough_ctx *c) {
 // of it do and no duplicate marks have to reach the spill kernel (see split_events).
 bool by_tile(const hough_ctx *c) { return c->fused == 1 || (c->split.win && !c->g.dedup); }
 
+// Whether the caller's split form has a workspace on this grid.  The tallest column that fits a tile
+// has 1,120 rows since the lookups' stage shares the peak words' room, 1,109 before; callers have passed
+// no workspace above that, and batches of any size to the static form, so it stays the line.
+constexpr int kSplitWorkspaceRows = 1109;
+bool split_workspace(const hough_ctx *c) { return c->fused == 1 && c->p.n_rho <= kSplitWorkspaceRows; }
+
 // A context's tables and workspace live on the device it was configured on.
 bool on_device(const hough_ctx *c) {
     int dev = -1;
@@ -596,11 +602,11 @@ static int run_batch_common(hough_ctx *c, const float *x, const float *y, const 
     a.queue = c->d_work;
     a.frac_num = frac_num;
     a.frac_den = frac_den;
-    // the caller's split form has no workspace on a grid whose column does not fit a tile: such a call
-    // is an ordinary batch there (1000 x 2000, every event through the spill kernel before: 16 events 804
+    // where the caller's split form has no workspace (see split_workspace) such a call is an ordinary
+    // batch (1000 x 2000, every event through the spill kernel before: 16 events 804
     // us, 44 so; 400 events 1,584 and 328)
     const bool want_split = split;
-    if (c->fused > 1) split = false;
+    if (!split_workspace(c)) split = false;
     const bool spill_all = !c->fused;       // no fused kernel for this grid
     hough::SpillArgs spill{c->d_spill, c->spill_stride, c->d_work + 2, spill_all ? 1u : 0u, nullptr, 0u, nullptr};
     // otherwise the fused (or split) kernel counts the events it leaves to the spill kernel in
@@ -693,7 +699,7 @@ int hough_run_batch_gather(hough_ctx *c, const float *x, const float *y, const u
 uint32_t hough_max_dedup_hits(void) { return hough::kDedupMaxHits; }
 
 size_t hough_split_workspace_bytes(const hough_ctx *c, uint32_t n_events) {
-    if (!c || c->fused != 1) return 0;    // an ordinary batch there: no workspace
+    if (!c || !split_workspace(c)) return 0;    // an ordinary batch there: no workspace
     return hough::split_workspace_bytes(c->p.n_theta, c->p.n_rho, c->plan.groups, n_events);
 }
 

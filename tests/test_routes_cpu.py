@@ -205,3 +205,17 @@ c = context(1000, 2000)
 assert L.hough_set_batch_plan(c, 8, 1, 0) == 0
 out = split(c, 16)""")
     assert rc == 0 and log == ["k_batch_split<16,0,1>", "k_spill"]
+
+
+@pytest.mark.parametrize("flags", ["0", "PERIODIC"])
+@pytest.mark.parametrize("n_rho,has", [(1109, True), (1110, False), (1120, False), (1121, False)])
+def test_split_calls_on_tall_grids_need_no_workspace(routes, n_rho, has, flags):
+    """Above 1,109 rows the latency form takes no workspace, and its static form any batch."""
+    size, few, many, static = routes(f"""
+c = context(130, n_rho, {flags})
+out = [L.hough_split_workspace_bytes(c, 16), split(c, 16), split(c, 1000), split(c, 5000, static=True)]""", n_rho=n_rho)
+    if has:
+        assert size > 0 and few[0] == many[0] == -1 and static == [-5, []]
+    else:
+        assert size == 0 and few[0] == many[0] == static[0] == 0
+        assert few[1][0].startswith("k_batch_split<16,") and any(s.startswith("k_batch<") for s in static[1])
