@@ -122,10 +122,12 @@ typedef struct hough_ctx hough_ctx;   /* opaque; owned by the library */
  * rounded once to float) and upload them, and allocate the workspace on the current device.
  * On success *out receives a new context.  Returns HOUGH_EINVAL for a bad grid or parameter
  * (including n_rho above hough_max_n_rho()), HOUGH_ENOMEM / HOUGH_EDEVICE on allocation or
- * copy failure.  The workspace includes the spill path's per-event slices (peak counts, peak
- * masks and places, dilated bits: about 2.4 bytes per grid cell; see hough_run_batch): a few
- * events' worth, or for a grid taller than the fused kernel's tile one event's worth per CU up
- * to 2 GiB (fewer where the device has not that much free). */
+ * copy failure.  The workspace includes 32 MiB for the mapped hits of the events the fused kernel has
+ * in flight, on grids that have one (where the device has not that much free the hits are mapped once
+ * per theta tile instead), about 1 MiB of lists and schedules, and the spill path's per-event slices
+ * (peak counts, peak masks and places, dilated bits: about 2.4 bytes per grid cell; see
+ * hough_run_batch): a few events' worth, or for a grid taller than the fused kernel's tile one event's
+ * worth per CU up to 2 GiB (fewer where the device has not that much free). */
 int hough_config(const hough_params *p, hough_ctx **out);
 
 /* Release a context (waits for nothing: the caller must have finished its work on it). */

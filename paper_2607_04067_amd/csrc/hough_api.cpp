@@ -30,7 +30,7 @@ struct hough_ctx {
                             // has not set one (win 0: none), see auto_window
     int chosen;             // the caller has set a launch shape
     uint32_t *d_defer;      // [kOrderMaxEvents] the events that did not fit its window
-    float *d_uv;            // [kMappedFloats] the fused kernel's mapped hits, shared out by launch
+    float *d_uv;            // [kMappedFloats] the fused kernel's mapped hits, shared out by launch (null: none)
     hough::SplitPlan split; // the split form's (whole columns, or windows on taller grids)
     uint32_t *d_slots;      // its slots for batches of up to split_events() events
     int fused;              // 1: the fused kernel holds the grid's whole column (and windows of it);
@@ -320,9 +320,14 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         c->fused ? kMappedFloats * sizeof(float) : 0};                                           // d_uv
     size_t at[9] = {0};
     for (int i = 0; i < 8; ++i) at[i + 1] = (at[i] + sizes[i] + 255) & ~(size_t)255;
+    bool mapped = c->fused != 0;
     if (hipMalloc(&c->d_block, at[8]) != hipSuccess) {
-        delete c;
-        return HOUGH_ENOMEM;
+        (void)hipGetLastError();             // clear the failed allocation's error
+        mapped = false;                      // without the room for mapped hits, then
+        if (at[8] == at[7] || hipMalloc(&c->d_block, at[7]) != hipSuccess) {
+            delete c;
+            return HOUGH_ENOMEM;
+        }
     }
     c->d_work = reinterpret_cast<uint32_t *>(c->d_block + at[0]);
     c->d_slots = reinterpret_cast<uint32_t *>(c->d_block + at[1]);
@@ -331,7 +336,7 @@ int hough_config(const hough_params *p, hough_ctx **out) {
     c->d_iter_list = reinterpret_cast<uint64_t *>(c->d_block + at[4]);
     c->d_order = reinterpret_cast<uint32_t *>(c->d_block + at[5]);
     c->d_defer = reinterpret_cast<uint32_t *>(c->d_block + at[6]);
-    c->d_uv = reinterpret_cast<float *>(c->d_block + at[7]);
+    c->d_uv = mapped ? reinterpret_cast<float *>(c->d_block + at[7]) : nullptr;
     c->spill_stride = hough::spill_stride(p->n_theta, p->n_rho);
     c->spill_wgs = spill_workgroups(c->spill_stride, c->n_cu, c->fused != 1);
     // fewer slices where the device cannot spare the budget

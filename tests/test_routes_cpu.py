@@ -219,3 +219,15 @@ out = [L.hough_split_workspace_bytes(c, 16), split(c, 16), split(c, 1000), split
     else:
         assert size == 0 and few[0] == many[0] == static[0] == 0
         assert few[1][0].startswith("k_batch_split<16,") and any(s.startswith("k_batch<") for s in static[1])
+
+
+def test_a_context_does_without_the_room_for_mapped_hits(routes):
+    """Where the device cannot spare the 32 MiB a context is made without them (and batches run); where
+    it cannot spare the rest either, none is."""
+    out = routes("""
+FAKE.fake_largest_malloc(ctypes.c_size_t(32 << 20))
+out = [batch(context(360, 256), 1000)]
+FAKE.fake_largest_malloc(ctypes.c_size_t(4096))
+p, c = Params(360, 256, -0.01, 0.01, 2, 10, 1, 64, 0, 0), vp()
+out.append([L.hough_config(ctypes.byref(p), ctypes.byref(c)), c.value])""")
+    assert out[0] == [0, ["k_batch<8,1,0,0,0>", "k_spill"]] and out[1] == [-2, None]
