@@ -379,3 +379,111 @@ def test_batch_finder_tiles(H, orc, n_theta, n_rho, rng_lo, rng_hi, dedup):
                 assert bool(st[e] & H.EV_PEAKS_TRUNCATED) == (n_ref[i] > cap)
             assert npk[3] == 0 and st[3] == H.EV_TOO_MANY_HITS and not kp[off[3]:off[4]].any()
         ctx.close()
+
+
+PLANS = [(w, g, 0) for w in (4, 6, 8, 12, 16) for g in (1, 2)] + [(8, 1, 2), (4, 1, 3)]
+
+
+@pytest.mark.parametrize("grid", VOTE_GRIDS + [(200, 530, -1 / 170, 1 / 170, 160.0),
+                                               (130, 1000, -0.01, 0.01, 210.0)])
+@pytest.mark.parametrize("flags", ["plain", "periodic", "dedup"])
+def test_every_fused_shape_equals_the_oracle(H, orc, grid, flags):
+    """A set shape runs the fused kernel whatever the number of events: every count of waves and column
+    groups, whole columns and windows of them, with events at the edges of its blocks of hits, an empty one
+    and the largest it takes, narrow and wide retention windows, and rho ranges of every mix of votes in
+    and out of the grid."""
+    n_theta, n_rho, lo, hi, r_lo = grid
+    periodic, dedup = flags == "periodic", flags == "dedup"
+    if periodic and lo != -hi:
+        pytest.skip("a periodic grid is symmetric")
+    sizes = [1, 7, 9, 64, 65, 513, 520, 0, 2600, 8192 if dedup else 32767]
+    x, y, off = _events(sizes, 41, r_lo, 0.02)
+    a = int(off[8])
+    x[a + 300:a + 700], y[a + 300:a + 700] = x[a:a + 400], y[a:a + 400]           # copies
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    xt, yt, ot = _t(x), _t(y), _t(off.astype(np.int32))
+    for T, W in ((1, 1), (4, 40), (9, 300), (12, 0)):
+        cap = 6000
+        ref, n_ref, keep_ref = orc.run_batch(g, x, y, off, threshold=T, rho_window=W, cap=cap, n_threads=8,
+                                             periodic=periodic, dedup=dedup)
+        ctx = H.Context(n_theta, n_rho, lo, hi, "i32", T, W, cap, periodic=periodic, dedup=dedup)
+        tried = 0
+        for plan in PLANS:
+            try:
+                ctx.set_batch_plan(*plan)
+            except H.HoughError:
+                continue
+            tried += 1
+            pk, npk, keep, st = ctx.run_batch(xt, yt, ot)
+            p = pk.cpu().numpy()
+            assert np.array_equal(npk.cpu().numpy()[:len(sizes)].astype(np.int64), n_ref), (plan, T, W)
+            assert np.array_equal(keep.cpu().numpy()[:x.size], keep_ref), (plan, T, W)
+            for e in range(len(sizes)):
+                m = int(min(n_ref[e], cap))
+                assert np.array_equal(H.decode_peaks(p[e], m), ref[e, :m].astype(np.int64)), (plan, T, W, e)
+        assert tried >= (11 if n_rho < 531 else 5)             # (two groups: up to some 550 rows)
+        ctx.close()
+
+
+@pytest.mark.parametrize("flags", ["plain", "periodic", "dedup"])
+@pytest.mark.parametrize("frac", [None, (1, 2)])
+def test_events_around_the_room_for_mapped_hits(H, orc, flags, frac):
+    """A launch of 1,024 workgroups leaves each room for 4,096 mapped hits: in a larger event the first
+    waves read theirs back on the later tiles while the others map the hits again.  Events on both sides
+    of the room, up to the largest the kernel takes, among many small ones."""
+    import torch
+    periodic, dedup = flags == "periodic", flags == "dedup"
+    n_theta, n_rho, lo, hi = 190, 96, -1 / 180, 1 / 180
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    large = [4095, 4096, 4097, 4103, 4104, 4600, 5000, 7000, 8191, 8192] + ([] if dedup else [8193, 10000, 20000, 32767])
+    rng = np.random.default_rng(3)
+    sizes = np.concatenate([large * 3, rng.integers(0, 40, 4 * cu + 30 - 3 * len(large))])
+    sizes = sizes[rng.permutation(sizes.size)]
+    x, y, off = _events([int(n) for n in sizes], 71, 170.0, 0.01)
+    for e in np.nonzero(sizes > 4000)[0]:                      # copies, and a run of hits no kernel votes
+        a = int(off[e])
+        x[a + 3000:a + 3200], y[a + 3000:a + 3200] = x[a:a + 200], y[a:a + 200]
+        x[a + 3900:a + 4000] = np.nan
+    T, cap = 12, 2000
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", T, 1, cap, periodic=periodic, dedup=dedup)
+    ctx.set_batch_plan(8, 1, 4)
+    xt, yt, ot = _t(x), _t(y), _t(off.astype(np.int32))
+    ref, n_ref, keep_ref = orc.run_batch(orc.Grid(n_theta, n_rho, lo, hi), x, y, off, threshold=T, rho_window=1, cap=cap,
+                                         n_threads=8, periodic=periodic, dedup=dedup, frac=frac)
+    for _ in range(2):
+        pk, npk, keep, st = ctx.run_batch(xt, yt, ot, frac=frac)
+        p = pk.cpu().numpy()
+        assert np.array_equal(npk.cpu().numpy()[:sizes.size].astype(np.int64), n_ref)
+        assert np.array_equal(keep.cpu().numpy()[:x.size], keep_ref)
+        for e in range(sizes.size):
+            m = int(min(n_ref[e], cap))
+            assert np.array_equal(H.decode_peaks(p[e], m), ref[e, :m].astype(np.int64)), e
+    ctx.close()
+
+
+@pytest.mark.parametrize("dedup", [False, True])
+def test_batch_finder_over_several_passes(H, orc, dedup):
+    """A grid of 65,535 columns takes 64 events at a time: 130 events are three passes, each on its own
+    part of the offsets, the workspace and the outputs, over the same heads."""
+    import torch
+    n_theta, n_rho, lo, hi = 65535, 3, -1 / 170, 1 / 170
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    E = 130
+    sizes = [(37 * e) % 90 for e in range(E)]
+    x, y, off = _events(sizes, 19, 160.0, 0.02)
+    a = int(off[2])
+    x[a:a + 30], y[a:a + 30] = x[a + 30:a + 60], y[a + 30:a + 60]
+    cap, floor, frac = 16, 20, (9, 10)
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", floor, 0, cap, dedup=dedup)
+    ref, n_ref, keep_ref = orc.run_batch_iterative_fast(g, x, y, off, floor, frac, 4000, 1, 0, cap, dedup=dedup, n_threads=8)
+    assert (n_ref[64:] > 0).any() and (n_ref[128:] >= 0).all()
+    pk, npk, keep, st = ctx.run_batch_iterative(_t(x), _t(y), _t(off.astype(np.int32)), frac, 4000, 1,
+                                                ctx.iterative_workspace(E))
+    torch.cuda.synchronize()
+    p = pk.cpu().numpy()
+    assert np.array_equal(npk.cpu().numpy()[:E].astype(np.int64), n_ref)
+    assert np.array_equal(keep.cpu().numpy()[:x.size], keep_ref)
+    for e in range(E):
+        m = int(min(n_ref[e], cap))
+        assert np.array_equal(H.decode_peaks(p[e], m), ref[e, :m].astype(np.int64)), e
+    ctx.close()
