@@ -575,7 +575,7 @@ int hough_retain(hough_ctx *c, const float *x, const float *y, uint32_t n_hits,
     if (!on_device(c)) return HOUGH_EINVAL;
     if (n_hits && (!x || !y || !keep)) return HOUGH_EINVAL;
     if (((uintptr_t)peaks & 7u) != 0) return HOUGH_EINVAL;
-    const hipError_t e = hough::launch_retain(c->g, x, y, n_hits, peaks, n_peaks, cap, keep,
+    const hipError_t e = hough::launch_retain(c->g, x, y, n_hits, peaks, n_peaks, cap, keep, c->n_cu,
                                               (hipStream_t)stream);
     return e == hipSuccess ? HOUGH_OK : HOUGH_EDEVICE;
 }

@@ -205,7 +205,7 @@ hipError_t launch_peaks(const GridArgs &g, const void *acc, int acc_type, hough_
                         uint32_t cap, uint32_t *n_peaks, uint32_t *counts, hipStream_t s);
 hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
                          const hough_peak *peaks, const uint32_t *n_peaks, uint32_t cap,
-                         uint8_t *keep, hipStream_t s);
+                         uint8_t *keep, int n_cu, hipStream_t s);
 hipError_t launch_batch(const GridArgs &g, const BatchPlan &p, const BatchArgs &a, hipStream_t s);
 hipError_t launch_batch_split(const GridArgs &g, const SplitPlan &p, const BatchArgs &a, const SplitArgs &sp,
                               int n_cu, hipStream_t s);

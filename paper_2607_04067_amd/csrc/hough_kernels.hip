@@ -2047,8 +2047,10 @@ __global__ __launch_bounds__(kTrackWaves * 64) void k_track_params(GridArgs g, c
 //     of words per column (different words of a column lie in different banks) and a zero one
 //     after its last, beside the columns' constants, and every lane looks its own bin up in one
 //     column after the other, until all 64 hits are kept.
-// One event (SPLIT): a workgroup takes 64 hits and its 16 waves share the peaks or the columns,
-// since the hits alone would leave most of the chip idle.  A batch (offsets given): workgroup
+// SHARE of the workgroup's 16 waves share each 64 hits, a part of the peaks or the columns each.  A few
+// hits leave most of the chip idle otherwise; the more hits there are the fewer waves share them, down
+// to one, which stops at the column that keeps the last of its hits (see launch_retain).
+// A batch (offsets given, SHARE 1): workgroup
 // (e, b) takes event e's chunks b * 16 + wave, + 16 * gridDim.y, ..., each wave a chunk; event
 // e's peaks are at peaks + e * cap, n_peaks[e]; the keep bytes of an event the vote skipped for
 // its size are zeroed (malformed offsets: nothing is touched).
@@ -2067,11 +2069,13 @@ __device__ __forceinline__ uint64_t kept_in_columns(const uint32_t *dil, const f
     const uint32_t zero_row = ((uint32_t)g.n_rho + 31u) & ~31u;
     uint32_t m = 0;
     uint64_t kept = 0;
-    for (int j = 0; j < n; j += 8) {
+    // rounds of 8 columns, evenly spaced: neighbouring columns mostly keep the same hits
+    const int rounds = (n + 7) / 8;
+    for (int r = 0; r < rounds; ++r) {
         uint32_t word[8], k[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int jj = min(j + i, n - 1);
+            const int jj = min(r + i * rounds, n - 1);
             const float2 c = cs[jj];
             const float t = __builtin_fmaf(u, c.x, __builtin_fmaf(v, c.y, g.Bf));
             // a bin outside the grid looks at the column's zero word
@@ -2086,7 +2090,7 @@ __device__ __forceinline__ uint64_t kept_in_columns(const uint32_t *dil, const f
     return kept;
 }
 
-template <bool SPLIT>
+template <int SHARE>
 __global__ __launch_bounds__(kRetainWaves * 64) void k_retain(GridArgs g, const float *__restrict__ x,
                                                               const float *__restrict__ y, uint32_t n_hits,
                                                               const hough_peak *__restrict__ peaks,
@@ -2094,6 +2098,7 @@ __global__ __launch_bounds__(kRetainWaves * 64) void k_retain(GridArgs g, const 
                                                               uint8_t *keep, int cols_per_block,
                                                               const uint32_t *offsets) {
     constexpr int NT = kRetainWaves * 64;
+    constexpr uint32_t PER = kRetainWaves / SHARE;             // chunks of 64 hits a workgroup takes at a time
     // the block's columns: constants [cols_per_block], dilated bits [cols_per_block][pitch]
     extern __shared__ __align__(16) float2 cs[];
     uint32_t *dil = reinterpret_cast<uint32_t *>(cs + cols_per_block);
@@ -2101,7 +2106,7 @@ __global__ __launch_bounds__(kRetainWaves * 64) void k_retain(GridArgs g, const 
     __shared__ uint64_t s_kept[kRetainWaves];
     __shared__ uint32_t s_edge;
     const int lane = threadIdx.x & 63, wave = wave_id();
-    if (!SPLIT) {
+    if (SHARE == 1 && offsets) {
         const uint32_t e = blockIdx.x, h0 = offsets[e], h1 = offsets[e + 1];
         if (h1 < h0) return;
         if (h1 - h0 > kMaxBatchHits) {
@@ -2116,21 +2121,21 @@ __global__ __launch_bounds__(kRetainWaves * 64) void k_retain(GridArgs g, const 
         peaks += (size_t)e * cap;
         n_peaks += e;
     }
-    // this wave's chunks of 64 hits
+    // the workgroup's chunks of 64 hits, this wave's among them, and its part of the work on it
     const uint32_t chunks = n_hits / 64u + (n_hits % 64u != 0u);
-    const uint32_t chunk0 = SPLIT ? blockIdx.x : blockIdx.y * kRetainWaves + (uint32_t)wave;
-    const uint32_t step = SPLIT ? gridDim.x : gridDim.y * kRetainWaves;
+    const uint32_t first = blockIdx.y * PER, step = gridDim.y * PER, mine = (uint32_t)(wave / SHARE);
+    const int part = wave % SHARE;
     const uint32_t np = min(*n_peaks, cap);
     const uint2 *pk = reinterpret_cast<const uint2 *>(peaks);
     const bool listed = np <= kRetainList;
     const uint32_t pitch = retain_pitch(g.n_rho);
     const int W = g.rho_window;
     if (threadIdx.x == 0) s_edge = 0u;
-    // a split workgroup's first hits, on their way while the peaks are laid out
+    // the first hits, on their way while the peaks are laid out
     float x0 = 0.0f, y0 = 0.0f;
-    if (SPLIT && chunk0 * 64u + (uint32_t)lane < n_hits) {
-        x0 = x[chunk0 * 64u + lane];
-        y0 = y[chunk0 * 64u + lane];
+    if (SHARE > 1 && (first + mine) * 64u + (uint32_t)lane < n_hits) {
+        x0 = x[(first + mine) * 64u + lane];
+        y0 = y[(first + mine) * 64u + lane];
     }
     __syncthreads();
     for (int ja = 0; ja < (listed ? 1 : g.n_theta); ja += cols_per_block) {
@@ -2170,20 +2175,19 @@ __global__ __launch_bounds__(kRetainWaves * 64) void k_retain(GridArgs g, const 
         }
         __syncthreads();
         const bool edge = s_edge != 0u;
-        // a split chunk's share of this wave
-        const uint32_t p0 = SPLIT ? np * (uint32_t)wave / kRetainWaves : 0u;
-        const uint32_t p1 = SPLIT ? np * (uint32_t)(wave + 1) / kRetainWaves : np;
-        const int c0 = SPLIT ? jn * wave / kRetainWaves : 0, c1 = SPLIT ? jn * (wave + 1) / kRetainWaves : jn;
-        // (every wave of a split workgroup sees the same chunks, so the barriers below are uniform)
-        for (uint32_t c = chunk0; c < chunks; c += step) {
-            const uint32_t i = c * 64u + (uint32_t)lane;
+        const uint32_t p0 = np * (uint32_t)part / SHARE, p1 = np * (uint32_t)(part + 1) / SHARE;
+        const int c0 = jn * part / SHARE, c1 = jn * (part + 1) / SHARE;
+        // (every wave goes round as often as the others, so the barriers below are uniform)
+        for (uint32_t cb = first; cb < chunks; cb += step) {
+            const uint32_t i = (cb + mine) * 64u + (uint32_t)lane;
+            const bool in = cb + mine < chunks && i < n_hits;
             float xi = x0, yi = y0;
-            if (!(SPLIT && c == chunk0)) {
+            if (!(SHARE > 1 && cb == first)) {
                 xi = yi = 0.0f;
-                if (i < n_hits) { xi = x[i]; yi = y[i]; }
+                if (in) { xi = x[i]; yi = y[i]; }
             }
             float u, v;
-            const bool valid = conformal(xi, yi, u, v) && i < n_hits;
+            const bool valid = conformal(xi, yi, u, v) && in;
             const uint64_t want = __ballot(valid);
             uint64_t kept = 0;
             if (listed) {
@@ -2197,21 +2201,21 @@ __global__ __launch_bounds__(kRetainWaves * 64) void k_retain(GridArgs g, const 
                 else if (want)
                     kept = kept_in_columns<false>(d, cs + c0, pitch, um, vm, want, c1 - c0, g);
             }
-            if (SPLIT) {
+            if (SHARE > 1) {
                 if (lane == 0) s_kept[wave] = kept;
                 __syncthreads();
-                if (wave == 0) {
+                if (part == 0) {
 #pragma unroll
-                    for (int w = 1; w < kRetainWaves; ++w) kept |= s_kept[w];
+                    for (int w = 1; w < SHARE; ++w) kept |= s_kept[wave + w];
                 }
             }
             // later blocks of columns only add to the verdicts
-            if ((!SPLIT || wave == 0) && i < n_hits) {
+            if (part == 0 && in) {
                 const bool k_me = (kept >> lane) & 1ull;
                 if (ja == 0) keep[i] = k_me ? 1u : 0u;
                 else if (k_me) keep[i] = 1u;
             }
-            if (SPLIT) __syncthreads();
+            if (SHARE > 1) __syncthreads();
         }
     }
 }
@@ -3658,19 +3662,37 @@ hipError_t launch_track_params(const GridArgs &g, const float *x, const float *y
     return hipGetLastError();
 }
 
-hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
-                         const hough_peak *peaks, const uint32_t *n_peaks, uint32_t cap,
-                         uint8_t *keep, hipStream_t s) {
-    if (n_hits == 0) return hipSuccess;
+template <int SHARE>
+static hipError_t launch_retain_t(const GridArgs &g, const float *x, const float *y, uint32_t n_hits, uint32_t chunks,
+                                  const hough_peak *peaks, const uint32_t *n_peaks, uint32_t cap, uint8_t *keep,
+                                  int n_cu, hipStream_t s) {
     const int cols = retain_cols_per_block(g);
-    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<true>),
+    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<SHARE>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kRetainDilBytes);
     if (lds_ok != hipSuccess) return lds_ok;
-    // one workgroup per 64 hits up to twice the chip, then several chunks per built block
-    const uint32_t chunks = n_hits / 64u + (n_hits % 64u != 0u);
-    hipLaunchKernelGGL(k_retain<true>, dim3(std::min(chunks, 512u)), dim3(kRetainWaves * 64),
-                       retain_lds_bytes(g, cols), s, g, x, y, n_hits, peaks, n_peaks, cap, keep, cols, nullptr);
+    constexpr uint32_t per = kRetainWaves / SHARE;
+    const uint32_t blocks = std::min(chunks / per + (chunks % per != 0u), 2u * (uint32_t)n_cu);
+    hipLaunchKernelGGL(k_retain<SHARE>, dim3(1, blocks), dim3(kRetainWaves * 64), retain_lds_bytes(g, cols), s, g, x, y,
+                       n_hits, peaks, n_peaks, cap, keep, cols, nullptr);
     return hipGetLastError();
+}
+
+// As many waves share 64 hits as leave at most one workgroup per CU; where one wave each leaves more,
+// two workgroups per CU take several chunks per built block.  A lookup reads LDS at random words, so
+// the columns looked at cost the time, and a wave that has all of them stops early: us at 16, 8, 4, 2
+// and 1 waves per 64 hits (720 x 512, 7,000 to 9,000 peaks, 256 CUs, columns in order) 32,000 hits 21,
+// 16, 24, 35, 44; 64,000: 32, 30, 24, 36, 44; 128,000: 51, 48, 46, 38, 47; 256,000: 88, 82, 78, 77, 54;
+// 1,000,000: 284, 262, 249, 240, 150.
+hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
+                         const hough_peak *peaks, const uint32_t *n_peaks, uint32_t cap,
+                         uint8_t *keep, int n_cu, hipStream_t s) {
+    if (n_hits == 0) return hipSuccess;
+    const uint32_t chunks = n_hits / 64u + (n_hits % 64u != 0u), cu = (uint32_t)n_cu;
+    if (chunks <= cu) return launch_retain_t<16>(g, x, y, n_hits, chunks, peaks, n_peaks, cap, keep, n_cu, s);
+    if (chunks <= 2 * cu) return launch_retain_t<8>(g, x, y, n_hits, chunks, peaks, n_peaks, cap, keep, n_cu, s);
+    if (chunks <= 4 * cu) return launch_retain_t<4>(g, x, y, n_hits, chunks, peaks, n_peaks, cap, keep, n_cu, s);
+    if (chunks <= 8 * cu) return launch_retain_t<2>(g, x, y, n_hits, chunks, peaks, n_peaks, cap, keep, n_cu, s);
+    return launch_retain_t<1>(g, x, y, n_hits, chunks, peaks, n_peaks, cap, keep, n_cu, s);
 }
 
 // The iterative finder's batch form: (duplicate pass), votes into each tile's candidates (or
@@ -3690,7 +3712,7 @@ hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_
     static const hipError_t vote_ok =
         hipFuncSetAttribute(reinterpret_cast<const void *>(k_vote_batch<kIterVoteWaves>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (kIterSlabRows + 1) * 128);
-    static const hipError_t retain_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<false>),
+    static const hipError_t retain_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<1>),
                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kRetainDilBytes);
     if (vote_ok != hipSuccess) return vote_ok;
     if (retain_ok != hipSuccess) return retain_ok;
@@ -3714,7 +3736,7 @@ hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_
         if ((e = hipGetLastError()) != hipSuccess) return e;
         // a few events: several workgroups each, up to the largest event's chunks
         const uint32_t blocks = std::max(1u, std::min(most_blocks, 512u / n));
-        hipLaunchKernelGGL(k_retain<false>, dim3(n, blocks), dim3(kRetainWaves * 64), retain_lds_bytes(g, cols), s, g,
+        hipLaunchKernelGGL(k_retain<1>, dim3(n, blocks), dim3(kRetainWaves * 64), retain_lds_bytes(g, cols), s, g,
                            a.x, a.y, 0u, peaks, a.n_peaks + e0, a.max_peaks, a.keep, cols, off);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

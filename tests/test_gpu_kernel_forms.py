@@ -487,3 +487,33 @@ def test_batch_finder_over_several_passes(H, orc, dedup):
         m = int(min(n_ref[e], cap))
         assert np.array_equal(H.decode_peaks(p[e], m), ref[e, :m].astype(np.int64)), e
     ctx.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho,W", [(90, 64, 1), (300, 300, 2), (37, 2000, 1)])
+@pytest.mark.parametrize("chunks_per_cu", [1, 2, 4, 8, 20])
+def test_event_retain_large(H, orc, n_theta, n_rho, W, chunks_per_cu):
+    """hough_retain by the number of waves that share 64 hits (16 down to one, by the hits per CU): events
+    on both sides of each line, few peaks (listed) and many, most hits kept and few of them."""
+    import torch
+    lo, hi = -1 / 170, 1 / 170
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    edge = 64 * chunks_per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    x, y, _ = _events([edge + 65], 12, 160.0, 0.01)
+    xt, yt = _t(x), _t(y)
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", 3, W, 64)
+    rng = np.random.default_rng(chunks_per_cu)
+    for n in (3, 900, 1500, min(20000, n_theta * n_rho // 3)):
+        cell = rng.choice(n_theta * n_rho, n, replace=False)
+        pj, pk = cell // n_rho, cell % n_rho
+        if n == 1500:
+            pk[:] = rng.choice([0, 1, n_rho - 1], n)               # few hits near the rho edges
+        rec = np.zeros((n, 2), np.uint32)
+        rec[:, 0] = pj | (pk << 16)
+        recs, npk = _t(rec.view(np.int32)), _t(np.array([n], np.int32))
+        ref = orc.retain(g, x, y, pj, pk, W)
+        for m in (edge - 64, edge, edge + 1, edge + 65):
+            buf = torch.full((m + 1,), 7, dtype=torch.uint8, device="cuda")
+            keep = ctx.retain(xt[:m], yt[:m], recs, npk, n, buf[:m])
+            assert np.array_equal(keep.cpu().numpy(), ref[:m]), (n, m)
+            assert int(buf[m].item()) == 7
+    ctx.close()

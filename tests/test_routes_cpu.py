@@ -231,3 +231,12 @@ FAKE.fake_largest_malloc(ctypes.c_size_t(4096))
 p, c = Params(360, 256, -0.01, 0.01, 2, 10, 1, 64, 0, 0), vp()
 out.append([L.hough_config(ctypes.byref(p), ctypes.byref(c)), c.value])""")
     assert out[0] == [0, ["k_batch<8,1,0,0,0>", "k_spill"]] and out[1] == [-2, None]
+
+
+@pytest.mark.parametrize("hits,waves", [(1, 16), (64 * 256, 16), (64 * 256 + 1, 8), (64 * 512 + 1, 4), (64 * 1024, 4),
+                                        (64 * 1024 + 1, 2), (64 * 2048 + 1, 1), (10**6, 1), (2**32 - 1, 1)])
+def test_retention_of_one_event_fills_the_chip(routes, hits, waves):
+    """The waves that share 64 hits, by the hits per CU (256 of them here)."""
+    out = routes("out = journal(lambda: L.hough_retain(context(720, 512), X, X, u32(hits), X, X, u32(99999), X, None))",
+                 hits=hits)
+    assert out[0] == 0 and out[1][-1] == f"k_retain<{waves}>"
