@@ -199,8 +199,8 @@ hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_
                                   void *head, hipStream_t s);
 hipError_t launch_vote(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
                        void *acc, int acc_type, hipStream_t s);
-// counts: ceil(n_theta / kPeakRowsPerBlock) counters of device scratch (the context's).
-constexpr int kPeakRowsPerBlock = 16;
+// counts: a counter per workgroup, ceil(n_theta / g.peak_waves), of device scratch (the context's).
+constexpr int kPeakRowsPerBlock = 16;   // (at most: see peak_block_waves)
 hipError_t launch_peaks(const GridArgs &g, const void *acc, int acc_type, hough_peak *peaks,
                         uint32_t cap, uint32_t *n_peaks, uint32_t *counts, hipStream_t s);
 hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,

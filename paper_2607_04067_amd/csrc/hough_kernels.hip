@@ -1380,7 +1380,10 @@ __global__ __launch_bounds__(NW * 64) void k_vote_batch(GridArgs g, const float 
 // hough_peaks: workgroup b tests theta rows [NW*b, NW*b + NW), staged in LDS with one halo row
 // on each side, one wave per row, lanes over rho.  Two launches: the first writes each block's
 // peak count to counts[b]; the second lists each block's peaks at the sum of the earlier blocks'
-// counts plus the earlier waves' (raster order), and block 0 writes the total.
+// counts plus the earlier waves' (raster order), and block 0 writes the total.  Bound by latency: the
+// loads of the rows, then the counts.  (Eight loads per thread whatever the rows needed, each with its
+// 64-bit index and edge tests, made grids of many short columns slow: 4000 x 100 12.5 us, 8.2 so; 9000 x
+// 100 20.6 and 14.5; 65535 x 8 137 and 76; 1000 x 1000 21.2 and 18.8.)
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += (uint32_t)__shfl_xor((int)v, o, 64);
@@ -1402,24 +1405,33 @@ __global__ __launch_bounds__(NW * 64) void k_peaks(GridArgs g, const T *__restri
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int nr = g.n_rho;
     const int jb = (int)blockIdx.x * NW;
-    // the rows are one run of acc but for the grid's edges (zero, or on a periodic grid the other
-    // edge with rho reversed); eight loads in flight per thread
-    {
-        const int64_t q0 = (int64_t)(jb - 1) * nr, end = (int64_t)g.n_theta * nr;
-        constexpr int U = 8;
-        for (int i0 = threadIdx.x; i0 < (NW + 2) * nr; i0 += U * NW * 64) {
+    // The rows are one run of acc but for the grid's edges (zero, or on a periodic grid the other
+    // edge with rho reversed).  Up to eight loads in flight per thread, no more than the rows need.
+    const int total = (NW + 2) * nr, from = jb == 0 ? nr : 0, to = min(NW + 2, g.n_theta - jb + 1) * nr;
+    const T *src = acc + ((int64_t)jb - 1) * nr;
+    auto stage = [&](auto width) {
+        constexpr int U = decltype(width)::value;
+        for (int i0 = threadIdx.x; i0 < total; i0 += U * NW * 64) {
             uint32_t v[U];
 #pragma unroll
             for (int i = 0; i < U; ++i) {
                 const int idx = i0 + i * NW * 64;
-                int64_t q = q0 + idx;
-                if (g.periodic && q < 0) q = end - 1 - idx;                        // row -1: idx < nr
-                else if (g.periodic && q >= end) q = (int64_t)nr - 1 - (q - end);  // row n_theta (later ones: q < 0)
-                v[i] = idx < (NW + 2) * nr && q >= 0 && q < end ? (uint32_t)acc[q] : 0u;
+                v[i] = idx >= from && idx < to ? (uint32_t)src[idx] : 0u;
             }
 #pragma unroll
             for (int i = 0; i < U; ++i)
-                if (i0 + i * NW * 64 < (NW + 2) * nr) rows[i0 + i * NW * 64] = v[i];
+                if (i0 + i * NW * 64 < total) rows[i0 + i * NW * 64] = v[i];
+        }
+    };
+    if (total <= NW * 64) stage(std::integral_constant<int, 1>{});
+    else if (total <= 2 * NW * 64) stage(std::integral_constant<int, 2>{});
+    else if (total <= 4 * NW * 64) stage(std::integral_constant<int, 4>{});
+    else stage(std::integral_constant<int, 8>{});
+    if (g.periodic && (jb == 0 || to < total)) {
+        __syncthreads();
+        for (int k = threadIdx.x; k < nr; k += NW * 64) {
+            if (jb == 0) rows[k] = (uint32_t)acc[(int64_t)g.n_theta * nr - 1 - k];
+            if (to < total) rows[to + k] = (uint32_t)acc[nr - 1 - k];
         }
     }
     if (WRITE && wave == 0) {                     // peaks of the earlier blocks, and of all
@@ -3426,11 +3438,12 @@ size_t peaks_lds_bytes(int n_rho, int waves) {
     return (size_t)waves * ((n_rho + 63) / 64) * 8 + (size_t)(waves + 2) * n_rho * 4;
 }
 
-// Few rows per workgroup share one event's rows over more of the chip (one event, 720 x 512: 45
-// workgroups of 16 rows took 8 + 10 us, 180 of 4 take 6 + 8); every workgroup adds up all their counts, so grids of
-// many columns take more.
+// Few rows per workgroup share one event's rows over more of the chip; every workgroup adds up all
+// their counts and stages two halo rows, so grids of many columns take more (both launches, us at 4, 8
+// and 16 rows: 360 x 256 8.4, 8.4, 9.2; 1000 x 1000 19.2, 18.8, 20.2; 2000 x 100 8.7, 7.5, 7.4; 4000 x
+// 250 13.7, 11.4, 10.4; 4000 x 2000 72, 67, 38; 9000 x 100 22, 17, 15; 65535 x 8 273, 152, 76).
 int peak_block_waves(int n_theta, int n_rho, size_t lds_limit) {
-    for (int w = n_theta > 4096 ? kPeakWaves : 4; w >= 2; w >>= 1)
+    for (int w = n_theta <= 512 ? 4 : (n_theta <= 2048 ? 8 : kPeakWaves); w >= 2; w >>= 1)
         if (peaks_lds_bytes(n_rho, w) + 512 <= lds_limit) return w;
     return 0;
 }

@@ -517,3 +517,24 @@ def test_event_retain_large(H, orc, n_theta, n_rho, W, chunks_per_cu):
             assert np.array_equal(keep.cpu().numpy(), ref[:m]), (n, m)
             assert int(buf[m].item()) == 7
     ctx.close()
+
+
+# blocks of 4, 8 and 16 rows (up to 512, up to 2,048 and more columns; fewer where the rows are long), and
+# rows on both sides of what one, two and four loads per thread cover
+@pytest.mark.parametrize("n_theta,n_rhos", [(5, (42, 43, 85, 86, 170, 171)), (512, (9,)), (513, (9, 51, 52, 102, 103)),
+                                            (521, (204, 205)), (2048, (20,)), (2049, (20, 56, 57, 113, 114)),
+                                            (2063, (227, 228)), (600, (3000,)), (2050, (1900,)), (65535, (8,))])
+@pytest.mark.parametrize("acc_type", ["i32", "u16"])
+def test_event_peaks_staging(H, orc, n_theta, n_rhos, acc_type):
+    rng = np.random.default_rng(n_theta)
+    for n_rho in n_rhos:
+        acc = rng.integers(0, 9, (n_theta, n_rho)).astype(np.int32)
+        acc[0, :], acc[-1, :] = rng.integers(5, 12, n_rho), rng.integers(5, 12, n_rho)      # the wrapped border
+        for periodic in (False, True):
+            ctx = H.Context(n_theta, n_rho, -0.005, 0.005, acc_type, 5, 1, 64, periodic=periodic)
+            pj, pk, pc, m = orc.peaks(acc, 5, periodic=periodic)
+            cap = m + 3
+            got, n = ctx.peaks(_t(acc.astype(np.uint16).view(np.int16) if acc_type == "u16" else acc), cap)
+            assert int(n.item()) == m, (n_rho, periodic)
+            assert np.array_equal(H.decode_peaks(got, m), np.stack([pj, pk, pc], 1).astype(np.int64)), (n_rho, periodic)
+            ctx.close()
