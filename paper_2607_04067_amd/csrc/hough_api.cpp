@@ -152,11 +152,9 @@ int default_plan(hough_ctx *c) {
 // beyond the window go to the spill kernel.
 int windowed_plan(const hough_ctx *c, int waves, int groups, int groups_per_cu, hough::BatchPlan *out) {
     if (groups != 1) return -1;
-    const bool need_split = c->fused == 1;
     for (int win = ((c->p.n_rho - 1) / 32) * 32; win >= 32; win -= 32) {
         hough::BatchPlan p;
-        if (hough::plan_batch(c->p.n_theta, c->p.n_rho, waves, groups, c->lds_limit, &p, win, need_split) != 0)
-            continue;
+        if (hough::plan_batch(c->p.n_theta, c->p.n_rho, waves, groups, c->lds_limit, &p, win) != 0) continue;
         p.periodic = c->g.periodic;
         p.per_cu = hough::prepare_batch(&p);
         if (p.per_cu >= groups_per_cu) {

@@ -54,8 +54,6 @@ struct BatchPlan {
     int sparse;          // retention by peak list on tiles with few peaks (see kSparseRhoRows)
     int win;             // rows of a windowed tile (0: the tile holds the whole rho column)
     int periodic;        // a windowed plan for a theta-periodic grid
-    size_t split_lds_bytes;   // LDS of the whole column (a plan must leave room for it where the
-                              // grid has a split form)
 };
 // Waves per workgroup of the split form: for batches of at most one (event, tile) item per CU, and
 // for larger ones (0: the whole column does not fit).  win: rows of its windows where only windows
@@ -116,8 +114,6 @@ uint32_t tile_batch_events(const hough_ctx *c);
 int suggest_shape(hough_ctx *c, int32_t waves_per_group, int32_t column_groups, int32_t groups_per_cu);
 SplitPlan plan_split(int n_rho, size_t lds_limit);
 SplitPlan plan_split_window(int win, size_t lds_limit);
-// Keep words per event in the split form's workspace size.
-constexpr uint32_t kSplitKeepWords = (kMaxBatchHits + 31) / 32 + 1;
 size_t split_workspace_bytes(int n_theta, int n_rho, int groups, uint32_t n_events);
 bool split_layout(int n_theta, int n_rho, int groups, uint32_t n_events, void *ws, size_t bytes,
                   SplitArgs *out);
@@ -184,7 +180,6 @@ struct IterPlan {
     uint32_t keys;
     int gbm;
     size_t lds_bytes;    // dynamic LDS per workgroup
-    size_t sp_lds_bytes; // the same with the peak list (sparse grids, relative launches)
     size_t bm_bytes;     // bitmap bytes of one event (one bit per cell, whole 32-bit words)
 };
 // per_cu: workgroups per CU the plan should leave room for (the batch form runs one per event).
@@ -229,8 +224,7 @@ hipError_t launch_peaks_iterative(const GridArgs &g, const void *acc, int acc_ty
 constexpr uint32_t kIterScanKeys = 65536;
 // LDS of the fused kernel's workgroup: the whole column (win 0) or a window of win rows.
 size_t batch_lds_bytes(int n_rho, int waves, int groups, int win, bool sparse);
-int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, BatchPlan *out, int win = 0,
-               bool need_split = true);
+int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, BatchPlan *out, int win = 0);
 int prepare_batch(BatchPlan *p);
 
 }  // namespace hough

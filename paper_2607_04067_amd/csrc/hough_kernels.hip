@@ -1667,7 +1667,7 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(const T *__restrict_
 // HOUGH_EV_PEAKS_TRUNCATED into status[e] (which the batch vote wrote); events the vote skipped
 // get no peaks.  K: keys in the LDS buffer (a power of two, kIterMinKeys .. kIterMaxKeys).
 // gbm (GBM): device bitmaps of bm_words words, one per workgroup.
-// list, scan (one event, else null): what k_iter_scan left, in place of the first pass.
+// list, scan (one event, else null): what k_iter_scan left.
 template <typename T, bool GBM, bool BATCH>
 __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T *__restrict__ acc,
                                                              uint32_t frac_num, uint32_t frac_den, int r_theta,
@@ -1678,7 +1678,6 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
                                                              const uint2 *head) {
     extern __shared__ __align__(16) uint64_t keys[];       // [K]; the histograms reuse it as 2K words
     uint32_t *hist = reinterpret_cast<uint32_t *>(keys);
-    __shared__ uint32_t s_red[kIterWaves];
     __shared__ uint32_t s_n, s_m, s_first, s_taken;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t nr = (uint32_t)g.n_rho, nt = (uint32_t)g.n_theta;
@@ -1744,7 +1743,6 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     };
     const uint32_t floor_t = g.threshold;
     uint32_t mx = 0, thr, n1;
-    bool filtered;             // the keys held reach thr (else the floor)
     if constexpr (BATCH) {
         // the tiles' heads: the event's largest count, and where each tile's keys start
         uint32_t m = 0, run = 0;
@@ -1765,8 +1763,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         });
         __syncthreads();
         n1 = s_n;
-        filtered = true;
-    } else if (scan) {
+    } else {
         mx = scan[0];
         n1 = scan[1];
         thr = iter_threshold(mx, frac_num, frac_den, floor_t);
@@ -1779,21 +1776,6 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
             }
         __syncthreads();
         n1 = whole ? s_n : K + 1u;
-        filtered = true;
-    } else {
-        // pass 1: the maximum, and the candidates of the absolute floor while they fit
-        uint32_t m = 0;
-        each([&](uint32_t v, uint32_t r, bool in) {
-            m = max(m, v);
-            append_key(keys, &s_n, K, in && v >= floor_t, ((uint64_t)v << 32) | (uint64_t)(~r), lane);
-        });
-        m = wave_max(m);
-        if (lane == 0) s_red[wave] = m;
-        __syncthreads();
-        for (int w = 0; w < kIterWaves; ++w) mx = max(mx, s_red[w]);
-        thr = iter_threshold(mx, frac_num, frac_den, floor_t);
-        n1 = s_n;
-        filtered = thr == floor_t;
     }
     __syncthreads();
 
@@ -1802,20 +1784,8 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     bool have_chunk = false;
     uint32_t n = 0;
     uint64_t lo = 0;           // the chunk's lowest key (0: the chunk holds every candidate left)
-    if (n1 <= K) {
-        // every candidate is in LDS: keep those that reach thr, in place
-        if (!filtered) {
-            if (tid == 0) s_n = 0u;
-            __syncthreads();
-            for (uint32_t i0 = 0; i0 < n1; i0 += kIterThreads) {
-                const uint32_t i = i0 + tid;
-                const uint64_t key = i < n1 ? keys[i] : 0ull;
-                __syncthreads();
-                append_key(keys, &s_n, K, i < n1 && (uint32_t)(key >> 32) >= thr, key, lane);
-                __syncthreads();
-            }
-        }
-        n = s_n;
+    if (n1 <= K) {                       // every candidate is in LDS
+        n = n1;
         have_chunk = true;
     }
     for (;;) {
@@ -1979,7 +1949,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         *n_peaks = taken;
         const uint32_t tr = taken > cap ? HOUGH_EV_PEAKS_TRUNCATED : 0u;
         *status = BATCH ? (*status | tr) : tr;
-        if (scan) { scan[0] = 0u; scan[1] = 0u; }
+        if constexpr (!BATCH) { scan[0] = 0u; scan[1] = 0u; }
     }
 }
 
@@ -3460,8 +3430,7 @@ size_t batch_lds_bytes(int n_rho, int waves, int groups, int win, bool sparse) {
            (sparse ? kTilePeaks * sizeof(float4) : 0) + tw * 4;
 }
 
-int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, BatchPlan *out, int win,
-               bool need_split) {
+int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, BatchPlan *out, int win) {
     if (!(waves == 4 || waves == 6 || waves == 8 || waves == 12 || waves == 16) || !(groups == 1 || groups == 2)) return -1;
     // a window is a whole number of 32-row words, one column group, shorter than the grid
     if (win != 0 && (groups != 1 || win < 32 || win % 32 != 0 || win >= n_rho)) return -1;
@@ -3475,10 +3444,7 @@ int plan_batch(int n_theta, int n_rho, int waves, int groups, size_t lds_limit, 
     p.sparse = n_rho >= kSparseRhoRows ? 1 : 0;
     p.lds_bytes = batch_lds_bytes(n_rho, waves, groups, win, p.sparse != 0);
     p.sp_lds_bytes = batch_lds_bytes(n_rho, waves, groups, win, true);
-    p.split_lds_bytes = batch_lds_bytes(n_rho, waves, groups, 0, true);
-    // room for the kernel's static LDS; the caller's split form holds the whole column (need_split
-    // false on grids taller than that)
-    if (p.sp_lds_bytes + 256 > lds_limit || (need_split && p.split_lds_bytes + 256 > lds_limit)) return -1;
+    if (p.sp_lds_bytes + 256 > lds_limit) return -1;     // (room for the kernel's static LDS)
     p.grid = 0;
     *out = p;
     return 0;
@@ -3888,38 +3854,22 @@ SplitPlan plan_split(int n_rho, size_t lds_limit) {
     return p;
 }
 
-// Workspace size of the split form, part of its interface: room for every tile's list, keep bits
-// and counters, each section on a 256-byte boundary.  The kernel uses one slot per tile, at the
-// workspace's start.
-static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
-
-static void split_sizes(int n_theta, int n_rho, int groups, uint32_t n_events, uint32_t *n_tiles,
-                        uint32_t *tile_cap, size_t off[6]) {
-    const uint32_t out_cols = 64u * (uint32_t)groups - 2u;
-    *n_tiles = ((uint32_t)n_theta + out_cols - 1u) / out_cols;
-    *tile_cap = ((out_cols + 1u) / 2u) * (((uint32_t)n_rho + 1u) / 2u);
-    const size_t E = n_events, T = *n_tiles;
-    off[0] = 0;                                                          // counts
-    off[1] = align256(off[0] + E * T * 4);                               // staged
-    off[2] = align256(off[1] + E * T * (size_t)(*tile_cap) * sizeof(hough_peak));   // kept
-    off[3] = align256(off[2] + E * kSplitKeepWords * 4);                 // done
-    off[4] = align256(off[3] + E * 4);                                   // flags
-    off[5] = align256(off[4] + E * 4);                                   // end
-}
-
+// Workspace size of the split form.  The kernel needs one 4-byte slot per tile, at the workspace's start;
+// the size, and with it the largest batch of the static form, is part of the interface and stays what it
+// was when every tile's list (up to a peak in a quarter of the tile's cells), the events' keep bits and
+// two words per event lay there too, each section on a 256-byte boundary.
 size_t split_workspace_bytes(int n_theta, int n_rho, int groups, uint32_t n_events) {
-    uint32_t T, cap;
-    size_t off[6];
-    split_sizes(n_theta, n_rho, groups, n_events, &T, &cap, off);
-    return off[5];
+    const size_t E = n_events, cols = 64u * (size_t)groups - 2u, tiles = ((size_t)n_theta + cols - 1u) / cols;
+    const size_t list = ((cols + 1u) / 2u) * (((size_t)n_rho + 1u) / 2u) * sizeof(hough_peak);
+    const size_t keep_words = (kMaxBatchHits + 31) / 32 + 1;
+    auto section = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    return section(E * tiles * 4) + section(E * tiles * list) + section(E * keep_words * 4) + 2 * section(E * 4);
 }
 
 bool split_layout(int n_theta, int n_rho, int groups, uint32_t n_events, void *ws, size_t bytes,
                   SplitArgs *out) {
-    uint32_t T, cap;
-    size_t off[6];
-    split_sizes(n_theta, n_rho, groups, n_events, &T, &cap, off);
-    if (!ws || bytes < off[5] || ((uintptr_t)ws & 255u) != 0) return false;
+    if (!ws || bytes < split_workspace_bytes(n_theta, n_rho, groups, n_events) || ((uintptr_t)ws & 255u) != 0)
+        return false;
     const uint32_t tiles = split_tiles(n_theta);
     if (bytes / 4 < (size_t)n_events * tiles) return false;
     out->n_tiles = tiles;
