@@ -347,12 +347,20 @@ int hough_config(const hough_params *p, hough_ctx **out) {
         }
         c->spill_wgs = (c->spill_wgs + 1) / 2;
     }
-    // The tables and the zeros (work counters, slots) are waited for: the caller's first launch may be
-    // on a stream that does not wait for the null stream, and tiles of the split form wait for slots
-    // that a late clear would put back to zero.
-    if (hipMemset(c->d_block, 0, at[2]) != hipSuccess ||
-        hipMemcpy(c->d_tables, tab.data(), tab.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-        hipStreamSynchronize(nullptr) != hipSuccess) {
+    // The zeros (work counters, slots) and the tables after them go over in one blocking copy: the
+    // caller's first launch may be on a stream that does not wait for the null stream, where a clear of
+    // its own may still be on its way when hough_config returns, and tiles of the split form wait for
+    // slots that a late clear would put back to zero.
+    float *image = static_cast<float *>(calloc(at[2] / sizeof(float) + tab.size(), sizeof(float)));
+    if (!image) {
+        hough_destroy(c);
+        return HOUGH_ENOMEM;
+    }
+    memcpy(image + at[2] / sizeof(float), tab.data(), tab.size() * sizeof(float));
+    const bool sent =
+        hipMemcpy(c->d_block, image, at[2] + tab.size() * sizeof(float), hipMemcpyHostToDevice) == hipSuccess;
+    free(image);
+    if (!sent) {
         hough_destroy(c);
         return HOUGH_EDEVICE;
     }

@@ -94,7 +94,12 @@ hipError_t hipMalloc(void **p, size_t n) {
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::malloc(n ? n : 1); return hipSuccess; }
 hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
-hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
+    std::memcpy(d, s, n);                      // (a blocking call)
+    note("copy stream 0");
+    note("wait stream 0");
+    return hipSuccess;
+}
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
     std::memcpy(d, s, n);
     return hipSuccess;

@@ -124,8 +124,8 @@ def test_zeros_are_in_place_before_a_kernel_can_read_them(routes):
     hough_config (its caller may launch on any stream), and a serving slot's workspace is cleared on
     the stream its launches go to."""
     log = routes("out = journal(lambda: context(360, 256) and 0)[1]")
-    clears = [i for i, s in enumerate(log) if s == "clear stream 0"]
-    assert clears and "wait stream 0" in log[clears[-1]:]
+    writes = [i for i, s in enumerate(log) if s in ("clear stream 0", "copy stream 0")]
+    assert writes and "wait stream 0" in log[writes[-1]:]
     rc, log, n = routes("out = serve(context(360, 256), 4, streams=2)")
     assert rc == 0 and n == 4
     own = [s for s in log if s.startswith("clear stream")]
