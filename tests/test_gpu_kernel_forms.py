@@ -538,3 +538,93 @@ def test_event_peaks_staging(H, orc, n_theta, n_rhos, acc_type):
             assert int(n.item()) == m, (n_rho, periodic)
             assert np.array_equal(H.decode_peaks(got, m), np.stack([pj, pk, pc], 1).astype(np.int64)), (n_rho, periodic)
             ctx.close()
+
+
+def _graph_calls(H, form):
+    """(context, outputs of a call on one input set, the same on another) for a form of call."""
+    import torch
+    kw = dict(periodic="periodic" in form, dedup="dedup" in form)
+    n_theta, n_rho, rho, E = {"tile": (200, 128, 0.005, 64), "fused": (200, 128, 0.005, 300), "windows": (130, 1000, 0.01, 560),
+                              "tall": (130, 1500, 0.01, 24), "tallmany": (70, 1500, 0.01, 200)}.get(
+                                  form.split()[0], (200, 128, 0.005, 24))
+    ctx = H.Context(n_theta, n_rho, -rho, rho, "i32", 4, 1, 300, **kw)
+    call = form.split()[1]
+    rng = np.random.default_rng(E)
+    sets = []
+    for seed in (1, 2):
+        if call in ("event", "finder"):
+            x, y, off = _events([1100 + 60 * seed], seed, 170.0, 0.01)
+        else:
+            sizes = rng.integers(0, 200, E)
+            sizes[3], sizes[5] = 0, (33000 if E < 100 else 700)
+            parts = [_events([int(n)], seed * 1000 + i, 60.0 if rho == 0.01 and i % 9 == 4 else 215.0, 0.01)[:2]
+                     for i, n in enumerate(sizes)]
+            x, y = (np.concatenate([p[i] for p in parts]) for i in (0, 1))
+            off = np.concatenate([[0], np.cumsum(sizes)])
+        sets.append((_t(x), _t(y), _t(off.astype(np.int32))))
+    n = max(s[0].numel() for s in sets)
+    z = lambda shape, dt=torch.int32: torch.zeros(shape, dtype=dt, device="cuda")
+    outs = (z((E, 300, 2)), z(E), z(n, torch.uint8), z(E))
+    ws = ctx.split_workspace(E) if call == "split" else ctx.iterative_workspace(E) if call == "iterative" else None
+    acc, pk, one, st, tr = z((n_theta, n_rho)), z((4000, 2)), z(1), z(1), z((50, 6), torch.float64)
+
+    def run(i, stream=None):
+        x, y, o = sets[i]
+        if call == "batch":
+            ctx.run_batch(x, y, o, *outs, stream=stream)
+        elif call == "relative":
+            ctx.run_batch(x, y, o, *outs, stream=stream, frac=(1, 2))
+        elif call == "split":
+            ctx.run_batch_split(x, y, o, ws, *outs, stream=stream)
+        elif call == "static":
+            ctx.run_batch_split_static(x, y, o, *outs, stream=stream)
+        elif call == "iterative":
+            ctx.run_batch_iterative(x, y, o, (1, 2), 3, 3, ws, *outs, stream=stream)
+        else:
+            ctx.vote(x, y, acc, stream=stream)
+            if call == "event":
+                ctx.peaks(acc, 4000, pk, one, stream=stream)
+            else:
+                ctx.peaks_iterative(acc, 4000, (1, 2), 3, 3, pk, one, st, stream=stream)
+                ctx.track_params(x, y, pk, one, 50, 1.0, tr, stream=stream)
+            ctx.retain(x, y, pk, one, 4000, outs[2][:x.numel()], stream=stream)
+
+    def results(i):
+        m = sets[i][0].numel()
+        if call in ("event", "finder"):
+            k = int(one.item())
+            return [acc.clone(), one.clone(), pk[:k].clone(), outs[2][:m].clone()] + ([tr[:min(k, 50)].clone()] if call == "finder" else [])
+        npk = outs[1].cpu().numpy()
+        return [outs[1].clone(), outs[2][:m].clone(), outs[3].clone()] + \
+            [outs[0][e, :min(int(npk[e]), 300)].clone() for e in range(E)]
+
+    return ctx, run, results, [*outs, acc, pk, one, st, tr]
+
+
+@pytest.mark.parametrize("form", ["tile batch", "tile batch dedup", "tile batch periodic", "fused batch", "fused relative dedup",
+                                  "windows batch", "windows relative periodic", "tall batch", "tall batch periodic",
+                                  "tallmany batch dedup", "tallmany batch periodic", "few split", "tall split", "few static",
+                                  "few iterative", "few event", "few finder"])
+def test_calls_in_hip_graphs(H, form):
+    """Every route of a call captured once and replayed, with eager calls of the same context on other
+    data between the replays: each replay gives what the eager call gave."""
+    import torch
+    ctx, run, results, buffers = _graph_calls(H, form)
+    run(1)                                                     # other data first
+    run(0)
+    torch.cuda.synchronize()
+    ref = results(0)
+    assert any(int(t.count_nonzero()) for t in ref)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(0, torch.cuda.current_stream())
+    for r in range(4):
+        run(1)
+        for b in buffers:
+            b.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = results(0)
+        assert len(got) == len(ref) and all(torch.equal(a, b) for a, b in zip(ref, got)), r
+    ctx.close()
