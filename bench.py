@@ -70,11 +70,23 @@ def kernel_source_id() -> str:
     return h.hexdigest()[:16]
 
 
-def profiled_traffic(workload: str, plan):
+def plan_source(tuned, plan_given: bool = False) -> str:
+    """Where a context's launch shape comes from.  A context the tuner left alone keeps the library's own
+    choices, of which batch_plan reports the whole-column shape only: it may have run by tile (small
+    batches) or on windows (tall columns) instead."""
+    if plan_given:
+        return "fixed by --plan"
+    if tuned is None:
+        return "library default"
+    return "the library's own choice, kept by the autotuner" if tuned["automatic"] else "autotuned before timing"
+
+
+def profiled_traffic(workload: str, plan, own: bool | None = None):
     """HBM bytes per k_batch launch from the committed rocprofv3 counter summary of this
     workload (FETCH_SIZE and WRITE_SIZE, each scaled by what it reads for a 1 GiB device copy).
     None when there is no summary, or the kernel sources or the launch plan differ from the
-    ones the counters were taken with."""
+    ones the counters were taken with, or (given own) whether that shape was the library's own
+    choice, where the summary says."""
     path = os.path.join(ROOT, "profiles", f"k_batch_{workload}.md")
     if not os.path.exists(path):
         return None
@@ -86,7 +98,8 @@ def profiled_traffic(workload: str, plan):
     rec = json.loads(text[start + 7:text.index("```", start + 7)])
     cur = [plan["waves_per_group"], plan["column_groups"], plan["groups_per_cu"]]
     if (rec.get("source") != kernel_source_id() or rec.get("plan") != cur
-            or rec.get("window_rows", 0) != plan.get("window_rows", 0)):
+            or rec.get("window_rows", 0) != plan.get("window_rows", 0)
+            or (own is not None and rec.get("own", own) != own)):
         return None
     return rec
 
@@ -421,9 +434,10 @@ def secondary(H, names, ceiling: dict, tune: bool, reps: int = 20) -> dict:
         ctx = H.Context.for_workload(wl, max_peaks=cap)
         xt, yt, ot = H.to_device(ev)
         bufs = ctx.run_batch(xt, yt, ot)
+        tuned = None
         if tune:
             from paper_2607_04067_amd import autotune
-            autotune.tune(ctx, xt, yt, ot, bufs, mean_hits=ev.n_hits / max(ev.n_events, 1), cache=None)
+            tuned = autotune.tune(ctx, xt, yt, ot, bufs, mean_hits=ev.n_hits / max(ev.n_events, 1), cache=None)
         stream = torch.cuda.current_stream()
         for _ in range(3):
             ctx.run_batch(xt, yt, ot, *bufs, stream=stream)
@@ -436,9 +450,9 @@ def secondary(H, names, ceiling: dict, tune: bool, reps: int = 20) -> dict:
         ms = a.elapsed_time(b) / reps
         plan = ctx.batch_plan
         gv = ev.n_hits * wl.n_theta / (ms / 1e3) / 1e9
-        prof = profiled_traffic(name, plan)
+        prof = profiled_traffic(name, plan, own=tuned is None or tuned["automatic"])
         out[name] = {"events": ev.n_events, "hits": ev.n_hits, "plan": plan,
-                     "plan_source": "autotuned" if tune else "library default",
+                     "plan_source": plan_source(tuned),
                      "kernel_ms": round(ms, 4), "events_per_s": round(ev.n_events / (ms / 1e3), 1),
                      "gvotes_per_s": round(gv, 1), "frac": round(gv / lds_peak, 4),
                      "lds_atomic_frac": lds_atomic_rate(ev, plan, wl, ms, ceiling["lane_updates_per_s"])["frac"],
@@ -856,7 +870,8 @@ def main(argv=None):
     stored = int(np.minimum(npk.cpu().numpy().astype(np.int64), cap).sum())
     # algorithmic HBM bytes per launch: x, y and offsets in; keep, peak records, n_peaks, status out
     algo_bytes = 8 * ev.n_hits + 4 * (E + 1) + ev.n_hits + 8 * stored + 8 * E
-    prof = None if args.dedup else profiled_traffic(wl.name, ctx.batch_plan)   # counters: plain launch only
+    own = not args.plan and (tuned is None or tuned["automatic"])        # the shape is the library's own choice
+    prof = None if args.dedup else profiled_traffic(wl.name, ctx.batch_plan, own)   # counters: plain launch only
     ceiling = lds_atomic_ceiling()
     lds_peak = ceiling["lane_updates_per_s"] / 1e9            # Gvote/s: one LDS lane-update per vote at least
     fp32 = achieved * 1e9 * FLOPS_PER_VOTE / 1e12
@@ -872,8 +887,7 @@ def main(argv=None):
         "config": {"workload": wl.name, "events": E, "hits": ev.n_hits, "n_theta": wl.n_theta,
                    "n_rho": wl.n_rho, "threshold": wl.threshold, "rho_window": wl.rho_window,
                    "max_peaks": MAX_PEAKS[wl.name], "path": path, "plan": plan,
-                   "plan_source": "fixed by --plan" if args.plan else ("library default" if args.no_tune
-                                                                       else "autotuned before timing")},
+                   "plan_source": plan_source(tuned, bool(args.plan))},
         "gvotes_per_s": round(votes / (ms_per_step / 1e3) / 1e9, 2),
         "kernel_ms": round(kern_ms, 4),
         "kernel_ms_median": round(float(np.median(kern_times)), 4),
@@ -912,7 +926,6 @@ def main(argv=None):
         out["autotune_pick"] = tuned["plan"]
     if args.sweeps:
         # (a shape nobody set is not set there either: small batches then run by tile)
-        own = not args.plan and (tuned is None or tuned["automatic"])
         out["sweeps"] = sweeps(H, wl, ev, plan=None if own else ctx.batch_plan)
     if args.copy_reference_mb:
         n = args.copy_reference_mb << 20
