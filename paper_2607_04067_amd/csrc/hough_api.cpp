@@ -99,6 +99,8 @@ int spill_workgroups(size_t stride_words, int n_cu, bool all) {
 // With at most 7 tiles per event it wins for longer (fused / split at 200 and 256 events: 288 x 343
 // dense 144 / 111, 144 / 128; 360 x 256 81 / 67, 81 / 74; 372 x 500 dense 134 / 125, 135 / 146;
 // 309 x 99 68 / 60, 69 / 68; 372 x 900 128 / 105, 128 / 125): up to three quarters of the CUs then.
+// With more tiles nothing was measured between 128 and 256 events, where the dense grid loses and 1000 x
+// 1000 ties: the line is the last size at which every grid gains.
 uint32_t split_events(int n_cu, int n_theta, bool whole) {
     return whole && hough::split_tiles(n_theta) <= 7u ? (uint32_t)n_cu * 3u / 4u : (uint32_t)n_cu / 2u;
 }

@@ -290,7 +290,9 @@ __device__ __forceinline__ void vote_mfma(uint32_t *tile, float a, uint32_t rows
                         ? reinterpret_cast<uint32_t *>(base + (__mul24(k, vc.rs[h]) + vc.rb[h]))
                         : &tile[k * ST + 32 * (h >> 1) + (lane & 31)];
                     if (PER && CLAMP) {
-                        // a wrapped lane reverses the rows of the grid, not the dummy row
+                        // a wrapped lane reverses the rows of the grid, not the dummy row (which is row
+                        // n_rho here: an event with such hits reaches every row of a periodic grid, so
+                        // no window holds it)
                         const bool in = tt < g.nrho_f;
                         cell = in ? reinterpret_cast<uint32_t *>(base + (__mul24(k, vc.rs[h]) + vc.rb[h])) : cell;
                     }
@@ -2267,8 +2269,9 @@ struct PhaseClock {
 // Launch bounds: a windowed tile exists to fit two or three workgroups of at most 8 waves on a
 // CU, so 4 waves per SIMD are enough for it and leave it registers to spare.  The 8-wave kernel of
 // dense grids fits 64 registers, so that four workgroups of a 360 x 256 tile (39.6 KB of LDS)
-// share a CU: 32 waves hide the phases' latencies better than 24 (10,000 events 1,559 -> 1,470 us;
-// 1,000 events, which then all run at once, 159 -> 166 us).  The others keep 80.
+// share a CU: 32 waves hide the phases' latencies better than 24 (10,000 events 1,559 -> 1,478 us;
+// 1,000 events, which then all run at once, 159 -> 166 us), at the price of 3 registers in scratch (12
+// on theta-periodic grids, where the 10,000 events take 1,618 us).  The others keep 80.
 template <int NW, int G, bool PER, bool SP, bool WIN>
 __global__ __launch_bounds__(NW * 64, (NW == 16 || WIN) ? 4 : (G == 1 ? (NW == 8 && !SP ? 8 : 6) : 4)) void k_batch(GridArgs g, BatchArgs a,
                                                                                             int n_tiles, int nwords,
