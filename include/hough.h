@@ -244,7 +244,7 @@ int hough_run_batch_gather(hough_ctx *ctx, const float *x, const float *y, const
  * but each (event, theta tile) pair is a work item of its own, so the tiles of one event run on
  * different workgroups at once and a small batch finishes sooner (each tile examines the hits
  * the others have not kept yet, so a large batch finishes later than with hough_run_batch, which
- * takes this form by itself for small batches).
+ * takes this form by itself for small batches while no launch shape is set).
  * event_ids and keep_offsets are both NULL (events are offsets' own, keep indexed like x) or
  * both given (gather form).  workspace: device buffer of at least
  * hough_split_workspace_bytes(ctx, n_events) bytes, 256-byte aligned, filled with zeros before

@@ -3661,10 +3661,12 @@ static hipError_t launch_retain_t(const GridArgs &g, const float *x, const float
 
 // As many waves share 64 hits as leave at most one workgroup per CU; where one wave each leaves more,
 // two workgroups per CU take several chunks per built block.  A lookup reads LDS at random words, so
-// the columns looked at cost the time, and a wave that has all of them stops early: us at 16, 8, 4, 2
-// and 1 waves per 64 hits (720 x 512, 7,000 to 9,000 peaks, 256 CUs, columns in order) 32,000 hits 21,
-// 16, 24, 35, 44; 64,000: 32, 30, 24, 36, 44; 128,000: 51, 48, 46, 38, 47; 256,000: 88, 82, 78, 77, 54;
-// 1,000,000: 284, 262, 249, 240, 150.
+// the columns looked at cost the time, and a wave that has all of them stops early.  us at 16, 8, 4, 2
+// and 1 waves per 64 hits on 256 CUs, 720 x 512 with 4,000 to 9,000 peaks: 8,000 hits 10, 13, 20, 33, 22;
+// 32,000: 22, 17, 24, 35, 18; 64,000: 31, 31, 25, 36, 15; 256,000: 84, 78, 76, 74, 18; 1,000,000: 281,
+// 259, 245, 234, 56.  1000 x 1000, 17,000 to 22,000 peaks (waves stop late): 26, 30, 39, 58, 94; 53, 33,
+// 42, 60, 93; 71, 63, 44, 61, 96; 160, 132, 124, 119, 92; 508, 396, 374, 339, 242.  The line between two
+// and one lies where the second grid still gains by sharing (128,000: 63 and 90, the first 37 and 15).
 hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
                          const hough_peak *peaks, const uint32_t *n_peaks, uint32_t cap,
                          uint8_t *keep, int n_cu, hipStream_t s) {

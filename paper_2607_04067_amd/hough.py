@@ -232,6 +232,8 @@ class Context:
                 "groups_per_cu": p.groups_per_cu, "lds_bytes": p.lds_bytes, "window_rows": p.window_rows}
 
     def set_batch_plan(self, waves_per_group: int, column_groups: int, groups_per_cu: int = 0) -> None:
+        """Run every later batch in this launch shape (for good: small batches by tile and windows for large
+        ones are the library's choices while no shape is set)."""
         _check(self._lib.hough_set_batch_plan(self._ctx, int(waves_per_group), int(column_groups),
                                               int(groups_per_cu)), "hough_set_batch_plan")
 
