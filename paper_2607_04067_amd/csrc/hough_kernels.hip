@@ -2857,7 +2857,7 @@ __global__ __launch_bounds__(NW * 64, NW == 16 ? 4 : 6) void k_batch_split(GridA
 // kernel cannot take, not a fast path.
 constexpr int kSpillWaves = 16;
 constexpr int kSpillThreads = kSpillWaves * 64;
-constexpr uint32_t kSpillBlock = 4;      // events per counter pop when only some events spill
+constexpr uint32_t kSpillBlock = 4;      // at most this many events per counter pop when only some events spill
 // the slab: 143 KB of dynamic LDS, what the CU's 160 KB leave beside the kernel's static LDS
 // (slabs of 1,024 rows split a 2,000-row column into three, 3.4 against 4.1 ms per 1,000
 // events on 1000 x 2000 bins)
@@ -3213,22 +3213,25 @@ __global__ __launch_bounds__(kSpillThreads) void k_spill(GridArgs g, BatchArgs a
         return;
     }
     // only the events the fused or split kernel left (sp.queue[0] counts them; none: nothing to
-    // scan): the workgroups take blocks of kSpillBlock events from a counter (sp.queue[2]) and
+    // scan): the workgroups take blocks of up to kSpillBlock events from a counter (sp.queue[2]) and
     // process the left ones of each block, so that a batch whose events mostly spill (a window
-    // its events do not fit) keeps every workgroup busy.  The last workgroup to leave clears
+    // its events do not fit) keeps every workgroup busy.  A batch of fewer events than that many
+    // per workgroup takes smaller blocks, down to an event each (14 events on 621 x 1702, all left
+    // here: 2,384 us in blocks of four, 688 so).  The last workgroup to leave clears
     // the count and both counters.
     const uint32_t left = __hip_atomic_load(sp.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (uni(left) == 0u) return;               // (and the counters stay at zero)
+    const uint32_t block = min(max(a.n_events / gridDim.x, 1u), kSpillBlock);
     for (;;) {
         if (threadIdx.x == 0) {
             s_event = atomicAdd(sp.queue + 2, 1u);
             s_n = 0u;
         }
         __syncthreads();
-        const uint32_t b0 = uni(s_event) * kSpillBlock;
+        const uint32_t b0 = uni(s_event) * block;
         if (b0 >= a.n_events) break;                   // every thread leaves together
         const uint32_t e = b0 + threadIdx.x;
-        if (threadIdx.x < kSpillBlock && e < a.n_events) {
+        if (threadIdx.x < block && e < a.n_events) {
             const uint32_t pe_id = a.ids ? a.ids[e] : e;
             const uint32_t h0 = a.offsets[pe_id], h1 = a.offsets[pe_id + 1];
             // left here by the fused kernel or the split form

@@ -628,3 +628,28 @@ def test_calls_in_hip_graphs(H, form):
         got = results(0)
         assert len(got) == len(ref) and all(torch.equal(a, b) for a, b in zip(ref, got)), r
     ctx.close()
+
+
+@pytest.mark.parametrize("n_theta,n_rho,periodic", [(20, 1300, True), (20, 1300, False), (40, 64, False)])
+def test_spill_blocks_of_small_batches(H, orc, n_theta, n_rho, periodic):
+    """Events left to the spill kernel (beyond the window of a tall grid, or above the fused kernel's
+    hits), in batches on both sides of one, two and four events per workgroup: blocks of one to four
+    events, all of them left, none, and every third."""
+    import torch
+    tall = n_rho > 1200
+    wgs = torch.cuda.get_device_properties(0).multi_processor_count if tall else 4
+    lo, hi = -0.01, 0.01
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    T, cap = 2, 200
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", T, 1, cap, periodic=periodic)
+    rng = np.random.default_rng(n_theta)
+    for n in (1, 3, wgs - 1, wgs, wgs + 1, 2 * wgs - 1, 2 * wgs, 4 * wgs, 4 * wgs + 3):
+        for every in (1, 3):
+            left = np.arange(n) % every == 0
+            sizes = np.where(left, rng.integers(20, 60, n) if tall else 32768 + rng.integers(0, 9, n), rng.integers(0, 50, n))
+            parts = [_events([int(m)], 500 + i, 60.0 if tall and left[i] else 215.0, 0.01)[:2] for i, m in enumerate(sizes)]
+            x, y = (np.concatenate([p[i] for p in parts]) for i in (0, 1))
+            off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+            for _ in range(2):
+                _check(H, orc, ctx, g, T, 1, cap, x, y, off, periodic)
+    ctx.close()
