@@ -3185,16 +3185,26 @@ __global__ __launch_bounds__(kSpillThreads) void k_spill(GridArgs g, BatchArgs a
         for (uint32_t i = blockIdx.x * kSpillThreads + threadIdx.x; i < sp.n_slots; i += gridDim.x * kSpillThreads)
             sp.slots[i] = 0u;
         if (blockIdx.x == 0 && threadIdx.x == 0) *a.queue = 0u;
-        if (g.dedup)
-            for (uint32_t e = blockIdx.x; e < a.n_events; e += gridDim.x) {
+        if (g.dedup) {
+            // a workgroup per event, or as few waves each as it takes to have all events in hand at once
+            // (a few workgroups one event after the other: 123 events of 8 hits, whole call, 29 us)
+            uint32_t group = kSpillThreads;
+            while (group > 64u && gridDim.x * (kSpillThreads / group) < a.n_events) group >>= 1;
+            const uint32_t groups = kSpillThreads / group, mine = threadIdx.x / group, lane0 = threadIdx.x % group;
+            for (uint32_t e = blockIdx.x * groups + mine; e < a.n_events; e += gridDim.x * groups) {
                 const uint32_t pe_id = a.ids ? a.ids[e] : e, h0 = a.offsets[pe_id], h1 = a.offsets[pe_id + 1];
                 if (h1 <= h0 || h1 - h0 > kDedupMaxHits) continue;
                 uint8_t *ke = a.keep + (a.ids ? a.keep_offsets[e] : h0);
-                for (uint32_t i = threadIdx.x; i < h1 - h0; i += kSpillThreads) {
-                    const uint32_t v = ke[i];
-                    if (v & kKeepDuplicate) ke[i] = (uint8_t)(v & 1u);
+                for (uint32_t i0 = lane0; i0 < h1 - h0; i0 += 4u * group) {
+                    uint32_t v[4];
+#pragma unroll
+                    for (uint32_t q = 0; q < 4u; ++q) v[q] = i0 + q * group < h1 - h0 ? ke[i0 + q * group] : 0u;
+#pragma unroll
+                    for (uint32_t q = 0; q < 4u; ++q)
+                        if (v[q] & kKeepDuplicate) ke[i0 + q * group] = (uint8_t)(v[q] & 1u);
                 }
             }
+        }
     }
     if (sp.defer_count && blockIdx.x == 0 && threadIdx.x == 0) *sp.defer_count = 0u;   // (see BatchArgs)
     if (sp.all) {

@@ -653,3 +653,24 @@ def test_spill_blocks_of_small_batches(H, orc, n_theta, n_rho, periodic):
             for _ in range(2):
                 _check(H, orc, ctx, g, T, 1, cap, x, y, off, periodic)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 4, 5, 9, 33, 64, 65, 128])
+def test_duplicate_marks_leave_small_batches(H, orc, n):
+    """After a batch by tile the marks of later copies are dropped by one wave to a workgroup per event,
+    four bytes per lane at a time: counts of events and sizes on both sides of those."""
+    n_theta, n_rho, lo, hi = 70, 48, -0.005, 0.005
+    sizes = np.resize([255, 0, 257, 1023, 1025, 63, 4097, 1, 65, 8192 if n < 40 else 513], n)
+    x, y, off = _events([int(m) for m in sizes], 90 + n, 205.0, 0.02)
+    for e in range(n):
+        a, k = int(off[e]), int(sizes[e]) // 3
+        x[a + k:a + 2 * k], y[a + k:a + 2 * k] = x[a:a + k], y[a:a + k]
+    g = orc.Grid(n_theta, n_rho, lo, hi)
+    T, cap = 9, 600
+    ctx = H.Context(n_theta, n_rho, lo, hi, "i32", T, 0, cap, dedup=True)
+    ref, n_ref, keep_ref = orc.run_batch(g, x, y, off, threshold=T, rho_window=0, cap=cap, n_threads=8, dedup=True)
+    for _ in range(2):
+        pk, npk, keep, st = ctx.run_batch(_t(x), _t(y), _t(off.astype(np.int32)))
+        assert np.array_equal(npk.cpu().numpy()[:n].astype(np.int64), n_ref)
+        assert np.array_equal(keep.cpu().numpy()[:x.size], keep_ref)
+    ctx.close()
