@@ -315,8 +315,9 @@ typedef struct hough_batch_plan {
 /* The fused kernel's launch shape: the one the caller has set, or the one the library picked at
  * hough_config.  While the caller has not set one, some batches run in other ways, which this does not
  * report and which setting the reported shape would end: small ones by tile (see hough_run_batch), and
- * ones of at least twice as many events as CUs, on grids whose whole column leaves room for one
- * workgroup per CU, first on windows of rows and then, for the events that reach more, in this shape.  A
+ * ones of at least twice as many events as CUs, on grids of more than 248 columns whose whole column
+ * leaves room for one workgroup per CU, first on windows of rows and then, for the events that reach
+ * more, in this shape.  A
  * grid whose whole rho column does not fit the fused kernel's tile gets a windowed tile (theta
  * not periodic; window_rows > 0): each event whose hits reach only that many rows runs in the
  * fused kernel, the others through the spill path.  All

@@ -205,12 +205,17 @@ int default_windowed_plan(hough_ctx *c) {
 // 347 / 331, 364 / 385, with a relative threshold 348 / 318, 455 / 498, 456 / 533; 270 x 876 125 / 100,
 // 151 / 122, 156 / 148 and 135 / 114, 173 / 164, 174 / 185; 270 x 640 79 / 65, 104 / 114, 110 / 116).
 // Events that reach more rows run on whole columns in a second launch, which returns at once
-// when there are none (5 us); a batch of such events alone pays one more pass over its hits (38 us
-// for 1,000 of them: 1000 x 650 bins, every hit in reach of every row, 703 us on whole columns alone and
-// 750 so; 1000 x 1000, 532 and 574).
+// when there are none (5 us); a batch of such events alone pays one more pass over its hits, some 30 us
+// for 1,000 of them whatever the grid's width, where the gain for events that fit grows with it.  Us on
+// windows / whole columns, 1,000 events of 1,500 hits that fit, then 1,000 that do not:
+//   columns      62               124              186              310              1000
+//   600 rows   71/77  131/91   102/116 169/128  133/153 206/163  186/219 279/232   492/620  682/647
+//   1000 rows  77/89  138/98   110/136 211/171  142/181 287/243  201/263 438/402   530/761 1015/975
+// and 3,000 of 300 hits on 600 rows 103/128 210/124, 147/196 282/195, 188/264 351/261, 269/397 472/386,
+// 730/1161 1103/1019: up to four theta tiles of 62 columns the loss outweighs the gain, and whole columns stay.
 void auto_window(hough_ctx *c) {
     c->window.win = 0;
-    if (c->fused != 1 || c->plan.per_cu != 1) return;
+    if (c->fused != 1 || c->plan.per_cu != 1 || hough::split_tiles(c->p.n_theta) <= 4u) return;
     hough::BatchPlan p;
     if (windowed_plan(c, 8, 1, 2, &p) == 0) c->window = p;
 }

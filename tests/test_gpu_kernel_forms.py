@@ -304,6 +304,13 @@ def test_windows_over_many_events(H, orc, n_theta, n_rho, plan, flags):
     ctx.close()
 
 
+@pytest.mark.parametrize("n_theta,n_rho", [(248, 700), (249, 700), (251, 1000)])
+@pytest.mark.parametrize("flags", ["plain", "periodic", "dedup"])
+def test_windows_over_many_events_of_wide_grids(H, orc, n_theta, n_rho, flags):
+    """The same on both sides of the width from which such batches run on windows."""
+    test_windows_over_many_events(H, orc, n_theta, n_rho, None, flags)
+
+
 @pytest.mark.parametrize("n_theta,n_rho", [(2, 1500), (62, 1217), (63, 1500), (130, 2000), (1000, 1300)])
 @pytest.mark.parametrize("periodic", [False, True])
 @pytest.mark.parametrize("W", [1, 40])
@@ -544,7 +551,7 @@ def _graph_calls(H, form):
     """(context, outputs of a call on one input set, the same on another) for a form of call."""
     import torch
     kw = dict(periodic="periodic" in form, dedup="dedup" in form)
-    n_theta, n_rho, rho, E = {"tile": (200, 128, 0.005, 64), "fused": (200, 128, 0.005, 300), "windows": (130, 1000, 0.01, 560),
+    n_theta, n_rho, rho, E = {"tile": (200, 128, 0.005, 64), "fused": (200, 128, 0.005, 300), "windows": (250, 1000, 0.01, 560),
                               "tall": (130, 1500, 0.01, 24), "tallmany": (70, 1500, 0.01, 200)}.get(
                                   form.split()[0], (200, 128, 0.005, 24))
     ctx = H.Context(n_theta, n_rho, -rho, rho, "i32", 4, 1, 300, **kw)

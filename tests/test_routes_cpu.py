@@ -170,6 +170,10 @@ BATCH_ROUTES = [
     (720, 512, 0, None, 129, ["k_batch<12,1,0,0,0>", "k_spill"]),
     (1000, 2000, "PERIODIC", None, 64, ["k_batch_split<16,1,1>", "k_spill"]),
     (1000, 2000, "DEDUP", None, 64, ["k_dedup", "k_batch<16,1,0,1,1>", "k_spill"]),
+    # windows from five theta tiles on
+    (248, 700, 0, None, 600, ["k_order", "k_batch<16,1,0,0,0>", "k_spill"]),
+    (249, 700, 0, None, 600, ["k_order", "k_batch<8,1,0,0,1>", "k_batch<16,1,0,0,0>", "k_spill"]),
+    (249, 700, "PERIODIC", None, 600, ["k_order", "k_batch<8,1,1,0,1>", "k_batch<16,1,1,0,0>", "k_spill"]),
     # a shape the caller has set runs every batch, small ones too
     (360, 256, 0, (4, 2, 0), 1, ["k_batch<4,2,0,0,0>", "k_spill"]),
     (360, 256, 0, (6, 1, 3), 16, ["k_batch<6,1,0,0,0>", "k_spill"]),
