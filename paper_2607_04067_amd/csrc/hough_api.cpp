@@ -564,7 +564,7 @@ int hough_run_batch_iterative(hough_ctx *c, const float *x, const float *y, cons
     a.frac_den = 0;
     const hipError_t e = hough::launch_batch_iterative(c->g, a, static_cast<uint16_t *>(workspace), frac_num,
                                                        frac_den, r_theta, r_rho, c->iterb, gbm, c->d_iter_list,
-                                                       (hipStream_t)stream);
+                                                       c->n_cu, (hipStream_t)stream);
     return e == hipSuccess ? HOUGH_OK : HOUGH_EDEVICE;
 }
 

@@ -191,7 +191,7 @@ IterPlan plan_iterative_batch(int n_theta, int n_rho, size_t lds_limit, int per_
 constexpr uint32_t kIterHeads = 65536;
 hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_t *acc, uint32_t frac_num,
                                   uint32_t frac_den, int r_theta, int r_rho, const IterPlan &ip, uint32_t *gbm,
-                                  void *head, hipStream_t s);
+                                  void *head, int n_cu, hipStream_t s);
 hipError_t launch_vote(const GridArgs &g, const float *x, const float *y, uint32_t n_hits,
                        void *acc, int acc_type, hipStream_t s);
 // counts: a counter per workgroup, ceil(n_theta / g.peak_waves), of device scratch (the context's).

@@ -1191,7 +1191,7 @@ __device__ __forceinline__ uint32_t iter_threshold(uint32_t mx, uint32_t frac_nu
 // 640 of the 668 us of 300 events on 1000 x 1000; the lists hold some 20 keys per tile there, and
 // votes and finder take 138 and 64 us so.  Latency bounds the votes: half of the chip's VALU issue
 // and a third of its LDS cycles; several tiles per workgroup or 12 waves gained nothing.)
-// The LDS tile holds up to slab_rows rows (two workgroups per CU); hits that reach more go
+// The LDS tile holds up to slab_rows rows (launch_batch_iterative chooses); hits that reach more go
 // through it slab by slab, cells written.  Workgroup (e, 0) writes the event's status (invalid
 // hits, too many hits, duplicate pass skipped); the finder ORs into it.  An event above
 // kMaxBatchHits hits, or with malformed offsets, gets nothing.
@@ -3695,11 +3695,16 @@ hipError_t launch_retain(const GridArgs &g, const float *x, const float *y, uint
 // The iterative finder's batch form: (duplicate pass), votes into each tile's candidates (or
 // cells), the finder, and retention with each event's first `cap` peaks; as many events at a time as
 // the heads have room for.
-constexpr int kIterSlabRows = 600;               // 77 KB: two workgroups per CU
+// Rows of a tile held at a time: two workgroups per CU, or one with twice the rows where every (event,
+// tile) has a CU to itself anyway, so that fewer sweeps of the hits and fewer stores of the cells are made
+// (the whole call with 600 / 1,216 rows: 128 events of 1,500 hits on 63 x 1271 47 / 29 us, 40 on 360 x 2000 119 / 63,
+// 16 of 100 hits that reach every row of 1000 x 1000 134 / 44, 4 on 17 x 1110 25 / 18; where 600 rows hold
+// what the hits reach the two are equal).
+constexpr int kIterSlabRows = 600, kIterTallRows = 1216;
 constexpr int kIterVoteWaves = 8;
 hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_t *acc, uint32_t frac_num,
                                   uint32_t frac_den, int r_theta, int r_rho, const IterPlan &ip, uint32_t *gbm,
-                                  void *head, hipStream_t s) {
+                                  void *head, int n_cu, hipStream_t s) {
     if (a.n_events == 0) return hipSuccess;
     hipError_t e = hipSuccess;
     if (g.dedup) {
@@ -3708,17 +3713,18 @@ hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_
     }
     static const hipError_t vote_ok =
         hipFuncSetAttribute(reinterpret_cast<const void *>(k_vote_batch<kIterVoteWaves>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (kIterSlabRows + 1) * 128);
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (kIterTallRows + 1) * 128);
     static const hipError_t retain_ok = hipFuncSetAttribute(reinterpret_cast<const void *>(k_retain<1>),
                                                             hipFuncAttributeMaxDynamicSharedMemorySize, kRetainDilBytes);
     if (vote_ok != hipSuccess) return vote_ok;
     if (retain_ok != hipSuccess) return retain_ok;
     const size_t cells = (size_t)g.n_theta * (size_t)g.n_rho;
     const uint32_t tiles = (uint32_t)(g.n_theta + 63) / 64u, most_events = kIterHeads / tiles;
-    const int rows = std::min(g.n_rho, kIterSlabRows), cols = retain_cols_per_block(g);
+    const int cols = retain_cols_per_block(g);
     const uint32_t most_blocks = (kMaxBatchHits + kRetainWaves * 64 - 1) / (kRetainWaves * 64);
     for (uint32_t e0 = 0; e0 < a.n_events; e0 += most_events) {
         const uint32_t n = std::min(most_events, a.n_events - e0);
+        const int rows = std::min(g.n_rho, n * tiles <= (uint32_t)n_cu ? kIterTallRows : kIterSlabRows);
         const uint32_t *off = a.offsets + e0;
         hough_peak *peaks = a.peaks ? a.peaks + (size_t)e0 * a.max_peaks : nullptr;
         uint16_t *part = acc + e0 * cells;

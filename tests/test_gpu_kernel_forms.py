@@ -388,6 +388,31 @@ def test_batch_finder_tiles(H, orc, n_theta, n_rho, rng_lo, rng_hi, dedup):
         ctx.close()
 
 
+@pytest.mark.parametrize("n_theta,n_rho,E", [(60, 1216, 3), (60, 1217, 3), (3, 2500, 2), (130, 1300, 85), (130, 1300, 86)])
+def test_batch_finder_slabs(H, orc, n_theta, n_rho, E):
+    """The iterative finder over batches whose tiles have a CU each and over ones that do not, on columns at
+    the edges of the rows a tile then holds at a time, of events that reach every row and ones that reach few."""
+    import torch
+    g = orc.Grid(n_theta, n_rho, -0.01, 0.01)
+    parts = [_events([60 + 11 * (i % 7)], 70 + i, 110.0 if i % 3 else 400.0, 0.01)[:2] for i in range(E)]
+    x, y = (np.concatenate([p[i] for p in parts]) for i in (0, 1))
+    off = np.concatenate([[0], np.cumsum([p[0].size for p in parts])])
+    floor, cap = 3, 200
+    ctx = H.Context(n_theta, n_rho, -0.01, 0.01, "i32", floor, 1, cap)
+    for frac in ((1, 2), (1, 8)):
+        ref, n_ref, keep_ref = orc.run_batch_iterative_fast(g, x, y, off, floor, frac, 2, 3, 1, cap, n_threads=8)
+        pk, npk, keep, st = ctx.run_batch_iterative(_t(x), _t(y), _t(off.astype(np.int32)), frac, 2, 3,
+                                                    ctx.iterative_workspace(E))
+        torch.cuda.synchronize()
+        npk, p = npk.cpu().numpy(), pk.cpu().numpy()
+        assert np.array_equal(npk.astype(np.int64), n_ref)
+        assert np.array_equal(keep.cpu().numpy()[:x.size], keep_ref)
+        for e in range(E):
+            m = int(min(n_ref[e], cap))
+            assert np.array_equal(H.decode_peaks(p[e], m), ref[e, :m].astype(np.int64)), (frac, e)
+    ctx.close()
+
+
 PLANS = [(w, g, 0) for w in (4, 6, 8, 12, 16) for g in (1, 2)] + [(8, 1, 2), (4, 1, 3)]
 
 
