@@ -1669,7 +1669,7 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(const T *__restrict_
 // HOUGH_EV_PEAKS_TRUNCATED into status[e] (which the batch vote wrote); events the vote skipped
 // get no peaks.  K: keys in the LDS buffer (a power of two, kIterMinKeys .. kIterMaxKeys).
 // gbm (GBM): device bitmaps of bm_words words, one per workgroup.
-// list, scan (one event, else null): what k_iter_scan left.
+// list, scan (one event of more than kIterDirectCells cells, else null): what k_iter_scan left.
 template <typename T, bool GBM, bool BATCH>
 __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T *__restrict__ acc,
                                                              uint32_t frac_num, uint32_t frac_den, int r_theta,
@@ -1680,6 +1680,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
                                                              const uint2 *head) {
     extern __shared__ __align__(16) uint64_t keys[];       // [K]; the histograms reuse it as 2K words
     uint32_t *hist = reinterpret_cast<uint32_t *>(keys);
+    __shared__ uint32_t s_red[kIterWaves];
     __shared__ uint32_t s_n, s_m, s_first, s_taken;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t nr = (uint32_t)g.n_rho, nt = (uint32_t)g.n_theta;
@@ -1745,6 +1746,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     };
     const uint32_t floor_t = g.threshold;
     uint32_t mx = 0, thr, n1;
+    bool filtered = true;      // the keys held reach thr (else the floor)
     if constexpr (BATCH) {
         // the tiles' heads: the event's largest count, and where each tile's keys start
         uint32_t m = 0, run = 0;
@@ -1765,7 +1767,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         });
         __syncthreads();
         n1 = s_n;
-    } else {
+    } else if (scan) {
         mx = scan[0];
         n1 = scan[1];
         thr = iter_threshold(mx, frac_num, frac_den, floor_t);
@@ -1778,6 +1780,20 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
             }
         __syncthreads();
         n1 = whole ? s_n : K + 1u;
+    } else {
+        // the maximum, and the candidates of the absolute floor while they fit
+        uint32_t m = 0;
+        each([&](uint32_t v, uint32_t r, bool in) {
+            m = max(m, v);
+            append_key(keys, &s_n, K, in && v >= floor_t, ((uint64_t)v << 32) | (uint64_t)(~r), lane);
+        });
+        m = wave_max(m);
+        if (lane == 0) s_red[wave] = m;
+        __syncthreads();
+        for (int w = 0; w < kIterWaves; ++w) mx = max(mx, s_red[w]);
+        thr = iter_threshold(mx, frac_num, frac_den, floor_t);
+        n1 = s_n;
+        filtered = thr == floor_t;
     }
     __syncthreads();
 
@@ -1786,8 +1802,19 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
     bool have_chunk = false;
     uint32_t n = 0;
     uint64_t lo = 0;           // the chunk's lowest key (0: the chunk holds every candidate left)
-    if (n1 <= K) {                       // every candidate is in LDS
-        n = n1;
+    if (n1 <= K) {                       // every candidate is in LDS: those that reach thr, in place
+        if (!filtered) {
+            if (tid == 0) s_n = 0u;
+            __syncthreads();
+            for (uint32_t i0 = 0; i0 < n1; i0 += kIterThreads) {
+                const uint32_t i = i0 + tid;
+                const uint64_t key = i < n1 ? keys[i] : 0ull;
+                __syncthreads();
+                append_key(keys, &s_n, K, i < n1 && (uint32_t)(key >> 32) >= thr, key, lane);
+                __syncthreads();
+            }
+        }
+        n = s_n;
         have_chunk = true;
     }
     for (;;) {
@@ -1951,7 +1978,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         *n_peaks = taken;
         const uint32_t tr = taken > cap ? HOUGH_EV_PEAKS_TRUNCATED : 0u;
         *status = BATCH ? (*status | tr) : tr;
-        if constexpr (!BATCH) { scan[0] = 0u; scan[1] = 0u; }
+        if (!BATCH && scan) { scan[0] = 0u; scan[1] = 0u; }
     }
 }
 
@@ -3623,11 +3650,22 @@ static void launch_iter_t(const GridArgs &g, const T *acc, uint32_t frac_num, ui
     }
 }
 
+// The finder reads an accumulator of up to this many cells by itself: that costs less than a launch ahead
+// of it (us listed / by itself, threshold of half the maximum: 10 x 12 11.4 / 8.7, 95 x 60 of a 100-hit
+// event 36.5 / 33.8 and of 20,000 hits 25.4 / 24.5, 90 x 100 37.4 / 35.2 and 17.1 / 17.9, 96 x 128 33.5 / 31.9
+// and 11.6 / 13.5).
+constexpr uint32_t kIterDirectCells = 8192;
+
 template <typename T>
 static void launch_iter_one(const GridArgs &g, const T *acc, uint32_t frac_num, uint32_t frac_den, int r_theta,
                             int r_rho, hough_peak *peaks, uint32_t cap, uint32_t *n_peaks, uint32_t *status,
                             const IterPlan &ip, uint32_t *gbm, uint64_t *list, uint32_t *scan, hipStream_t s) {
     const uint32_t cells = (uint32_t)g.n_theta * (uint32_t)g.n_rho, tile = kScanThreads * kScanCells;
+    if (cells <= kIterDirectCells) {
+        launch_iter_t<T, false>(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, nullptr, 1u, ip,
+                                gbm, nullptr, nullptr, nullptr, s);
+        return;
+    }
     hipLaunchKernelGGL(k_iter_scan<T>, dim3(std::min((cells + tile - 1u) / tile, 1024u)), dim3(kScanThreads), 0, s,
                        acc, cells, g.threshold, frac_num, frac_den, list, scan);
     launch_iter_t<T, false>(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, nullptr, 1u, ip, gbm,

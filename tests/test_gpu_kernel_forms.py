@@ -185,6 +185,26 @@ def test_event_finder_listed_candidates(H, orc, n_theta, n_rho, frac):
     ctx.close()
 
 
+@pytest.mark.parametrize("n_theta,n_rho", [(2, 4096), (64, 128), (3, 2731), (90, 100)])
+@pytest.mark.parametrize("acc_type", ["i32", "u16"])
+def test_event_finder_on_either_side_of_the_list(H, orc, n_theta, n_rho, acc_type):
+    """The iterative finder on accumulators it reads by itself and on ones listed for it, one context after the
+    other use, from no candidate to more than its key buffer holds."""
+    rng = np.random.default_rng(n_rho)
+    ctx = H.Context(n_theta, n_rho, -0.005, 0.005, acc_type, 4, 1, 64)
+    cap = 400
+    for top, frac in ((4, (1, 2)), (200, (9, 10)), (60, (1, 2)), (60, (0, 1)), (5, (1, 1))):
+        acc = rng.integers(0, top, (n_theta, n_rho)).astype(np.int32 if acc_type == "i32" else np.int16)
+        acc.flat[-1] = top - 1
+        pk, n, st = ctx.peaks_iterative(_t(acc), cap, frac, 3, 4)
+        pj, pkk, pc, m = orc.peaks_iterative(acc.astype(np.int32), 4, frac, 3, 4, cap=cap, sorted_form=True)
+        k = min(m, cap)
+        assert int(n.item()) == m, (top, frac)
+        assert np.array_equal(H.decode_peaks(pk, k), np.stack([pj[:k], pkk[:k], pc[:k]], 1).astype(np.int64)), (top, frac)
+        assert int(st.item()) == (H.EV_PEAKS_TRUNCATED if m > cap else 0)
+    ctx.close()
+
+
 @pytest.mark.parametrize("n_theta,n_rho", [(2, 2), (3, 70), (5, 64), (8, 100), (130, 257), (4100, 12)])
 def test_event_peaks_blocks(H, orc, n_theta, n_rho):
     """hough_peaks' blocks of 4 (many columns: 16) rows, their edges and the periodic border."""
