@@ -1669,8 +1669,8 @@ __global__ __launch_bounds__(kScanThreads) void k_iter_scan(const T *__restrict_
 // HOUGH_EV_PEAKS_TRUNCATED into status[e] (which the batch vote wrote); events the vote skipped
 // get no peaks.  K: keys in the LDS buffer (a power of two, kIterMinKeys .. kIterMaxKeys).
 // gbm (GBM): device bitmaps of bm_words words, one per workgroup.
-// list, scan (one event of more than kIterDirectCells cells, else null): what k_iter_scan left.
-template <typename T, bool GBM, bool BATCH>
+// list, scan (LIST: one event of more than kIterDirectCells cells): what k_iter_scan left.
+template <typename T, bool GBM, bool BATCH, bool LIST>
 __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T *__restrict__ acc,
                                                              uint32_t frac_num, uint32_t frac_den, int r_theta,
                                                              int r_rho, hough_peak *out, uint32_t cap,
@@ -1767,7 +1767,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         });
         __syncthreads();
         n1 = s_n;
-    } else if (scan) {
+    } else if constexpr (LIST) {
         mx = scan[0];
         n1 = scan[1];
         thr = iter_threshold(mx, frac_num, frac_den, floor_t);
@@ -1978,7 +1978,7 @@ __global__ __launch_bounds__(kIterThreads) void k_peaks_iter(GridArgs g, const T
         *n_peaks = taken;
         const uint32_t tr = taken > cap ? HOUGH_EV_PEAKS_TRUNCATED : 0u;
         *status = BATCH ? (*status | tr) : tr;
-        if (!BATCH && scan) { scan[0] = 0u; scan[1] = 0u; }
+        if constexpr (LIST) { scan[0] = 0u; scan[1] = 0u; }
     }
 }
 
@@ -3629,25 +3629,17 @@ IterPlan plan_iterative(int n_theta, int n_rho, size_t lds_limit, int per_cu) {
     return p;
 }
 
-template <typename T, bool BATCH>
+template <typename T, bool GBM, bool BATCH, bool LIST>
 static void launch_iter_t(const GridArgs &g, const T *acc, uint32_t frac_num, uint32_t frac_den, int r_theta,
                           int r_rho, hough_peak *peaks, uint32_t cap, uint32_t *n_peaks, uint32_t *status,
                           const uint32_t *offsets, uint32_t n_blocks, const IterPlan &ip, uint32_t *gbm,
                           const uint64_t *list, uint32_t *scan, const uint2 *head, hipStream_t s) {
     const size_t lds = ip.lds_bytes + (BATCH ? iter_tile_bytes(g.n_theta) : 0);
-    if (ip.gbm) {
-        static const bool lds_ok = (allow_lds(k_peaks_iter<T, true, BATCH>), true);
-        (void)lds_ok;
-        hipLaunchKernelGGL((k_peaks_iter<T, true, BATCH>), dim3(n_blocks), dim3(kIterThreads), lds, s, g, acc,
-                           frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, offsets, ip.keys, gbm,
-                           list, scan, head);
-    } else {
-        static const bool lds_ok = (allow_lds(k_peaks_iter<T, false, BATCH>), true);
-        (void)lds_ok;
-        hipLaunchKernelGGL((k_peaks_iter<T, false, BATCH>), dim3(n_blocks), dim3(kIterThreads), lds, s, g, acc,
-                           frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, offsets, ip.keys,
-                           nullptr, list, scan, head);
-    }
+    static const bool lds_ok = (allow_lds(k_peaks_iter<T, GBM, BATCH, LIST>), true);
+    (void)lds_ok;
+    hipLaunchKernelGGL((k_peaks_iter<T, GBM, BATCH, LIST>), dim3(n_blocks), dim3(kIterThreads), lds, s, g, acc, frac_num,
+                       frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, offsets, ip.keys, GBM ? gbm : nullptr,
+                       list, scan, head);
 }
 
 // The finder reads an accumulator of up to this many cells by itself: that costs less than a launch ahead
@@ -3661,15 +3653,16 @@ static void launch_iter_one(const GridArgs &g, const T *acc, uint32_t frac_num, 
                             int r_rho, hough_peak *peaks, uint32_t cap, uint32_t *n_peaks, uint32_t *status,
                             const IterPlan &ip, uint32_t *gbm, uint64_t *list, uint32_t *scan, hipStream_t s) {
     const uint32_t cells = (uint32_t)g.n_theta * (uint32_t)g.n_rho, tile = kScanThreads * kScanCells;
-    if (cells <= kIterDirectCells) {
-        launch_iter_t<T, false>(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, nullptr, 1u, ip,
-                                gbm, nullptr, nullptr, nullptr, s);
+    if (cells <= kIterDirectCells && !ip.gbm) {
+        launch_iter_t<T, false, false, false>(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status,
+                                              nullptr, 1u, ip, nullptr, nullptr, nullptr, nullptr, s);
         return;
     }
     hipLaunchKernelGGL(k_iter_scan<T>, dim3(std::min((cells + tile - 1u) / tile, 1024u)), dim3(kScanThreads), 0, s,
                        acc, cells, g.threshold, frac_num, frac_den, list, scan);
-    launch_iter_t<T, false>(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, nullptr, 1u, ip, gbm,
-                     list, scan, nullptr, s);
+    const auto finder = ip.gbm ? launch_iter_t<T, true, false, true> : launch_iter_t<T, false, false, true>;
+    finder(g, acc, frac_num, frac_den, r_theta, r_rho, peaks, cap, n_peaks, status, nullptr, 1u, ip, gbm, list, scan,
+           nullptr, s);
 }
 
 hipError_t launch_peaks_iterative(const GridArgs &g, const void *acc, int acc_type, uint32_t frac_num,
@@ -3771,9 +3764,9 @@ hipError_t launch_batch_iterative(const GridArgs &g, const BatchArgs &a, uint16_
                            g, a.x, a.y, off, part, a.keep, a.status + e0, rows, frac_num, frac_den,
                            static_cast<uint2 *>(head));
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        launch_iter_t<uint16_t, true>(g, part, frac_num, frac_den, r_theta, r_rho, peaks, a.max_peaks, a.n_peaks + e0,
-                                      a.status + e0, off, n, ip, bm, nullptr, nullptr, static_cast<const uint2 *>(head),
-                                      s);
+        const auto finder = ip.gbm ? launch_iter_t<uint16_t, true, true, false> : launch_iter_t<uint16_t, false, true, false>;
+        finder(g, part, frac_num, frac_den, r_theta, r_rho, peaks, a.max_peaks, a.n_peaks + e0, a.status + e0, off, n, ip,
+               bm, nullptr, nullptr, static_cast<const uint2 *>(head), s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         // a few events: several workgroups each, up to the largest event's chunks
         const uint32_t blocks = std::max(1u, std::min(most_blocks, 512u / n));
